@@ -1,0 +1,6 @@
+// Odd- and large-group kernels instantiated for bf16 activations, buffers and outputs.
+#include "aqsgd_anygroup.h"
+
+namespace aqsgd {
+AQSGD_INSTANTIATE_ANYGROUP_DTYPE(AQSGD_BF16)
+}

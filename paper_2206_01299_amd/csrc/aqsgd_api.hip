@@ -5,11 +5,22 @@
 #include <limits>
 #include <vector>
 
+#include "aqsgd_anygroup.h"
 #include "aqsgd_kernels.h"
 #include "aqsgd_lowbit.h"
 #include "aqsgd_topk.h"
 
 namespace aqsgd {
+
+// Instantiated in the dtypes' own translation units.
+#define AQSGD_EXTERN_DTYPE(DT)                                                                        \
+    extern template hipError_t launch_quant_odd_dt<DT>(int, int, const QuantJob&, hipStream_t);       \
+    extern template hipError_t launch_dequant_odd_dt<DT>(const DequantJob&, hipStream_t);             \
+    extern template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
+    extern template hipError_t launch_lowbit_dt<DT>(int, int, int, bool, LaunchGeom, const LowbitArgs&, hipStream_t);
+AQSGD_EXTERN_DTYPE(AQSGD_F32)
+AQSGD_EXTERN_DTYPE(AQSGD_F16)
+AQSGD_EXTERN_DTYPE(AQSGD_BF16)
 
 thread_local ProfileRequest g_profile_request = {nullptr, nullptr};
 
@@ -43,6 +54,31 @@ hipError_t launch_dequant_anyshape(int dtype, const DequantJob& a, hipStream_t s
     case AQSGD_F32:  return launch_dequant_anyshape_dt<AQSGD_F32>(a, s);
     case AQSGD_F16:  return launch_dequant_anyshape_dt<AQSGD_F16>(a, s);
     case AQSGD_BF16: return launch_dequant_anyshape_dt<AQSGD_BF16>(a, s);
+    default:         return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_quant_odd(int dtype, int rounding, int shape, const QuantJob& a, hipStream_t s) {
+    switch (dtype) {
+    case AQSGD_F32:  return launch_quant_odd_dt<AQSGD_F32>(rounding, shape, a, s);
+    case AQSGD_F16:  return launch_quant_odd_dt<AQSGD_F16>(rounding, shape, a, s);
+    case AQSGD_BF16: return launch_quant_odd_dt<AQSGD_BF16>(rounding, shape, a, s);
+    default:         return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_dequant_odd(int dtype, const DequantJob& a, hipStream_t s) {
+    switch (dtype) {
+    case AQSGD_F32:  return launch_dequant_odd_dt<AQSGD_F32>(a, s);
+    case AQSGD_F16:  return launch_dequant_odd_dt<AQSGD_F16>(a, s);
+    case AQSGD_BF16: return launch_dequant_odd_dt<AQSGD_BF16>(a, s);
+    default:         return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_quant_large(int dtype, int rounding, const QuantJob& a, const LargeGeom& geom, hipStream_t s) {
+    switch (dtype) {
+    case AQSGD_F32:  return launch_quant_large_dt<AQSGD_F32>(rounding, a, geom, s);
+    case AQSGD_F16:  return launch_quant_large_dt<AQSGD_F16>(rounding, a, geom, s);
+    case AQSGD_BF16: return launch_quant_large_dt<AQSGD_BF16>(rounding, a, geom, s);
     default:         return hipErrorInvalidValue;
     }
 }
@@ -174,11 +210,18 @@ struct SeenArgs {
     uint32_t stamp = 0;
 };
 
+// Which kernels a message takes.  Groups of whole chunks that fit a workgroup's registers are
+// jobs of the shared launches; the rest are launched on their own: odd groups (8 elements or
+// more, not whole chunks), groups beyond a workgroup (quantising side only: reconstruction needs
+// no maximum), and the scalar kernels for groups of 1 to 7 elements, which have no 16-byte piece.
+enum class Route { kJob, kOdd, kLarge, kAnyShape };
+
 // One message as the kernels see it.  Quantising side: aqsgd_encode, aqsgd_grad_quant.
 struct QuantPlan {
     QuantJob job;
     int dtype, bits, rounding;
-    int shape;                 // team shape, or -1: any-shape kernel (launched on its own)
+    Route route;
+    int shape;                 // team shape (kJob, kOdd)
 };
 
 QuantPlan plan_quant(const aqsgd_desc* d, int64_t batch, int64_t n_per, const void* src, const int64_t* ids,
@@ -187,11 +230,15 @@ QuantPlan plan_quant(const aqsgd_desc* d, int64_t batch, int64_t n_per, const vo
     QuantJob& a = p.job;
     a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
     a.n_per = n_per; a.gps = n_per / d->group;
-    a.batch = static_cast<int32_t>(batch); a.group = d->group; a.cpg = d->group / kChunk; a.bits = d->bits;
+    a.batch = static_cast<int32_t>(batch); a.group = d->group; a.bits = d->bits;
+    a.cpg = static_cast<int32_t>((static_cast<int64_t>(d->group) + kChunk - 1) / kChunk);
     a.grid_x = a.grid_y = 1; a.rcp_grid_x = 1.0f;
     a.seed = d->rng_seed; a.seen = sa.seen; a.first = sa.first; a.stamp = sa.stamp;
     p.dtype = d->dtype; p.bits = d->bits; p.rounding = d->rounding;
-    p.shape = (d->group % kChunk == 0 && a.cpg <= kMaxTeamChunks) ? team_shape_for(a.cpg) : -1;
+    p.route = a.group < kChunk ? Route::kAnyShape
+              : a.cpg > kMaxTeamChunks ? Route::kLarge
+              : a.group % kChunk != 0 ? Route::kOdd : Route::kJob;
+    p.shape = team_shape_for(a.cpg);
     return p;
 }
 
@@ -199,7 +246,7 @@ QuantPlan plan_quant(const aqsgd_desc* d, int64_t batch, int64_t n_per, const vo
 struct DequantPlan {
     DequantJob job;
     int dtype;
-    bool flat;                 // false: any-shape kernel (launched on its own)
+    Route route;               // kJob, kOdd or kAnyShape
 };
 
 DequantPlan plan_dequant(const aqsgd_desc* d, int64_t batch, int64_t n_per, const uint8_t* codes,
@@ -213,7 +260,9 @@ DequantPlan plan_dequant(const aqsgd_desc* d, int64_t batch, int64_t n_per, cons
     a.grid_x = a.grid_y = 1; a.rcp_grid_x = 1.0f;
     a.seen = sa.seen; a.stamp = sa.stamp;
     p.dtype = d->dtype;
-    p.flat = d->group % kChunk == 0;
+    const int64_t piece = d->dtype == AQSGD_F32 ? kUnit : kChunk;
+    const bool odd_fits = a.group >= kChunk && a.gps * ((a.group + piece - 1) / piece) < kMaxOddPieces;
+    p.route = a.group % kChunk == 0 ? Route::kJob : odd_fits ? Route::kOdd : Route::kAnyShape;
     return p;
 }
 
@@ -277,6 +326,58 @@ void number_blocks(JobTable& t, int64_t quant_step, int64_t dequant_step, int64_
     t.total_blocks = static_cast<uint32_t>(blocks);
 }
 
+// Spans of a large group: as many as give the launch about kLargeMaxBlocks workgroups, none
+// shorter than one step of a workgroup.
+LargeGeom large_geometry(const QuantJob& a) {
+    const int64_t pieces = a.cpg;
+    int64_t spans = kLargeMaxBlocks / (a.gps < kLargeMaxBlocks ? a.gps : kLargeMaxBlocks);
+    spans = spans / (a.batch < spans ? a.batch : spans);
+    const int64_t most = (pieces + kLargeMinSpanPieces - 1) / kLargeMinSpanPieces;
+    if (spans > most) spans = most;
+    LargeGeom g;
+    g.span_pieces = static_cast<int32_t>(((pieces + spans - 1) / spans + kBlock - 1) / kBlock * kBlock);
+    g.spans = static_cast<int32_t>((pieces + g.span_pieces - 1) / g.span_pieces);
+    return g;
+}
+
+// A quantising message outside the job kernels' range.
+hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_blocks, hipStream_t stream) {
+    QuantJob& a = p.job;
+    LaunchGeom g;
+    switch (p.route) {
+    case Route::kOdd: {
+        const int64_t budget = launch_budget(p.shape, launch_blocks);
+        g = geometry(a.gps, groups_per_block_step(p.shape), a.batch, budget < max_blocks ? budget : max_blocks);
+        a.grid_x = g.grid_x; a.grid_y = g.grid_y;
+        return launch_quant_odd(p.dtype, p.rounding, p.shape, a, stream);
+    }
+    case Route::kLarge: {
+        const LargeGeom lg = large_geometry(a);
+        g = geometry(a.gps * lg.spans, 1, a.batch, max_blocks);
+        a.grid_x = g.grid_x; a.grid_y = g.grid_y;
+        return launch_quant_large(p.dtype, p.rounding, a, lg, stream);
+    }
+    default:
+        g = geometry(a.gps, kBlock, a.batch, max_blocks);
+        a.grid_x = g.grid_x; a.grid_y = g.grid_y;
+        return launch_quant_anyshape(p.dtype, p.bits, p.rounding, a, stream);
+    }
+}
+
+hipError_t launch_dequant_alone(DequantPlan& p, int64_t max_blocks, hipStream_t stream) {
+    DequantJob& a = p.job;
+    if (p.route == Route::kOdd) {
+        const int64_t piece = p.dtype == AQSGD_F32 ? kUnit : kChunk;
+        const LaunchGeom g = geometry(a.gps * ((a.group + piece - 1) / piece), static_cast<int64_t>(kBlock) * kOddUnroll,
+                                      a.batch, max_blocks);
+        a.grid_x = g.grid_x; a.grid_y = g.grid_y;
+        return launch_dequant_odd(p.dtype, a, stream);
+    }
+    const LaunchGeom g = geometry(a.gps, kBlock, a.batch, max_blocks);
+    a.grid_x = g.grid_x; a.grid_y = g.grid_y;
+    return launch_dequant_anyshape(p.dtype, a, stream);
+}
+
 // The launches of a set of independent messages: quantising jobs that share dtype,
 // rounding mode and team shape go into one grid, together with the dequantising
 // jobs of that dtype that are still waiting; dequantising jobs without such a host get a
@@ -292,7 +393,7 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
     const int64_t launch_blocks = launch_blocks_knob().load(std::memory_order_relaxed);
     auto add_dequant = [&](JobTable& t, int dtype) {
         for (size_t k = 0; k < ds.size() && t.n_dequant < kMaxDequantJobs; ++k) {
-            if (d_done[k] || !ds[k].flat || ds[k].dtype != dtype) continue;
+            if (d_done[k] || ds[k].route != Route::kJob || ds[k].dtype != dtype) continue;
             t.d[t.n_dequant++] = ds[k].job;
             d_done[k] = true;
         }
@@ -301,10 +402,8 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
     for (size_t i = 0; i < qs.size() && err == hipSuccess; ++i) {
         if (q_done[i]) continue;
         QuantPlan& lead = qs[i];
-        if (lead.shape < 0) {                            // any-shape kernel, on its own
-            const LaunchGeom g = geometry(lead.job.gps, kBlock, lead.job.batch, max_blocks);
-            lead.job.grid_x = g.grid_x; lead.job.grid_y = g.grid_y;
-            err = launch_quant_anyshape(lead.dtype, lead.bits, lead.rounding, lead.job, stream);
+        if (lead.route != Route::kJob) {
+            err = launch_quant_alone(lead, max_blocks, launch_blocks, stream);
             q_done[i] = true;
             continue;
         }
@@ -313,7 +412,8 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
         bool three = false;                              // a 3-bit job among them: the kernel variant that has those bodies
         for (size_t k = i; k < qs.size() && t.n_quant < kMaxQuantJobs; ++k) {
             const QuantPlan& c = qs[k];
-            if (q_done[k] || c.shape != lead.shape || c.dtype != lead.dtype || c.rounding != lead.rounding)
+            if (q_done[k] || c.route != Route::kJob || c.shape != lead.shape || c.dtype != lead.dtype ||
+                c.rounding != lead.rounding)
                 continue;
             three = three || c.bits == 3;
             t.q[t.n_quant++] = c.job;
@@ -327,11 +427,8 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
     }
     for (size_t i = 0; i < ds.size() && err == hipSuccess; ++i) {
         if (d_done[i]) continue;
-        if (!ds[i].flat) {
-            DequantJob& a = ds[i].job;
-            const LaunchGeom g = geometry(a.gps, kBlock, a.batch, max_blocks);
-            a.grid_x = g.grid_x; a.grid_y = g.grid_y;
-            err = launch_dequant_anyshape(ds[i].dtype, a, stream);
+        if (ds[i].route != Route::kJob) {
+            err = launch_dequant_alone(ds[i], max_blocks, stream);
             d_done[i] = true;
             continue;
         }

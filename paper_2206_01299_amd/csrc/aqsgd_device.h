@@ -51,6 +51,27 @@ __device__ __forceinline__ Raw<DT> load_raw_at(const char* p) {
     return r;
 }
 
+// The same from any element's address: rows and groups that are no whole number of chunks
+// start anywhere, and gfx950 loads and stores 16 bytes at any address (the compiler emits one
+// access for an under-aligned vector, as its HSA target runs with unaligned access on).
+typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t u16_any_t __attribute__((aligned(1)));
+typedef uint32_t u32_any_t __attribute__((aligned(1)));
+typedef uint64_t u64_any_t __attribute__((aligned(1)));
+
+template <int DT>
+__device__ __forceinline__ Raw<DT> load_raw_any(const char* p) {
+    Raw<DT> r;
+    if constexpr (DT == AQSGD_F32) {
+        r.lo = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any_t*>(p));
+        r.hi = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any_t*>(p + 16));
+    } else {
+        r.v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any_t*>(p));
+    }
+    return r;
+}
+
 // A 16-byte streaming store that is also written through the L2 at system scope (nt with
 // sc0 sc1).  The launches here end with tens of MB of freshly written lines, and lines
 // that only stream (nt) still wait in the eight L2s for the write-back at the end of the
@@ -318,6 +339,27 @@ __device__ __forceinline__ void chunk_uniforms(uint64_t seed, uint64_t j0, float
     for (int e = 0; e < 4; ++e) r[4 + e] = offset32_from_word(w[e]);
 }
 
+// The same for N elements from any index j0: they straddle up to N/4 + 1 blocks, whose words
+// are moved down by j0 mod 4 places in two selecting steps (no indexed register access).
+template <int N>
+__device__ __forceinline__ void uniforms_any(uint64_t seed, uint64_t j0, float (&r)[N]) {
+    const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
+    const uint64_t blk = j0 >> 2;
+    const bool by1 = (j0 & 1) != 0, by2 = (j0 & 2) != 0;
+    uint32_t w[N + 4];
+#pragma unroll
+    for (int b = 0; b < N / 4 + 1; ++b) {
+        uint32_t x[4];
+        philox4x32_10(static_cast<uint32_t>(blk + b), static_cast<uint32_t>((blk + b) >> 32), k0, k1, x);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[4 * b + e] = x[e];
+    }
+#pragma unroll
+    for (int e = 0; e < N + 2; ++e) w[e] = by1 ? w[e + 1] : w[e];
+#pragma unroll
+    for (int e = 0; e < N; ++e) r[e] = offset32_from_word(by2 ? w[e + 2] : w[e]);
+}
+
 // ---------------------------------------------------------------------------
 // Max over the TEAM consecutive lanes a lane belongs to (TEAM = 1..64, power of
 // two).  The first four steps are DPP lane permutations inside a 16-lane row;
@@ -546,6 +588,39 @@ __device__ __forceinline__ uint64_t load_codes_at(const uint8_t* p) {
     }
 }
 
+// Codes of N elements (N * BITS is a whole number of bytes) at any byte address.
+template <int NBYTES>
+__device__ __forceinline__ void store_bytes_any(uint8_t* p, uint64_t w) {
+    static_assert(NBYTES >= 1 && NBYTES <= 8, "the code bytes of one chunk or unit");
+    if constexpr (NBYTES == 8) {
+        *reinterpret_cast<u64_any_t*>(p) = w;
+    } else {
+        if constexpr (NBYTES >= 4) *reinterpret_cast<u32_any_t*>(p) = static_cast<uint32_t>(w);
+        constexpr int at2 = NBYTES & 4;
+        if constexpr ((NBYTES & 2) != 0)
+            *reinterpret_cast<u16_any_t*>(p + at2) = static_cast<uint16_t>(w >> (8 * at2));
+        constexpr int at1 = NBYTES & 6;
+        if constexpr ((NBYTES & 1) != 0) p[at1] = static_cast<uint8_t>(w >> (8 * at1));
+    }
+}
+
+template <int NBYTES>
+__device__ __forceinline__ uint64_t load_bytes_any(const uint8_t* p) {
+    static_assert(NBYTES >= 1 && NBYTES <= 8, "the code bytes of one chunk or unit");
+    if constexpr (NBYTES == 8) {
+        return *reinterpret_cast<const u64_any_t*>(p);
+    } else {
+        uint64_t w = 0;
+        if constexpr (NBYTES >= 4) w = *reinterpret_cast<const u32_any_t*>(p);
+        constexpr int at2 = NBYTES & 4;
+        if constexpr ((NBYTES & 2) != 0)
+            w |= static_cast<uint64_t>(*reinterpret_cast<const u16_any_t*>(p + at2)) << (8 * at2);
+        constexpr int at1 = NBYTES & 6;
+        if constexpr ((NBYTES & 1) != 0) w |= static_cast<uint64_t>(p[at1]) << (8 * at1);
+        return w;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // float32 in 16-byte units.
 //
@@ -567,6 +642,13 @@ __device__ __forceinline__ Raw<AQSGD_F32> load_raw_units(const char* pa, const c
     Raw<AQSGD_F32> r;
     r.lo = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(pa));
     r.hi = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(pb));
+    return r;
+}
+
+__device__ __forceinline__ Raw<AQSGD_F32> load_raw_units_any(const char* pa, const char* pb) {
+    Raw<AQSGD_F32> r;
+    r.lo = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any_t*>(pa));
+    r.hi = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any_t*>(pb));
     return r;
 }
 
@@ -616,6 +698,23 @@ __device__ __forceinline__ uint32_t load_unit_codes(const uint8_t* p) {
         return static_cast<uint32_t>(p[0]) | (static_cast<uint32_t>(p[1]) << 8) |
                (static_cast<uint32_t>(p[2]) << 16);
     }
+}
+
+// A chunk, or a lane's two units, from an aligned place or (ANY) from any element's address.
+template <int DT, bool ANY>
+__device__ __forceinline__ Raw<DT> load_chunk(const char* p) {
+    if constexpr (ANY) return load_raw_any<DT>(p);
+    else return load_raw_at<DT>(p);
+}
+template <bool ANY>
+__device__ __forceinline__ Raw<AQSGD_F32> load_units(const char* pa, const char* pb) {
+    if constexpr (ANY) return load_raw_units_any(pa, pb);
+    else return load_raw_units(pa, pb);
+}
+template <int BITS, bool ANY>
+__device__ __forceinline__ void store_codes_of_unit(uint8_t* p, uint32_t w) {
+    if constexpr (ANY) store_bytes_any<BITS / 2>(p, w);
+    else store_unit_codes<BITS>(p, w);
 }
 
 // Rounding offsets (times 2^32) of two units whose first elements have flat indices

@@ -136,8 +136,31 @@ __host__ __device__ constexpr int groups_per_team(int team, int cpl) {
 // a copy of its results (loaded by the same instruction as the original) and
 // store the same bytes to the same place.  Only a team past the last group of
 // the sample (ragged last step) is switched off, as a whole.
+//
+// ODD: groups that are no whole number of chunks (at least eight elements).  The last
+// chunk starts eight elements before the group's end and so repeats some elements of the
+// one before it: same values, same results, stored twice to the same place, as the lanes
+// past the end do, and its codes are whole bytes because the group's are.  A lane then
+// holds the element offsets of its chunks instead of their numbers, and everything is
+// accessed at any address.
 // ---------------------------------------------------------------------------
-template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF, int NG>
+
+// Where a lane's chunk (or unit) starts within its group: its number, or for ODD groups
+// its first element.
+template <bool ODD, int ELEMS> struct Place {
+    static __device__ __forceinline__ uint32_t elem(uint32_t c) { return ODD ? c : c * ELEMS; }
+    template <int BITS>
+    static __device__ __forceinline__ uint32_t code_byte(uint32_t c) {
+        return ODD ? c * BITS / 8 : c * (ELEMS * BITS / 8);
+    }
+};
+// First code byte of element `off` of a call (off * BITS is whole bytes at a group's start).
+template <bool ODD, int BITS>
+__device__ __forceinline__ int64_t code_offset(int64_t off) {
+    return ODD ? off * BITS / 8 : off / kChunk * BITS;
+}
+
+template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF, int NG, bool ODD>
 __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* src_s, char* m_s,
                                                  uint8_t* codes_s, float* scales_s, int64_t src0,
                                                  int64_t g0, int64_t gstride, const uint32_t (&cc)[CPL],
@@ -146,10 +169,11 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
     constexpr bool kMultiWave = TEAM > kWave;
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
     constexpr int kEB = ElemBytes<DT>::value;
-    constexpr int kChunkBytes = kChunk * kEB;
-    constexpr int kUnitBytes = kUnit * kEB;
     constexpr bool kUnits = UnitLayout<DT, BITS>::value;   // float32: a chunk is two separate 16-byte units
+    using Chunk = Place<ODD, kChunk>;
+    using Unit = Place<ODD, kUnit>;
     static_assert(NG == 1 || !kMultiWave, "several groups per step: teams inside a wavefront only");
+    static_assert(!ODD || BITS != 3, "3-bit groups are whole chunks");
 
     // The team takes NG groups per step, gstride apart: g0, g0 + gstride, ...
     // ---- issue every load of the groups -----------------------------------------
@@ -160,16 +184,17 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
         goff[u] = (g0 + u * gstride) * a.group;
 #pragma unroll
         for (int k = 0; k < CPL; ++k) {
+            const char* src_g = src_s + goff[u] * kEB;
+            const char* m_g = HAS_BUF ? m_s + goff[u] * kEB : nullptr;
             if constexpr (kUnits) {
-                ra[u][k] = load_raw_units(src_s + goff[u] * kEB + ua[k] * kUnitBytes,
-                                          src_s + goff[u] * kEB + ub[k] * kUnitBytes);
-                if constexpr (HAS_BUF)
-                    rm[u][k] = load_raw_units(m_s + goff[u] * kEB + ua[k] * kUnitBytes,
-                                              m_s + goff[u] * kEB + ub[k] * kUnitBytes);
+                const uint32_t a0 = Unit::elem(ua[k]) * kEB, b0 = Unit::elem(ub[k]) * kEB;
+                ra[u][k] = load_units<ODD>(src_g + a0, src_g + b0);
+                if constexpr (HAS_BUF) rm[u][k] = load_units<ODD>(m_g + a0, m_g + b0);
                 else rm[u][k] = zero_raw<DT>();
             } else {
-                ra[u][k] = load_raw_at<DT>(src_s + goff[u] * kEB + cc[k] * kChunkBytes);
-                if constexpr (HAS_BUF) rm[u][k] = load_raw_at<DT>(m_s + goff[u] * kEB + cc[k] * kChunkBytes);
+                const uint32_t c0 = Chunk::elem(cc[k]) * kEB;
+                ra[u][k] = load_chunk<DT, ODD>(src_g + c0);
+                if constexpr (HAS_BUF) rm[u][k] = load_chunk<DT, ODD>(m_g + c0);
                 else rm[u][k] = zero_raw<DT>();
             }
         }
@@ -186,11 +211,20 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
 #pragma unroll
         for (int k = 0; k < CPL; ++k) {
             if constexpr (ROUND == AQSGD_ROUND_STOCHASTIC) {
-                if constexpr (kUnits)
-                    units_uniforms(a.seed, static_cast<uint64_t>(src0 + goff[u]) + ua[k] * kUnit,
-                                   static_cast<uint64_t>(src0 + goff[u]) + ub[k] * kUnit, r[u][k]);
-                else
-                    chunk_uniforms(a.seed, static_cast<uint64_t>(src0 + goff[u]) + cc[k] * kChunk, r[u][k]);
+                const uint64_t j0 = static_cast<uint64_t>(src0 + goff[u]);
+                if constexpr (ODD && kUnits) {
+                    float ra4[kUnit], rb4[kUnit];
+                    uniforms_any<kUnit>(a.seed, j0 + ua[k], ra4);
+                    uniforms_any<kUnit>(a.seed, j0 + ub[k], rb4);
+#pragma unroll
+                    for (int e = 0; e < kUnit; ++e) { r[u][k][e] = ra4[e]; r[u][k][kUnit + e] = rb4[e]; }
+                } else if constexpr (ODD) {
+                    uniforms_any<kChunk>(a.seed, j0 + cc[k], r[u][k]);
+                } else if constexpr (kUnits) {
+                    units_uniforms(a.seed, j0 + ua[k] * kUnit, j0 + ub[k] * kUnit, r[u][k]);
+                } else {
+                    chunk_uniforms(a.seed, j0 + cc[k] * kChunk, r[u][k]);
+                }
             } else {
 #pragma unroll
                 for (int e = 0; e < kChunk; ++e) r[u][k][e] = kNearestOffset32;
@@ -233,13 +267,14 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
                 q[e] = level_of<BITS, ROUND>(d[u][k][e], sc[u], r[u][k][e]);
                 dh[e] = value_of(q[e], sc[u]);
             }
-            uint8_t* group_codes = codes_s + goff[u] / kChunk * BITS;
+            uint8_t* group_codes = codes_s + code_offset<ODD, BITS>(goff[u]);
+            char* m_g = HAS_BUF ? m_s + goff[u] * kEB : nullptr;
             if constexpr (kUnits) {
                 const uint64_t w = pack_levels<BITS>(q);
-                store_unit_codes<BITS>(group_codes + ua[k] * (BITS / 2), low_unit_codes<BITS>(w));
-                store_unit_codes<BITS>(group_codes + ub[k] * (BITS / 2), high_unit_codes<BITS>(w));
+                store_codes_of_unit<BITS, ODD>(group_codes + Unit::template code_byte<BITS>(ua[k]), low_unit_codes<BITS>(w));
+                store_codes_of_unit<BITS, ODD>(group_codes + Unit::template code_byte<BITS>(ub[k]), high_unit_codes<BITS>(w));
                 if constexpr (HAS_BUF)
-                    store_raw_units(m_s + goff[u] * kEB + ua[k] * kUnitBytes, m_s + goff[u] * kEB + ub[k] * kUnitBytes,
+                    store_raw_units(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB,
                                     updated_chunk<DT>(rm[u][k], dh));
                 continue;
             }
@@ -248,11 +283,13 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
                 const bool inside = k * TEAM + lane_in_team < a.cpg;
                 store_codes3_quad(group_codes + (cc[k] & ~3u) * 3, static_cast<uint32_t>(pack_levels<BITS>(q)),
                                   lane_in_team & 3, inside);
+            } else if constexpr (ODD) {
+                store_bytes_any<BITS>(group_codes + Chunk::template code_byte<BITS>(cc[k]), pack_levels<BITS>(q));
             } else {
                 store_codes_at<BITS>(group_codes + cc[k] * BITS, pack_levels<BITS>(q));
             }
             if constexpr (HAS_BUF)
-                store_raw_at<DT>(m_s + goff[u] * kEB + cc[k] * kChunkBytes, updated_chunk<DT>(rm[u][k], dh));
+                store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, updated_chunk<DT>(rm[u][k], dh));
         }
         if (lane_in_team == 0) scales_s[g0 + u * gstride] = sc[u].s_tx;
     }
@@ -261,34 +298,36 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
 // First visit of a sample on the sender: the team's chunks of the group go from act
 // to m unchanged (the activation itself is the message).  Same chunk ownership and
 // clamping as above, so the two paths write a row with the same access pattern.
-template <int DT, int BITS, int TEAM, int CPL>
+template <int DT, int BITS, int TEAM, int CPL, bool ODD>
 __device__ __forceinline__ void copy_team_group(const QuantJob& a, const char* src_s, char* m_s, int64_t g,
                                                 const uint32_t (&cc)[CPL], const uint32_t (&ua)[CPL],
                                                 const uint32_t (&ub)[CPL]) {
     constexpr int kEB = ElemBytes<DT>::value;
-    constexpr int kChunkBytes = kChunk * kEB;
-    constexpr int kUnitBytes = kUnit * kEB;
     constexpr bool kUnits = UnitLayout<DT, BITS>::value;
+    using Chunk = Place<ODD, kChunk>;
+    using Unit = Place<ODD, kUnit>;
     const int64_t goff = g * a.group;
+    const char* src_g = src_s + goff * kEB;
+    char* m_g = m_s + goff * kEB;
     Raw<DT> ra[CPL];
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
         if constexpr (kUnits)
-            ra[k] = load_raw_units(src_s + goff * kEB + ua[k] * kUnitBytes, src_s + goff * kEB + ub[k] * kUnitBytes);
+            ra[k] = load_units<ODD>(src_g + Unit::elem(ua[k]) * kEB, src_g + Unit::elem(ub[k]) * kEB);
         else
-            ra[k] = load_raw_at<DT>(src_s + goff * kEB + cc[k] * kChunkBytes);
+            ra[k] = load_chunk<DT, ODD>(src_g + Chunk::elem(cc[k]) * kEB);
     }
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
         if constexpr (kUnits)
-            store_raw_units(m_s + goff * kEB + ua[k] * kUnitBytes, m_s + goff * kEB + ub[k] * kUnitBytes, ra[k]);
+            store_raw_units(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB, ra[k]);
         else
-            store_raw_at<DT>(m_s + goff * kEB + cc[k] * kChunkBytes, ra[k]);
+            store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, ra[k]);
     }
 }
 
 // Workgroup (bx, by) of a quantising job's grid_x x grid_y rectangle.
-template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF>
+template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF, bool ODD = false>
 __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
     constexpr bool kMultiWave = TEAM > kWave;
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
@@ -307,15 +346,17 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
     uint32_t cc[CPL];           // this lane's chunks within a group, clamped to the last one
 #pragma unroll
     for (int k = 0; k < CPL; ++k)
-        cc[k] = static_cast<uint32_t>(min(k * TEAM + lane_in_team, a.cpg - 1));
+        cc[k] = static_cast<uint32_t>(ODD ? min(kChunk * (k * TEAM + lane_in_team), a.group - kChunk)
+                                          : min(k * TEAM + lane_in_team, a.cpg - 1));
     // The same ownership in 16-byte units for the float32 layout: row k of the team
     // covers units [2k TEAM, 2(k+1) TEAM), a lane takes one from each half of the row;
     // past the group's end a lane repeats the last unit (same values, same stores).
     uint32_t ua[CPL], ub[CPL];
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
-        ua[k] = static_cast<uint32_t>(min(2 * k * TEAM + lane_in_team, 2 * a.cpg - 1));
-        ub[k] = static_cast<uint32_t>(min((2 * k + 1) * TEAM + lane_in_team, 2 * a.cpg - 1));
+        const int u0 = 2 * k * TEAM + lane_in_team, u1 = u0 + TEAM;
+        ua[k] = static_cast<uint32_t>(ODD ? min(kUnit * u0, a.group - kUnit) : min(u0, 2 * a.cpg - 1));
+        ub[k] = static_cast<uint32_t>(ODD ? min(kUnit * u1, a.group - kUnit) : min(u1, 2 * a.cpg - 1));
     }
 
     for (int i = by; i < a.batch; i += a.grid_y) {
@@ -323,7 +364,7 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
         const int64_t src0 = static_cast<int64_t>(i) * a.n_per;      // flat offset of sample i
         const char* src_s = static_cast<const char*>(a.src) + src0 * kEB;
         char* m_s = HAS_BUF ? static_cast<char*>(a.m_buf) + row * a.n_per * kEB : nullptr;
-        uint8_t* codes_s = a.codes + src0 / kChunk * BITS;
+        uint8_t* codes_s = a.codes + code_offset<ODD, BITS>(src0);
         float* scales_s = a.scales + static_cast<int64_t>(i) * a.gps;
 
         bool fresh = false;
@@ -342,7 +383,7 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
              gbase += static_cast<int64_t>(a.grid_x) * kGroupsPerStep) {
             if constexpr (kGroupsPerTeam > 1) {
                 if (!fresh && gbase + kGroupsPerStep <= a.gps) {         // uniform over the workgroup
-                    quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, kGroupsPerTeam>(
+                    quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, kGroupsPerTeam, ODD>(
                         a, src_s, m_s, codes_s, scales_s, src0, gbase + team, kTeamsPerBlock, cc, ua, ub,
                         lane_in_team, wave_max);
                     continue;
@@ -355,12 +396,12 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
                 if (g >= a.gps) continue;
                 if constexpr (HAS_BUF) {
                     if (fresh) {                         // uniform over the workgroup
-                        copy_team_group<DT, BITS, TEAM, CPL>(a, src_s, m_s, g, cc, ua, ub);
+                        copy_team_group<DT, BITS, TEAM, CPL, ODD>(a, src_s, m_s, g, cc, ua, ub);
                         continue;
                     }
                 }
-                quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, 1>(a, src_s, m_s, codes_s, scales_s, src0, g,
-                                                                         0, cc, ua, ub, lane_in_team, wave_max);
+                quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, 1, ODD>(a, src_s, m_s, codes_s, scales_s, src0,
+                                                                              g, 0, cc, ua, ub, lane_in_team, wave_max);
             }
         }
     }
@@ -702,9 +743,10 @@ void dequant_jobs_kernel(const JobTable t) {
 }
 
 // ---------------------------------------------------------------------------
-// Any-shape fallbacks: one thread per group, scalar accesses.  Used when the
-// group size is not a multiple of 8 or too large for a workgroup's registers;
-// correct for every shape the ABI admits, not tuned.
+// Any-shape fallbacks: one thread per group, scalar accesses.  Used for groups of 1
+// to 7 elements, which hold no 16-byte piece (neighbouring threads' groups lie next
+// to each other, so the accesses of a wave fall into few cache lines), and for the
+// reconstruction of odd groups whose pieces pass 32-bit indices.
 // ---------------------------------------------------------------------------
 template <int DT>
 __global__ __launch_bounds__(kBlock)

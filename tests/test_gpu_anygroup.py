@@ -1,0 +1,84 @@
+"""GPU parity of groups outside the job kernels' range, byte for byte against the oracle:
+odd groups (8 elements or more, no whole number of chunks) at the edges of every team
+shape, and groups beyond a workgroup's registers (split over workgroups), both with
+previous messages, with first visits and as backward messages."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2206_01299_amd import binding as B
+from paper_2206_01299_amd import workloads as W
+from test_gpu_seen import _replay as replay_seen
+
+
+@pytest.fixture(scope="module")
+def H():
+    if not torch.cuda.is_available():
+        pytest.fail("these tests need the MI355X; run them with -m gpu on the GPU box")
+    B.lib()
+    import oracle
+    oracle.build()
+    import gpu_harness
+    return gpu_harness
+
+
+def _sweep(H, dtype, bits, group, rounding, gps, batch=3):
+    cfg = W.BoundaryConfig(
+        name=f"any_{dtype}_b{bits}_g{group}_r{rounding}", n_samples=7, batch=batch, seq=gps, hidden=group,
+        dtype=dtype, fwd_bits=bits, fwd_group=group, fwd_rounding=rounding, bwd_bits=bits, bwd_group=group,
+        bwd_rounding=rounding, law="normal", drift=0.05, epochs=2, shuffle_ids=True, seed=bits * 7 + group)
+    H.replay_and_compare(cfg, calls_per_epoch=2, epochs=2, log=lambda *a, **k: None)
+
+
+# last chunk shares 1 to 7 elements with the one before; team widths 8 .. 1024 and their last lanes
+ODD = {8: [9, 15, 57, 63, 65, 121, 127, 250, 257, 505, 519, 1001, 1023, 1531, 2041, 4001, 8185, 16001, 32767],
+       4: [10, 62, 66, 254, 510, 514, 1020, 1026, 2046, 4098, 8194, 16390, 32766],
+       6: [12, 60, 252, 1020, 1028, 4100, 32764], 2: [12, 68, 500, 1020, 2044, 8196, 32764]}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("bits", [2, 4, 6, 8])
+def test_odd_groups(H, dtype, bits):
+    for k, group in enumerate(ODD[bits]):
+        for rounding in (W.NEAREST, W.STOCHASTIC):
+            print(f"odd {dtype} b{bits} G{group} r{rounding}", flush=True)
+            _sweep(H, dtype, bits, group, rounding, 1 if group > 8000 else (67, 5, 130)[k % 3])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("bits,group", [(4, 32776), (3, 32776), (8, 32769), (2, 32772), (6, 40004), (8, 65537),
+                                        (4, 262144), (3, 262152), (8, 300001)])
+def test_groups_beyond_a_workgroup(H, dtype, bits, group):
+    for rounding, gps in ((W.NEAREST, 3), (W.STOCHASTIC, 1)):
+        print(f"large {dtype} b{bits} G{group} r{rounding}", flush=True)
+        _sweep(H, dtype, bits, group, rounding, gps, batch=2)
+
+
+def test_large_groups_without_a_change_send_scale_zero(H):
+    """Groups whose maximum is zero or below the 2^-120 floor next to one that is not."""
+    import oracle
+    d = H.dev()
+    G, n_per = 32776, 3 * 32776
+    act = np.zeros((1, n_per), dtype=np.float32)
+    act[0, G:2 * G] = np.float32(2.0 ** -121)
+    act[0, 2 * G + 5] = -3.0
+    m_np = np.zeros((2, n_per), dtype=np.float32)
+    desc = B.make_desc(batch=1, n_per=n_per, n_samples=2, bits=4, group=G, dtype="f32")
+    m = torch.zeros((2, n_per), device=d)
+    ids_np = np.array([1], dtype=np.int64)
+    codes = torch.full((B.codes_bytes(desc),), 0x5A, dtype=torch.uint8, device=d)
+    scales = torch.full((3,), -1.0, device=d)
+    B.encode(desc, torch.from_numpy(act).to(d), torch.from_numpy(ids_np).to(d), m, codes, scales)
+    wc, ws = oracle.encode(act, ids_np, m_np, dtype="f32", bits=4, group=G)
+    torch.cuda.synchronize()
+    assert H.same_bytes(scales.cpu().numpy(), ws) and ws[0] == 0 and ws[1] == 0 and ws[2] == 3
+    assert H.same_bytes(codes.cpu().numpy(), wc)
+    assert H.same_bytes(m.cpu().numpy(), m_np)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("group,gps", [(1020, 9), (12, 50), (32772, 2), (40000, 1)])
+def test_first_visits(H, dtype, group, gps):
+    replay_seen(H, dtype, 4, group, gps * group, 12, 4, 4, W.NEAREST, group)
