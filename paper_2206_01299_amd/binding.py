@@ -1,20 +1,28 @@
-"""Thin ctypes binding over ``libaqsgd.so`` (the C ABI in ``include/aqsgd.h``).
+"""Thin binding over ``libaqsgd.so`` (the C ABI in ``include/aqsgd.h``).
 
 Argument marshalling only: every step of the codec runs in the HIP kernels.
 torch supplies device memory (``tensor.data_ptr()``) and the stream
 (``torch.cuda.current_stream()``); no tensor maths happens here.  There is no
 CPU fallback: if the library is missing, loading raises.
+
+A call is first offered to ``_native`` (``csrc/binding_native.cpp``), which does the
+same checks and the foreign call in native code; only a call that is not of the
+ordinary form comes back (``None``) and takes the ctypes path below, whose checks
+say what is wrong with it.  On a small message the host's work per call is what the
+call takes.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
+import os
 from pathlib import Path
 
 import torch
 
-import os
-
 _HERE = Path(__file__).resolve().parent
+NATIVE_PATH = _HERE / "_native.so"
 # AQSGD_LIB names another build of the same library (used to compare two builds in one session)
 LIB_PATH = Path(os.environ["AQSGD_LIB"]) if os.environ.get("AQSGD_LIB") else _HERE / "libaqsgd.so"
 
@@ -137,6 +145,26 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _LoadNative:
+    """Stands in for the native module until the first call needs it."""
+
+    def __getattr__(self, name):
+        global _native
+        L = lib()
+        if not NATIVE_PATH.exists():
+            raise FileNotFoundError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2206_01299_amd.build` "
+                                    "(there is no fallback path)")
+        loader = importlib.machinery.ExtensionFileLoader("_native", str(NATIVE_PATH))
+        mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_native", loader))
+        loader.exec_module(mod)
+        mod.setup(Desc, Job, {n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in EXPORTS})
+        _native = mod
+        return getattr(mod, name)
+
+
+_native = _LoadNative()
+
+
 def version() -> str:
     return lib().aqsgd_version().decode()
 
@@ -226,6 +254,9 @@ def _raise(status: int):
 
 def encode(desc: Desc, act, sample_ids, m_buf, codes, scales, stream=None) -> None:
     """``aqsgd_encode``: updates ``m_buf`` in place, fills ``codes`` and ``scales``."""
+    rc = None if _debug_ids else _native.encode(desc, act, sample_ids, m_buf, codes, scales, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check(desc, rows=[(act, "act")], ids=sample_ids, m_buf=m_buf, codes=codes, scales=scales, stream=stream)
     _raise(lib().aqsgd_encode(ctypes.byref(desc), _dev(act, "act"), _dev(sample_ids, "sample_ids"),
                               _dev(m_buf, "m_buf"), _dev(codes, "codes"), _dev(scales, "scales"),
@@ -234,6 +265,9 @@ def encode(desc: Desc, act, sample_ids, m_buf, codes, scales, stream=None) -> No
 
 def decode(desc: Desc, codes, scales, sample_ids, m_buf, out, stream=None) -> None:
     """``aqsgd_decode``: updates ``m_buf`` in place, fills ``out``."""
+    rc = None if _debug_ids else _native.decode(desc, codes, scales, sample_ids, m_buf, out, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check(desc, rows=[(out, "out")], ids=sample_ids, m_buf=m_buf, codes=codes, scales=scales, stream=stream)
     _raise(lib().aqsgd_decode(ctypes.byref(desc), _dev(codes, "codes"), _dev(scales, "scales"),
                               _dev(sample_ids, "sample_ids"), _dev(m_buf, "m_buf"), _dev(out, "out"),
@@ -241,12 +275,18 @@ def decode(desc: Desc, codes, scales, sample_ids, m_buf, out, stream=None) -> No
 
 
 def grad_quant(desc: Desc, grad, codes, scales, stream=None) -> None:
+    rc = _native.grad_quant(desc, grad, codes, scales, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check(desc, rows=[(grad, "grad")], codes=codes, scales=scales)
     _raise(lib().aqsgd_grad_quant(ctypes.byref(desc), _dev(grad, "grad"), _dev(codes, "codes"),
                                   _dev(scales, "scales"), _stream(stream)))
 
 
 def grad_dequant(desc: Desc, codes, scales, out, stream=None) -> None:
+    rc = _native.grad_dequant(desc, codes, scales, out, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check(desc, rows=[(out, "out")], codes=codes, scales=scales)
     _raise(lib().aqsgd_grad_dequant(ctypes.byref(desc), _dev(codes, "codes"), _dev(scales, "scales"),
                                     _dev(out, "out"), _stream(stream)))
@@ -254,6 +294,9 @@ def grad_dequant(desc: Desc, codes, scales, out, stream=None) -> None:
 
 def seed(desc: Desc, act, sample_ids, m_buf, stream=None) -> None:
     """``aqsgd_seed``: uncompressed first visit, ``m_buf[sample_ids] <- act``."""
+    rc = None if _debug_ids else _native.seed(desc, act, sample_ids, m_buf, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check(desc, rows=[(act, "act")], ids=sample_ids, m_buf=m_buf, stream=stream)
     _raise(lib().aqsgd_seed(ctypes.byref(desc), _dev(act, "act"), _dev(sample_ids, "sample_ids"),
                             _dev(m_buf, "m_buf"), _stream(stream)))
@@ -266,24 +309,36 @@ def _copy_desc(desc: Desc) -> Desc:
 
 def encode_job(desc: Desc, act, sample_ids, m_buf, codes, scales) -> Job:
     """An ``aqsgd_encode`` call as one job of :func:`run_jobs` (the descriptor is copied)."""
+    job = None if _debug_ids else _native.encode_job(desc, act, sample_ids, m_buf, codes, scales)
+    if job is not None:
+        return job
     _check(desc, rows=[(act, "act")], ids=sample_ids, m_buf=m_buf, codes=codes, scales=scales)
     return Job(JOB_ENCODE, _copy_desc(desc), _dev(act, "act"), _dev(sample_ids, "sample_ids"),
                _dev(m_buf, "m_buf"), _dev(codes, "codes"), _dev(scales, "scales"), None)
 
 
 def decode_job(desc: Desc, codes, scales, sample_ids, m_buf, out) -> Job:
+    job = None if _debug_ids else _native.decode_job(desc, codes, scales, sample_ids, m_buf, out)
+    if job is not None:
+        return job
     _check(desc, rows=[(out, "out")], ids=sample_ids, m_buf=m_buf, codes=codes, scales=scales)
     return Job(JOB_DECODE, _copy_desc(desc), None, _dev(sample_ids, "sample_ids"), _dev(m_buf, "m_buf"),
                _dev(codes, "codes"), _dev(scales, "scales"), _dev(out, "out"))
 
 
 def grad_quant_job(desc: Desc, grad, codes, scales) -> Job:
+    job = _native.grad_quant_job(desc, grad, codes, scales)
+    if job is not None:
+        return job
     _check(desc, rows=[(grad, "grad")], codes=codes, scales=scales)
     return Job(JOB_GRAD_QUANT, _copy_desc(desc), _dev(grad, "grad"), None, None, _dev(codes, "codes"),
                _dev(scales, "scales"), None)
 
 
 def grad_dequant_job(desc: Desc, codes, scales, out) -> Job:
+    job = _native.grad_dequant_job(desc, codes, scales, out)
+    if job is not None:
+        return job
     _check(desc, rows=[(out, "out")], codes=codes, scales=scales)
     return Job(JOB_GRAD_DEQUANT, _copy_desc(desc), None, None, None, _dev(codes, "codes"),
                _dev(scales, "scales"), _dev(out, "out"))
@@ -312,6 +367,9 @@ def run_jobs(jobs, stream=None) -> None:
     """``aqsgd_run_jobs``: independent messages (built with the ``*_job`` helpers) in as few
     launches as possible.  The tensors the jobs point at must stay alive until the stream
     has run them, as for the single calls."""
+    rc = _native.run_jobs(jobs, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     arr = (Job * len(jobs))(*jobs)
     _raise(lib().aqsgd_run_jobs(arr, len(jobs), _stream(stream)))
 
@@ -320,6 +378,9 @@ def encode_seen(desc: Desc, act, sample_ids, m_buf, seen, stamp: int, first, cod
     """``aqsgd_encode_seen``: Algorithm 1's sender with the first-visit branch.  ``seen`` is an
     int32 tensor (one 32-bit word per sample, zero = never visited); ``stamp`` a non-zero
     32-bit number that no earlier call on this buffer has used."""
+    rc = None if _debug_ids else _native.encode_seen(desc, act, sample_ids, m_buf, seen, stamp, first, codes, scales, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check(desc, rows=[(act, "act")], ids=sample_ids, m_buf=m_buf, codes=codes, scales=scales, stream=stream)
     _want(seen, "seen", torch.int32, desc.n_samples, exact=True)
     _want(first, "first", torch.int32, desc.batch, exact=True)
@@ -331,6 +392,9 @@ def encode_seen(desc: Desc, act, sample_ids, m_buf, seen, stamp: int, first, cod
 
 def decode_seen(desc: Desc, codes, scales, full, sample_ids, m_buf, seen, stamp: int, out, stream=None) -> None:
     """``aqsgd_decode_seen``: Algorithm 1's receiver with the first-visit branch."""
+    rc = None if _debug_ids else _native.decode_seen(desc, codes, scales, full, sample_ids, m_buf, seen, stamp, out, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check(desc, rows=[(out, "out"), (full, "full")], ids=sample_ids, m_buf=m_buf, codes=codes,
            scales=scales, stream=stream)
     _want(seen, "seen", torch.int32, desc.n_samples, exact=True)
@@ -353,6 +417,9 @@ def _check_lowbit_store(desc: Desc, m_bits: int, m_codes, m_scales) -> None:
 def encode_lowbit(desc: Desc, m_bits: int, act, sample_ids, m_codes, m_scales, codes, scales,
                   stream=None) -> None:
     """``aqsgd_encode_lowbit``: sender with z-bit storage of the previous messages."""
+    rc = None if _debug_ids else _native.encode_lowbit(desc, m_bits, act, sample_ids, m_codes, m_scales, codes, scales, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check(desc, rows=[(act, "act")], ids=sample_ids, codes=codes, scales=scales, stream=stream)
     _check_lowbit_store(desc, m_bits, m_codes, m_scales)
     _raise(lib().aqsgd_encode_lowbit(ctypes.byref(desc), m_bits, _dev(act, "act"),
@@ -364,6 +431,9 @@ def encode_lowbit(desc: Desc, m_bits: int, act, sample_ids, m_codes, m_scales, c
 def decode_lowbit(desc: Desc, m_bits: int, codes, scales, sample_ids, m_codes, m_scales, out,
                   stream=None) -> None:
     """``aqsgd_decode_lowbit``: receiver with z-bit storage of the previous messages."""
+    rc = None if _debug_ids else _native.decode_lowbit(desc, m_bits, codes, scales, sample_ids, m_codes, m_scales, out, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check(desc, rows=[(out, "out")], ids=sample_ids, codes=codes, scales=scales, stream=stream)
     _check_lowbit_store(desc, m_bits, m_codes, m_scales)
     _raise(lib().aqsgd_decode_lowbit(ctypes.byref(desc), m_bits, _dev(codes, "codes"),
@@ -392,6 +462,9 @@ def _check_topk(desc: Desc, keep: int, rows, what: str, bitmap, codes, scales) -
 
 def grad_topk_quant(desc: Desc, keep: int, grad, bitmap, codes, scales, stream=None) -> None:
     """``aqsgd_grad_topk_quant``: the ``keep`` largest entries per group, at 8 bits."""
+    rc = _native.grad_topk_quant(desc, keep, grad, bitmap, codes, scales, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check_topk(desc, keep, grad, "grad", bitmap, codes, scales)
     _raise(lib().aqsgd_grad_topk_quant(ctypes.byref(desc), keep, _dev(grad, "grad"), _dev(bitmap, "bitmap"),
                                        _dev(codes, "codes"), _dev(scales, "scales"), _stream(stream)))
@@ -399,6 +472,9 @@ def grad_topk_quant(desc: Desc, keep: int, grad, bitmap, codes, scales, stream=N
 
 def grad_topk_dequant(desc: Desc, keep: int, bitmap, codes, scales, out, stream=None) -> None:
     """``aqsgd_grad_topk_dequant``: kept entries reconstructed, the rest +0."""
+    rc = _native.grad_topk_dequant(desc, keep, bitmap, codes, scales, out, stream)
+    if rc is not None:
+        return _raise(rc) if rc else None
     _check_topk(desc, keep, out, "out", bitmap, codes, scales)
     _raise(lib().aqsgd_grad_topk_dequant(ctypes.byref(desc), keep, _dev(bitmap, "bitmap"),
                                          _dev(codes, "codes"), _dev(scales, "scales"), _dev(out, "out"),

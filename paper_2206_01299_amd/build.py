@@ -1,4 +1,5 @@
-"""Build step: compile csrc/*.hip for gfx950 into ``libaqsgd.so`` beside this file.
+"""Build step: compile csrc/*.hip for gfx950 into ``libaqsgd.so`` beside this file, and
+csrc/binding_native.cpp (host code, against torch's headers) into ``_native.so``.
 
 Run as ``python -m paper_2206_01299_amd.build``.  hipcc cross-compiles without a
 GPU.  Flags that matter for correctness:
@@ -10,6 +11,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
@@ -18,6 +20,7 @@ CSRC = HERE / "csrc"
 INCLUDE = HERE.parent / "include"
 OBJDIR = HERE / "_build"
 LIB = HERE / "libaqsgd.so"
+NATIVE = HERE / "_native.so"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -47,18 +50,33 @@ def _compile(src: Path) -> Path:
     return obj
 
 
+def _build_native() -> None:
+    import torch
+    t = Path(torch.__file__).resolve().parent
+    tmp = NATIVE.with_suffix(f".tmp{os.getpid()}.so")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", f"-I{sysconfig.get_paths()['include']}", f"-I{t}/include",
+           f"-I{t}/include/torch/csrc/api/include", "-I/opt/rocm/include", f"-I{INCLUDE}",
+           str(CSRC / "binding_native.cpp"), "-o", str(tmp),
+           f"-L{t}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]   # loaded by `import torch`
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, NATIVE)
+
+
 def build(verbose: bool = True) -> Path:
     OBJDIR.mkdir(exist_ok=True)
     srcs = sources()
     jobs = min(len(srcs), int(os.environ.get("MAX_JOBS", "8")), 16)
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        native = pool.submit(_build_native)
         objs = list(pool.map(_compile, srcs))
+        native.result()
     tmp = LIB.with_suffix(f".tmp{os.getpid()}.so")
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *map(str, objs), "-o", str(tmp)],
                    check=True)
     os.replace(tmp, LIB)
     if verbose:
-        print(f"built {LIB} from {len(srcs)} sources")
+        print(f"built {LIB} from {len(srcs)} sources, and {NATIVE.name}")
     return LIB
 
 
