@@ -5,6 +5,8 @@ Run as ``python -m paper_2206_01299_amd.build``.  hipcc cross-compiles without a
 GPU.  Flags that matter for correctness:
   -ffp-contract=off   one rounding per written operation (the wire format)
   -packed-fp32-ops off  no packed binary32 instructions
+and for launches:
+  -amdgpu-kernarg-preload-count=14  a kernel's leading plain arguments arrive in scalar registers
 """
 from __future__ import annotations
 
@@ -28,6 +30,7 @@ FLAGS = [
     "-ffp-contract=off", "-fno-fast-math", "-fhip-fp32-correctly-rounded-divide-sqrt",
     "-fno-gpu-flush-denormals-to-zero",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-Wall", "-Wno-unused-function", "-Wno-unknown-warning-option",
     f"-I{INCLUDE}", f"-I{CSRC}",
 ]

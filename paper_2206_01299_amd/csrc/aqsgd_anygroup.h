@@ -1,9 +1,9 @@
 // Kernels for groups outside the job kernels' range (one message per launch):
 //
-//   odd groups    8 elements or more but no whole number of chunks: the team bodies of
-//                 aqsgd_kernels.h with ODD offsets (a group's last chunk starts eight
-//                 elements before its end), and a flat dequantising body whose last chunk
-//                 of a group stores only the elements that are its own
+//   odd groups    8 elements or more but no whole number of chunks: the flat dequantising
+//                 body whose last chunk of a group stores only the elements that are its
+//                 own (the quantising side is the team bodies with ODD offsets, launched
+//                 from aqsgd_single.h)
 //   large groups  more than a workgroup's registers hold (over 32768 elements): the maximum
 //                 is taken by many workgroups into the message's scale word, and a second
 //                 pass over the same elements quantises with it
@@ -12,34 +12,9 @@
 #pragma once
 
 #include "aqsgd_kernels.h"
+#include "aqsgd_single.h"
 
 namespace aqsgd {
-
-// ---------------------------------------------------------------------------
-// Odd groups, quantising side.  Bound by memory like the job kernels: the repeated
-// elements of a group's last chunk are 7 at most.  (One thread per group with an access
-// per element, which these groups used to take, leaves one lane per group busy and its
-// accesses in a chain: float16 rows of 1020, 1000 of them, forward and backward in four
-// calls took 2390 us, with these kernels 34 us.)
-// ---------------------------------------------------------------------------
-template <int DT, int BITS, int ROUND, int TEAM, int CPL>
-__device__ __forceinline__ void quant_odd_bits(const QuantJob& a, float* wave_max) {
-    if (a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, true>(a, blockIdx.x, blockIdx.y, wave_max);
-    else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false, true>(a, blockIdx.x, blockIdx.y, wave_max);
-}
-
-template <int DT, int ROUND, int TEAM, int CPL>
-__global__ __launch_bounds__((TEAM > kWave ? TEAM : kBlock))
-void quant_odd_kernel(const QuantJob a) {
-    constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
-    [[maybe_unused]] __shared__ float wave_max[kThreads / kWave];
-    switch (a.bits) {                                    // 3-bit groups are always whole chunks
-    case 2: quant_odd_bits<DT, 2, ROUND, TEAM, CPL>(a, wave_max); break;
-    case 4: quant_odd_bits<DT, 4, ROUND, TEAM, CPL>(a, wave_max); break;
-    case 6: quant_odd_bits<DT, 6, ROUND, TEAM, CPL>(a, wave_max); break;
-    default: quant_odd_bits<DT, 8, ROUND, TEAM, CPL>(a, wave_max); break;
-    }
-}
 
 // ---------------------------------------------------------------------------
 // One 16-byte piece of elements (eight, or four of binary32) and its codes, at any address.
@@ -107,7 +82,7 @@ __device__ __forceinline__ void unpack_piece(uint64_t w, float (&q)[N]) {
 constexpr int kOddUnroll = 2;
 constexpr int64_t kMaxOddPieces = int64_t{1} << 31;      // pieces of a sample: 32-bit indices with room for a step
 
-template <int DT, int BITS, bool HAS_BUF>
+template <int DT, int BITS, bool HAS_BUF, bool LOOPS>
 __device__ __forceinline__ void dequant_odd_body(const DequantJob& a) {
     using P = Piece<DT, BITS>;
     constexpr int N = P::elems;
@@ -118,7 +93,7 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a) {
     const uint32_t pps = static_cast<uint32_t>(a.gps) * ppg;                     // pieces per sample
     const uint32_t last_at = static_cast<uint32_t>(a.group) - N;                 // first element of a group's last piece
     const int own_last = a.group - N * static_cast<int>(ppg - 1);
-    for (int i = blockIdx.y; i < a.batch; i += gridDim.y) {
+    for (int i = blockIdx.y; !LOOPS || i < a.batch; i += a.grid_y) {
         const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
         const int64_t out0 = static_cast<int64_t>(i) * a.n_per;
         char* out_s = static_cast<char*>(a.out) + out0 * kEB;
@@ -133,7 +108,7 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a) {
                 if (fresh && blockIdx.x == 0 && threadIdx.x == 0) a.seen[row] = a.stamp;   // one writer per sample
             }
         }
-        for (uint32_t base = blockIdx.x * kStep; base < pps; base += gridDim.x * kStep) {
+        for (uint32_t base = blockIdx.x * kStep; !LOOPS || base < pps; base += a.grid_x * kStep) {
             const uint32_t g0 = base / ppg;              // uniform; per lane a small correction
             const uint32_t r0 = base - g0 * ppg;
             uint64_t w[kOddUnroll];
@@ -191,24 +166,31 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a) {
                     store_piece<DT, N>(out_s + at[u] * kEB, v);
                 }
             }
+            if constexpr (!LOOPS) break;
         }
+        if constexpr (!LOOPS) break;
     }
 }
 
-template <int DT, int BITS>
+template <int DT, int BITS, bool LOOPS>
 __device__ __forceinline__ void dequant_odd_bits(const DequantJob& a) {
-    if (a.m_buf) dequant_odd_body<DT, BITS, true>(a);
-    else dequant_odd_body<DT, BITS, false>(a);
+    if (a.m_buf) dequant_odd_body<DT, BITS, true, LOOPS>(a);
+    else dequant_odd_body<DT, BITS, false, LOOPS>(a);
 }
 
-template <int DT>
+template <int DT, bool LOOPS>
 __global__ __launch_bounds__(kBlock)
-void dequant_odd_kernel(const DequantJob a) {
-    switch (a.bits) {
-    case 2: dequant_odd_bits<DT, 2>(a); break;
-    case 4: dequant_odd_bits<DT, 4>(a); break;
-    case 6: dequant_odd_bits<DT, 6>(a); break;
-    default: dequant_odd_bits<DT, 8>(a); break;
+void dequant_odd_kernel(AQSGD_DEQUANT_ARGS) {
+    DequantJob a;
+    a.codes = codes; a.scales = scales; a.ids = ids; a.m_buf = m_buf; a.out = out; a.full = full;
+    a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
+    a.grid_x = grid_x; a.grid_y = grid_y;
+    a.seen = seen; a.stamp = stamp;
+    switch (bits) {
+    case 2: dequant_odd_bits<DT, 2, LOOPS>(a); break;
+    case 4: dequant_odd_bits<DT, 4, LOOPS>(a); break;
+    case 6: dequant_odd_bits<DT, 6, LOOPS>(a); break;
+    default: dequant_odd_bits<DT, 8, LOOPS>(a); break;
     }
 }
 
@@ -412,40 +394,15 @@ void large_quant_kernel(const QuantJob a, const LargeGeom geom) {
 }
 
 // Per-dtype pieces (defined by AQSGD_INSTANTIATE_ANYGROUP_DTYPE in the dtype's .hip file).
-template <int DT> hipError_t launch_quant_odd_dt(int rounding, int shape, const QuantJob& a, hipStream_t stream);
-template <int DT> hipError_t launch_dequant_odd_dt(const DequantJob& a, hipStream_t stream);
+template <int DT> hipError_t launch_dequant_odd_dt(bool covers, const DequantJob& a, hipStream_t stream);
 template <int DT> hipError_t launch_quant_large_dt(int rounding, const QuantJob& a, const LargeGeom& geom,
                                                    hipStream_t stream);
 
 // ---- launch tables (instantiated per dtype in aqsgd_anygroup_<dtype>.hip) --------------
-template <int DT, int ROUND>
-static hipError_t launch_odd_shape(int shape, const QuantJob& a, hipStream_t s) {
-    const dim3 grid(a.grid_x, a.grid_y);
-    switch (shape) {
-    case kTeam8x1:    return launch_kernel(quant_odd_kernel<DT, ROUND, 8, 1>, grid, dim3(kBlock), s, a);
-    case kTeam16x1:   return launch_kernel(quant_odd_kernel<DT, ROUND, 16, 1>, grid, dim3(kBlock), s, a);
-    case kTeam32x1:   return launch_kernel(quant_odd_kernel<DT, ROUND, 32, 1>, grid, dim3(kBlock), s, a);
-    case kTeam64x1:   return launch_kernel(quant_odd_kernel<DT, ROUND, 64, 1>, grid, dim3(kBlock), s, a);
-    case kTeam64x2:   return launch_kernel(quant_odd_kernel<DT, ROUND, 64, 2>, grid, dim3(kBlock), s, a);
-    case kTeam64x3:   return launch_kernel(quant_odd_kernel<DT, ROUND, 64, 3>, grid, dim3(kBlock), s, a);
-    case kTeam64x4:   return launch_kernel(quant_odd_kernel<DT, ROUND, 64, 4>, grid, dim3(kBlock), s, a);
-    case kTeam256x2:  return launch_kernel(quant_odd_kernel<DT, ROUND, 256, 2>, grid, dim3(256), s, a);
-    case kTeam256x4:  return launch_kernel(quant_odd_kernel<DT, ROUND, 256, 4>, grid, dim3(256), s, a);
-    case kTeam1024x2: return launch_kernel(quant_odd_kernel<DT, ROUND, 1024, 2>, grid, dim3(1024), s, a);
-    case kTeam1024x4: return launch_kernel(quant_odd_kernel<DT, ROUND, 1024, 4>, grid, dim3(1024), s, a);
-    default:          return hipErrorInvalidValue;
-    }
-}
-
 template <int DT>
-hipError_t launch_quant_odd_dt(int rounding, int shape, const QuantJob& a, hipStream_t s) {
-    return rounding == AQSGD_ROUND_STOCHASTIC ? launch_odd_shape<DT, AQSGD_ROUND_STOCHASTIC>(shape, a, s)
-                                              : launch_odd_shape<DT, AQSGD_ROUND_NEAREST>(shape, a, s);
-}
-
-template <int DT>
-hipError_t launch_dequant_odd_dt(const DequantJob& a, hipStream_t s) {
-    return launch_kernel(dequant_odd_kernel<DT>, dim3(a.grid_x, a.grid_y), dim3(kBlock), s, a);
+hipError_t launch_dequant_odd_dt(bool covers, const DequantJob& a, hipStream_t s) {
+    return covers ? launch_dequant_with(dequant_odd_kernel<DT, false>, a, s)
+                  : launch_dequant_with(dequant_odd_kernel<DT, true>, a, s);
 }
 
 template <int DT>
@@ -463,8 +420,7 @@ hipError_t launch_quant_large_dt(int rounding, const QuantJob& a, const LargeGeo
 }
 
 #define AQSGD_INSTANTIATE_ANYGROUP_DTYPE(DT)                                                          \
-    template hipError_t launch_quant_odd_dt<DT>(int, int, const QuantJob&, hipStream_t);              \
-    template hipError_t launch_dequant_odd_dt<DT>(const DequantJob&, hipStream_t);                    \
+    template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);                   \
     template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t);
 
 }  // namespace aqsgd

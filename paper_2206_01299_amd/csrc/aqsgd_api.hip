@@ -8,14 +8,16 @@
 #include "aqsgd_anygroup.h"
 #include "aqsgd_kernels.h"
 #include "aqsgd_lowbit.h"
+#include "aqsgd_single.h"
 #include "aqsgd_topk.h"
 
 namespace aqsgd {
 
 // Instantiated in the dtypes' own translation units.
 #define AQSGD_EXTERN_DTYPE(DT)                                                                        \
-    extern template hipError_t launch_quant_odd_dt<DT>(int, int, const QuantJob&, hipStream_t);       \
-    extern template hipError_t launch_dequant_odd_dt<DT>(const DequantJob&, hipStream_t);             \
+    extern template hipError_t launch_quant_single_dt<DT>(int, int, bool, const QuantJob&, hipStream_t); \
+    extern template hipError_t launch_dequant_single_dt<DT>(int, const DequantJob&, hipStream_t);     \
+    extern template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);       \
     extern template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
     extern template hipError_t launch_lowbit_dt<DT>(int, int, int, bool, LaunchGeom, const LowbitArgs&, hipStream_t);
 AQSGD_EXTERN_DTYPE(AQSGD_F32)
@@ -58,19 +60,27 @@ hipError_t launch_dequant_anyshape(int dtype, const DequantJob& a, hipStream_t s
     }
 }
 
-hipError_t launch_quant_odd(int dtype, int rounding, int shape, const QuantJob& a, hipStream_t s) {
+hipError_t launch_quant_single(int dtype, int rounding, int shape, bool covers, const QuantJob& a, hipStream_t s) {
     switch (dtype) {
-    case AQSGD_F32:  return launch_quant_odd_dt<AQSGD_F32>(rounding, shape, a, s);
-    case AQSGD_F16:  return launch_quant_odd_dt<AQSGD_F16>(rounding, shape, a, s);
-    case AQSGD_BF16: return launch_quant_odd_dt<AQSGD_BF16>(rounding, shape, a, s);
+    case AQSGD_F32:  return launch_quant_single_dt<AQSGD_F32>(rounding, shape, covers, a, s);
+    case AQSGD_F16:  return launch_quant_single_dt<AQSGD_F16>(rounding, shape, covers, a, s);
+    case AQSGD_BF16: return launch_quant_single_dt<AQSGD_BF16>(rounding, shape, covers, a, s);
     default:         return hipErrorInvalidValue;
     }
 }
-hipError_t launch_dequant_odd(int dtype, const DequantJob& a, hipStream_t s) {
+hipError_t launch_dequant_single(int dtype, int unroll, const DequantJob& a, hipStream_t s) {
     switch (dtype) {
-    case AQSGD_F32:  return launch_dequant_odd_dt<AQSGD_F32>(a, s);
-    case AQSGD_F16:  return launch_dequant_odd_dt<AQSGD_F16>(a, s);
-    case AQSGD_BF16: return launch_dequant_odd_dt<AQSGD_BF16>(a, s);
+    case AQSGD_F32:  return launch_dequant_single_dt<AQSGD_F32>(unroll, a, s);
+    case AQSGD_F16:  return launch_dequant_single_dt<AQSGD_F16>(unroll, a, s);
+    case AQSGD_BF16: return launch_dequant_single_dt<AQSGD_BF16>(unroll, a, s);
+    default:         return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_dequant_odd(int dtype, bool covers, const DequantJob& a, hipStream_t s) {
+    switch (dtype) {
+    case AQSGD_F32:  return launch_dequant_odd_dt<AQSGD_F32>(covers, a, s);
+    case AQSGD_F16:  return launch_dequant_odd_dt<AQSGD_F16>(covers, a, s);
+    case AQSGD_BF16: return launch_dequant_odd_dt<AQSGD_BF16>(covers, a, s);
     default:         return hipErrorInvalidValue;
     }
 }
@@ -340,16 +350,24 @@ LargeGeom large_geometry(const QuantJob& a) {
     return g;
 }
 
+// The rectangle of a message launched by itself: one workgroup for every sample and step if
+// that stays below `cap` and the grid's second dimension, which is what this tells.
+template <typename Job>
+bool one_step_grid(Job& a, int64_t units, int64_t units_per_block, int64_t cap) {
+    const LaunchGeom g = geometry(units, units_per_block, a.batch, cap);
+    a.grid_x = g.grid_x; a.grid_y = g.grid_y;
+    return g.grid_y == static_cast<uint32_t>(a.batch) && static_cast<int64_t>(g.grid_x) * units_per_block >= units;
+}
+
 // A quantising message outside the job kernels' range.
 hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_blocks, hipStream_t stream) {
     QuantJob& a = p.job;
     LaunchGeom g;
     switch (p.route) {
     case Route::kOdd: {
-        const int64_t budget = launch_budget(p.shape, launch_blocks);
-        g = geometry(a.gps, groups_per_block_step(p.shape), a.batch, budget < max_blocks ? budget : max_blocks);
-        a.grid_x = g.grid_x; a.grid_y = g.grid_y;
-        return launch_quant_odd(p.dtype, p.rounding, p.shape, a, stream);
+        const int64_t cap = launch_blocks > 0 && launch_blocks < max_blocks ? launch_blocks : max_blocks;
+        const bool covers = one_step_grid(a, a.gps, groups_per_block_step(p.shape), cap);
+        return launch_quant_single(p.dtype, p.rounding, p.shape, covers, a, stream);
     }
     case Route::kLarge: {
         const LargeGeom lg = large_geometry(a);
@@ -368,10 +386,9 @@ hipError_t launch_dequant_alone(DequantPlan& p, int64_t max_blocks, hipStream_t 
     DequantJob& a = p.job;
     if (p.route == Route::kOdd) {
         const int64_t piece = p.dtype == AQSGD_F32 ? kUnit : kChunk;
-        const LaunchGeom g = geometry(a.gps * ((a.group + piece - 1) / piece), static_cast<int64_t>(kBlock) * kOddUnroll,
-                                      a.batch, max_blocks);
-        a.grid_x = g.grid_x; a.grid_y = g.grid_y;
-        return launch_dequant_odd(p.dtype, a, stream);
+        const bool covers = one_step_grid(a, a.gps * ((a.group + piece - 1) / piece),
+                                          static_cast<int64_t>(kBlock) * kOddUnroll, max_blocks);
+        return launch_dequant_odd(p.dtype, covers, a, stream);
     }
     const LaunchGeom g = geometry(a.gps, kBlock, a.batch, max_blocks);
     a.grid_x = g.grid_x; a.grid_y = g.grid_y;
@@ -381,7 +398,8 @@ hipError_t launch_dequant_alone(DequantPlan& p, int64_t max_blocks, hipStream_t 
 // The launches of a set of independent messages: quantising jobs that share dtype,
 // rounding mode and team shape go into one grid, together with the dequantising
 // jobs of that dtype that are still waiting; dequantising jobs without such a host get a
-// grid of their own; jobs that need the any-shape kernels are launched one by one.
+// grid of their own; jobs outside the shared launches' range are launched one by one, and so
+// is a message that comes alone (its kernel opens sooner, see aqsgd_single.h).
 int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipStream_t stream) {
     // a job's workgroup numbers must be exact in binary32 (place_in_job)
     const int64_t knob = max_blocks_knob().load(std::memory_order_relaxed);
@@ -391,6 +409,21 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
     hipError_t err = hipSuccess;
 
     const int64_t launch_blocks = launch_blocks_knob().load(std::memory_order_relaxed);
+    // A message that comes alone takes the single-message kernels, which open sooner (see
+    // aqsgd_single.h); their workgroups do one step each, so one that would pass the caps on a
+    // grid (or one asked for in a sweep) goes out as a table of one instead.
+    if (qs.size() + ds.size() == 1 && launch_blocks == 0) {
+        if (!qs.empty() && qs[0].route == Route::kJob &&
+            one_step_grid(qs[0].job, qs[0].job.gps, groups_per_block_step(qs[0].shape), max_blocks)) {
+            err = launch_quant_single(qs[0].dtype, qs[0].rounding, qs[0].shape, true, qs[0].job, stream);
+            return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
+        }
+        if (!ds.empty() && ds[0].route == Route::kJob &&
+            one_step_grid(ds[0].job, ds[0].job.cps, static_cast<int64_t>(kBlock) * unroll, max_blocks)) {
+            err = launch_dequant_single(ds[0].dtype, unroll, ds[0].job, stream);
+            return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
+        }
+    }
     auto add_dequant = [&](JobTable& t, int dtype) {
         for (size_t k = 0; k < ds.size() && t.n_dequant < kMaxDequantJobs; ++k) {
             if (d_done[k] || ds[k].route != Route::kJob || ds[k].dtype != dtype) continue;

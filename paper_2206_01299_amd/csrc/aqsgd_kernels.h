@@ -179,24 +179,25 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
     // ---- issue every load of the groups -----------------------------------------
     int64_t goff[NG];                                    // element offsets within the sample
     Raw<DT> ra[NG][CPL], rm[NG][CPL];
+    // (the activations first: only the previous messages wait for the sample id)
 #pragma unroll
     for (int u = 0; u < NG; ++u) {
         goff[u] = (g0 + u * gstride) * a.group;
+        const char* src_g = src_s + goff[u] * kEB;
 #pragma unroll
         for (int k = 0; k < CPL; ++k) {
-            const char* src_g = src_s + goff[u] * kEB;
-            const char* m_g = HAS_BUF ? m_s + goff[u] * kEB : nullptr;
-            if constexpr (kUnits) {
-                const uint32_t a0 = Unit::elem(ua[k]) * kEB, b0 = Unit::elem(ub[k]) * kEB;
-                ra[u][k] = load_units<ODD>(src_g + a0, src_g + b0);
-                if constexpr (HAS_BUF) rm[u][k] = load_units<ODD>(m_g + a0, m_g + b0);
-                else rm[u][k] = zero_raw<DT>();
-            } else {
-                const uint32_t c0 = Chunk::elem(cc[k]) * kEB;
-                ra[u][k] = load_chunk<DT, ODD>(src_g + c0);
-                if constexpr (HAS_BUF) rm[u][k] = load_chunk<DT, ODD>(m_g + c0);
-                else rm[u][k] = zero_raw<DT>();
-            }
+            if constexpr (kUnits) ra[u][k] = load_units<ODD>(src_g + Unit::elem(ua[k]) * kEB, src_g + Unit::elem(ub[k]) * kEB);
+            else ra[u][k] = load_chunk<DT, ODD>(src_g + Chunk::elem(cc[k]) * kEB);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NG; ++u) {
+        const char* m_g = HAS_BUF ? m_s + goff[u] * kEB : nullptr;
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) {
+            if constexpr (!HAS_BUF) rm[u][k] = zero_raw<DT>();
+            else if constexpr (kUnits) rm[u][k] = load_units<ODD>(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB);
+            else rm[u][k] = load_chunk<DT, ODD>(m_g + Chunk::elem(cc[k]) * kEB);
         }
     }
     // Keep all of the loads ahead of the first use: the scheduler would otherwise
@@ -326,8 +327,10 @@ __device__ __forceinline__ void copy_team_group(const QuantJob& a, const char* s
     }
 }
 
-// Workgroup (bx, by) of a quantising job's grid_x x grid_y rectangle.
-template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF, bool ODD = false>
+// Workgroup (bx, by) of a quantising job's grid_x x grid_y rectangle.  LOOPS: the rectangle may
+// be smaller than the message; without, every workgroup has exactly one sample and one step,
+// and nothing is kept for a next one.
+template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF, bool ODD = false, bool LOOPS = true>
 __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
     constexpr bool kMultiWave = TEAM > kWave;
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
@@ -359,7 +362,7 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
         ub[k] = static_cast<uint32_t>(ODD ? min(kUnit * u1, a.group - kUnit) : min(u1, 2 * a.cpg - 1));
     }
 
-    for (int i = by; i < a.batch; i += a.grid_y) {
+    for (int i = by; !LOOPS || i < a.batch; i += a.grid_y) {
         const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
         const int64_t src0 = static_cast<int64_t>(i) * a.n_per;      // flat offset of sample i
         const char* src_s = static_cast<const char*>(a.src) + src0 * kEB;
@@ -379,31 +382,31 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
         }
 
         // One step of the workgroup: kGroupsPerStep consecutive groups, kGroupsPerTeam per team.
-        for (int64_t gbase = static_cast<int64_t>(bx) * kGroupsPerStep; gbase < a.gps;
+        for (int64_t gbase = static_cast<int64_t>(bx) * kGroupsPerStep; !LOOPS || gbase < a.gps;
              gbase += static_cast<int64_t>(a.grid_x) * kGroupsPerStep) {
-            if constexpr (kGroupsPerTeam > 1) {
-                if (!fresh && gbase + kGroupsPerStep <= a.gps) {         // uniform over the workgroup
-                    quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, kGroupsPerTeam, ODD>(
-                        a, src_s, m_s, codes_s, scales_s, src0, gbase + team, kTeamsPerBlock, cc, ua, ub,
-                        lane_in_team, wave_max);
-                    continue;
-                }
-            }
-            // a sample's ragged last step, first visits, and the shapes with one group per team
+            if (kGroupsPerTeam > 1 && !fresh && gbase + kGroupsPerStep <= a.gps) {   // uniform over the workgroup
+                quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, kGroupsPerTeam, ODD>(
+                    a, src_s, m_s, codes_s, scales_s, src0, gbase + team, kTeamsPerBlock, cc, ua, ub,
+                    lane_in_team, wave_max);
+            } else {
+                // a sample's ragged last step, first visits, and the shapes with one group per team
 #pragma unroll 1
-            for (int u = 0; u < kGroupsPerTeam; ++u) {
-                const int64_t g = gbase + u * kTeamsPerBlock + team;     // uniform over the team
-                if (g >= a.gps) continue;
-                if constexpr (HAS_BUF) {
-                    if (fresh) {                         // uniform over the workgroup
-                        copy_team_group<DT, BITS, TEAM, CPL, ODD>(a, src_s, m_s, g, cc, ua, ub);
-                        continue;
+                for (int u = 0; u < kGroupsPerTeam; ++u) {
+                    const int64_t g = gbase + u * kTeamsPerBlock + team;     // uniform over the team
+                    if (g >= a.gps) continue;
+                    if constexpr (HAS_BUF) {
+                        if (fresh) {                     // uniform over the workgroup
+                            copy_team_group<DT, BITS, TEAM, CPL, ODD>(a, src_s, m_s, g, cc, ua, ub);
+                            continue;
+                        }
                     }
+                    quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, 1, ODD>(
+                        a, src_s, m_s, codes_s, scales_s, src0, g, 0, cc, ua, ub, lane_in_team, wave_max);
                 }
-                quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, 1, ODD>(a, src_s, m_s, codes_s, scales_s, src0,
-                                                                              g, 0, cc, ua, ub, lane_in_team, wave_max);
             }
+            if constexpr (!LOOPS) break;
         }
+        if constexpr (!LOOPS) break;
     }
 }
 
@@ -413,7 +416,7 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
 // workgroup step plus a small per-lane correction.  THREADS is the size of the
 // workgroup the body runs in (the hosting kernel's).
 // ---------------------------------------------------------------------------
-template <int DT, int BITS, int UNROLL, bool HAS_BUF, int THREADS>
+template <int DT, int BITS, int UNROLL, bool HAS_BUF, int THREADS, bool LOOPS>
 __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t bx, uint32_t by) {
     constexpr int kEB = ElemBytes<DT>::value;
     constexpr int kChunkBytes = kChunk * kEB;
@@ -421,7 +424,7 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
     const uint32_t cpg = static_cast<uint32_t>(a.cpg);
     const float rcp_cpg = 1.0f / static_cast<float>(cpg);
     const uint32_t cps = static_cast<uint32_t>(a.cps);
-    for (int i = by; i < a.batch; i += a.grid_y) {
+    for (int i = by; !LOOPS || i < a.batch; i += a.grid_y) {
         const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
         const int64_t out0 = static_cast<int64_t>(i) * a.n_per;
         char* out_s = static_cast<char*>(a.out) + out0 * kEB;
@@ -440,12 +443,13 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
                         store_raw_at<DT>(m_s + static_cast<uint64_t>(c) * kChunkBytes, v);
                         store_raw_at<DT>(out_s + static_cast<uint64_t>(c) * kChunkBytes, v);
                     }
-                    continue;
+                    if constexpr (!LOOPS) return;
+                    else continue;
                 }
             }
         }
 
-        for (uint32_t cbase = bx * kStep; cbase < cps; cbase += a.grid_x * kStep) {
+        for (uint32_t cbase = bx * kStep; !LOOPS || cbase < cps; cbase += a.grid_x * kStep) {
             // group and position of the step's first chunk (uniform), then per lane
             const uint32_t g0 = cbase / cpg;
             const uint32_t r0 = cbase - g0 * cpg;
@@ -494,7 +498,9 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
                     store_raw_at<DT>(out_s + static_cast<uint64_t>(cs[u]) * kChunkBytes, packed);
                 }
             }
+            if constexpr (!LOOPS) break;
         }
+        if constexpr (!LOOPS) break;
     }
 }
 
@@ -503,14 +509,14 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
 // consecutive 16 bytes of m, out and, b/2 bytes each, of the codes.
 constexpr int64_t kMaxUnitChunks = int64_t{1} << 30;     // unit indices of a sample fit 32 bits
 
-template <int BITS, int UNITS, bool HAS_BUF, int THREADS>
+template <int BITS, int UNITS, bool HAS_BUF, int THREADS, bool LOOPS>
 __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t bx, uint32_t by) {
     constexpr int kUnitBytes = kUnit * 4;
     constexpr uint32_t kStep = THREADS * UNITS;
     const uint32_t upg = 2u * static_cast<uint32_t>(a.cpg);              // units per group
     const float rcp_upg = 1.0f / static_cast<float>(upg);
     const uint32_t ups = 2u * static_cast<uint32_t>(a.cps);              // units per sample
-    for (int i = by; i < a.batch; i += a.grid_y) {
+    for (int i = by; !LOOPS || i < a.batch; i += a.grid_y) {
         const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
         const int64_t out0 = static_cast<int64_t>(i) * a.n_per;
         char* out_s = static_cast<char*>(a.out) + out0 * 4;
@@ -530,12 +536,13 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
                         store16_through(m_s + static_cast<uint64_t>(u) * kUnitBytes, v);
                         store16_through(out_s + static_cast<uint64_t>(u) * kUnitBytes, v);
                     }
-                    continue;
+                    if constexpr (!LOOPS) return;
+                    else continue;
                 }
             }
         }
 
-        for (uint32_t ubase = bx * kStep; ubase < ups; ubase += a.grid_x * kStep) {
+        for (uint32_t ubase = bx * kStep; !LOOPS || ubase < ups; ubase += a.grid_x * kStep) {
             const uint32_t g0 = ubase / upg;
             const uint32_t r0 = ubase - g0 * upg;
             uint32_t w[UNITS];
@@ -581,33 +588,35 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
                     store16_through(out_s + static_cast<uint64_t>(us[u]) * kUnitBytes, v);
                 }
             }
+            if constexpr (!LOOPS) break;
         }
+        if constexpr (!LOOPS) break;
     }
 }
 
 // One dequantising job in a workgroup of THREADS lanes: the body for its bit width
 // and for with / without previous messages.
-template <int DT, int BITS, int UNROLL, int THREADS>
+template <int DT, int BITS, int UNROLL, int THREADS, bool LOOPS>
 __device__ __forceinline__ void dequant_job_bits(const DequantJob& a, uint32_t bx, uint32_t by) {
     if constexpr (UnitLayout<DT, BITS>::value) {
         if (a.cps <= kMaxUnitChunks) {                   // else the unit index would pass 32 bits
-            if (a.m_buf) dequant_units_body<BITS, 2 * UNROLL, true, THREADS>(a, bx, by);
-            else dequant_units_body<BITS, 2 * UNROLL, false, THREADS>(a, bx, by);
+            if (a.m_buf) dequant_units_body<BITS, 2 * UNROLL, true, THREADS, LOOPS>(a, bx, by);
+            else dequant_units_body<BITS, 2 * UNROLL, false, THREADS, LOOPS>(a, bx, by);
             return;
         }
     }
-    if (a.m_buf) dequant_flat_body<DT, BITS, UNROLL, true, THREADS>(a, bx, by);
-    else dequant_flat_body<DT, BITS, UNROLL, false, THREADS>(a, bx, by);
+    if (a.m_buf) dequant_flat_body<DT, BITS, UNROLL, true, THREADS, LOOPS>(a, bx, by);
+    else dequant_flat_body<DT, BITS, UNROLL, false, THREADS, LOOPS>(a, bx, by);
 }
 
-template <int DT, int UNROLL, int THREADS>
+template <int DT, int UNROLL, int THREADS, bool LOOPS = true>
 __device__ __forceinline__ void dequant_job(const DequantJob& a, uint32_t bx, uint32_t by) {
     switch (a.bits) {                                    // uniform over the workgroup
-    case 2: dequant_job_bits<DT, 2, UNROLL, THREADS>(a, bx, by); break;
-    case 3: dequant_job_bits<DT, 3, UNROLL, THREADS>(a, bx, by); break;
-    case 4: dequant_job_bits<DT, 4, UNROLL, THREADS>(a, bx, by); break;
-    case 6: dequant_job_bits<DT, 6, UNROLL, THREADS>(a, bx, by); break;
-    default: dequant_job_bits<DT, 8, UNROLL, THREADS>(a, bx, by); break;
+    case 2: dequant_job_bits<DT, 2, UNROLL, THREADS, LOOPS>(a, bx, by); break;
+    case 3: dequant_job_bits<DT, 3, UNROLL, THREADS, LOOPS>(a, bx, by); break;
+    case 4: dequant_job_bits<DT, 4, UNROLL, THREADS, LOOPS>(a, bx, by); break;
+    case 6: dequant_job_bits<DT, 6, UNROLL, THREADS, LOOPS>(a, bx, by); break;
+    default: dequant_job_bits<DT, 8, UNROLL, THREADS, LOOPS>(a, bx, by); break;
     }
 }
 

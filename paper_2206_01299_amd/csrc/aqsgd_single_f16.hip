@@ -1,0 +1,6 @@
+// Kernels of single messages instantiated for f16 activations, buffers and outputs.
+#include "aqsgd_single.h"
+
+namespace aqsgd {
+AQSGD_INSTANTIATE_SINGLE_DTYPE(AQSGD_F16)
+}

@@ -52,3 +52,16 @@ def test_launch_shape_rejects_bad_values():
     assert L.aqsgd_set_launch_shape(-1, 0) == -5
     assert L.aqsgd_set_launch_shape(0, 3) == -5
     assert L.aqsgd_set_launch_shape(0, 0) == 0
+
+
+@pytest.mark.parametrize("bits,group", [(4, 8), (8, 9)])
+def test_more_samples_than_the_grid_has_rows(bits, group):
+    """A call of its own gets one grid row per sample; beyond 65535 of them its kernels loop."""
+    if not torch.cuda.is_available():
+        pytest.fail("needs the MI355X")
+    B.lib()
+    import oracle
+    oracle.build()
+    import gpu_harness as H
+    H.replay_and_compare(_cfg("f16", bits, group, W.NEAREST, 1, batch=65538, n_samples=65540),
+                         calls_per_epoch=1, epochs=2, log=lambda *a, **k: None)
