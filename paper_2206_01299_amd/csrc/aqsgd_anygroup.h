@@ -4,9 +4,11 @@
 //                 body whose last chunk of a group stores only the elements that are its
 //                 own (the quantising side is the team bodies with ODD offsets, launched
 //                 from aqsgd_single.h)
-//   large groups  more than a workgroup's registers hold (over 32768 elements): the maximum
-//                 is taken by many workgroups into the message's scale word, and a second
-//                 pass over the same elements quantises with it
+//   wide groups   more elements than the job kernels' shapes take (over 32768) that one
+//                 workgroup still holds in registers as stored: one pass
+//   large groups  more than that: the maximum is taken by many workgroups into the
+//                 message's scale word, and a second pass over the same elements quantises
+//                 with it
 //
 // All of them access 16 bytes per lane at any element's address.
 #pragma once
@@ -195,6 +197,176 @@ void dequant_odd_kernel(AQSGD_DEQUANT_ARGS) {
 }
 
 // ---------------------------------------------------------------------------
+// Wide groups, quantising side: a workgroup of 1024 lanes holds a whole group the way it is
+// stored, eight 16-byte pieces of activations and eight of previous messages per lane (twelve
+// in binary32), and forms the change twice, for the maximum and for the levels, instead of
+// keeping it.  That is 64 (96) of the 128 registers a lane of such a workgroup has, and the
+// group is read once, in one launch, where the large groups' way takes three launches and two
+// readings.  All loads of a workgroup are back before its first store (the maximum waits for
+// them), so a group's last piece may repeat elements of the one before it: same values, same
+// results, same place.  Few groups are bound by what one compute unit draws (about 10 us for an
+// encode of 49152 elements, however few groups), many by memory.  Measured as four calls on
+// groups of 49152, large groups' way -> this: bfloat16, 8 groups 29.4 -> 19.2 us, 256 groups
+// 74 -> 48.5, 1024 groups 237 -> 182; float32, 8 groups 27.6 -> 26.0, 256 groups 117 -> 80,
+// 1024 groups 431 -> 326.
+// ---------------------------------------------------------------------------
+constexpr int kWideThreads = 1024;
+template <int DT> struct WideRounds { static constexpr int value = DT == AQSGD_F32 ? 12 : 8; };
+// Largest group: pieces of 16 bytes, one per lane and round.
+constexpr int wide_most_elements(int dtype) {
+    return dtype == AQSGD_F32 ? kWideThreads * 4 * WideRounds<AQSGD_F32>::value
+                              : kWideThreads * 8 * WideRounds<AQSGD_F16>::value;
+}
+
+// A piece as stored.
+template <int DT, int N> struct PieceRaw { u32x4_t v[N * ElemBytes<DT>::value / 16]; };
+
+template <int DT, int N>
+__device__ __forceinline__ void load_piece_raw(const char* p, PieceRaw<DT, N>& r) {
+#pragma unroll
+    for (int q = 0; q < N * ElemBytes<DT>::value / 16; ++q)
+        r.v[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any_t*>(p + 16 * q));
+}
+template <int DT, int N>
+__device__ __forceinline__ void piece_values(const PieceRaw<DT, N>& r, float (&f)[N]) {
+    if constexpr (DT == AQSGD_F32) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) f[e] = __uint_as_float(r.v[e / 4][e % 4]);
+    } else {
+        Raw<DT> x;
+        x.v = r.v[0];
+        unpack_raw<DT>(x, f);
+    }
+}
+
+// One group in a workgroup: blockIdx.x is the group of the sample, blockIdx.y the sample.
+template <int DT, int BITS, int ROUND, bool HAS_BUF>
+__device__ __forceinline__ void quant_wide_body(const QuantJob& a, float* wave_max) {
+    using P = Piece<DT, BITS>;
+    constexpr int N = P::elems;
+    constexpr int kEB = ElemBytes<DT>::value;
+    constexpr int kRounds = WideRounds<DT>::value * 16 / (N * kEB);
+    const int lane = threadIdx.x;
+    const int rounds = ((a.group + N - 1) / N + kWideThreads - 1) / kWideThreads;    // 1 .. kRounds: checked by the host
+    const int i = blockIdx.y;
+    const int64_t g = blockIdx.x;
+    const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
+    bool fresh = false;
+    if constexpr (HAS_BUF) {
+        if (a.seen != nullptr) {
+            fresh = __builtin_amdgcn_readfirstlane(first_visit(a.seen, row, a.stamp) ? 1 : 0) != 0;
+            if (g == 0 && lane == 0) {                   // one writer per sample
+                a.first[i] = fresh ? 1 : 0;
+                if (fresh) a.seen[row] = a.stamp;
+            }
+        }
+    }
+    const int64_t src0 = static_cast<int64_t>(i) * a.n_per + g * a.group;    // the group's first element in the call
+    const char* src_g = static_cast<const char*>(a.src) + src0 * kEB;
+    char* m_g = HAS_BUF ? static_cast<char*>(a.m_buf) + (row * a.n_per + g * a.group) * kEB : nullptr;
+    uint8_t* codes_g = a.codes + src0 * BITS / 8;
+    // the first element of the lane's piece of a round
+    auto place = [&](int k) {
+        uint32_t at = static_cast<uint32_t>(min((k * kWideThreads + lane) * N, a.group - N));
+        asm volatile("" : "+v"(at));                     // formed where it is used, not kept for every round
+        return at;
+    };
+    PieceRaw<DT, N> ra[kRounds], rm[kRounds];
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k)
+        if (k < rounds) {                                // uniform over the launch
+            const uint32_t at = place(k) * kEB;
+            load_piece_raw<DT, N>(src_g + at, ra[k]);
+            if constexpr (HAS_BUF) load_piece_raw<DT, N>(m_g + at, rm[k]);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    if (fresh) {                                         // uniform over the workgroup
+        __syncthreads();                                 // a repeated element is loaded before it is stored
+        if constexpr (HAS_BUF) {
+#pragma unroll
+            for (int k = 0; k < kRounds; ++k)
+                if (k < rounds) {
+                    const uint32_t at = place(k) * kEB;
+#pragma unroll
+                    for (int q = 0; q < N * kEB / 16; ++q) store16_through(m_g + at + 16 * q, ra[k].v[q]);
+                }
+        }
+        return;
+    }
+    float mx = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k)
+        if (k < rounds) {
+            float x[N], m[N];
+            piece_values<DT, N>(ra[k], x);
+            if constexpr (HAS_BUF) piece_values<DT, N>(rm[k], m);
+#pragma unroll
+            for (int e = 0; e < N; ++e) mx = __builtin_fmaxf(mx, __builtin_fabsf(HAS_BUF ? x[e] - m[e] : x[e] - 0.0f));
+#pragma unroll
+            for (int w = 0; w < N * kEB / 16; ++w) asm volatile("" : "+v"(ra[k].v[w]));  // the change is formed again, not kept
+        }
+    mx = team_max<kWave>(mx);
+    if (lane % kWave == 0) wave_max[lane / kWave] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWideThreads / kWave; ++w) mx = __builtin_fmaxf(mx, wave_max[w]);
+    const GroupScale sc = make_scale<BITS>(mx);
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k)
+        if (k < rounds) {
+            float x[N], m[N], r[N], q[N], v[N];
+            const uint32_t at = place(k);
+            if constexpr (ROUND == AQSGD_ROUND_STOCHASTIC) {
+                if (a.group % 4 != 0) {                  // uniform over the launch
+                    uniforms_any<N>(a.seed, static_cast<uint64_t>(src0) + at, r);
+                } else {                                 // whole Philox blocks
+#pragma unroll
+                    for (int b = 0; b < N; b += 4) block_uniforms(a.seed, (static_cast<uint64_t>(src0) + at + b) >> 2, &r[b]);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < N; ++e) r[e] = kNearestOffset32;
+            }
+            piece_values<DT, N>(ra[k], x);
+            if constexpr (HAS_BUF) piece_values<DT, N>(rm[k], m);
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                q[e] = level_of<BITS, ROUND>(HAS_BUF ? x[e] - m[e] : x[e] - 0.0f, sc, r[e]);
+                v[e] = value_of(q[e], sc);
+                if constexpr (HAS_BUF) v[e] = m[e] + v[e];
+            }
+            store_bytes_any<P::code_bytes>(codes_g + at * BITS / 8, pack_piece<BITS, N>(q));
+            if constexpr (HAS_BUF) store_piece<DT, N>(m_g + at * kEB, v);
+            __builtin_amdgcn_sched_barrier(0);           // one piece's temporaries at a time
+        }
+    if (lane == 0) a.scales[static_cast<int64_t>(i) * a.gps + g] = sc.s_tx;
+}
+
+template <int DT, int BITS, int ROUND>
+__device__ __forceinline__ void quant_wide_bits(const QuantJob& a, float* wave_max) {
+    if (a.m_buf) quant_wide_body<DT, BITS, ROUND, true>(a, wave_max);
+    else quant_wide_body<DT, BITS, ROUND, false>(a, wave_max);
+}
+
+template <int DT, int ROUND>
+__global__ __launch_bounds__(kWideThreads)
+void quant_wide_kernel(AQSGD_QUANT_ARGS) {
+    __shared__ float wave_max[kWideThreads / kWave];
+    QuantJob a;
+    a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
+    a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group;
+    a.grid_x = grid_x; a.grid_y = grid_y;
+    a.seed = seed; a.seen = seen; a.first = first; a.stamp = stamp;
+    switch (bits) {
+    case 2: quant_wide_bits<DT, 2, ROUND>(a, wave_max); break;
+    case 3: quant_wide_bits<DT, 3, ROUND>(a, wave_max); break;
+    case 4: quant_wide_bits<DT, 4, ROUND>(a, wave_max); break;
+    case 6: quant_wide_bits<DT, 6, ROUND>(a, wave_max); break;
+    default: quant_wide_bits<DT, 8, ROUND>(a, wave_max); break;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Large groups, quantising side: three launches.  The message's scale word of a group
 // collects the maximum (magnitudes order like unsigned integers, and any order of an
 // atomic maximum gives the same bits), so no memory beyond the call's own is needed:
@@ -202,8 +374,8 @@ void dequant_odd_kernel(AQSGD_DEQUANT_ARGS) {
 //   2. every workgroup takes the maximum of its span of a group into the group's word
 //   3. the same spans are read again, quantised with the finished word and stored
 // A group's spans are read twice, the second time mostly from the last-level cache.
-// (bfloat16, eight samples with one scale each, 49152 elements, forward and backward in
-// four calls: one thread per group 31.9 ms, now 47 us.)
+// (bfloat16, eight groups of 49152, forward and backward in four calls: one thread per group
+// 31.9 ms, this way 29.4 us.)
 // ---------------------------------------------------------------------------
 struct LargeGeom {
     int32_t spans;             // spans per group
@@ -395,6 +567,7 @@ void large_quant_kernel(const QuantJob a, const LargeGeom geom) {
 
 // Per-dtype pieces (defined by AQSGD_INSTANTIATE_ANYGROUP_DTYPE in the dtype's .hip file).
 template <int DT> hipError_t launch_dequant_odd_dt(bool covers, const DequantJob& a, hipStream_t stream);
+template <int DT> hipError_t launch_quant_wide_dt(int rounding, const QuantJob& a, hipStream_t stream);
 template <int DT> hipError_t launch_quant_large_dt(int rounding, const QuantJob& a, const LargeGeom& geom,
                                                    hipStream_t stream);
 
@@ -403,6 +576,13 @@ template <int DT>
 hipError_t launch_dequant_odd_dt(bool covers, const DequantJob& a, hipStream_t s) {
     return covers ? launch_dequant_with(dequant_odd_kernel<DT, false>, a, s)
                   : launch_dequant_with(dequant_odd_kernel<DT, true>, a, s);
+}
+
+template <int DT>
+hipError_t launch_quant_wide_dt(int rounding, const QuantJob& a, hipStream_t s) {
+    return rounding == AQSGD_ROUND_STOCHASTIC
+               ? launch_quant_with(quant_wide_kernel<DT, AQSGD_ROUND_STOCHASTIC>, dim3(kWideThreads), a, s)
+               : launch_quant_with(quant_wide_kernel<DT, AQSGD_ROUND_NEAREST>, dim3(kWideThreads), a, s);
 }
 
 template <int DT>
@@ -421,6 +601,7 @@ hipError_t launch_quant_large_dt(int rounding, const QuantJob& a, const LargeGeo
 
 #define AQSGD_INSTANTIATE_ANYGROUP_DTYPE(DT)                                                          \
     template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);                   \
+    template hipError_t launch_quant_wide_dt<DT>(int, const QuantJob&, hipStream_t);                       \
     template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t);
 
 }  // namespace aqsgd

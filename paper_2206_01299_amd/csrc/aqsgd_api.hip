@@ -18,6 +18,7 @@ namespace aqsgd {
     extern template hipError_t launch_quant_single_dt<DT>(int, int, bool, const QuantJob&, hipStream_t); \
     extern template hipError_t launch_dequant_single_dt<DT>(int, const DequantJob&, hipStream_t);     \
     extern template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);       \
+    extern template hipError_t launch_quant_wide_dt<DT>(int, const QuantJob&, hipStream_t);           \
     extern template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
     extern template hipError_t launch_lowbit_dt<DT>(int, int, int, bool, LaunchGeom, const LowbitArgs&, hipStream_t);
 AQSGD_EXTERN_DTYPE(AQSGD_F32)
@@ -81,6 +82,14 @@ hipError_t launch_dequant_odd(int dtype, bool covers, const DequantJob& a, hipSt
     case AQSGD_F32:  return launch_dequant_odd_dt<AQSGD_F32>(covers, a, s);
     case AQSGD_F16:  return launch_dequant_odd_dt<AQSGD_F16>(covers, a, s);
     case AQSGD_BF16: return launch_dequant_odd_dt<AQSGD_BF16>(covers, a, s);
+    default:         return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_quant_wide(int dtype, int rounding, const QuantJob& a, hipStream_t s) {
+    switch (dtype) {
+    case AQSGD_F32:  return launch_quant_wide_dt<AQSGD_F32>(rounding, a, s);
+    case AQSGD_F16:  return launch_quant_wide_dt<AQSGD_F16>(rounding, a, s);
+    case AQSGD_BF16: return launch_quant_wide_dt<AQSGD_BF16>(rounding, a, s);
     default:         return hipErrorInvalidValue;
     }
 }
@@ -222,9 +231,9 @@ struct SeenArgs {
 
 // Which kernels a message takes.  Groups of whole chunks that fit a workgroup's registers are
 // jobs of the shared launches; the rest are launched on their own: odd groups (8 elements or
-// more, not whole chunks), groups beyond a workgroup (quantising side only: reconstruction needs
-// no maximum), and the scalar kernels for groups of 1 to 7 elements, which have no 16-byte piece.
-enum class Route { kJob, kOdd, kLarge, kAnyShape };
+// more, not whole chunks), groups beyond the job kernels' team shapes and those beyond any
+// workgroup (quantising side only: reconstruction needs no maximum), and the scalar kernels for groups of 1 to 7 elements, which have no 16-byte piece.
+enum class Route { kJob, kOdd, kWide, kLarge, kAnyShape };
 
 // One message as the kernels see it.  Quantising side: aqsgd_encode, aqsgd_grad_quant.
 struct QuantPlan {
@@ -246,7 +255,8 @@ QuantPlan plan_quant(const aqsgd_desc* d, int64_t batch, int64_t n_per, const vo
     a.seed = d->rng_seed; a.seen = sa.seen; a.first = sa.first; a.stamp = sa.stamp;
     p.dtype = d->dtype; p.bits = d->bits; p.rounding = d->rounding;
     p.route = a.group < kChunk ? Route::kAnyShape
-              : a.cpg > kMaxTeamChunks ? Route::kLarge
+              : a.group > wide_most_elements(d->dtype) ? Route::kLarge
+              : a.cpg > kMaxTeamChunks ? Route::kWide
               : a.group % kChunk != 0 ? Route::kOdd : Route::kJob;
     p.shape = team_shape_for(a.cpg);
     return p;
@@ -369,6 +379,9 @@ hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_b
         const bool covers = one_step_grid(a, a.gps, groups_per_block_step(p.shape), cap);
         return launch_quant_single(p.dtype, p.rounding, p.shape, covers, a, stream);
     }
+    case Route::kWide:
+        if (one_step_grid(a, a.gps, 1, max_blocks)) return launch_quant_wide(p.dtype, p.rounding, a, stream);
+        [[fallthrough]];                                 // too many for a grid: the kernels that loop
     case Route::kLarge: {
         const LargeGeom lg = large_geometry(a);
         g = geometry(a.gps * lg.spans, 1, a.batch, max_blocks);

@@ -324,19 +324,27 @@ __device__ __forceinline__ float offset32_from_word(uint32_t w) {
     return static_cast<float>(w & 0xffffff00u);
 }
 
-// Rounding offsets (times 2^32) of one chunk whose first element has flat index j0
-// (a multiple of 8): block j0/4 feeds elements 0..3, block j0/4 + 1 elements 4..7.
-__device__ __forceinline__ void chunk_uniforms(uint64_t seed, uint64_t j0, float (&r)[kChunk]) {
-    const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
-    const uint64_t blk = j0 >> 2;
+// Rounding offsets (times 2^32) of the four elements of Philox block `blk` (elements
+// 4 blk .. 4 blk + 3 of the call).
+__device__ __forceinline__ void block_uniforms(uint64_t seed, uint64_t blk, float* r) {
     uint32_t w[4];
-    philox4x32_10(static_cast<uint32_t>(blk), static_cast<uint32_t>(blk >> 32), k0, k1, w);
+    philox4x32_10(static_cast<uint32_t>(blk), static_cast<uint32_t>(blk >> 32), static_cast<uint32_t>(seed),
+                  static_cast<uint32_t>(seed >> 32), w);
 #pragma unroll
     for (int e = 0; e < 4; ++e) r[e] = offset32_from_word(w[e]);
-    const uint64_t blk1 = blk + 1;
-    philox4x32_10(static_cast<uint32_t>(blk1), static_cast<uint32_t>(blk1 >> 32), k0, k1, w);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[4 + e] = offset32_from_word(w[e]);
+}
+
+// Rounding offsets of one chunk whose first element has flat index j0 (a multiple of 8).
+__device__ __forceinline__ void chunk_uniforms(uint64_t seed, uint64_t j0, float (&r)[kChunk]) {
+    block_uniforms(seed, j0 >> 2, r);
+    block_uniforms(seed, (j0 >> 2) + 1, r + 4);
+}
+
+// c ? a : b on values: of two array elements the compiler would make one access at a chosen
+// index instead, and with it an array in scratch memory.
+__device__ __forceinline__ uint32_t select_word(bool c, uint32_t a, uint32_t b) {
+    asm("" : "+v"(a), "+v"(b));
+    return c ? a : b;
 }
 
 // The same for N elements from any index j0: they straddle up to N/4 + 1 blocks, whose words
@@ -355,9 +363,9 @@ __device__ __forceinline__ void uniforms_any(uint64_t seed, uint64_t j0, float (
         for (int e = 0; e < 4; ++e) w[4 * b + e] = x[e];
     }
 #pragma unroll
-    for (int e = 0; e < N + 2; ++e) w[e] = by1 ? w[e + 1] : w[e];
+    for (int e = 0; e < N + 2; ++e) w[e] = select_word(by1, w[e + 1], w[e]);
 #pragma unroll
-    for (int e = 0; e < N; ++e) r[e] = offset32_from_word(by2 ? w[e + 2] : w[e]);
+    for (int e = 0; e < N; ++e) r[e] = offset32_from_word(select_word(by2, w[e + 2], w[e]));
 }
 
 // ---------------------------------------------------------------------------
@@ -717,18 +725,11 @@ __device__ __forceinline__ void store_codes_of_unit(uint8_t* p, uint32_t w) {
     else store_unit_codes<BITS>(p, w);
 }
 
-// Rounding offsets (times 2^32) of two units whose first elements have flat indices
-// ja and jb (multiples of 4): one Philox block each.
+// Rounding offsets of two units whose first elements have flat indices ja and jb (multiples
+// of 4).
 __device__ __forceinline__ void units_uniforms(uint64_t seed, uint64_t ja, uint64_t jb, float (&r)[kChunk]) {
-    const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
-    const uint64_t blka = ja >> 2, blkb = jb >> 2;
-    uint32_t w[4];
-    philox4x32_10(static_cast<uint32_t>(blka), static_cast<uint32_t>(blka >> 32), k0, k1, w);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = offset32_from_word(w[e]);
-    philox4x32_10(static_cast<uint32_t>(blkb), static_cast<uint32_t>(blkb >> 32), k0, k1, w);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[4 + e] = offset32_from_word(w[e]);
+    block_uniforms(seed, ja >> 2, r);
+    block_uniforms(seed, jb >> 2, r + 4);
 }
 
 }  // namespace aqsgd

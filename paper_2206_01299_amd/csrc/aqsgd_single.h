@@ -80,11 +80,16 @@ void dequant_single_kernel(AQSGD_DEQUANT_ARGS) {
     dequant_job<DT, UNROLL, kBlock, false>(a, blockIdx.x, blockIdx.y);
 }
 
+template <typename Kernel>
+static hipError_t launch_quant_with(Kernel kernel, dim3 block, const QuantJob& a, hipStream_t s) {
+    return launch_kernel(kernel, dim3(a.grid_x, a.grid_y), block, s, a.src, a.ids, a.m_buf, a.codes, a.scales,
+                         a.group, a.bits, a.n_per, a.gps, a.batch, a.grid_x, a.grid_y, a.stamp, a.seed, a.seen,
+                         a.first);
+}
+
 template <int DT, int ROUND, int TEAM, int CPL, int KIND>
 static hipError_t launch_quant_single_as(const QuantJob& a, hipStream_t s) {
-    return launch_kernel(quant_single_kernel<DT, ROUND, TEAM, CPL, KIND>, dim3(a.grid_x, a.grid_y),
-                         dim3(TEAM > kWave ? TEAM : kBlock), s, a.src, a.ids, a.m_buf, a.codes, a.scales, a.group,
-                         a.bits, a.n_per, a.gps, a.batch, a.grid_x, a.grid_y, a.stamp, a.seed, a.seen, a.first);
+    return launch_quant_with(quant_single_kernel<DT, ROUND, TEAM, CPL, KIND>, dim3(TEAM > kWave ? TEAM : kBlock), a, s);
 }
 
 template <int DT, int ROUND, int KIND>

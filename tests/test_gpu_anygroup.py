@@ -49,7 +49,10 @@ def test_odd_groups(H, dtype, bits):
 
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("bits,group", [(4, 32776), (3, 32776), (8, 32769), (2, 32772), (6, 40004), (8, 65537),
-                                        (4, 262144), (3, 262152), (8, 300001)])
+                                        (4, 262144), (3, 262152), (8, 300001),
+                                        # the last group one workgroup holds, and the first beyond
+                                        (6, 49152), (3, 49152), (8, 49153), (3, 49160), (2, 65536), (3, 65536),
+                                        (3, 65544)])
 def test_groups_beyond_a_workgroup(H, dtype, bits, group):
     for rounding, gps in ((W.NEAREST, 3), (W.STOCHASTIC, 1)):
         print(f"large {dtype} b{bits} G{group} r{rounding}", flush=True)
