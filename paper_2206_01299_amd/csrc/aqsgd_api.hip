@@ -28,11 +28,11 @@ AQSGD_EXTERN_DTYPE(AQSGD_BF16)
 thread_local ProfileRequest g_profile_request = {nullptr, nullptr};
 
 // -- dtype fan-out (each dtype's kernels live in their own translation unit) ----
-hipError_t launch_codec_jobs(int dtype, int rounding, int shape, bool three, const JobTable& t, hipStream_t s) {
+hipError_t launch_codec_jobs(int dtype, int rounding, int shape, TableKind kind, const JobTable& t, hipStream_t s) {
     switch (dtype) {
-    case AQSGD_F32:  return launch_codec_jobs_dt<AQSGD_F32>(rounding, shape, three, t, s);
-    case AQSGD_F16:  return launch_codec_jobs_dt<AQSGD_F16>(rounding, shape, three, t, s);
-    case AQSGD_BF16: return launch_codec_jobs_dt<AQSGD_BF16>(rounding, shape, three, t, s);
+    case AQSGD_F32:  return launch_codec_jobs_dt<AQSGD_F32>(rounding, shape, kind, t, s);
+    case AQSGD_F16:  return launch_codec_jobs_dt<AQSGD_F16>(rounding, shape, kind, t, s);
+    case AQSGD_BF16: return launch_codec_jobs_dt<AQSGD_BF16>(rounding, shape, kind, t, s);
     default:         return hipErrorInvalidValue;
     }
 }
@@ -143,7 +143,7 @@ std::atomic<int>& dequant_unroll_knob() {
 }
 
 // Workgroups per launch that carries several jobs; 0 = the library's own choice (see
-// launch_budget).  For sweeps only: AQSGD_LAUNCH_BLOCKS in the environment.
+// steps_per_workgroup).  For sweeps only: AQSGD_LAUNCH_BLOCKS in the environment.
 int64_t env_launch_blocks() { return env_int("AQSGD_LAUNCH_BLOCKS", 0); }
 std::atomic<int64_t>& launch_blocks_knob() {
     static std::atomic<int64_t> v{env_launch_blocks()};
@@ -286,64 +286,54 @@ DequantPlan plan_dequant(const aqsgd_desc* d, int64_t batch, int64_t n_per, cons
     return p;
 }
 
-// Workgroup budget of a launch led by quantising jobs of team shape `shape`.  A step of a
-// small team (one chunk per lane) is short next to what opens a workgroup (job lookup,
-// sample id, row addresses: dependent fetches), so a launch of many such workgroups keeps
-// much of the chip in that opening; such launches get about as many workgroups as are
-// resident at once (eight per compute unit) and each loops over several steps.  Measured
-// on the 2-bit G = 128 and the 3-bit G = 64 boundaries: whole step 7-8 % shorter in the
-// pipelined schedule, the launch on its own up to 7 % longer.  Launches of the wider
-// shapes (a step is four chunks per lane or a whole workgroup's row) lose from it and
-// keep one step per workgroup.
-int64_t launch_budget(int shape, int64_t knob) {
-    if (knob > 0) return knob;
-    switch (shape) {
-    case kTeam8x1: case kTeam16x1: case kTeam32x1: return 2048;
-    default: return int64_t{1} << 40;
-    }
+// Steps a workgroup of a shared launch takes (`total`: steps of all its jobs; `shape`: team
+// shape of the quantising ones, -1 without).  One, but for small teams (one chunk per lane) in
+// large launches: a step of theirs is short next to what opens a workgroup (job lookup, sample
+// id, row addresses: dependent fetches), and a launch that is several times what the chip holds
+// at once (eight workgroups per compute unit, 2048) does better as one round of workgroups that
+// loop, the same number of steps each, while another stream's launch runs beside it.  Measured,
+// whole step in the two-stream schedule, one step -> loops: 2-bit stochastic G = 128 (6400 steps
+// a launch, four each) 20.1 -> 19.1 us, 3-bit G = 64 (12288, six each) 36.8 -> 35.6.  Smaller
+// launches gain more from one step each when they are alone on the chip than they lose beside
+// another: 2-bit stochastic, 3200 steps, one launch a stage 27.5 -> 25.5 us, forward pair on two
+// streams 13.3 -> 13.5; so the loops start at 4096.  The wider shapes (a step is four chunks per
+// lane or a workgroup's row) lose from loops throughout.
+int64_t steps_per_workgroup(int shape, int64_t total, int64_t launch_blocks) {
+    const bool small = shape == kTeam8x1 || shape == kTeam16x1 || shape == kTeam32x1;
+    if (launch_blocks == 0 && small && total >= 4096) launch_blocks = 2048;
+    return launch_blocks > 0 ? (total + launch_blocks - 1) / launch_blocks : 1;
 }
 
 // Workgroup numbers of a table whose jobs are all in: every job gets the grid its size
-// asks for (at most max_blocks), and when the launch as a whole would pass
-// `launch_blocks` workgroups the jobs share that budget in proportion to what they asked
-// for (the kernels loop over what is left).  quant_step / dequant_step: groups, chunks one
-// workgroup step covers.
-void number_blocks(JobTable& t, int64_t quant_step, int64_t dequant_step, int64_t max_blocks,
+// asks for (at most max_blocks), shortened by the steps a workgroup takes.  quant_step /
+// dequant_step: groups, chunks one workgroup step covers.  Tells whether there is a workgroup
+// for every step of every sample (else the kernel has to loop over what is left).
+bool number_blocks(JobTable& t, int shape, int64_t quant_step, int64_t dequant_step, int64_t max_blocks,
                    int64_t launch_blocks) {
-    int64_t want[kMaxQuantJobs + kMaxDequantJobs];
     int64_t total = 0;
-    for (int k = 0; k < t.n_quant; ++k) {
-        const LaunchGeom g = geometry(t.q[k].gps, quant_step, t.q[k].batch, max_blocks);
-        total += want[k] = static_cast<int64_t>(g.grid_x) * g.grid_y;
-    }
-    for (int k = 0; k < t.n_dequant; ++k) {
-        const LaunchGeom g = geometry(t.d[k].cps, dequant_step, t.d[k].batch, max_blocks);
-        total += want[kMaxQuantJobs + k] = static_cast<int64_t>(g.grid_x) * g.grid_y;
-    }
-    const bool shrink = total > launch_blocks;
-    auto share = [&](int64_t w) {
-        if (!shrink) return max_blocks;
-        const int64_t part = static_cast<int64_t>(static_cast<double>(launch_blocks) * static_cast<double>(w) /
-                                                  static_cast<double>(total));
-        return part < 1 ? int64_t{1} : (part < max_blocks ? part : max_blocks);
+    auto want = [&](int64_t units, int64_t step, int64_t batch) {
+        const LaunchGeom g = geometry(units, step, batch, max_blocks);
+        total += static_cast<int64_t>(g.grid_x) * g.grid_y;
     };
-    int64_t blocks = 0;
-    for (int k = 0; k < t.n_quant; ++k) {
-        QuantJob& a = t.q[k];
-        const LaunchGeom g = geometry(a.gps, quant_step, a.batch, share(want[k]));
+    for (int k = 0; k < t.n_quant; ++k) want(t.q[k].gps, quant_step, t.q[k].batch);
+    for (int k = 0; k < t.n_dequant; ++k) want(t.d[k].cps, dequant_step, t.d[k].batch);
+    const int64_t steps = steps_per_workgroup(shape, total, launch_blocks);
+    bool covers = true;
+    uint32_t blocks = 0;
+    auto place = [&](auto& a, int64_t units, int64_t step) {
+        const LaunchGeom g = geometry(units, step * steps, a.batch, max_blocks);
         a.grid_x = g.grid_x; a.grid_y = g.grid_y; a.rcp_grid_x = 1.0f / static_cast<float>(g.grid_x);
-        t.q_block0[k] = static_cast<uint32_t>(blocks);
-        blocks += static_cast<int64_t>(g.grid_x) * g.grid_y;
-    }
-    t.dequant_block0 = static_cast<uint32_t>(blocks);
-    for (int k = 0; k < t.n_dequant; ++k) {
-        DequantJob& a = t.d[k];
-        const LaunchGeom g = geometry(a.cps, dequant_step, a.batch, share(want[kMaxQuantJobs + k]));
-        a.grid_x = g.grid_x; a.grid_y = g.grid_y; a.rcp_grid_x = 1.0f / static_cast<float>(g.grid_x);
-        t.d_block0[k] = static_cast<uint32_t>(blocks);
-        blocks += static_cast<int64_t>(g.grid_x) * g.grid_y;
-    }
-    t.total_blocks = static_cast<uint32_t>(blocks);
+        covers = covers && g.grid_y == static_cast<uint32_t>(a.batch) &&
+                 static_cast<int64_t>(g.grid_x) * step >= units;
+        const uint32_t at = blocks;
+        blocks += g.grid_x * g.grid_y;
+        return at;
+    };
+    for (int k = 0; k < t.n_quant; ++k) t.q_block0[k] = place(t.q[k], t.q[k].gps, quant_step);
+    t.dequant_block0 = blocks;
+    for (int k = 0; k < t.n_dequant; ++k) t.d_block0[k] = place(t.d[k], t.d[k].cps, dequant_step);
+    t.total_blocks = blocks;
+    return covers;
 }
 
 // Spans of a large group: as many as give the launch about kLargeMaxBlocks workgroups, none
@@ -455,7 +445,7 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
         }
         JobTable t;
         t.n_quant = t.n_dequant = 0;
-        bool three = false;                              // a 3-bit job among them: the kernel variant that has those bodies
+        bool three = false;                              // a 3-bit job among them
         for (size_t k = i; k < qs.size() && t.n_quant < kMaxQuantJobs; ++k) {
             const QuantPlan& c = qs[k];
             if (q_done[k] || c.route != Route::kJob || c.shape != lead.shape || c.dtype != lead.dtype ||
@@ -466,10 +456,12 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
             q_done[k] = true;
         }
         add_dequant(t, lead.dtype);
-        number_blocks(t, groups_per_block_step(lead.shape),
-                      static_cast<int64_t>(threads_of_shape(lead.shape)) * kHostedDequantUnroll, max_blocks,
-                      launch_budget(lead.shape, launch_blocks));
-        err = launch_codec_jobs(lead.dtype, lead.rounding, lead.shape, three, t, stream);
+        const bool covers = number_blocks(t, lead.shape, groups_per_block_step(lead.shape),
+                                          static_cast<int64_t>(threads_of_shape(lead.shape)) * kHostedDequantUnroll,
+                                          max_blocks, launch_blocks);
+        const TableKind kind = covers ? (three ? kTableOneStepThree : kTableOneStep)
+                                      : (three ? kTableLoopsThree : kTableLoops);
+        err = launch_codec_jobs(lead.dtype, lead.rounding, lead.shape, kind, t, stream);
     }
     for (size_t i = 0; i < ds.size() && err == hipSuccess; ++i) {
         if (d_done[i]) continue;
@@ -481,7 +473,7 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
         JobTable t;
         t.n_quant = t.n_dequant = 0;
         add_dequant(t, ds[i].dtype);
-        number_blocks(t, 1, static_cast<int64_t>(kBlock) * unroll, max_blocks, launch_budget(-1, launch_blocks));
+        number_blocks(t, -1, 1, static_cast<int64_t>(kBlock) * unroll, max_blocks, launch_blocks);
         err = launch_dequant_jobs(ds[i].dtype, unroll, t, stream);
     }
     return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;

@@ -678,38 +678,50 @@ __device__ __forceinline__ void place_in_job(uint32_t local, uint32_t grid_x, fl
 
 constexpr int kHostedDequantUnroll = 2;      // dequantising jobs inside a quantising kernel's launch
 
+// Which bodies a kernel of shared launches holds.  The 3-bit quantising bodies (codes
+// leave through a lane transpose) need a sixth more registers than the others, which
+// would cost every launch a wave of occupancy per SIMD, so a table with a 3-bit quantising
+// job has kernels of its own.  In the one-step kinds every workgroup does one step of one
+// sample, which is how a launch goes out whose grid holds a workgroup for each: loops around
+// the bodies keep what the next step needs in registers and with them waves off the chip
+// (float16, 64 lanes by 4 chunks: 107 registers and four waves a SIMD with loops, 73 and six
+// without; 16 lanes by 1, stochastic: 82 and five, 67 and seven).  Measured, loops -> one step:
+// the time slot of the float16 [4,1024,1600] 4/8-bit boundary 21.2 -> 20.7 us; its 2/4-bit
+// stochastic G = 128 messages, one launch a stage, 28.0 -> 25.5 us.
+enum TableKind {
+    kTableOneStep = 0,     // 2, 4, 6 and 8 bits
+    kTableOneStepThree,    // every width
+    kTableLoops,           // 2, 4, 6 and 8 bits, any grid
+    kTableLoopsThree       // every width, any grid
+};
+
 // One quantising job in a team kernel: the body for its bit width and for with /
-// without previous messages.  The 3-bit bodies (codes leave through a lane
-// transpose) need a sixth more registers than the others, which would cost every
-// launch a wave of occupancy per SIMD, so the kernel comes in two variants: without
-// them (THREE = false: 2, 4, 6 and 8 bits), and with them for a table in which at
-// least one quantising job is 3-bit (THREE = true: every width, at the 3-bit bodies'
-// register count).
-template <int DT, int BITS, int ROUND, int TEAM, int CPL>
+// without previous messages.
+template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool LOOPS>
 __device__ __forceinline__ void quant_job_bits(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
-    if (a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true>(a, bx, by, wave_max);
-    else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false>(a, bx, by, wave_max);
+    if (a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, false, LOOPS>(a, bx, by, wave_max);
+    else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false, false, LOOPS>(a, bx, by, wave_max);
 }
 
-template <int DT, int ROUND, int TEAM, int CPL, bool THREE>
+template <int DT, int ROUND, int TEAM, int CPL, int KIND>
 __device__ __forceinline__ void quant_job(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
-    if constexpr (THREE) {
+    constexpr bool LOOPS = KIND == kTableLoops || KIND == kTableLoopsThree;
+    if constexpr (KIND == kTableOneStepThree || KIND == kTableLoopsThree) {
         if (a.bits == 3) {                               // uniform over the workgroup
-            quant_job_bits<DT, 3, ROUND, TEAM, CPL>(a, bx, by, wave_max);
+            quant_job_bits<DT, 3, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max);
             return;
         }
     }
     switch (a.bits) {
-    case 2: quant_job_bits<DT, 2, ROUND, TEAM, CPL>(a, bx, by, wave_max); break;
-    case 4: quant_job_bits<DT, 4, ROUND, TEAM, CPL>(a, bx, by, wave_max); break;
-    case 6: quant_job_bits<DT, 6, ROUND, TEAM, CPL>(a, bx, by, wave_max); break;
-    default: quant_job_bits<DT, 8, ROUND, TEAM, CPL>(a, bx, by, wave_max); break;
+    case 2: quant_job_bits<DT, 2, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max); break;
+    case 4: quant_job_bits<DT, 4, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max); break;
+    case 6: quant_job_bits<DT, 6, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max); break;
+    default: quant_job_bits<DT, 8, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max); break;
     }
 }
 
-// The quantising jobs of one rounding mode and team shape (THREE: 3-bit ones among them)
-// plus any dequantising jobs.
-template <int DT, int ROUND, int TEAM, int CPL, bool THREE>
+// The quantising jobs of one rounding mode and team shape plus any dequantising jobs.
+template <int DT, int ROUND, int TEAM, int CPL, int KIND>
 __global__ __launch_bounds__((TEAM > kWave ? TEAM : kBlock))
 void codec_jobs_kernel(const JobTable t) {
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
@@ -726,13 +738,14 @@ void codec_jobs_kernel(const JobTable t) {
         const int j = job_of_block(qs, t.n_quant, b);
         const QuantJob& a = t.q[j];
         place_in_job(b - start_of_job(qs, j), a.grid_x, a.rcp_grid_x, bx, by);
-        quant_job<DT, ROUND, TEAM, CPL, THREE>(a, bx, by, wave_max);
+        quant_job<DT, ROUND, TEAM, CPL, KIND>(a, bx, by, wave_max);
     } else {
         const BlockStarts ds = block_starts(t.d_block0);
         const int j = job_of_block(ds, t.n_dequant, b);
         const DequantJob& d = t.d[j];
         place_in_job(b - start_of_job(ds, j), d.grid_x, d.rcp_grid_x, bx, by);
-        dequant_job<DT, kHostedDequantUnroll, kThreads>(d, bx, by);
+        constexpr bool LOOPS = KIND == kTableLoops || KIND == kTableLoopsThree;
+        dequant_job<DT, kHostedDequantUnroll, kThreads, LOOPS>(d, bx, by);
     }
 }
 
@@ -921,16 +934,15 @@ enum TeamShape {
 };
 
 // A launch of codec_jobs_kernel (the table's quantising jobs all have this rounding
-// mode and team shape; `three`: at least one of them is 3-bit) or, with no quantising
-// job, of dequant_jobs_kernel.
-hipError_t launch_codec_jobs(int dtype, int rounding, int shape, bool three, const JobTable& t,
+// mode and team shape) or, with no quantising job, of dequant_jobs_kernel.
+hipError_t launch_codec_jobs(int dtype, int rounding, int shape, TableKind kind, const JobTable& t,
                              hipStream_t stream);
 hipError_t launch_dequant_jobs(int dtype, int unroll, const JobTable& t, hipStream_t stream);
 hipError_t launch_quant_anyshape(int dtype, int bits, int rounding, const QuantJob& a, hipStream_t stream);
 hipError_t launch_dequant_anyshape(int dtype, const DequantJob& a, hipStream_t stream);
 
 // Per-dtype pieces (defined by AQSGD_INSTANTIATE_DTYPE in the dtype's .hip file).
-template <int DT> hipError_t launch_codec_jobs_dt(int rounding, int shape, bool three, const JobTable& t,
+template <int DT> hipError_t launch_codec_jobs_dt(int rounding, int shape, TableKind kind, const JobTable& t,
                                                   hipStream_t stream);
 template <int DT> hipError_t launch_dequant_jobs_dt(int unroll, const JobTable& t, hipStream_t stream);
 template <int DT> hipError_t launch_quant_anyshape_dt(int bits, int rounding, const QuantJob& a,

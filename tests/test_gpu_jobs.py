@@ -198,9 +198,9 @@ def test_3bit_jobs_share_a_grid_with_other_widths(H, case):
 
 
 def test_a_time_slot_over_the_launch_budget_of_small_teams(H):
-    """Small-team launches get a bounded number of workgroups, shared by the jobs in
-    proportion to their sizes, and every workgroup loops over several steps: a slot of four
-    messages whose grids would ask for several times that budget, with a ragged last step."""
+    """Large small-team launches get about as many workgroups as the chip holds, and every
+    workgroup loops over several steps: a slot of four messages whose grids would ask for
+    several times that, with a ragged last step."""
     rng = np.random.default_rng(8)
     b = Boundary(H, rng, "f16", 2, 128, 1, 4, 128, 1, 3, 128 * 20011, n_rows=4, seed=77)
     for step in range(3):
@@ -211,6 +211,25 @@ def test_a_time_slot_over_the_launch_budget_of_small_teams(H):
         jobs.append(b.encode_job(step))
         B.run_jobs(jobs)
         b.verify(f"over budget slot {step}")
+
+
+@pytest.mark.parametrize("dtype,bits,group,gps", [
+    ("f16", 2, 128, 32 * 1023),       # 4092 steps of a workgroup in the last slot: one step each
+    ("f16", 2, 128, 32 * 1024),       # 4096: two each
+    ("bf16", 3, 64, 64 * 1024 + 5),   # the same with the 3-bit bodies, ragged
+    ("f32", 4, 256, 32 * 1024 + 31),  # float32 in units, 32-lane teams, ragged
+])
+def test_slots_around_the_size_from_which_small_teams_loop(H, dtype, bits, group, gps):
+    rng = np.random.default_rng(gps)
+    b = Boundary(H, rng, dtype, bits, group, 0, 8, group, 0, 1, group * gps, n_rows=2, seed=78)
+    for step in range(3):
+        print("slot", dtype, bits, group, gps, step, flush=True)
+        jobs = [b.grad_dequant_job()] if step >= 2 else []
+        if step >= 1:
+            jobs += [b.decode_job(), b.grad_quant_job()]
+        jobs.append(b.encode_job(step))
+        B.run_jobs(jobs)
+        b.verify(f"slot {step}")
 
 
 def test_more_jobs_than_one_grid_holds_and_any_shape_jobs(H):
