@@ -145,18 +145,19 @@ __device__ __forceinline__ void lowbit_team_group(const LowbitArgs& a, const cha
     uint8_t* const m_group = mcodes_s + gchunk * MBITS;
     uint8_t* const c_group = codes_s + gchunk * BITS;
 
-    // ---- issue every load of the group ------------------------------------------
+    // ---- issue every load of the group (what needs no sample id first) --------------------
     uint64_t mw[CPL], cw[CPL];
     Raw<DT> ra[CPL];
-    const float m_scale = mscales_s[g];
     float wire_scale = 0.0f;
     if constexpr (!SENDER) wire_scale = scales_s[g];
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
-        mw[k] = load_codes_at<MBITS>(m_group + cc[k] * static_cast<uint32_t>(MBITS));
         if constexpr (SENDER) ra[k] = load_raw_at<DT>(act_s + goff * kEB + cc[k] * kChunkBytes);
         else cw[k] = load_codes_at<BITS>(c_group + cc[k] * static_cast<uint32_t>(BITS));
     }
+    const float m_scale = mscales_s[g];
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) mw[k] = load_codes_at<MBITS>(m_group + cc[k] * static_cast<uint32_t>(MBITS));
     // the tail: element CPL * 64 * 8 + lane of the group (a lane past the end repeats the last one)
     [[maybe_unused]] const bool tail_valid = TAIL && lane_in_team < tail_entries;
     [[maybe_unused]] const int tail_l = min(lane_in_team, tail_entries - 1);
@@ -314,7 +315,13 @@ enum LowbitMode { kLbReceiver = 0, kLbSenderNearest = 1, kLbSenderStochastic = 2
 // element per lane (the host picks this variant; see lowbit_tail_chunks).
 template <int DT, int BITS, int MBITS, int TEAM, int CPL, int MODE, bool TAILK = false>
 __global__ __launch_bounds__((TEAM > kWave ? TEAM : kBlock)) __attribute__((amdgpu_waves_per_eu(4)))
-void lowbit_team_kernel(const LowbitArgs a) {
+void lowbit_team_kernel(void* data, const int64_t* ids, uint8_t* m_codes, float* m_scales, uint8_t* codes,
+                        int32_t group, int32_t cpg, int64_t n_per, float* scales, int64_t gps, int32_t batch,
+                        uint64_t seed) {
+    LowbitArgs a;
+    a.act = data; a.out = data; a.ids = ids; a.m_codes = m_codes; a.m_scales = m_scales; a.codes = codes;
+    a.scales = scales; a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.cpg = cpg;
+    a.stochastic = MODE == kLbSenderStochastic; a.seed = seed;
     constexpr bool SENDER = MODE != kLbReceiver;
     constexpr int ROUND = MODE == kLbSenderStochastic ? AQSGD_ROUND_STOCHASTIC : AQSGD_ROUND_NEAREST;
     constexpr bool kMultiWave = TEAM > kWave;
@@ -394,35 +401,36 @@ inline bool lowbit_tail_chunks(int cpg, int cpl) {
 }
 
 // ---- launch table (instantiated per dtype in aqsgd_lowbit_<dtype>.hip) ----------------
+template <int DT, int BITS, int MBITS, int MODE, int TEAM, int CPL, bool TAILK = false>
+static hipError_t launch_lb(LaunchGeom g, const LowbitArgs& a, hipStream_t s) {
+    void* data = MODE == kLbReceiver ? a.out : const_cast<void*>(a.act);
+    return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, TEAM, CPL, MODE, TAILK>, dim3(g.grid_x, g.grid_y),
+                         dim3(TEAM > kWave ? TEAM : kBlock), s, data, a.ids, a.m_codes, a.m_scales, a.codes,
+                         a.group, a.cpg, a.n_per, a.scales, a.gps, a.batch, a.seed);
+}
+
+// One wave per group, CPL chunks per lane: the single-element-tail variant where it applies.
+template <int DT, int BITS, int MBITS, int MODE, int CPL>
+static hipError_t launch_lb_wave(LaunchGeom g, const LowbitArgs& a, hipStream_t s) {
+    if constexpr (lowbit_tail_variant<DT, BITS, MODE>()) {
+        if (lowbit_tail_chunks(a.cpg, CPL)) return launch_lb<DT, BITS, MBITS, MODE, 64, CPL, true>(g, a, s);
+    }
+    return launch_lb<DT, BITS, MBITS, MODE, 64, CPL>(g, a, s);
+}
+
 template <int DT, int BITS, int MBITS, int MODE>
 static hipError_t launch_lb_shape(int shape, LaunchGeom g, const LowbitArgs& a, hipStream_t s) {
-    const dim3 grid(g.grid_x, g.grid_y);
     switch (shape) {
-    case kLb8x1:    return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 8, 1, MODE>, grid, dim3(kBlock), s, a);
-    case kLb16x1:   return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 16, 1, MODE>, grid, dim3(kBlock), s, a);
-    case kLb32x1:   return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 32, 1, MODE>, grid, dim3(kBlock), s, a);
-    case kLb64x1:   return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 64, 1, MODE>, grid, dim3(kBlock), s, a);
-    case kLb64x2:
-        if constexpr (lowbit_tail_variant<DT, BITS, MODE>()) {
-            if (lowbit_tail_chunks(a.cpg, 2))
-                return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 64, 2, MODE, true>, grid, dim3(kBlock), s, a);
-        }
-        return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 64, 2, MODE>, grid, dim3(kBlock), s, a);
-    case kLb64x3:
-        if constexpr (lowbit_tail_variant<DT, BITS, MODE>()) {
-            if (lowbit_tail_chunks(a.cpg, 3))
-                return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 64, 3, MODE, true>, grid, dim3(kBlock), s, a);
-        }
-        return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 64, 3, MODE>, grid, dim3(kBlock), s, a);
-    case kLb64x4:
-        if constexpr (lowbit_tail_variant<DT, BITS, MODE>()) {
-            if (lowbit_tail_chunks(a.cpg, 4))
-                return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 64, 4, MODE, true>, grid, dim3(kBlock), s, a);
-        }
-        return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 64, 4, MODE>, grid, dim3(kBlock), s, a);
-    case kLb256x2:  return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 256, 2, MODE>, grid, dim3(256), s, a);
-    case kLb256x4:  return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 256, 4, MODE>, grid, dim3(256), s, a);
-    case kLb1024x2: return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, 1024, 2, MODE>, grid, dim3(1024), s, a);
+    case kLb8x1:    return launch_lb<DT, BITS, MBITS, MODE, 8, 1>(g, a, s);
+    case kLb16x1:   return launch_lb<DT, BITS, MBITS, MODE, 16, 1>(g, a, s);
+    case kLb32x1:   return launch_lb<DT, BITS, MBITS, MODE, 32, 1>(g, a, s);
+    case kLb64x1:   return launch_lb<DT, BITS, MBITS, MODE, 64, 1>(g, a, s);
+    case kLb64x2:   return launch_lb_wave<DT, BITS, MBITS, MODE, 2>(g, a, s);
+    case kLb64x3:   return launch_lb_wave<DT, BITS, MBITS, MODE, 3>(g, a, s);
+    case kLb64x4:   return launch_lb_wave<DT, BITS, MBITS, MODE, 4>(g, a, s);
+    case kLb256x2:  return launch_lb<DT, BITS, MBITS, MODE, 256, 2>(g, a, s);
+    case kLb256x4:  return launch_lb<DT, BITS, MBITS, MODE, 256, 4>(g, a, s);
+    case kLb1024x2: return launch_lb<DT, BITS, MBITS, MODE, 1024, 2>(g, a, s);
     default:        return hipErrorInvalidValue;
     }
 }

@@ -690,15 +690,23 @@ __device__ __forceinline__ uint32_t xcd_contiguous_slot(uint32_t block, uint32_t
 }
 
 // MODE: 0 receiver, 1 sender with nearest rounding, 2 sender with stochastic rounding.
+// `data`: the sender's grad, the receiver's out.  Plain arguments, the first fourteen words of
+// them in scalar registers before a wave starts (see aqsgd_single.h): all but the seed, and
+// the grid's size among them, which the numbering needs before anything can be addressed and
+// which would be a fetch of its own otherwise.
 template <int DT, int CPL, int MODE>
 __global__ __launch_bounds__(kTopkBlock)
-void topk_kernel(const TopkArgs a) {
+void topk_kernel(void* data, uint8_t* bitmap, uint8_t* codes, float* scales, int64_t n_groups, int32_t group,
+                 int32_t cpg, int32_t keep, uint32_t n_blocks, uint64_t seed) {
+    TopkArgs a;
+    a.grad = data; a.out = data; a.bitmap = bitmap; a.codes = codes; a.scales = scales;
+    a.n_groups = n_groups; a.group = group; a.cpg = cpg; a.keep = keep; a.stochastic = MODE == 2; a.seed = seed;
     constexpr int kWaves = kTopkBlock / kWave;
     __shared__ __align__(16) TopkLds lds_all[kWaves];
 
     const int lane = threadIdx.x % kWave;
     const int wave = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const uint32_t slot = xcd_contiguous_slot(blockIdx.x, gridDim.x);
+    const uint32_t slot = xcd_contiguous_slot(blockIdx.x, n_blocks);
     uint32_t cc[CPL];
     bool valid[CPL];
 #pragma unroll
@@ -707,7 +715,7 @@ void topk_kernel(const TopkArgs a) {
         valid[k] = c < a.cpg;
         cc[k] = static_cast<uint32_t>(min(c, a.cpg - 1));
     }
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kWaves;
+    const int64_t stride = static_cast<int64_t>(n_blocks) * kWaves;
     int64_t g = static_cast<int64_t>(slot) * kWaves + wave;
     if constexpr (MODE == 1 && KeyBytes<DT>::value == 2) {
         // The loads of the wave's first group go out before anything else: a launch is one

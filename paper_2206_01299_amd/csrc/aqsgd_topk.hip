@@ -4,13 +4,20 @@
 
 namespace aqsgd {
 
+template <int DT, int CPL, int MODE>
+static hipError_t launch_topk_as(unsigned blocks, const TopkArgs& a, hipStream_t s) {
+    void* data = MODE == 0 ? a.out : const_cast<void*>(a.grad);
+    return launch_kernel(topk_kernel<DT, CPL, MODE>, dim3(blocks), dim3(kTopkBlock), s, data, a.bitmap, a.codes,
+                         a.scales, a.n_groups, a.group, a.cpg, a.keep, blocks, a.seed);
+}
+
 template <int DT, int MODE>
 static hipError_t launch_topk_cpl(int cpl, unsigned blocks, const TopkArgs& a, hipStream_t s) {
     switch (cpl) {
-    case 1: return launch_kernel(topk_kernel<DT, 1, MODE>, dim3(blocks), dim3(kTopkBlock), s, a);
-    case 2: return launch_kernel(topk_kernel<DT, 2, MODE>, dim3(blocks), dim3(kTopkBlock), s, a);
-    case 3: return launch_kernel(topk_kernel<DT, 3, MODE>, dim3(blocks), dim3(kTopkBlock), s, a);
-    case 4: return launch_kernel(topk_kernel<DT, 4, MODE>, dim3(blocks), dim3(kTopkBlock), s, a);
+    case 1: return launch_topk_as<DT, 1, MODE>(blocks, a, s);
+    case 2: return launch_topk_as<DT, 2, MODE>(blocks, a, s);
+    case 3: return launch_topk_as<DT, 3, MODE>(blocks, a, s);
+    case 4: return launch_topk_as<DT, 4, MODE>(blocks, a, s);
     default: return hipErrorInvalidValue;
     }
 }
