@@ -204,8 +204,8 @@ void dequant_odd_kernel(AQSGD_DEQUANT_ARGS) {
 // group is read once, in one launch, where the large groups' way takes three launches and two
 // readings.  All loads of a workgroup are back before its first store (the maximum waits for
 // them), so a group's last piece may repeat elements of the one before it: same values, same
-// results, same place.  Few groups are bound by what one compute unit draws (about 10 us for an
-// encode of 49152 elements, however few groups), many by memory.  Measured as four calls on
+// results, same place.  Few groups are bound by one compute unit's arithmetic (about 10 us for an
+// encode of 49152 elements, however few groups; those are split, see below), many by memory.  Measured as four calls on
 // groups of 49152, large groups' way -> this: bfloat16, 8 groups 29.4 -> 19.2 us, 256 groups
 // 74 -> 48.5, 1024 groups 237 -> 182; float32, 8 groups 27.6 -> 26.0, 256 groups 117 -> 80,
 // 1024 groups 431 -> 326.
@@ -386,6 +386,20 @@ constexpr int kLargeUnroll = 4;                          // pieces per lane and 
 constexpr int64_t kLargeMinSpanPieces = static_cast<int64_t>(kBlock) * kLargeUnroll;
 constexpr int64_t kLargeMaxBlocks = 2048;                // about what is resident at once
 
+// Pieces (of 4 elements in float32, 8 else) per lane and step of a split group's workgroup: 4096
+// elements a step, which is the length the host aims a span at.
+constexpr int kSplitSpanElements = 4096;
+template <int DT> constexpr int kSplitUnroll = kSplitSpanElements / (kBlock * (DT == AQSGD_F32 ? 4 : 8));
+constexpr int kSplitMaxSpans = 16;                       // slots read by one wave; a span's codes hold them all
+
+// Where the spans of a split group leave their maxima for span `span`: one word for each span,
+// in the place that span's own codes are going to take (at any byte).
+__device__ __forceinline__ u32_any_t* split_slots(const QuantJob& a, const LargeGeom& geom, int i, int64_t g, int span) {
+    const int64_t first = static_cast<int64_t>(i) * a.n_per + g * a.group;
+    uint8_t* codes_g = a.codes + first * a.bits / 8;
+    return reinterpret_cast<u32_any_t*>(codes_g + static_cast<int64_t>(span) * geom.span_pieces * a.bits);
+}
+
 template <bool HAS_BUF>
 __device__ __forceinline__ bool large_fresh(const QuantJob& a, int64_t row) {
     if constexpr (HAS_BUF)
@@ -405,8 +419,9 @@ void large_clear_kernel(const QuantJob a) {
     }
 }
 
-template <int DT, bool HAS_BUF>
+template <int DT, bool HAS_BUF, bool SLOTS = false>
 __device__ __forceinline__ void large_max_body(const QuantJob& a, const LargeGeom geom, float* wave_max) {
+    constexpr int kUnroll = SLOTS ? kSplitUnroll<DT> : kLargeUnroll;
     constexpr int N = DT == AQSGD_F32 ? 4 : 8;
     constexpr int kEB = ElemBytes<DT>::value;
     const int64_t last_at = a.group - N;
@@ -423,17 +438,17 @@ __device__ __forceinline__ void large_max_body(const QuantJob& a, const LargeGeo
             const char* m_g = HAS_BUF ? m_s + g * a.group * kEB : nullptr;
             float mx = 0.0f;
             for (int64_t e = e0 + static_cast<int64_t>(threadIdx.x) * N; e < e1;
-                 e += static_cast<int64_t>(kBlock) * N * kLargeUnroll) {
-                float x[kLargeUnroll][N], m[kLargeUnroll][N];
+                 e += static_cast<int64_t>(kBlock) * N * kUnroll) {
+                float x[kUnroll][N], m[kUnroll][N];
 #pragma unroll
-                for (int u = 0; u < kLargeUnroll; ++u) { // past the end: the group's last piece once more
+                for (int u = 0; u < kUnroll; ++u) { // past the end: the group's last piece once more
                     const int64_t at = min(e + static_cast<int64_t>(u) * kBlock * N, last_at);
                     load_piece<DT, N>(src_g + at * kEB, x[u]);
                     if constexpr (HAS_BUF) load_piece<DT, N>(m_g + at * kEB, m[u]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int u = 0; u < kLargeUnroll; ++u)
+                for (int u = 0; u < kUnroll; ++u)
 #pragma unroll
                     for (int k = 0; k < N; ++k) {
                         const float d = HAS_BUF ? x[u][k] - m[u][k] : x[u][k];
@@ -444,7 +459,13 @@ __device__ __forceinline__ void large_max_body(const QuantJob& a, const LargeGeo
             __syncthreads();                             // earlier readers of wave_max are done
             if (threadIdx.x % kWave == 0) wave_max[threadIdx.x / kWave] = mx;
             __syncthreads();
-            if (threadIdx.x == 0) {
+            if constexpr (SLOTS) {                       // into every span's slots, see split_slots()
+#pragma unroll
+                for (int w = 0; w < kBlock / kWave; ++w) mx = __builtin_fmaxf(mx, wave_max[w]);
+                const int to = threadIdx.x;
+                if (to < geom.spans)
+                    split_slots(a, geom, i, g, to)[s - g * geom.spans] = __float_as_uint(mx);
+            } else if (threadIdx.x == 0) {
 #pragma unroll
                 for (int w = 0; w < kBlock / kWave; ++w) mx = __builtin_fmaxf(mx, wave_max[w]);
                 atomicMax(reinterpret_cast<unsigned int*>(a.scales) + static_cast<int64_t>(i) * a.gps + g,
@@ -464,11 +485,12 @@ void large_max_kernel(const QuantJob a, const LargeGeom geom) {
 
 // A group below the 2^-120 floor sends scale 0; one thread rewrites its word while other
 // workgroups may still read it, and both values mean "nothing to send" to them.
-template <int DT, int BITS, int ROUND, bool HAS_BUF>
+template <int DT, int BITS, int ROUND, bool HAS_BUF, bool SLOTS = false>
 __device__ __forceinline__ void large_quant_body(const QuantJob& a, const LargeGeom geom) {
     using P = Piece<DT, BITS>;
     constexpr int N = P::elems;
     constexpr int kEB = ElemBytes<DT>::value;
+    constexpr int kUnroll = !SLOTS ? kLargeUnroll : DT == AQSGD_F32 && N == 8 ? kSplitUnroll<DT> / 2 : kSplitUnroll<DT>;
     const int64_t last_at = a.group - N;
     for (int i = blockIdx.y; i < a.batch; i += gridDim.y) {
         const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
@@ -492,23 +514,31 @@ __device__ __forceinline__ void large_quant_body(const QuantJob& a, const LargeG
             uint8_t* codes_g = a.codes + (src0 + goff) * BITS / 8;
             float* const word = a.scales + static_cast<int64_t>(i) * a.gps + g;
             GroupScale sc;
-            if (!fresh) {
+            if constexpr (SLOTS) {
+                if (!fresh) {                            // uniform over the workgroup
+                    const int span = static_cast<int>(s - g * geom.spans), from = threadIdx.x % kWave;
+                    const uint32_t part = split_slots(a, geom, i, g, span)[min(from, geom.spans - 1)];
+                    sc = make_scale<BITS>(team_max<kWave>(__uint_as_float(part)));
+                    __syncthreads();                     // every wave has read the slots: codes may go there
+                    if (span == 0 && threadIdx.x == 0) *word = sc.s_tx;
+                }
+            } else if (!fresh) {
                 sc = make_scale<BITS>(*word);
                 if (e0 == 0 && threadIdx.x == 0 && sc.s_tx == 0.0f) *word = 0.0f;
             }
             for (int64_t e = e0 + static_cast<int64_t>(threadIdx.x) * N; e < e1;
-                 e += static_cast<int64_t>(kBlock) * N * kLargeUnroll) {
-                float x[kLargeUnroll][N], m[kLargeUnroll][N];
-                int64_t at[kLargeUnroll];
+                 e += static_cast<int64_t>(kBlock) * N * kUnroll) {
+                float x[kUnroll][N], m[kUnroll][N];
+                int64_t at[kUnroll];
 #pragma unroll
-                for (int u = 0; u < kLargeUnroll; ++u) {
+                for (int u = 0; u < kUnroll; ++u) {
                     at[u] = min(e + static_cast<int64_t>(u) * kBlock * N, last_at);
                     load_piece<DT, N>(src_g + at[u] * kEB, x[u]);
                     if constexpr (HAS_BUF) load_piece<DT, N>(m_g + at[u] * kEB, m[u]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int u = 0; u < kLargeUnroll; ++u) {
+                for (int u = 0; u < kUnroll; ++u) {
                     const int64_t eu = e + static_cast<int64_t>(u) * kBlock * N;
                     if (eu >= e1) continue;
                     // the group's last piece owns what the one before it does not
@@ -519,7 +549,13 @@ __device__ __forceinline__ void large_quant_body(const QuantJob& a, const LargeG
                     }
                     float r[N], q[N], v[N];
                     if constexpr (ROUND == AQSGD_ROUND_STOCHASTIC) {
-                        uniforms_any<N>(a.seed, static_cast<uint64_t>(src0 + goff + at[u]), r);
+                        const uint64_t j0 = static_cast<uint64_t>(src0 + goff + at[u]);
+                        if (a.group % 4 != 0) {          // uniform over the launch
+                            uniforms_any<N>(a.seed, j0, r);
+                        } else {                         // whole Philox blocks
+#pragma unroll
+                            for (int b = 0; b < N; b += 4) block_uniforms(a.seed, (j0 + b) >> 2, &r[b]);
+                        }
                     } else {
 #pragma unroll
                         for (int k = 0; k < N; ++k) r[k] = kNearestOffset32;
@@ -565,10 +601,57 @@ void large_quant_kernel(const QuantJob a, const LargeGeom geom) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// Few wide groups: one workgroup a group leaves most of the chip idle and
+// is bound by one compute unit's arithmetic, so each group is split into spans of about 4096
+// elements, a workgroup each, in two launches: every span's maximum, then the levels.  The maxima
+// travel in the code bytes of the group: each span writes its maximum into a slot of every span,
+// and the second launch's workgroup reads its own span's slots before its codes take their place.
+// No clearing, no atomics, no memory beyond the call's own, and nothing waits inside a launch.
+// (When it pays, and what it measured: split_pays() in the dispatch.)
+// ---------------------------------------------------------------------------
+template <int DT>
+__global__ __launch_bounds__(kBlock)
+void split_max_kernel(AQSGD_QUANT_ARGS, int32_t spans, int32_t span_pieces) {
+    __shared__ float wave_max[kBlock / kWave];
+    QuantJob a;
+    a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
+    a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
+    a.seen = seen; a.stamp = stamp;
+    const LargeGeom geom{spans, span_pieces};
+    if (a.m_buf) large_max_body<DT, true, true>(a, geom, wave_max);
+    else large_max_body<DT, false, true>(a, geom, wave_max);
+}
+
+template <int DT, int BITS, int ROUND>
+__device__ __forceinline__ void split_quant_bits(const QuantJob& a, const LargeGeom geom) {
+    if (a.m_buf) large_quant_body<DT, BITS, ROUND, true, true>(a, geom);
+    else large_quant_body<DT, BITS, ROUND, false, true>(a, geom);
+}
+
+template <int DT, int ROUND>
+__global__ __launch_bounds__(kBlock)
+void split_quant_kernel(AQSGD_QUANT_ARGS, int32_t spans, int32_t span_pieces) {
+    QuantJob a;
+    a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
+    a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
+    a.seed = seed; a.seen = seen; a.first = first; a.stamp = stamp;
+    const LargeGeom geom{spans, span_pieces};
+    switch (bits) {
+    case 2: split_quant_bits<DT, 2, ROUND>(a, geom); break;
+    case 3: split_quant_bits<DT, 3, ROUND>(a, geom); break;
+    case 4: split_quant_bits<DT, 4, ROUND>(a, geom); break;
+    case 6: split_quant_bits<DT, 6, ROUND>(a, geom); break;
+    default: split_quant_bits<DT, 8, ROUND>(a, geom); break;
+    }
+}
+
 // Per-dtype pieces (defined by AQSGD_INSTANTIATE_ANYGROUP_DTYPE in the dtype's .hip file).
 template <int DT> hipError_t launch_dequant_odd_dt(bool covers, const DequantJob& a, hipStream_t stream);
 template <int DT> hipError_t launch_quant_wide_dt(int rounding, const QuantJob& a, hipStream_t stream);
 template <int DT> hipError_t launch_quant_large_dt(int rounding, const QuantJob& a, const LargeGeom& geom,
+                                                   hipStream_t stream);
+template <int DT> hipError_t launch_quant_split_dt(int rounding, const QuantJob& a, const LargeGeom& geom,
                                                    hipStream_t stream);
 
 // ---- launch tables (instantiated per dtype in aqsgd_anygroup_<dtype>.hip) --------------
@@ -599,9 +682,23 @@ hipError_t launch_quant_large_dt(int rounding, const QuantJob& a, const LargeGeo
     return err;
 }
 
+template <int DT>
+hipError_t launch_quant_split_dt(int rounding, const QuantJob& a, const LargeGeom& geom, hipStream_t s) {
+    auto go = [&](auto kernel) {
+        return launch_kernel(kernel, dim3(a.grid_x, a.grid_y), dim3(kBlock), s, a.src, a.ids, a.m_buf, a.codes,
+                             a.scales, a.group, a.bits, a.n_per, a.gps, a.batch, a.grid_x, a.grid_y, a.stamp,
+                             a.seed, a.seen, a.first, geom.spans, geom.span_pieces);
+    };
+    const hipError_t err = go(split_max_kernel<DT>);
+    if (err != hipSuccess) return err;
+    return rounding == AQSGD_ROUND_STOCHASTIC ? go(split_quant_kernel<DT, AQSGD_ROUND_STOCHASTIC>)
+                                              : go(split_quant_kernel<DT, AQSGD_ROUND_NEAREST>);
+}
+
 #define AQSGD_INSTANTIATE_ANYGROUP_DTYPE(DT)                                                          \
     template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);                   \
     template hipError_t launch_quant_wide_dt<DT>(int, const QuantJob&, hipStream_t);                       \
-    template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t);
+    template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t);   \
+    template hipError_t launch_quant_split_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t);
 
 }  // namespace aqsgd

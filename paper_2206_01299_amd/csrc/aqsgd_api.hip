@@ -20,6 +20,7 @@ namespace aqsgd {
     extern template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);       \
     extern template hipError_t launch_quant_wide_dt<DT>(int, const QuantJob&, hipStream_t);           \
     extern template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
+    extern template hipError_t launch_quant_split_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
     extern template hipError_t launch_lowbit_dt<DT>(int, int, int, bool, LaunchGeom, const LowbitArgs&, hipStream_t);
 AQSGD_EXTERN_DTYPE(AQSGD_F32)
 AQSGD_EXTERN_DTYPE(AQSGD_F16)
@@ -98,6 +99,14 @@ hipError_t launch_quant_large(int dtype, int rounding, const QuantJob& a, const 
     case AQSGD_F32:  return launch_quant_large_dt<AQSGD_F32>(rounding, a, geom, s);
     case AQSGD_F16:  return launch_quant_large_dt<AQSGD_F16>(rounding, a, geom, s);
     case AQSGD_BF16: return launch_quant_large_dt<AQSGD_BF16>(rounding, a, geom, s);
+    default:         return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_quant_split(int dtype, int rounding, const QuantJob& a, const LargeGeom& geom, hipStream_t s) {
+    switch (dtype) {
+    case AQSGD_F32:  return launch_quant_split_dt<AQSGD_F32>(rounding, a, geom, s);
+    case AQSGD_F16:  return launch_quant_split_dt<AQSGD_F16>(rounding, a, geom, s);
+    case AQSGD_BF16: return launch_quant_split_dt<AQSGD_BF16>(rounding, a, geom, s);
     default:         return hipErrorInvalidValue;
     }
 }
@@ -350,6 +359,31 @@ LargeGeom large_geometry(const QuantJob& a) {
     return g;
 }
 
+// Few wide groups go out as spans (see split_max_kernel) where one compute unit's arithmetic on a
+// group lasts longer than a second launch: with stochastic rounding, and in float32 with previous
+// messages, up to the number of groups from which one workgroup each is as fast.  Groups of
+// 49152, four calls (encode and grad_quant are the two that may split), one workgroup -> spans:
+// float32 nearest, 1 group 24.4 -> 19.7 us, 8 groups 26.4 -> 19.3, 32 groups 31.1 -> 27.3, 64
+// groups 36.8 -> 35.9; stochastic, 8 groups 34.5 -> 22.7 (bfloat16 28.2 -> 21.3), 32 groups
+// 39.6 -> 28.6 (31.8 -> 24.0), 128 groups 58.0 -> 64.6 (42.4 -> 44.9).  Nearest rounding of 16-bit
+// types stays with one workgroup: 8 groups 19.2 us, split 18.0 to 21.7 with how fast the host
+// issues the fifth launch.
+bool split_pays(const QuantJob& a, int dtype, int rounding) {
+    const int64_t groups = a.gps * a.batch;
+    return rounding == AQSGD_ROUND_STOCHASTIC ? groups <= 64
+                                              : dtype == AQSGD_F32 && a.m_buf != nullptr && groups <= 32;
+}
+
+// Their spans are of nearly equal length, so that the last one, too, has codes enough for the
+// slots (groups of 32769 elements and more: never fewer than 1800 elements a span).
+LargeGeom split_geometry(const QuantJob& a) {
+    LargeGeom g;
+    const int spans = (a.group + kSplitSpanElements - 1) / kSplitSpanElements;
+    g.spans = spans < kSplitMaxSpans ? spans : kSplitMaxSpans;
+    g.span_pieces = (a.cpg + g.spans - 1) / g.spans;
+    return g;
+}
+
 // The rectangle of a message launched by itself: one workgroup for every sample and step if
 // that stays below `cap` and the grid's second dimension, which is what this tells.
 template <typename Job>
@@ -370,6 +404,11 @@ hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_b
         return launch_quant_single(p.dtype, p.rounding, p.shape, covers, a, stream);
     }
     case Route::kWide:
+        if (split_pays(a, p.dtype, p.rounding)) {
+            const LargeGeom sg = split_geometry(a);
+            if (one_step_grid(a, a.gps * sg.spans, 1, max_blocks))
+                return launch_quant_split(p.dtype, p.rounding, a, sg, stream);
+        }
         if (one_step_grid(a, a.gps, 1, max_blocks)) return launch_quant_wide(p.dtype, p.rounding, a, stream);
         [[fallthrough]];                                 // too many for a grid: the kernels that loop
     case Route::kLarge: {

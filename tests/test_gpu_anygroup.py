@@ -59,6 +59,16 @@ def test_groups_beyond_a_workgroup(H, dtype, bits, group):
         _sweep(H, dtype, bits, group, rounding, gps, batch=2)
 
 
+@pytest.mark.parametrize("dtype,bits,group,gps", [("bf16", 8, 32776, 16), ("bf16", 8, 32776, 17), ("f32", 3, 49152, 17),
+                                                  ("f16", 8, 32769, 17)])
+def test_wide_groups_few_and_many(H, dtype, bits, group, gps):
+    """Up to 32 groups in a call (64 with stochastic rounding) go out as spans, more as one
+    workgroup each (two samples a call)."""
+    for rounding, n in ((W.NEAREST, gps), (W.STOCHASTIC, 2 * gps)):
+        print(f"wide {dtype} b{bits} G{group} x {n} r{rounding}", flush=True)
+        _sweep(H, dtype, bits, group, rounding, n, batch=2)
+
+
 def test_large_groups_without_a_change_send_scale_zero(H):
     """Groups whose maximum is zero or below the 2^-120 floor next to one that is not."""
     import oracle
