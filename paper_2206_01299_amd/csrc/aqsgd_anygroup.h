@@ -139,7 +139,7 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a) {
                     load_piece<DT, N>(static_cast<const char*>(a.full) + (out0 + at[u]) * kEB, m[u]);
                     continue;
                 }
-                w[u] = load_bytes_any<P::code_bytes>(codes_s + (g * a.group * BITS / 8 + in_group * BITS / 8));
+                w[u] = load_bytes_any<P::code_bytes>(codes_s + static_cast<uint64_t>(at[u]) * BITS / 8);   // whole bytes
                 scale[u] = scales_s[g];
                 if constexpr (HAS_BUF) load_piece<DT, N>(m_s + at[u] * kEB, m[u]);
             }

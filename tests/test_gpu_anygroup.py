@@ -95,3 +95,53 @@ def test_large_groups_without_a_change_send_scale_zero(H):
 @pytest.mark.parametrize("group,gps", [(1020, 9), (12, 50), (32772, 2), (40000, 1)])
 def test_first_visits(H, dtype, group, gps):
     replay_seen(H, dtype, 4, group, gps * group, 12, 4, 4, W.NEAREST, group)
+
+
+@pytest.mark.parametrize("dtype,bits,group", [("f16", 8, 2**29 + 9), ("f32", 8, 2**29 + 12), ("bf16", 4, 2**30 + 10),
+                                              ("f16", 6, 715828012)])
+def test_code_offsets_beyond_32_bits(H, dtype, bits, group):
+    """One odd group whose code bits pass 2^32: every element is reconstructed from its own code.
+    The oracle would take minutes; the wire format's formula in plain torch, one rounding per
+    operation, is compared whole.  The 8-bit message is also quantised, by the large groups' way."""
+    d, td = H.dev(), B.DTYPE_NAME[dtype]
+    desc = B.make_desc(batch=1, n_per=group, n_samples=1, bits=bits, group=group, dtype=dtype)
+    print(f"huge {dtype} b{bits} G{group}", flush=True)
+    gen = torch.Generator(device=d)
+    gen.manual_seed(group)
+    codes = torch.randint(0, 256, (B.codes_bytes(desc),), dtype=torch.uint8, device=d, generator=gen)
+    s, half = np.float32(3.0), np.float32(((1 << bits) - 1) / 2)
+    scales = torch.full((1,), float(s), device=d)
+    step = float(s / half)
+    m = torch.randn(group, dtype=torch.float32, device=d, generator=gen).to(td).view(1, -1)
+    m_old, out = m.clone(), torch.empty((1, group), dtype=td, device=d)
+    grad = torch.empty((1, group), dtype=td, device=d)
+    B.decode(desc, codes, scales, torch.zeros(1, dtype=torch.int64, device=d), m, out)
+    B.grad_dequant(desc, codes, scales, grad)
+
+    def levels(lo, hi):                                      # of elements lo .. hi, lo a multiple of 8
+        b = codes[lo * bits // 8:hi * bits // 8].int()
+        if bits == 8:
+            return b
+        if bits == 4:
+            return torch.stack((b & 15, b >> 4), 1).view(-1)
+        b = b.view(-1, 3)
+        w = b[:, 0] | (b[:, 1] << 8) | (b[:, 2] << 16)
+        return torch.stack([(w >> (6 * e)) & 63 for e in range(4)], 1).view(-1)
+
+    span = 1 << 26
+    for lo in range(0, group, span):
+        hi = min(lo + span, group)
+        v = (levels(lo, hi).float() - float(half)) * step
+        assert torch.equal(grad[0, lo:hi], v.to(td)), f"grad_dequant, elements from {lo}"
+        want = (m_old[0, lo:hi].float() + v).to(td)
+        assert torch.equal(out[0, lo:hi], want) and torch.equal(m[0, lo:hi], want), f"decode, elements from {lo}"
+    if bits == 8:
+        x, got = m_old, torch.empty_like(codes)
+        B.grad_quant(desc, x, got, scales)
+        top = np.float32(x.abs().max().item())
+        assert scales.item() == top
+        inv = float(half / top)
+        for lo in range(0, group, span):
+            hi = min(lo + span, group)
+            q = torch.floor((x[0, lo:hi].float() * inv + float(half)) + 0.5).to(torch.uint8)
+            assert torch.equal(got[lo:hi], q), f"grad_quant, elements from {lo}"
