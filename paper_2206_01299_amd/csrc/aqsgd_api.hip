@@ -393,6 +393,17 @@ bool one_step_grid(Job& a, int64_t units, int64_t units_per_block, int64_t cap) 
     return g.grid_y == static_cast<uint32_t>(a.batch) && static_cast<int64_t>(g.grid_x) * units_per_block >= units;
 }
 
+// A workgroup's step is one sample's at most.  Where a sample fits one chunk per lane, the further
+// chunks of a step have nothing of their own: their lanes read the row's last piece once more while
+// another wave writes it, and with thousands of such workgroups in flight that is what bounds the
+// launch.  So those go out with one chunk per lane.  Measured, decode at 4 bits, two chunks a lane ->
+// one (as tables of one): float32 768 elements, 1024 samples 5.13 -> 4.45 us (5.62), 16384 samples
+// 43.6 -> 27.8 (32.5); float16 2048 elements, 1024 samples 4.82 -> 4.71 (5.38), 16384 samples 36.6
+// -> 32.1 (34.4).  With 256 samples the launch is over sooner than that matters (float32 1536
+// elements 3.64 -> 3.88), and beyond one chunk per lane it costs (float32 3072 elements, 4096
+// samples 26.6 -> 28.9).
+bool many_short_samples(const DequantJob& a) { return a.cps <= kBlock && a.batch >= 1024; }
+
 // A quantising message outside the job kernels' range.
 hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_blocks, hipStream_t stream) {
     QuantJob& a = p.job;
@@ -460,10 +471,12 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
             err = launch_quant_single(qs[0].dtype, qs[0].rounding, qs[0].shape, true, qs[0].job, stream);
             return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
         }
-        if (!ds.empty() && ds[0].route == Route::kJob &&
-            one_step_grid(ds[0].job, ds[0].job.cps, static_cast<int64_t>(kBlock) * unroll, max_blocks)) {
-            err = launch_dequant_single(ds[0].dtype, unroll, ds[0].job, stream);
-            return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
+        if (!ds.empty() && ds[0].route == Route::kJob) {
+            const int chunks = many_short_samples(ds[0].job) ? 1 : unroll;
+            if (one_step_grid(ds[0].job, ds[0].job.cps, static_cast<int64_t>(kBlock) * chunks, max_blocks)) {
+                err = launch_dequant_single(ds[0].dtype, chunks, ds[0].job, stream);
+                return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
+            }
         }
     }
     auto add_dequant = [&](JobTable& t, int dtype) {

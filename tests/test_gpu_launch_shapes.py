@@ -65,3 +65,19 @@ def test_more_samples_than_the_grid_has_rows(bits, group):
     import gpu_harness as H
     H.replay_and_compare(_cfg("f16", bits, group, W.NEAREST, 1, batch=65538, n_samples=65540),
                          calls_per_epoch=1, epochs=2, log=lambda *a, **k: None)
+
+
+@pytest.mark.parametrize("dtype,bits", [("f32", 4), ("f32", 3), ("f16", 8), ("bf16", 3)])
+def test_many_samples_of_about_one_chunk_per_lane(dtype, bits):
+    """Reconstruction takes one chunk a lane from 1024 samples of at most 256 chunks on: both
+    sides of both limits, and rows far below them."""
+    if not torch.cuda.is_available():
+        pytest.fail("needs the MI355X")
+    B.lib()
+    import oracle
+    oracle.build()
+    import gpu_harness as H
+    for n_per, batch in ((2048, 1024), (2056, 1024), (2048, 1023), (8, 1025), (520, 1500)):
+        print("short samples", dtype, bits, n_per, batch, flush=True)
+        H.replay_and_compare(_cfg(dtype, bits, n_per, W.NEAREST, 1, batch=batch, n_samples=batch + 3),
+                             calls_per_epoch=1, epochs=2, log=lambda *a, **k: None)
