@@ -930,7 +930,9 @@ hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStr
 // Team shapes the dispatcher may pick; index into the table below.
 enum TeamShape {
     kTeam8x1 = 0, kTeam16x1, kTeam32x1, kTeam64x1, kTeam64x2, kTeam64x3, kTeam64x4,
-    kTeam256x2, kTeam256x4, kTeam1024x2, kTeam1024x4, kNumTeamShapes
+    kTeam256x2, kTeam256x4, kTeam1024x2, kTeam1024x4,
+    kTeam2x1,                                            // odd groups of 9 to 15 elements only
+    kNumTeamShapes
 };
 
 // A launch of codec_jobs_kernel (the table's quantising jobs all have this rounding

@@ -95,6 +95,9 @@ static hipError_t launch_quant_single_as(const QuantJob& a, hipStream_t s) {
 template <int DT, int ROUND, int KIND>
 static hipError_t launch_quant_single_shape(int shape, const QuantJob& a, hipStream_t s) {
     switch (shape) {
+    case kTeam2x1:
+        if constexpr (KIND == kSingleOdd || KIND == kSingleOddLoops) return launch_quant_single_as<DT, ROUND, 2, 1, KIND>(a, s);
+        else return hipErrorInvalidValue;
     case kTeam8x1:    return launch_quant_single_as<DT, ROUND, 8, 1, KIND>(a, s);
     case kTeam16x1:   return launch_quant_single_as<DT, ROUND, 16, 1, KIND>(a, s);
     case kTeam32x1:   return launch_quant_single_as<DT, ROUND, 32, 1, KIND>(a, s);

@@ -48,6 +48,16 @@ def test_odd_groups(H, dtype, bits):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("bits,group", [(8, 9), (8, 11), (8, 15), (4, 10), (4, 14), (6, 12), (2, 12), (8, 17)])
+def test_odd_groups_of_two_chunks(H, dtype, bits, group):
+    """Teams of two lanes, 256 groups to a workgroup's step: whole and ragged steps."""
+    for rounding in (W.NEAREST, W.STOCHASTIC):
+        for gps in (1, 255, 256, 613):
+            print(f"two chunks {dtype} b{bits} G{group} r{rounding} x{gps}", flush=True)
+            _sweep(H, dtype, bits, group, rounding, gps)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("bits,group", [(4, 32776), (3, 32776), (8, 32769), (2, 32772), (6, 40004), (8, 65537),
                                         (4, 262144), (3, 262152), (8, 300001),
                                         # the last group one workgroup holds, and the first beyond
