@@ -205,34 +205,46 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- rounding offsets: they depend on the element index only, so the generator
-    //      runs while the loads are in flight (second barrier: it stays up here) -------
+    //      runs while the loads are in flight (second barrier: it stays up here).  The widest
+    //      team has 128 registers a lane and, with previous messages, none left to hold them:
+    //      bfloat16, float32 and all odd groups had 52 to 336 bytes a lane in scratch.  They
+    //      draw a chunk's where these are used (scratch none, float32 12 bytes).  Encode of 512
+    //      groups of 24576, drawn ahead -> at use: bfloat16 27.4 -> 21.5 us, float32 45.2 -> 40.2;
+    //      of 24570: bfloat16 49.9 -> 24.9, float32 105.6 -> 43.8, float16 34.4 -> 25.3.  Where
+    //      they do fit, ahead is faster: float16, 512 groups of 32768, encode 19.9 us and 23.5 at
+    //      use, grad_quant 13.3 and 14.4 --------------------------------------------------------
+    constexpr bool kDrawAhead =
+        ROUND == AQSGD_ROUND_STOCHASTIC && !(TEAM * CPL >= 4096 && HAS_BUF && (ODD || DT != AQSGD_F16));
+    auto draw = [&](int u, int k, float (&r)[kChunk]) {
+        const uint64_t j0 = static_cast<uint64_t>(src0 + goff[u]);
+        if constexpr (ODD && kUnits) {
+            float ra4[kUnit], rb4[kUnit];
+            uniforms_any<kUnit>(a.seed, j0 + ua[k], ra4);
+            uniforms_any<kUnit>(a.seed, j0 + ub[k], rb4);
+#pragma unroll
+            for (int e = 0; e < kUnit; ++e) { r[e] = ra4[e]; r[kUnit + e] = rb4[e]; }
+        } else if constexpr (ODD) {
+            uniforms_any<kChunk>(a.seed, j0 + cc[k], r);
+        } else if constexpr (kUnits) {
+            units_uniforms(a.seed, j0 + ua[k] * kUnit, j0 + ub[k] * kUnit, r);
+        } else {
+            chunk_uniforms(a.seed, j0 + cc[k] * kChunk, r);
+        }
+    };
     float r[NG][CPL][kChunk];
 #pragma unroll
     for (int u = 0; u < NG; ++u) {
 #pragma unroll
         for (int k = 0; k < CPL; ++k) {
-            if constexpr (ROUND == AQSGD_ROUND_STOCHASTIC) {
-                const uint64_t j0 = static_cast<uint64_t>(src0 + goff[u]);
-                if constexpr (ODD && kUnits) {
-                    float ra4[kUnit], rb4[kUnit];
-                    uniforms_any<kUnit>(a.seed, j0 + ua[k], ra4);
-                    uniforms_any<kUnit>(a.seed, j0 + ub[k], rb4);
-#pragma unroll
-                    for (int e = 0; e < kUnit; ++e) { r[u][k][e] = ra4[e]; r[u][k][kUnit + e] = rb4[e]; }
-                } else if constexpr (ODD) {
-                    uniforms_any<kChunk>(a.seed, j0 + cc[k], r[u][k]);
-                } else if constexpr (kUnits) {
-                    units_uniforms(a.seed, j0 + ua[k] * kUnit, j0 + ub[k] * kUnit, r[u][k]);
-                } else {
-                    chunk_uniforms(a.seed, j0 + cc[k] * kChunk, r[u][k]);
-                }
-            } else {
+            if constexpr (kDrawAhead) {
+                draw(u, k, r[u][k]);
+            } else if constexpr (ROUND == AQSGD_ROUND_NEAREST) {
 #pragma unroll
                 for (int e = 0; e < kChunk; ++e) r[u][k][e] = kNearestOffset32;
             }
         }
     }
-    if constexpr (ROUND == AQSGD_ROUND_STOCHASTIC) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kDrawAhead) __builtin_amdgcn_sched_barrier(0);
 
     // ---- delta and each group's max-abs ---------------------------------------------
     float d[NG][CPL][kChunk];
@@ -263,6 +275,10 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
 #pragma unroll
         for (int k = 0; k < CPL; ++k) {
             float q[kChunk], dh[kChunk];
+            if constexpr (ROUND == AQSGD_ROUND_STOCHASTIC && !kDrawAhead) {
+                __builtin_amdgcn_sched_barrier(0);       // one chunk's temporaries at a time
+                draw(u, k, r[u][k]);
+            }
 #pragma unroll
             for (int e = 0; e < kChunk; ++e) {
                 q[e] = level_of<BITS, ROUND>(d[u][k][e], sc[u], r[u][k][e]);
