@@ -377,9 +377,11 @@ int aqsgd_set_launch_shape(int64_t max_blocks, int32_t dequant_unroll);
  * Measurement helper (per-thread state): the next codec launch made by the calling host thread
  * stamps `start_event` and `stop_event` (hipEvent_t created with timing enabled,
  * passed as void*; either may be NULL) with the kernel's own begin and end, so
- * hipEventElapsedTime(start, stop) is that launch's duration on the device.  The
- * request applies to one launch and is then cleared.  Such a launch cannot be
- * recorded into a HIP graph.
+ * hipEventElapsedTime(start, stop) is that launch's duration on the device.  A message
+ * that takes two or three kernels (groups of more than 32768 elements) counts as one
+ * launch: its first kernel's begin and its last one's end.  The request applies to one
+ * launch, the first of an aqsgd_run_jobs call that makes several, and is then cleared.
+ * Such a launch cannot be recorded into a HIP graph.
  */
 int aqsgd_profile_next_launch(void* start_event, void* stop_event);
 

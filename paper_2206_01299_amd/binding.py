@@ -498,7 +498,8 @@ def set_launch_shape(max_blocks: int = 0, dequant_unroll: int = 0) -> None:
 
 def profile_next_launch(start: "torch.cuda.Event", stop: "torch.cuda.Event") -> None:
     """Have the next codec launch of this thread stamp two timing events with the
-    kernel's own begin and end.  The events must already exist on the device
+    kernel's own begin and end (of a message's first and last kernel where it takes
+    several).  The events must already exist on the device
     (a torch event is created by its first ``record()``)."""
     _raise(lib().aqsgd_profile_next_launch(ctypes.c_void_p(start.cuda_event),
                                            ctypes.c_void_p(stop.cuda_event)))

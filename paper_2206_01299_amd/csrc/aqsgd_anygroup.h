@@ -672,14 +672,15 @@ template <int DT>
 hipError_t launch_quant_large_dt(int rounding, const QuantJob& a, const LargeGeom& geom, hipStream_t s) {
     const int64_t clear_x = (a.gps + kBlock - 1) / kBlock;
     const dim3 grid(a.grid_x, a.grid_y), block(kBlock);
+    ProfileSpan span;
     hipError_t err = launch_kernel(large_clear_kernel, dim3(static_cast<unsigned>(clear_x < 1024 ? clear_x : 1024), a.grid_y),
                                    block, s, a);
     if (err == hipSuccess) err = launch_kernel(large_max_kernel<DT>, grid, block, s, a, geom);
-    if (err == hipSuccess)
-        err = rounding == AQSGD_ROUND_STOCHASTIC
-                  ? launch_kernel(large_quant_kernel<DT, AQSGD_ROUND_STOCHASTIC>, grid, block, s, a, geom)
-                  : launch_kernel(large_quant_kernel<DT, AQSGD_ROUND_NEAREST>, grid, block, s, a, geom);
-    return err;
+    if (err != hipSuccess) return err;
+    span.last();
+    return rounding == AQSGD_ROUND_STOCHASTIC
+               ? launch_kernel(large_quant_kernel<DT, AQSGD_ROUND_STOCHASTIC>, grid, block, s, a, geom)
+               : launch_kernel(large_quant_kernel<DT, AQSGD_ROUND_NEAREST>, grid, block, s, a, geom);
 }
 
 template <int DT>
@@ -689,8 +690,10 @@ hipError_t launch_quant_split_dt(int rounding, const QuantJob& a, const LargeGeo
                              a.scales, a.group, a.bits, a.n_per, a.gps, a.batch, a.grid_x, a.grid_y, a.stamp,
                              a.seed, a.seen, a.first, geom.spans, geom.span_pieces);
     };
+    ProfileSpan span;
     const hipError_t err = go(split_max_kernel<DT>);
     if (err != hipSuccess) return err;
+    span.last();
     return rounding == AQSGD_ROUND_STOCHASTIC ? go(split_quant_kernel<DT, AQSGD_ROUND_STOCHASTIC>)
                                               : go(split_quant_kernel<DT, AQSGD_ROUND_NEAREST>);
 }

@@ -924,6 +924,19 @@ struct LaunchGeom { uint32_t grid_x, grid_y; };
 struct ProfileRequest { hipEvent_t start, stop; };
 extern thread_local ProfileRequest g_profile_request;
 
+// A message that takes several kernels is one launch to such a request: the first kernel stamps
+// its begin, the last one its end.  Constructed before the first kernel; last() before the last.
+class ProfileSpan {
+public:
+    ProfileSpan() : stop_(g_profile_request.stop) { g_profile_request.stop = nullptr; }
+    void last() { g_profile_request = {nullptr, stop_}; }
+    ProfileSpan(const ProfileSpan&) = delete;
+    ProfileSpan& operator=(const ProfileSpan&) = delete;
+
+private:
+    hipEvent_t stop_;
+};
+
 // Returns the status of this launch alone (an earlier error that the calling
 // thread has not collected is neither reported here nor cleared).
 template <typename... KArgs, typename... Args>

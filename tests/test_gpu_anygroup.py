@@ -155,3 +155,34 @@ def test_code_offsets_beyond_32_bits(H, dtype, bits, group):
             hi = min(lo + span, group)
             q = torch.floor((x[0, lo:hi].float() * inv + float(half)) + 0.5).to(torch.uint8)
             assert torch.equal(got[lo:hi], q), f"grad_quant, elements from {lo}"
+
+
+def test_a_message_of_several_kernels_is_timed_as_one_launch(H):
+    """aqsgd_profile_next_launch on a group that takes three kernels (clear, maximum, quantise) and on
+    one that takes two.  The first reads act and m twice and writes m once, 1 GiB each and far beyond
+    the caches: at 8 TB/s the last pass alone takes 0.4 ms, the kernel that clears one word microseconds."""
+    d = H.dev()
+
+    def timed(group, batch, rounding):
+        desc = B.make_desc(batch=batch, n_per=group, n_samples=batch, bits=8, group=group, dtype="f32", rounding=rounding)
+        act = torch.ones((batch, group), device=d)
+        m = torch.zeros_like(act)
+        codes = torch.empty(B.codes_bytes(desc), dtype=torch.uint8, device=d)
+        scales = torch.empty(batch, device=d)
+        ids = torch.arange(batch, device=d)
+        a, b, c = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+        for e in (a, b):
+            e.record()
+        torch.cuda.synchronize()
+        B.encode(desc, act, ids, m, codes, scales)
+        B.profile_next_launch(a, b)
+        B.encode(desc, act, ids, m, codes, scales)
+        c.record()
+        B.encode(desc, act, ids, m, codes, scales)           # the request is over: does not stamp again
+        torch.cuda.synchronize()
+        print("timed", group, batch, a.elapsed_time(b), a.elapsed_time(c), flush=True)
+        assert 0 < a.elapsed_time(b) <= a.elapsed_time(c)
+        return a.elapsed_time(b)
+
+    assert timed(1 << 28, 1, B.NEAREST) > 0.4
+    assert 0.002 < timed(49152, 8, B.STOCHASTIC) < 1
