@@ -47,7 +47,9 @@
  *     m_buf: undefined results, all accesses in bounds), non-finite inputs
  *     (undefined results), buffers smaller than the descriptor says.
  *     aqsgd_check_ids() checks the first two on the device.  AQSGD_ERR_LAUNCH
- *     reports the status of the call's own launch.
+ *     reports the status of the call's own launches (or that host memory ran out,
+ *     before any): where a message or a job list takes several, those before the
+ *     refused one are enqueued, and codes, scales and m_buf are not to be used.
  *   - Arithmetic is IEEE binary32 with one rounding per operation and no fused
  *     multiply-add; stores to float16/bfloat16 round to nearest-even.  Results are
  *     bit-identical for any launch configuration.
@@ -73,7 +75,7 @@ typedef enum {
     AQSGD_ERR_DTYPE = -4,     /* unknown dtype or rounding mode                     */
     AQSGD_ERR_SHAPE = -5,     /* negative or overflowing batch / n_per / n_samples  */
     AQSGD_ERR_ALIGN = -6,     /* a pointer misses its alignment                     */
-    AQSGD_ERR_LAUNCH = -7,    /* the HIP runtime refused the launch                 */
+    AQSGD_ERR_LAUNCH = -7,    /* the HIP runtime refused the launch, or no memory   */
     AQSGD_ERR_IO = -8         /* file tier: open / read / write failed              */
 } aqsgd_status;
 

@@ -545,16 +545,32 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
     return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
 }
 
+// No C++ exception leaves a C entry: a caller in another language cannot catch it, and one that
+// has let go of a lock (an interpreter's) could not take it up again.  What can be thrown is the
+// want of host memory for the lists of messages, before anything is enqueued.
+template <typename F>
+int without_exceptions(F&& f) {
+    try {
+        return f();
+    } catch (...) {
+        return AQSGD_ERR_LAUNCH;
+    }
+}
+
 int launch_one(const QuantPlan& q, hipStream_t stream) {
-    std::vector<QuantPlan> qs(1, q);
-    std::vector<DequantPlan> ds;
-    return launch_plans(qs, ds, stream);
+    return without_exceptions([&] {
+        std::vector<QuantPlan> qs(1, q);
+        std::vector<DequantPlan> ds;
+        return launch_plans(qs, ds, stream);
+    });
 }
 
 int launch_one(const DequantPlan& d, hipStream_t stream) {
-    std::vector<QuantPlan> qs;
-    std::vector<DequantPlan> ds(1, d);
-    return launch_plans(qs, ds, stream);
+    return without_exceptions([&] {
+        std::vector<QuantPlan> qs;
+        std::vector<DequantPlan> ds(1, d);
+        return launch_plans(qs, ds, stream);
+    });
 }
 
 // Row copy for the uncompressed first visit of aqsgd_seed: m_buf[ids[i]] <- act[i].
@@ -722,6 +738,63 @@ int run_topk(const aqsgd_desc* d, int32_t keep, bool sender, const void* grad, v
     return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
 }
 
+// Every job is checked before anything is enqueued.
+int run_jobs(const aqsgd_job* jobs, int32_t n_jobs, hipStream_t stream) {
+    std::vector<QuantPlan> qs;
+    std::vector<DequantPlan> ds;
+    for (int32_t k = 0; k < n_jobs; ++k) {
+        const aqsgd_job& j = jobs[k];
+        const aqsgd_desc* d = &j.desc;
+        int rc;
+        switch (j.kind) {
+        case AQSGD_JOB_ENCODE:
+            rc = check_encode(d, j.src, j.sample_ids, j.m_buf, j.codes, j.scales);
+            if (rc == AQSGD_OK && d->batch > 0)
+                qs.push_back(plan_quant(d, d->batch, d->n_per, j.src, j.sample_ids, j.m_buf, j.codes, j.scales));
+            break;
+        case AQSGD_JOB_DECODE:
+            rc = check_decode(d, j.codes, j.scales, j.sample_ids, j.m_buf, j.out);
+            if (rc == AQSGD_OK && d->batch > 0)
+                ds.push_back(plan_dequant(d, d->batch, d->n_per, j.codes, j.scales, j.sample_ids, j.m_buf, j.out));
+            break;
+        case AQSGD_JOB_GRAD_QUANT:
+            rc = check_grad_quant(d, j.src, j.codes, j.scales);
+            if (rc == AQSGD_OK && d->batch > 0) qs.push_back(plan_grad_quant(d, j.src, j.codes, j.scales));
+            break;
+        case AQSGD_JOB_GRAD_DEQUANT:
+            rc = check_grad_dequant(d, j.codes, j.scales, j.out);
+            if (rc == AQSGD_OK && d->batch > 0) ds.push_back(plan_grad_dequant(d, j.codes, j.scales, j.out));
+            break;
+        case AQSGD_JOB_ENCODE_SEEN: {
+            rc = check_encode(d, j.src, j.sample_ids, j.m_buf, j.codes, j.scales);
+            if (rc == AQSGD_OK && j.stamp == 0) rc = AQSGD_ERR_SHAPE;
+            if (rc != AQSGD_OK || d->batch == 0) break;
+            if (!j.seen || !j.first) { rc = AQSGD_ERR_NULL; break; }
+            if (!aligned(j.first, 4) || !aligned(j.seen, 4)) { rc = AQSGD_ERR_ALIGN; break; }
+            SeenArgs sa;
+            sa.seen = j.seen; sa.first = j.first; sa.stamp = j.stamp;
+            qs.push_back(plan_quant(d, d->batch, d->n_per, j.src, j.sample_ids, j.m_buf, j.codes, j.scales, sa));
+            break;
+        }
+        case AQSGD_JOB_DECODE_SEEN: {
+            rc = check_decode(d, j.codes, j.scales, j.sample_ids, j.m_buf, j.out);
+            if (rc == AQSGD_OK && j.stamp == 0) rc = AQSGD_ERR_SHAPE;
+            if (rc != AQSGD_OK || d->batch == 0) break;
+            if (!j.seen || !j.full) { rc = AQSGD_ERR_NULL; break; }
+            if (!aligned(j.full, 16) || !aligned(j.seen, 4)) { rc = AQSGD_ERR_ALIGN; break; }
+            SeenArgs sa;
+            sa.seen = j.seen; sa.full = j.full; sa.stamp = j.stamp;
+            ds.push_back(plan_dequant(d, d->batch, d->n_per, j.codes, j.scales, j.sample_ids, j.m_buf, j.out, sa));
+            break;
+        }
+        default:
+            rc = AQSGD_ERR_SHAPE;
+        }
+        if (rc != AQSGD_OK) return rc;
+    }
+    return launch_plans(qs, ds, stream);
+}
+
 __global__ void check_ids_kernel(const int64_t* ids, int64_t batch, int64_t n_samples, int32_t* flag) {
     int bad = 0;
     for (int64_t i = threadIdx.x + static_cast<int64_t>(blockIdx.x) * blockDim.x; i < batch;
@@ -785,59 +858,7 @@ int aqsgd_run_jobs(const aqsgd_job* jobs, int32_t n_jobs, void* stream) {
     if (n_jobs < 0) return AQSGD_ERR_SHAPE;
     if (n_jobs == 0) return AQSGD_OK;
     if (!jobs) return AQSGD_ERR_NULL;
-    std::vector<QuantPlan> qs;
-    std::vector<DequantPlan> ds;
-    for (int32_t k = 0; k < n_jobs; ++k) {               // every job is checked before anything is enqueued
-        const aqsgd_job& j = jobs[k];
-        const aqsgd_desc* d = &j.desc;
-        int rc;
-        switch (j.kind) {
-        case AQSGD_JOB_ENCODE:
-            rc = check_encode(d, j.src, j.sample_ids, j.m_buf, j.codes, j.scales);
-            if (rc == AQSGD_OK && d->batch > 0)
-                qs.push_back(plan_quant(d, d->batch, d->n_per, j.src, j.sample_ids, j.m_buf, j.codes, j.scales));
-            break;
-        case AQSGD_JOB_DECODE:
-            rc = check_decode(d, j.codes, j.scales, j.sample_ids, j.m_buf, j.out);
-            if (rc == AQSGD_OK && d->batch > 0)
-                ds.push_back(plan_dequant(d, d->batch, d->n_per, j.codes, j.scales, j.sample_ids, j.m_buf, j.out));
-            break;
-        case AQSGD_JOB_GRAD_QUANT:
-            rc = check_grad_quant(d, j.src, j.codes, j.scales);
-            if (rc == AQSGD_OK && d->batch > 0) qs.push_back(plan_grad_quant(d, j.src, j.codes, j.scales));
-            break;
-        case AQSGD_JOB_GRAD_DEQUANT:
-            rc = check_grad_dequant(d, j.codes, j.scales, j.out);
-            if (rc == AQSGD_OK && d->batch > 0) ds.push_back(plan_grad_dequant(d, j.codes, j.scales, j.out));
-            break;
-        case AQSGD_JOB_ENCODE_SEEN: {
-            rc = check_encode(d, j.src, j.sample_ids, j.m_buf, j.codes, j.scales);
-            if (rc == AQSGD_OK && j.stamp == 0) rc = AQSGD_ERR_SHAPE;
-            if (rc != AQSGD_OK || d->batch == 0) break;
-            if (!j.seen || !j.first) { rc = AQSGD_ERR_NULL; break; }
-            if (!aligned(j.first, 4) || !aligned(j.seen, 4)) { rc = AQSGD_ERR_ALIGN; break; }
-            SeenArgs sa;
-            sa.seen = j.seen; sa.first = j.first; sa.stamp = j.stamp;
-            qs.push_back(plan_quant(d, d->batch, d->n_per, j.src, j.sample_ids, j.m_buf, j.codes, j.scales, sa));
-            break;
-        }
-        case AQSGD_JOB_DECODE_SEEN: {
-            rc = check_decode(d, j.codes, j.scales, j.sample_ids, j.m_buf, j.out);
-            if (rc == AQSGD_OK && j.stamp == 0) rc = AQSGD_ERR_SHAPE;
-            if (rc != AQSGD_OK || d->batch == 0) break;
-            if (!j.seen || !j.full) { rc = AQSGD_ERR_NULL; break; }
-            if (!aligned(j.full, 16) || !aligned(j.seen, 4)) { rc = AQSGD_ERR_ALIGN; break; }
-            SeenArgs sa;
-            sa.seen = j.seen; sa.full = j.full; sa.stamp = j.stamp;
-            ds.push_back(plan_dequant(d, d->batch, d->n_per, j.codes, j.scales, j.sample_ids, j.m_buf, j.out, sa));
-            break;
-        }
-        default:
-            rc = AQSGD_ERR_SHAPE;
-        }
-        if (rc != AQSGD_OK) return rc;
-    }
-    return launch_plans(qs, ds, static_cast<hipStream_t>(stream));
+    return without_exceptions([&] { return run_jobs(jobs, n_jobs, static_cast<hipStream_t>(stream)); });
 }
 
 int aqsgd_seed(const aqsgd_desc* d, const void* act, const int64_t* sample_ids, void* m_buf,
@@ -984,7 +1005,7 @@ const char* aqsgd_strerror(int status) {
     case AQSGD_ERR_DTYPE:  return "unknown dtype or rounding mode";
     case AQSGD_ERR_SHAPE:  return "a size, count, stamp or slot is negative, zero, too large or out of turn";
     case AQSGD_ERR_ALIGN:  return "a pointer misses its required alignment";
-    case AQSGD_ERR_LAUNCH: return "the HIP runtime refused the kernel launch";
+    case AQSGD_ERR_LAUNCH: return "the HIP runtime refused the kernel launch, or host memory ran out";
     case AQSGD_ERR_IO:     return "the file tier could not open, size, read or write its file";
     default:               return "unknown status";
     }

@@ -154,6 +154,31 @@ def test_job_layout_matches_header():
     assert B.Job.desc.offset == 8 and B.Job.src.offset == 56 and B.Job.out.offset == 96
 
 
+def test_want_of_host_memory_is_a_status(tmp_path):
+    """No C++ exception crosses the C ABI: a job list whose bookkeeping finds no host memory is
+    refused with a status, before anything is enqueued (in a process of its own, whose address
+    space is closed behind the list)."""
+    import subprocess
+    import sys
+    code = """
+import ctypes, resource
+from paper_2206_01299_amd import binding as B
+L = B.lib()
+n = 400_000
+jobs = (B.Job * n)()
+d = B.make_desc(batch=2, n_per=64, n_samples=4, bits=4, group=64, dtype="f16")
+one = B.Job(B.JOB_ENCODE, d, 4096, 4096, 4096, 4096, 4096)        # never dereferenced
+for k in range(n):
+    ctypes.memmove(ctypes.byref(jobs, k * ctypes.sizeof(B.Job)), ctypes.byref(one), ctypes.sizeof(B.Job))
+pages = int(open("/proc/self/statm").read().split()[0])
+resource.setrlimit(resource.RLIMIT_AS, (pages * resource.getpagesize() + (16 << 20),) * 2)
+print("status", L.aqsgd_run_jobs(jobs, n, None))
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, f"ended with {r.returncode}: {r.stderr[-300:]}"
+    assert "status -7" in r.stdout
+
+
 def test_header_is_plain_c_and_a_c_client_links(tmp_path):
     """The boundary is a C ABI: the header compiles as C99 on its own, and a C program
     that only knows the header links against the library and reads a size through it."""
