@@ -9,7 +9,8 @@ A call is first offered to ``_native`` (``csrc/binding_native.cpp``), which does
 same checks and the foreign call in native code; only a call that is not of the
 ordinary form comes back (``None``) and takes the ctypes path below, whose checks
 say what is wrong with it.  On a small message the host's work per call is what the
-call takes.
+call takes.  Without ``_native`` every call takes the ctypes path, with a warning: the
+same kernels, more host time.
 """
 from __future__ import annotations
 
@@ -17,6 +18,8 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import threading
+import warnings
 from pathlib import Path
 
 import torch
@@ -145,23 +148,45 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _Ctypes:
+    """Stands in for the native module where it was not built: hands every call back."""
+
+    def __getattr__(self, name):
+        return _hand_back
+
+
+def _hand_back(*args):
+    return None
+
+
 class _LoadNative:
     """Stands in for the native module until the first call needs it."""
 
     def __getattr__(self, name):
+        if name.startswith("__"):                   # what looks a module over makes no call
+            raise AttributeError(name)
         global _native
-        L = lib()
-        if not NATIVE_PATH.exists():
-            raise FileNotFoundError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2206_01299_amd.build` "
-                                    "(there is no fallback path)")
+        with _load_lock:                            # the first calls of several threads
+            if isinstance(_native, _LoadNative):
+                _native = _load_native()
+        return getattr(_native, name)
+
+
+def _load_native():
+    L = lib()
+    try:
         loader = importlib.machinery.ExtensionFileLoader("_native", str(NATIVE_PATH))
         mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_native", loader))
         loader.exec_module(mod)
-        mod.setup(Desc, Job, {n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in EXPORTS})
-        _native = mod
-        return getattr(mod, name)
+    except ImportError as e:                        # not built, or for another torch
+        warnings.warn(f"{NATIVE_PATH.name} cannot be loaded ({e}): calls go through ctypes, which takes the host some "
+                      "7 us instead of 3 per call; build it with `python -m paper_2206_01299_amd.build`", RuntimeWarning)
+        return _Ctypes()
+    mod.setup(Desc, Job, {n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in EXPORTS})
+    return mod
 
 
+_load_lock = threading.Lock()
 _native = _LoadNative()
 
 

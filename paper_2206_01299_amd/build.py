@@ -62,7 +62,9 @@ def _build_native() -> None:
            f"-I{t}/include/torch/csrc/api/include", "-I/opt/rocm/include", f"-I{INCLUDE}",
            str(CSRC / "binding_native.cpp"), "-o", str(tmp),
            f"-L{t}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]   # loaded by `import torch`
-    subprocess.run(cmd, check=True)
+    if subprocess.run(cmd).returncode != 0:
+        NATIVE.unlink(missing_ok=True)                  # none rather than an older one: calls take the ctypes path
+        raise RuntimeError(f"the host compiler failed on binding_native.cpp ({LIB.name} works without it)")
     os.replace(tmp, NATIVE)
 
 
@@ -73,11 +75,11 @@ def build(verbose: bool = True) -> Path:
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         native = pool.submit(_build_native)
         objs = list(pool.map(_compile, srcs))
-        native.result()
     tmp = LIB.with_suffix(f".tmp{os.getpid()}.so")
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *map(str, objs), "-o", str(tmp)],
                    check=True)
     os.replace(tmp, LIB)
+    native.result()                                     # a failure there leaves the library in place
     if verbose:
         print(f"built {LIB} from {len(srcs)} sources, and {NATIVE.name}")
     return LIB

@@ -4,6 +4,7 @@ element), and turns every host-checkable mistake into an error code before any
 launch."""
 import ctypes
 import re
+import warnings
 from pathlib import Path
 
 import pytest
@@ -100,6 +101,33 @@ def test_binding_has_no_cpu_route():
                  torch.zeros(1))
     src = (ROOT / "paper_2206_01299_amd" / "binding.py").read_text()
     assert "import oracle" not in src and "from oracle" not in src
+
+
+def test_without_the_native_module_calls_take_the_ctypes_path(monkeypatch, tmp_path):
+    """Only libaqsgd.so is needed: where _native.so was not built, or was for another torch, every
+    call goes through ctypes and its checks, and says so once."""
+    import torch
+    broken = tmp_path / "_native.so"
+    broken.write_bytes(b"not a library")
+    d = B.make_desc(batch=1, n_per=64, n_samples=1, bits=4, group=64, dtype="f32")
+    t = torch.zeros(64)
+    args = (d, t, torch.zeros(1, dtype=torch.int64), t, torch.zeros(32, dtype=torch.uint8), torch.zeros(1))
+    for path in (tmp_path / "missing.so", broken):
+        monkeypatch.setattr(B, "_native", B._LoadNative())
+        monkeypatch.setattr(B, "NATIVE_PATH", path)
+        assert not hasattr(B._native, "__wrapped__") and isinstance(B._native, B._LoadNative)
+        with pytest.warns(RuntimeWarning, match="ctypes"):
+            with pytest.raises(ValueError, match="device tensor"):
+                B.encode(*args)
+        with warnings.catch_warnings():
+            warnings.simplefilter("error")
+            with pytest.raises(ValueError, match="device tensor"):
+                B.encode(*args)
+            monkeypatch.setattr(B, "_dev", lambda t, what: ctypes.c_void_p(0))
+            with pytest.raises(B.AqsgdError) as e:             # as far as the library's own check
+                B.encode(*args, stream=type("S", (), {"cuda_stream": 0})())
+            assert e.value.status == -1
+            monkeypatch.undo()
 
 
 def test_binding_checks_tensor_types_and_sizes_against_the_descriptor(monkeypatch):
