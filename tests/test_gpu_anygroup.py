@@ -69,11 +69,13 @@ def test_groups_beyond_a_workgroup(H, dtype, bits, group):
         _sweep(H, dtype, bits, group, rounding, gps, batch=2)
 
 
-@pytest.mark.parametrize("dtype,bits,group,gps", [("bf16", 8, 32776, 16), ("bf16", 8, 32776, 17), ("f32", 3, 49152, 17),
-                                                  ("f16", 8, 32769, 17)])
+@pytest.mark.parametrize("dtype,bits,group,gps", [("bf16", 8, 32776, 16), ("bf16", 8, 32776, 17), ("f32", 3, 49152, 16),
+                                                  ("f32", 3, 49152, 17), ("f32", 8, 32769, 16), ("f32", 8, 32769, 17),
+                                                  ("f16", 8, 32769, 16), ("f16", 8, 32769, 17)])
 def test_wide_groups_few_and_many(H, dtype, bits, group, gps):
-    """Up to 32 groups in a call (64 with stochastic rounding) go out as spans, more as one
-    workgroup each (two samples a call)."""
+    """The number of groups up to which a call goes out as spans, and one pair more: 64 with
+    stochastic rounding in every type, 32 with nearest rounding in float32 with previous messages
+    (the backward message, which has none, and 16-bit types never split there).  Two samples a call."""
     for rounding, n in ((W.NEAREST, gps), (W.STOCHASTIC, 2 * gps)):
         print(f"wide {dtype} b{bits} G{group} x {n} r{rounding}", flush=True)
         _sweep(H, dtype, bits, group, rounding, n, batch=2)
@@ -102,9 +104,26 @@ def test_large_groups_without_a_change_send_scale_zero(H):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
-@pytest.mark.parametrize("group,gps", [(1020, 9), (12, 50), (32772, 2), (40000, 1)])
-def test_first_visits(H, dtype, group, gps):
-    replay_seen(H, dtype, 4, group, gps * group, 12, 4, 4, W.NEAREST, group)
+@pytest.mark.parametrize("rounding", [W.NEAREST, W.STOCHASTIC])
+@pytest.mark.parametrize("bits,group,gps", [(4, 1020, 9), (4, 12, 50), (4, 32772, 2), (4, 40000, 1),
+                                            # beyond one workgroup in every type: three launches
+                                            (4, 65544, 2), (8, 65537, 1), (3, 131080, 1)])
+def test_first_visits(H, dtype, bits, rounding, group, gps):
+    replay_seen(H, dtype, bits, group, gps * group, 12, 4, 4, rounding, group)
+
+
+@pytest.mark.parametrize("max_blocks", [3, 7])
+@pytest.mark.parametrize("dtype,bits,group,gps", [("f32", 4, 1020, 9), ("bf16", 8, 11, 700), ("f16", 4, 32776, 3),
+                                                  ("f32", 8, 40001, 2), ("bf16", 3, 65544, 2), ("f32", 2, 131080, 1)])
+def test_first_visits_with_a_capped_grid(H, dtype, bits, group, gps, max_blocks):
+    """The loops over groups and spans, and beside them samples that are new and skip these."""
+    B.set_launch_shape(max_blocks, 0)
+    try:
+        for rounding in (W.NEAREST, W.STOCHASTIC):
+            print("capped first visits", dtype, bits, group, max_blocks, rounding, flush=True)
+            replay_seen(H, dtype, bits, group, gps * group, 12, 4, 4, rounding, group)
+    finally:
+        B.set_launch_shape(0, 0)
 
 
 @pytest.mark.parametrize("dtype,bits,group", [("f16", 8, 2**29 + 9), ("f32", 8, 2**29 + 12), ("bf16", 4, 2**30 + 10),

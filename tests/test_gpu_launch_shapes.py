@@ -11,7 +11,14 @@ from paper_2206_01299_amd import workloads as W
 
 CASES = [("f16", 4, 1600, W.NEAREST, 41), ("f16", 2, 128, W.STOCHASTIC, 301), ("bf16", 3, 64, W.NEAREST, 517),
          ("bf16", 6, 64, W.NEAREST, 130), ("f32", 4, 4096, W.NEAREST, 9), ("f32", 8, 256, W.STOCHASTIC, 77),
-         ("f32", 3, 64, W.NEAREST, 99), ("f16", 8, 8200, W.NEAREST, 5), ("f16", 8, 50, W.NEAREST, 333)]
+         ("f32", 3, 64, W.NEAREST, 99), ("f16", 8, 8200, W.NEAREST, 5), ("f16", 8, 50, W.NEAREST, 333),
+         # odd groups: the looping kernels of every width, of one and several waves to a team
+         ("f32", 6, 52, W.STOCHASTIC, 333), ("bf16", 8, 11, W.STOCHASTIC, 700), ("bf16", 4, 1020, W.NEAREST, 77),
+         ("f16", 2, 12, W.NEAREST, 601), ("f32", 2, 4100, W.NEAREST, 9), ("f16", 4, 16390, W.STOCHASTIC, 5),
+         # wide groups, which a capped grid hands to the large groups' kernels, and large ones: their
+         # loops over spans
+         ("bf16", 4, 32776, W.NEAREST, 3), ("f32", 8, 32772, W.STOCHASTIC, 3), ("f16", 8, 40001, W.STOCHASTIC, 2),
+         ("f32", 3, 65544, W.NEAREST, 3), ("bf16", 8, 65545, W.STOCHASTIC, 2), ("f16", 6, 262148, W.NEAREST, 1)]
 
 
 def _cfg(dtype, bits, group, rounding, gps, batch=3, n_samples=7):
@@ -81,3 +88,36 @@ def test_many_samples_of_about_one_chunk_per_lane(dtype, bits):
         print("short samples", dtype, bits, n_per, batch, flush=True)
         H.replay_and_compare(_cfg(dtype, bits, n_per, W.NEAREST, 1, batch=batch, n_samples=batch + 3),
                              calls_per_epoch=1, epochs=2, log=lambda *a, **k: None)
+
+
+def test_more_samples_of_a_wide_group_than_the_grid_has_rows():
+    """Beyond 65535 samples a wide group's message falls to the large groups' kernels, which loop over
+    samples (skipping the new ones).  The oracle would take minutes: the call is compared with the same
+    samples in two calls, which go out as one workgroup a group."""
+    if not torch.cuda.is_available():
+        pytest.fail("needs the MI355X")
+    batch, group = 65538, 32776
+    d = torch.device("cuda:0")
+    gen = torch.Generator(device=d)
+    gen.manual_seed(7)
+    act = torch.randn((batch, group), device=d, dtype=torch.float16, generator=gen)
+    ids = torch.randperm(batch, device=d, generator=gen)
+    print("many wide samples", flush=True)
+
+    def encode(parts):
+        m = torch.zeros((batch, group), dtype=torch.float16, device=d)
+        seen = (torch.arange(batch, device=d) % 3 != 0).int()
+        out = []
+        for lo, hi in parts:
+            desc = B.make_desc(batch=hi - lo, n_per=group, n_samples=batch, bits=8, group=group, dtype="f16")
+            codes = torch.full((B.codes_bytes(desc),), 0x5A, dtype=torch.uint8, device=d)
+            scales = torch.full((hi - lo,), -1.0, device=d)
+            first = torch.full((hi - lo,), -7, dtype=torch.int32, device=d)
+            B.encode_seen(desc, act[lo:hi], ids[lo:hi], m, seen, 9, first, codes, scales)
+            out.append((codes, scales, first))
+        return [torch.cat(x) for x in zip(*out)] + [m, seen]
+
+    one, two = encode([(0, batch)]), encode([(0, 30000), (30000, batch)])
+    for name, a, b in zip(("codes", "scales", "first", "m", "seen"), one, two):
+        assert torch.equal(a, b), name
+    assert one[2].sum().item() == (batch + 2) // 3 and (one[1] > 0).sum().item() == batch - (batch + 2) // 3
