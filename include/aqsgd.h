@@ -210,7 +210,7 @@ int aqsgd_seed(const aqsgd_desc* desc, const void* act, const int64_t* sample_id
 /*
  * Algorithm 1 with its first-visit branch (a sample without a previous message: the
  * activation is sent in full precision and m(xi) <- a(xi); otherwise the quantised
- * change is sent).  One launch per call.
+ * change is sent).
  * `seen` holds one 32-bit word per sample of m_buf, zero-initialised by the caller:
  * 0 = no previous message yet, otherwise the stamp of the call that first visited the
  * sample.  Every call carries a `stamp` of the caller's choosing that is not 0 and
@@ -370,8 +370,10 @@ int aqsgd_check_ids(const int64_t* sample_ids, int64_t batch, int64_t n_samples,
  * thread is inside a codec call applies to that thread's next call.  AQSGD_ERR_SHAPE for
  * values out of range.  A third setting of the same kind has no setter and exists for
  * measurements only: AQSGD_LAUNCH_BLOCKS in the environment (read once per process) bounds
- * the workgroups of a whole launch, shared by its jobs in proportion to their sizes; unset,
- * the library bounds only launches of small groups (fewer than 512 elements), at 2048.
+ * the workgroups of a whole launch: each takes the same number of steps, as many as bring the
+ * launch down to it.  Unset, only launches of groups of up to 256 elements that ask for 4096
+ * steps or more are cut so, to about 2048 workgroups.  Set, it also sends messages that come
+ * alone through the kernels of the shared launches.
  */
 int aqsgd_set_launch_shape(int64_t max_blocks, int32_t dequant_unroll);
 

@@ -179,8 +179,8 @@ def _load_native():
         mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_native", loader))
         loader.exec_module(mod)
     except ImportError as e:                        # not built, or for another torch
-        warnings.warn(f"{NATIVE_PATH.name} cannot be loaded ({e}): calls go through ctypes, which takes the host some "
-                      "7 us instead of 3 per call; build it with `python -m paper_2206_01299_amd.build`", RuntimeWarning)
+        warnings.warn(f"{NATIVE_PATH.name} cannot be loaded ({e}): calls go through ctypes, which costs the host some "
+                      "9 us a call instead of 4; build it with `python -m paper_2206_01299_amd.build`", RuntimeWarning)
         return _Ctypes()
     mod.setup(Desc, Job, {n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in EXPORTS})
     return mod

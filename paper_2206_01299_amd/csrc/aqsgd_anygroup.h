@@ -377,9 +377,11 @@ void quant_wide_kernel(AQSGD_QUANT_ARGS) {
 // (bfloat16, eight groups of 49152, forward and backward in four calls: one thread per group
 // 31.9 ms, this way 29.4 us.)
 // ---------------------------------------------------------------------------
+// The bodies rely on no more of a span's length than that the spans cover the group (the host
+// rounds it to whole workgroup steps for large groups, and not for split ones).
 struct LargeGeom {
     int32_t spans;             // spans per group
-    int32_t span_pieces;       // pieces of 8 elements per span: a multiple of kBlock
+    int32_t span_pieces;       // pieces of 8 elements per span; the last span may be shorter
 };
 
 constexpr int kLargeUnroll = 4;                          // pieces per lane and step

@@ -375,13 +375,24 @@ LargeGeom large_geometry(const QuantJob& a) {
 
 // Few wide groups go out as spans (see split_max_kernel) where one compute unit's arithmetic on a
 // group lasts longer than a second launch: with stochastic rounding, and in float32 with previous
-// messages, up to the number of groups from which one workgroup each is as fast.  Groups of
-// 49152, four calls (encode and grad_quant are the two that may split), one workgroup -> spans:
-// float32 nearest, 1 group 24.4 -> 19.7 us, 8 groups 26.4 -> 19.3, 32 groups 31.1 -> 27.3, 64
-// groups 36.8 -> 35.9; stochastic, 8 groups 34.5 -> 22.7 (bfloat16 28.2 -> 21.3), 32 groups
-// 39.6 -> 28.6 (31.8 -> 24.0), 128 groups 58.0 -> 64.6 (42.4 -> 44.9).  Nearest rounding of 16-bit
-// types stays with one workgroup: 8 groups 19.2 us, split 18.0 to 21.7 with how fast the host
-// issues the fifth launch.
+// messages, up to the number of groups from which one workgroup each is as fast.  One call on the
+// device, 8-bit, one workgroup each -> spans, in us:
+//   stochastic           8 groups                64 groups               96 groups
+//     encode     f32     32776  16.1 ->  9.6     17.4 -> 13.4            18.7 -> 17.8
+//                        49152  19.1 ->  8.8     20.1 -> 13.1            20.6 -> 20.1
+//                bf16    32776  12.7 ->  9.0     13.3 -> 12.0            13.6 -> 13.8
+//                        65536  18.1 ->  8.5     18.8 -> 13.0            19.7 -> 16.9
+//     grad_quant f32     32776   8.8 ->  7.3      9.7 ->  9.2             9.2 -> 11.2
+//                        49152  10.7 ->  7.2     11.1 ->  9.3            12.8 -> 12.4
+//                bf16    32776   8.8 ->  6.8      9.0 ->  8.9             9.3 -> 10.2
+//                        65536  12.3 ->  6.8     12.8 -> 10.2            13.2 -> 13.0
+// so 64 is the last size at which every one gains.  Nearest encode in float32, which has less
+// arithmetic to spread: 8 groups of 32776 14.1 -> 9.1, of 49152 15.2 -> 8.2; 32 groups 14.8 -> 10.3
+// and 15.5 -> 9.7; 96 groups 16.5 -> 17.4 and 17.0 -> 19.0.  It stops at 32: in a row of single calls
+// the second launch is host time too (four calls, 32 groups of 49152 31.1 -> 27.3 us, 64 groups
+// 36.8 -> 35.9).  For the same reason nearest rounding of 16-bit types stays with one workgroup (8
+// groups of 49152, encode alone 10.1 -> 7.6, four calls 19.2 -> 18.0 to 21.7 with how fast the host
+// issues the fifth launch), and nearest grad_quant gains nothing (6.0 -> 6.5).
 bool split_pays(const QuantJob& a, int dtype, int rounding) {
     const int64_t groups = a.gps * a.batch;
     return rounding == AQSGD_ROUND_STOCHASTIC ? groups <= 64

@@ -119,8 +119,8 @@ constexpr int kBlock = 256;
 // Groups a team of the quantising kernel takes per step.  A lane of a small team holds
 // one chunk of a group, so a workgroup step over one group per team would set up a
 // workgroup (job lookup, sample id, row addresses) for eight elements per lane and keep
-// two loads per lane in flight; such teams take four groups per step instead, all loads
-// first, which is the register budget of the four-chunks-per-lane shapes.
+// two loads per lane in flight; such teams take two groups per step instead, all loads
+// first (four would need twice the registers, and measured slower).
 __host__ __device__ constexpr int groups_per_team(int team, int cpl) {
     return (team < kWave && cpl == 1) ? 2 : 1;
 }
@@ -701,7 +701,7 @@ constexpr int kHostedDequantUnroll = 2;      // dequantising jobs inside a quant
 // sample, which is how a launch goes out whose grid holds a workgroup for each: loops around
 // the bodies keep what the next step needs in registers and with them waves off the chip
 // (float16, 64 lanes by 4 chunks: 107 registers and four waves a SIMD with loops, 73 and six
-// without; 16 lanes by 1, stochastic: 82 and five, 67 and seven).  Measured, loops -> one step:
+// without; 16 lanes by 1, stochastic: 77 and six, 67 and seven).  Measured, loops -> one step:
 // the time slot of the float16 [4,1024,1600] 4/8-bit boundary 21.2 -> 20.7 us; its 2/4-bit
 // stochastic G = 128 messages, one launch a stage, 28.0 -> 25.5 us.
 enum TableKind {

@@ -10,8 +10,8 @@
 // -amdgpu-kernarg-preload-count; structures are passed by reference and do not qualify).
 // The workgroup's place is the grid's own x and y, and it does one step: what a loop would
 // keep for the next one costs registers (loops around these bodies: 124 instead of 73) and
-// with them waves in flight.  The arguments are 124 bytes where a table is 2.3 KB that the
-// host copies for every launch.
+// with them waves in flight.  The arguments are 104 bytes (96 to reconstruct) where a table is 2000
+// that the host copies for every launch.
 // Measured, single calls as tables of one -> here: float16 [4,1024,1600] 4/8-bit, four calls
 // 30.2 -> 27.9 us (20 us of it are the bytes); bfloat16 [32,256,1536] G = 64 3/6-bit, four
 // calls 49.8 -> 46.8; first visits of half of that float16 batch 18.9 -> 17.6; 131072 float32
@@ -21,6 +21,8 @@
 #include "aqsgd_kernels.h"
 
 namespace aqsgd {
+
+static_assert(sizeof(JobTable) == 2000, "the size named above");
 
 // Words 0..13 are preloaded: five pointers, group, bits and n_per.
 #define AQSGD_QUANT_ARGS                                                                                  \
