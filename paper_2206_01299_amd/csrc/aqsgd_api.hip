@@ -10,6 +10,7 @@
 #include "aqsgd_lowbit.h"
 #include "aqsgd_single.h"
 #include "aqsgd_topk.h"
+#include "aqsgd_topk_small.h"
 
 namespace aqsgd {
 
@@ -742,6 +743,13 @@ int run_topk(const aqsgd_desc* d, int32_t keep, bool sender, const void* grad, v
     a.n_groups = d->batch * (d->n_per / d->group);
     a.group = d->group; a.cpg = d->group / kChunk; a.keep = keep;
     a.stochastic = d->rounding == AQSGD_ROUND_STOCHASTIC; a.seed = d->rng_seed;
+    const TopkSmallShape small = topk_small_shape(d->dtype, sender, a.cpg, a.n_groups);
+    if (small.lanes > 0) {
+        const LaunchGeom g = geometry(a.n_groups, kWave / small.lanes, 1,
+                                      max_blocks_knob().load(std::memory_order_relaxed));
+        const hipError_t err = launch_topk_small(d->dtype, small, sender, g.grid_x, a, stream);
+        return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
+    }
     const int cpl = a.cpg <= kWave ? 1 : (a.cpg <= 2 * kWave ? 2 : (a.cpg <= 3 * kWave ? 3 : 4));
     const LaunchGeom g = geometry(a.n_groups, kTopkBlock / kWave, 1,
                                   max_blocks_knob().load(std::memory_order_relaxed));

@@ -9,10 +9,12 @@
 // histograms the byte in 256 LDS counters, a prefix sum over the lanes (each
 // holding four counters) finds the counter that contains the wanted rank, and the
 // next level only looks at entries that share the bytes decided so far.  Two
-// levels for the 16-bit types, four for binary32.  Positions in the compacted
+// levels for the 16-bit types, up to four for binary32 (it ends where all entries that share
+// the bytes are kept, mostly after three: 4096 groups of 1600 16.1 -> 15.2 us).  Positions in the compacted
 // byte string come from per-lane population counts and the same wave prefix sum.
 // The kept bytes are gathered in LDS and leave as full-width stores; the receiver
-// stages them the same way.
+// stages them the same way.  Many groups of at most 512 entries share waves instead
+// (aqsgd_topk_small.h).
 #pragma once
 
 #include "aqsgd_kernels.h"
@@ -156,6 +158,10 @@ __device__ __forceinline__ void kth_largest(const uint32_t (&u)[CPL][kChunk], co
         need -= __builtin_amdgcn_readlane(above, src);
         in_bin = __builtin_amdgcn_readlane(count, src);
         prefix = (prefix << 8) | digit;
+        if (KeyBytes<DT>::value == 4 && level > 0 && need == in_bin) {       // wave-uniform: all that share these bytes are kept
+            prefix <<= shift;
+            break;
+        }
     }
     threshold = prefix;
     equal_kept = static_cast<int>(need);
@@ -201,6 +207,29 @@ __device__ __forceinline__ void lanes_before(const uint32_t (&cnt)[CPL], int lan
             totals[k1] = tot >> 16;
         }
     }
+}
+
+// A string of nb bytes between LDS (16-byte aligned) and any
+// address: four bytes a lane, or one where that is a single round.
+__device__ __forceinline__ void string_out(uint8_t* dst, const uint8_t* lds, int nb, int lane) {
+    if (nb <= kWave) {                                   // uniform over the launch
+        if (lane < nb) dst[lane] = lds[lane];
+        return;
+    }
+    const int words = nb & ~3;
+    for (int i = 4 * lane; i < words; i += 4 * kWave)
+        *reinterpret_cast<u32_any_t*>(dst + i) = *reinterpret_cast<const uint32_t*>(lds + i);
+    if (words + lane < nb) dst[words + lane] = lds[words + lane];
+}
+__device__ __forceinline__ void string_in(uint8_t* lds, const uint8_t* src, int nb, int lane) {
+    if (nb <= kWave) {
+        if (lane < nb) lds[lane] = src[lane];
+        return;
+    }
+    const int words = nb & ~3;
+    for (int i = 4 * lane; i < words; i += 4 * kWave)
+        *reinterpret_cast<uint32_t*>(lds + i) = *reinterpret_cast<const u32_any_t*>(src + i);
+    if (words + lane < nb) lds[words + lane] = src[words + lane];
 }
 
 // ---------------------------------------------------------------------------
@@ -468,7 +497,7 @@ __device__ __forceinline__ void topk_quant_group16(const TopkArgs& a, int64_t g,
         for (int i = lane; i < a.keep / 16; i += kWave)
             *reinterpret_cast<u32x4_t*>(dst + 16 * i) = *reinterpret_cast<const u32x4_t*>(lds.stage + 16 * i);
     } else {
-        for (int i = lane; i < a.keep; i += kWave) dst[i] = lds.stage[i];
+        string_out(dst, lds.stage, a.keep, lane);
     }
     if (lane == 0) a.scales[g] = sc.s_tx;
     wave_lds_sync();                                     // the next group reuses the staging bytes
@@ -622,7 +651,7 @@ __device__ __forceinline__ void topk_quant_group(const TopkArgs& a, int64_t g, c
         for (int i = lane; i < a.keep / 16; i += kWave)
             *reinterpret_cast<u32x4_t*>(dst + 16 * i) = *reinterpret_cast<const u32x4_t*>(lds.stage + 16 * i);
     } else {
-        for (int i = lane; i < a.keep; i += kWave) dst[i] = lds.stage[i];
+        string_out(dst, lds.stage, a.keep, lane);
     }
     if (lane == 0) a.scales[g] = sc.s_tx;
     wave_lds_sync();                                     // the next group reuses the staging bytes
@@ -645,7 +674,7 @@ __device__ __forceinline__ void topk_dequant_group(const TopkArgs& a, int64_t g,
         for (int i = lane; i < a.keep / 16; i += kWave)
             *reinterpret_cast<u32x4_t*>(lds.stage + 16 * i) = *reinterpret_cast<const u32x4_t*>(src + 16 * i);
     } else {
-        for (int i = lane; i < a.keep; i += kWave) lds.stage[i] = src[i];
+        string_in(lds.stage, src, a.keep, lane);
     }
     wave_lds_sync();
 

@@ -106,6 +106,35 @@ def test_topk_degenerate_groups(H, dtype):
         _run(H, dtype, group, keep, n_groups=8, kind="edge")
 
 
+# Several groups to a wave: widths at which a team of lanes is full, one chunk short of it and one
+# chunk past it, and at each the numbers of groups around those from which the teams take over; none
+# of them fills the last wave.
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("group", [8, 24, 32, 40, 64, 72, 120, 128, 136, 256, 264, 512])
+def test_topk_groups_that_share_a_wave(H, dtype, group):
+    cpg = group // 8
+    lines = [2048] if cpg <= 8 else [3072, 24576] if cpg <= 16 else [2048, 6144] if cpg <= 32 else [8192, 16384]
+    keeps = sorted({1, max(1, group // 20), max(1, group // 5), group // 2, group - 1, group})
+    kinds = ("heavy", "ties", "sparse", "edge")
+    for i, n_groups in enumerate([1, 37] + lines + [n - 1 for n in lines] + [n + 5 for n in lines]):
+        for rounding in (0, 1):
+            kind = kinds[(i + rounding) % 4]
+            if kind == "edge" and n_groups % 8:
+                kind = "heavy"
+            _run(H, dtype, group, keeps[(2 * i + rounding + cpg) % len(keeps)], n_groups=n_groups, kind=kind,
+                 rounding=rounding, seed=5 + i)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("group", [32, 64, 128, 256])
+def test_topk_every_kept_count_of_groups_that_share_a_wave(H, dtype, group):
+    """Heavy-tailed groups next to degenerate ones (all zero, all equal, subnormal: thresholds far below the
+    group's largest entry) in one wave, over the counts kept."""
+    for keep in range(1, group + 1, max(1, group // 16)):
+        for kind in ("edge", "sparse", "ties"):
+            _run(H, dtype, group, keep, n_groups=6144, kind=kind, seed=keep)
+
+
 @pytest.mark.parametrize("dtype", ["f16", "f32"])
 def test_topk_stochastic_rounding(H, dtype):
     _run(H, dtype, 1600, 320, n_groups=9, kind="heavy", rounding=1, seed=77)
