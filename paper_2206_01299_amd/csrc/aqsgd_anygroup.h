@@ -84,18 +84,18 @@ __device__ __forceinline__ void unpack_piece(uint64_t w, float (&q)[N]) {
 constexpr int kOddUnroll = 2;
 constexpr int64_t kMaxOddPieces = int64_t{1} << 31;      // pieces of a sample: 32-bit indices with room for a step
 
-template <int DT, int BITS, bool HAS_BUF, bool LOOPS>
-__device__ __forceinline__ void dequant_odd_body(const DequantJob& a) {
+template <int DT, int BITS, bool HAS_BUF, int THREADS, bool LOOPS>
+__device__ __forceinline__ void dequant_odd_body(const DequantJob& a, uint32_t bx, uint32_t by) {
     using P = Piece<DT, BITS>;
     constexpr int N = P::elems;
     constexpr int kEB = ElemBytes<DT>::value;
-    constexpr uint32_t kStep = kBlock * kOddUnroll;
+    constexpr uint32_t kStep = THREADS * kOddUnroll;
     const uint32_t ppg = (static_cast<uint32_t>(a.group) + N - 1) / N;           // pieces per group
     const float rcp_ppg = 1.0f / static_cast<float>(ppg);
     const uint32_t pps = static_cast<uint32_t>(a.gps) * ppg;                     // pieces per sample
     const uint32_t last_at = static_cast<uint32_t>(a.group) - N;                 // first element of a group's last piece
     const int own_last = a.group - N * static_cast<int>(ppg - 1);
-    for (int i = blockIdx.y; !LOOPS || i < a.batch; i += a.grid_y) {
+    for (int i = by; !LOOPS || i < a.batch; i += a.grid_y) {
         const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
         const int64_t out0 = static_cast<int64_t>(i) * a.n_per;
         char* out_s = static_cast<char*>(a.out) + out0 * kEB;
@@ -107,10 +107,10 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a) {
         if constexpr (HAS_BUF) {
             if (a.seen != nullptr) {
                 fresh = __builtin_amdgcn_readfirstlane(first_visit(a.seen, row, a.stamp) ? 1 : 0) != 0;
-                if (fresh && blockIdx.x == 0 && threadIdx.x == 0) a.seen[row] = a.stamp;   // one writer per sample
+                if (fresh && bx == 0 && threadIdx.x == 0) a.seen[row] = a.stamp;   // one writer per sample
             }
         }
-        for (uint32_t base = blockIdx.x * kStep; !LOOPS || base < pps; base += a.grid_x * kStep) {
+        for (uint32_t base = bx * kStep; !LOOPS || base < pps; base += a.grid_x * kStep) {
             const uint32_t g0 = base / ppg;              // uniform; per lane a small correction
             const uint32_t r0 = base - g0 * ppg;
             uint64_t w[kOddUnroll];
@@ -119,7 +119,7 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a) {
             bool ok[kOddUnroll], last[kOddUnroll];
 #pragma unroll
             for (int u = 0; u < kOddUnroll; ++u) {
-                const uint32_t p = base + u * kBlock + threadIdx.x;
+                const uint32_t p = base + u * THREADS + threadIdx.x;
                 ok[u] = p < pps;
                 const uint32_t x = r0 + ((ok[u] ? p : pps - 1) - base);
                 uint32_t dg;
@@ -174,10 +174,20 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a) {
     }
 }
 
-template <int DT, int BITS, bool LOOPS>
-__device__ __forceinline__ void dequant_odd_bits(const DequantJob& a) {
-    if (a.m_buf) dequant_odd_body<DT, BITS, true, LOOPS>(a);
-    else dequant_odd_body<DT, BITS, false, LOOPS>(a);
+template <int DT, int BITS, int THREADS, bool LOOPS>
+__device__ __forceinline__ void dequant_odd_bits(const DequantJob& a, uint32_t bx, uint32_t by) {
+    if (a.m_buf) dequant_odd_body<DT, BITS, true, THREADS, LOOPS>(a, bx, by);
+    else dequant_odd_body<DT, BITS, false, THREADS, LOOPS>(a, bx, by);
+}
+
+template <int DT, int THREADS, bool LOOPS>
+__device__ __forceinline__ void dequant_odd_job(const DequantJob& a, uint32_t bx, uint32_t by) {
+    switch (a.bits) {                                    // uniform over the workgroup; 3-bit groups are whole chunks
+    case 2: dequant_odd_bits<DT, 2, THREADS, LOOPS>(a, bx, by); break;
+    case 4: dequant_odd_bits<DT, 4, THREADS, LOOPS>(a, bx, by); break;
+    case 6: dequant_odd_bits<DT, 6, THREADS, LOOPS>(a, bx, by); break;
+    default: dequant_odd_bits<DT, 8, THREADS, LOOPS>(a, bx, by); break;
+    }
 }
 
 template <int DT, bool LOOPS>
@@ -188,12 +198,7 @@ void dequant_odd_kernel(AQSGD_DEQUANT_ARGS) {
     a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
     a.grid_x = grid_x; a.grid_y = grid_y;
     a.seen = seen; a.stamp = stamp;
-    switch (bits) {
-    case 2: dequant_odd_bits<DT, 2, LOOPS>(a); break;
-    case 4: dequant_odd_bits<DT, 4, LOOPS>(a); break;
-    case 6: dequant_odd_bits<DT, 6, LOOPS>(a); break;
-    default: dequant_odd_bits<DT, 8, LOOPS>(a); break;
-    }
+    dequant_odd_job<DT, kBlock, LOOPS>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -239,17 +244,17 @@ __device__ __forceinline__ void piece_values(const PieceRaw<DT, N>& r, float (&f
     }
 }
 
-// One group in a workgroup: blockIdx.x is the group of the sample, blockIdx.y the sample.
+// One group in a workgroup: bx is the group of the sample, by the sample.
 template <int DT, int BITS, int ROUND, bool HAS_BUF>
-__device__ __forceinline__ void quant_wide_body(const QuantJob& a, float* wave_max) {
+__device__ __forceinline__ void quant_wide_body(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
     using P = Piece<DT, BITS>;
     constexpr int N = P::elems;
     constexpr int kEB = ElemBytes<DT>::value;
     constexpr int kRounds = WideRounds<DT>::value * 16 / (N * kEB);
     const int lane = threadIdx.x;
     const int rounds = ((a.group + N - 1) / N + kWideThreads - 1) / kWideThreads;    // 1 .. kRounds: checked by the host
-    const int i = blockIdx.y;
-    const int64_t g = blockIdx.x;
+    const int i = by;
+    const int64_t g = bx;
     const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
     bool fresh = false;
     if constexpr (HAS_BUF) {
@@ -343,9 +348,20 @@ __device__ __forceinline__ void quant_wide_body(const QuantJob& a, float* wave_m
 }
 
 template <int DT, int BITS, int ROUND>
-__device__ __forceinline__ void quant_wide_bits(const QuantJob& a, float* wave_max) {
-    if (a.m_buf) quant_wide_body<DT, BITS, ROUND, true>(a, wave_max);
-    else quant_wide_body<DT, BITS, ROUND, false>(a, wave_max);
+__device__ __forceinline__ void quant_wide_bits(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
+    if (a.m_buf) quant_wide_body<DT, BITS, ROUND, true>(a, bx, by, wave_max);
+    else quant_wide_body<DT, BITS, ROUND, false>(a, bx, by, wave_max);
+}
+
+template <int DT, int ROUND>
+__device__ __forceinline__ void quant_wide_job(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
+    switch (a.bits) {                                    // uniform over the workgroup
+    case 2: quant_wide_bits<DT, 2, ROUND>(a, bx, by, wave_max); break;
+    case 3: quant_wide_bits<DT, 3, ROUND>(a, bx, by, wave_max); break;
+    case 4: quant_wide_bits<DT, 4, ROUND>(a, bx, by, wave_max); break;
+    case 6: quant_wide_bits<DT, 6, ROUND>(a, bx, by, wave_max); break;
+    default: quant_wide_bits<DT, 8, ROUND>(a, bx, by, wave_max); break;
+    }
 }
 
 template <int DT, int ROUND>
@@ -356,14 +372,9 @@ void quant_wide_kernel(AQSGD_QUANT_ARGS) {
     a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
     a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group;
     a.grid_x = grid_x; a.grid_y = grid_y;
+    a.bits = bits;
     a.seed = seed; a.seen = seen; a.first = first; a.stamp = stamp;
-    switch (bits) {
-    case 2: quant_wide_bits<DT, 2, ROUND>(a, wave_max); break;
-    case 3: quant_wide_bits<DT, 3, ROUND>(a, wave_max); break;
-    case 4: quant_wide_bits<DT, 4, ROUND>(a, wave_max); break;
-    case 6: quant_wide_bits<DT, 6, ROUND>(a, wave_max); break;
-    default: quant_wide_bits<DT, 8, ROUND>(a, wave_max); break;
-    }
+    quant_wide_job<DT, ROUND>(a, blockIdx.x, blockIdx.y, wave_max);
 }
 
 // ---------------------------------------------------------------------------
@@ -378,7 +389,8 @@ void quant_wide_kernel(AQSGD_QUANT_ARGS) {
 // 31.9 ms, this way 29.4 us.)
 // ---------------------------------------------------------------------------
 // The bodies rely on no more of a span's length than that the spans cover the group (the host
-// rounds it to whole workgroup steps for large groups, and not for split ones).
+// rounds it to whole workgroup steps for large groups, and not for split ones).  Split groups
+// (SLOTS) have a workgroup for every span, large ones loop.
 struct LargeGeom {
     int32_t spans;             // spans per group
     int32_t span_pieces;       // pieces of 8 elements per span; the last span may be shorter
@@ -394,6 +406,16 @@ constexpr int kSplitSpanElements = 4096;
 template <int DT> constexpr int kSplitUnroll = kSplitSpanElements / (kBlock * (DT == AQSGD_F32 ? 4 : 8));
 constexpr int kSplitMaxSpans = 16;                       // slots read by one wave; a span's codes hold them all
 
+// Their spans are of nearly equal length, so that the last one, too, has codes enough for the
+// slots (groups of 32769 elements and more: never fewer than 1800 elements a span).
+__host__ __device__ inline LargeGeom split_geometry(const QuantJob& a) {
+    LargeGeom g;
+    const int spans = (a.group + kSplitSpanElements - 1) / kSplitSpanElements;
+    g.spans = spans < kSplitMaxSpans ? spans : kSplitMaxSpans;
+    g.span_pieces = (a.cpg + g.spans - 1) / g.spans;
+    return g;
+}
+
 // Where the spans of a split group leave their maxima for span `span`: one word for each span,
 // in the place that span's own codes are going to take (at any byte).
 __device__ __forceinline__ u32_any_t* split_slots(const QuantJob& a, const LargeGeom& geom, int i, int64_t g, int span) {
@@ -401,6 +423,10 @@ __device__ __forceinline__ u32_any_t* split_slots(const QuantJob& a, const Large
     uint8_t* codes_g = a.codes + first * a.bits / 8;
     return reinterpret_cast<u32_any_t*>(codes_g + static_cast<int64_t>(span) * geom.span_pieces * a.bits);
 }
+
+// A workgroup's place in its message's rectangle of workgroups.
+struct Rect { uint32_t x, y, grid_x, grid_y; };
+__device__ __forceinline__ Rect whole_grid() { return {blockIdx.x, blockIdx.y, gridDim.x, gridDim.y}; }
 
 template <bool HAS_BUF>
 __device__ __forceinline__ bool large_fresh(const QuantJob& a, int64_t row) {
@@ -422,17 +448,20 @@ void large_clear_kernel(const QuantJob a) {
 }
 
 template <int DT, bool HAS_BUF, bool SLOTS = false>
-__device__ __forceinline__ void large_max_body(const QuantJob& a, const LargeGeom geom, float* wave_max) {
+__device__ __forceinline__ void large_max_body(const QuantJob& a, const LargeGeom geom, const Rect rect, float* wave_max) {
     constexpr int kUnroll = SLOTS ? kSplitUnroll<DT> : kLargeUnroll;
     constexpr int N = DT == AQSGD_F32 ? 4 : 8;
     constexpr int kEB = ElemBytes<DT>::value;
     const int64_t last_at = a.group - N;
-    for (int i = blockIdx.y; i < a.batch; i += gridDim.y) {
+    for (int i = rect.y; SLOTS || i < a.batch; i += rect.grid_y) {
         const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
-        if (large_fresh<HAS_BUF>(a, row)) continue;
+        if (large_fresh<HAS_BUF>(a, row)) {
+            if constexpr (SLOTS) return;
+            else continue;
+        }
         const char* src_s = static_cast<const char*>(a.src) + static_cast<int64_t>(i) * a.n_per * kEB;
         const char* m_s = HAS_BUF ? static_cast<const char*>(a.m_buf) + row * a.n_per * kEB : nullptr;
-        for (int64_t s = blockIdx.x; s < a.gps * geom.spans; s += gridDim.x) {
+        for (int64_t s = rect.x; SLOTS || s < a.gps * geom.spans; s += rect.grid_x) {
             const int64_t g = s / geom.spans;
             const int64_t e0 = (s - g * geom.spans) * geom.span_pieces * 8;
             const int64_t e1 = min(e0 + static_cast<int64_t>(geom.span_pieces) * 8, static_cast<int64_t>(a.group));
@@ -473,7 +502,9 @@ __device__ __forceinline__ void large_max_body(const QuantJob& a, const LargeGeo
                 atomicMax(reinterpret_cast<unsigned int*>(a.scales) + static_cast<int64_t>(i) * a.gps + g,
                           __float_as_uint(mx));
             }
+            if constexpr (SLOTS) break;
         }
+        if constexpr (SLOTS) break;
     }
 }
 
@@ -481,32 +512,32 @@ template <int DT>
 __global__ __launch_bounds__(kBlock)
 void large_max_kernel(const QuantJob a, const LargeGeom geom) {
     __shared__ float wave_max[kBlock / kWave];
-    if (a.m_buf) large_max_body<DT, true>(a, geom, wave_max);
-    else large_max_body<DT, false>(a, geom, wave_max);
+    if (a.m_buf) large_max_body<DT, true>(a, geom, whole_grid(), wave_max);
+    else large_max_body<DT, false>(a, geom, whole_grid(), wave_max);
 }
 
 // A group below the 2^-120 floor sends scale 0; one thread rewrites its word while other
 // workgroups may still read it, and both values mean "nothing to send" to them.
 template <int DT, int BITS, int ROUND, bool HAS_BUF, bool SLOTS = false>
-__device__ __forceinline__ void large_quant_body(const QuantJob& a, const LargeGeom geom) {
+__device__ __forceinline__ void large_quant_body(const QuantJob& a, const LargeGeom geom, const Rect rect) {
     using P = Piece<DT, BITS>;
     constexpr int N = P::elems;
     constexpr int kEB = ElemBytes<DT>::value;
     constexpr int kUnroll = !SLOTS ? kLargeUnroll : DT == AQSGD_F32 && N == 8 ? kSplitUnroll<DT> / 2 : kSplitUnroll<DT>;
     const int64_t last_at = a.group - N;
-    for (int i = blockIdx.y; i < a.batch; i += gridDim.y) {
+    for (int i = rect.y; SLOTS || i < a.batch; i += rect.grid_y) {
         const int64_t row = a.ids ? sample_id(a.ids, i) : static_cast<int64_t>(i);
         const int64_t src0 = static_cast<int64_t>(i) * a.n_per;
         const char* src_s = static_cast<const char*>(a.src) + src0 * kEB;
         char* m_s = HAS_BUF ? static_cast<char*>(a.m_buf) + row * a.n_per * kEB : nullptr;
         const bool fresh = large_fresh<HAS_BUF>(a, row);
         if constexpr (HAS_BUF) {
-            if (a.seen != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {      // one writer per sample
+            if (a.seen != nullptr && rect.x == 0 && threadIdx.x == 0) {      // one writer per sample
                 a.first[i] = fresh ? 1 : 0;
                 if (fresh) a.seen[row] = a.stamp;
             }
         }
-        for (int64_t s = blockIdx.x; s < a.gps * geom.spans; s += gridDim.x) {
+        for (int64_t s = rect.x; SLOTS || s < a.gps * geom.spans; s += rect.grid_x) {
             const int64_t g = s / geom.spans;
             const int64_t e0 = (s - g * geom.spans) * geom.span_pieces * 8;
             const int64_t e1 = min(e0 + static_cast<int64_t>(geom.span_pieces) * 8, static_cast<int64_t>(a.group));
@@ -581,14 +612,16 @@ __device__ __forceinline__ void large_quant_body(const QuantJob& a, const LargeG
                     }
                 }
             }
+            if constexpr (SLOTS) break;
         }
+        if constexpr (SLOTS) break;
     }
 }
 
 template <int DT, int BITS, int ROUND>
 __device__ __forceinline__ void large_quant_bits(const QuantJob& a, const LargeGeom geom) {
-    if (a.m_buf) large_quant_body<DT, BITS, ROUND, true>(a, geom);
-    else large_quant_body<DT, BITS, ROUND, false>(a, geom);
+    if (a.m_buf) large_quant_body<DT, BITS, ROUND, true>(a, geom, whole_grid());
+    else large_quant_body<DT, BITS, ROUND, false>(a, geom, whole_grid());
 }
 
 template <int DT, int ROUND>
@@ -613,6 +646,12 @@ void large_quant_kernel(const QuantJob a, const LargeGeom geom) {
 // (When it pays, and what it measured: split_pays() in the dispatch.)
 // ---------------------------------------------------------------------------
 template <int DT>
+__device__ __forceinline__ void split_max_job(const QuantJob& a, const LargeGeom geom, const Rect rect, float* wave_max) {
+    if (a.m_buf) large_max_body<DT, true, true>(a, geom, rect, wave_max);
+    else large_max_body<DT, false, true>(a, geom, rect, wave_max);
+}
+
+template <int DT>
 __global__ __launch_bounds__(kBlock)
 void split_max_kernel(AQSGD_QUANT_ARGS, int32_t spans, int32_t span_pieces) {
     __shared__ float wave_max[kBlock / kWave];
@@ -621,14 +660,24 @@ void split_max_kernel(AQSGD_QUANT_ARGS, int32_t spans, int32_t span_pieces) {
     a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
     a.seen = seen; a.stamp = stamp;
     const LargeGeom geom{spans, span_pieces};
-    if (a.m_buf) large_max_body<DT, true, true>(a, geom, wave_max);
-    else large_max_body<DT, false, true>(a, geom, wave_max);
+    split_max_job<DT>(a, geom, whole_grid(), wave_max);
 }
 
 template <int DT, int BITS, int ROUND>
-__device__ __forceinline__ void split_quant_bits(const QuantJob& a, const LargeGeom geom) {
-    if (a.m_buf) large_quant_body<DT, BITS, ROUND, true, true>(a, geom);
-    else large_quant_body<DT, BITS, ROUND, false, true>(a, geom);
+__device__ __forceinline__ void split_quant_bits(const QuantJob& a, const LargeGeom geom, const Rect rect) {
+    if (a.m_buf) large_quant_body<DT, BITS, ROUND, true, true>(a, geom, rect);
+    else large_quant_body<DT, BITS, ROUND, false, true>(a, geom, rect);
+}
+
+template <int DT, int ROUND>
+__device__ __forceinline__ void split_quant_job(const QuantJob& a, const LargeGeom geom, const Rect rect) {
+    switch (a.bits) {                                    // uniform over the workgroup
+    case 2: split_quant_bits<DT, 2, ROUND>(a, geom, rect); break;
+    case 3: split_quant_bits<DT, 3, ROUND>(a, geom, rect); break;
+    case 4: split_quant_bits<DT, 4, ROUND>(a, geom, rect); break;
+    case 6: split_quant_bits<DT, 6, ROUND>(a, geom, rect); break;
+    default: split_quant_bits<DT, 8, ROUND>(a, geom, rect); break;
+    }
 }
 
 template <int DT, int ROUND>
@@ -639,13 +688,7 @@ void split_quant_kernel(AQSGD_QUANT_ARGS, int32_t spans, int32_t span_pieces) {
     a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
     a.seed = seed; a.seen = seen; a.first = first; a.stamp = stamp;
     const LargeGeom geom{spans, span_pieces};
-    switch (bits) {
-    case 2: split_quant_bits<DT, 2, ROUND>(a, geom); break;
-    case 3: split_quant_bits<DT, 3, ROUND>(a, geom); break;
-    case 4: split_quant_bits<DT, 4, ROUND>(a, geom); break;
-    case 6: split_quant_bits<DT, 6, ROUND>(a, geom); break;
-    default: split_quant_bits<DT, 8, ROUND>(a, geom); break;
-    }
+    split_quant_job<DT, ROUND>(a, geom, whole_grid());
 }
 
 // Per-dtype pieces (defined by AQSGD_INSTANTIATE_ANYGROUP_DTYPE in the dtype's .hip file).

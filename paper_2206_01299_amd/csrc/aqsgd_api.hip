@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "aqsgd_anygroup.h"
+#include "aqsgd_jobs_anygroup.h"
 #include "aqsgd_kernels.h"
 #include "aqsgd_lowbit.h"
 #include "aqsgd_single.h"
@@ -22,6 +23,9 @@ namespace aqsgd {
     extern template hipError_t launch_quant_wide_dt<DT>(int, const QuantJob&, hipStream_t);           \
     extern template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
     extern template hipError_t launch_quant_split_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
+    extern template hipError_t launch_odd_jobs_dt<DT>(int, int, const JobTable&, hipStream_t);        \
+    extern template hipError_t launch_wide_jobs_dt<DT>(int, const JobTable&, hipStream_t);            \
+    extern template hipError_t launch_split_jobs_dt<DT>(int, const JobTable&, hipStream_t);           \
     extern template hipError_t launch_lowbit_dt<DT>(int, int, int, bool, LaunchGeom, const LowbitArgs&, hipStream_t);
 AQSGD_EXTERN_DTYPE(AQSGD_F32)
 AQSGD_EXTERN_DTYPE(AQSGD_F16)
@@ -108,6 +112,31 @@ hipError_t launch_quant_split(int dtype, int rounding, const QuantJob& a, const 
     case AQSGD_F32:  return launch_quant_split_dt<AQSGD_F32>(rounding, a, geom, s);
     case AQSGD_F16:  return launch_quant_split_dt<AQSGD_F16>(rounding, a, geom, s);
     case AQSGD_BF16: return launch_quant_split_dt<AQSGD_BF16>(rounding, a, geom, s);
+    default:         return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_odd_jobs(int dtype, int rounding, int shape, const JobTable& t, hipStream_t s) {
+    switch (dtype) {
+    case AQSGD_F32:  return launch_odd_jobs_dt<AQSGD_F32>(rounding, shape, t, s);
+    case AQSGD_F16:  return launch_odd_jobs_dt<AQSGD_F16>(rounding, shape, t, s);
+    case AQSGD_BF16: return launch_odd_jobs_dt<AQSGD_BF16>(rounding, shape, t, s);
+    default:         return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_wide_jobs(int dtype, int rounding, const JobTable& t, hipStream_t s) {
+    switch (dtype) {
+    case AQSGD_F32:  return launch_wide_jobs_dt<AQSGD_F32>(rounding, t, s);
+    case AQSGD_F16:  return launch_wide_jobs_dt<AQSGD_F16>(rounding, t, s);
+    case AQSGD_BF16: return launch_wide_jobs_dt<AQSGD_BF16>(rounding, t, s);
+    default:         return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_split_jobs(int dtype, int rounding, const JobTable& t, hipStream_t s) {
+    switch (dtype) {
+    case AQSGD_F32:  return launch_split_jobs_dt<AQSGD_F32>(rounding, t, s);
+    case AQSGD_F16:  return launch_split_jobs_dt<AQSGD_F16>(rounding, t, s);
+    case AQSGD_BF16: return launch_split_jobs_dt<AQSGD_BF16>(rounding, t, s);
     default:         return hipErrorInvalidValue;
     }
 }
@@ -252,6 +281,12 @@ struct SeenArgs {
     uint32_t stamp = 0;
 };
 
+// Pieces of 16 bytes (the dequantising side's unit for odd groups) of a sample.
+int64_t odd_pieces(const DequantJob& a, int dtype) {
+    const int64_t piece = dtype == AQSGD_F32 ? kUnit : kChunk;
+    return a.gps * ((a.group + piece - 1) / piece);
+}
+
 // Which kernels a message takes.  Groups of whole chunks that fit a workgroup's registers are
 // jobs of the shared launches; the rest are launched on their own: odd groups (8 elements or
 // more, not whole chunks), groups beyond the job kernels' team shapes and those beyond any
@@ -304,8 +339,7 @@ DequantPlan plan_dequant(const aqsgd_desc* d, int64_t batch, int64_t n_per, cons
     a.grid_x = a.grid_y = 1; a.rcp_grid_x = 1.0f;
     a.seen = sa.seen; a.stamp = sa.stamp;
     p.dtype = d->dtype;
-    const int64_t piece = d->dtype == AQSGD_F32 ? kUnit : kChunk;
-    const bool odd_fits = a.group >= kChunk && a.gps * ((a.group + piece - 1) / piece) < kMaxOddPieces;
+    const bool odd_fits = a.group >= kChunk && odd_pieces(a, d->dtype) < kMaxOddPieces;
     p.route = a.group % kChunk == 0 ? Route::kJob : odd_fits ? Route::kOdd : Route::kAnyShape;
     return p;
 }
@@ -328,34 +362,40 @@ int64_t steps_per_workgroup(int shape, int64_t total, int64_t launch_blocks) {
     return launch_blocks > 0 ? (total + launch_blocks - 1) / launch_blocks : 1;
 }
 
+// What a sample of a table's jobs holds of the units a workgroup's step is counted in.
+int64_t whole_units(const QuantJob& a) { return a.gps; }
+int64_t whole_units(const DequantJob& a) { return a.cps; }
+
 // Workgroup numbers of a table whose jobs are all in: every job gets the grid its size
-// asks for (at most max_blocks), shortened by the steps a workgroup takes.  quant_step /
-// dequant_step: groups, chunks one workgroup step covers.  Tells whether there is a workgroup
+// asks for (at most max_blocks), shortened by the steps a workgroup takes (`shape`: team shape
+// of the quantising jobs, -1 for one step each).  quant_step / dequant_step: units one
+// workgroup step covers; units(job): those of a sample.  Tells whether there is a workgroup
 // for every step of every sample (else the kernel has to loop over what is left).
+template <typename Units>
 bool number_blocks(JobTable& t, int shape, int64_t quant_step, int64_t dequant_step, int64_t max_blocks,
-                   int64_t launch_blocks) {
+                   int64_t launch_blocks, Units&& units) {
     int64_t total = 0;
-    auto want = [&](int64_t units, int64_t step, int64_t batch) {
-        const LaunchGeom g = geometry(units, step, batch, max_blocks);
+    auto want = [&](const auto& a, int64_t step) {
+        const LaunchGeom g = geometry(units(a), step, a.batch, max_blocks);
         total += static_cast<int64_t>(g.grid_x) * g.grid_y;
     };
-    for (int k = 0; k < t.n_quant; ++k) want(t.q[k].gps, quant_step, t.q[k].batch);
-    for (int k = 0; k < t.n_dequant; ++k) want(t.d[k].cps, dequant_step, t.d[k].batch);
+    for (int k = 0; k < t.n_quant; ++k) want(t.q[k], quant_step);
+    for (int k = 0; k < t.n_dequant; ++k) want(t.d[k], dequant_step);
     const int64_t steps = steps_per_workgroup(shape, total, launch_blocks);
     bool covers = true;
     uint32_t blocks = 0;
-    auto place = [&](auto& a, int64_t units, int64_t step) {
-        const LaunchGeom g = geometry(units, step * steps, a.batch, max_blocks);
+    auto place = [&](auto& a, int64_t step) {
+        const LaunchGeom g = geometry(units(a), step * steps, a.batch, max_blocks);
         a.grid_x = g.grid_x; a.grid_y = g.grid_y; a.rcp_grid_x = 1.0f / static_cast<float>(g.grid_x);
         covers = covers && g.grid_y == static_cast<uint32_t>(a.batch) &&
-                 static_cast<int64_t>(g.grid_x) * step >= units;
+                 static_cast<int64_t>(g.grid_x) * step >= units(a);
         const uint32_t at = blocks;
         blocks += g.grid_x * g.grid_y;
         return at;
     };
-    for (int k = 0; k < t.n_quant; ++k) t.q_block0[k] = place(t.q[k], t.q[k].gps, quant_step);
+    for (int k = 0; k < t.n_quant; ++k) t.q_block0[k] = place(t.q[k], quant_step);
     t.dequant_block0 = blocks;
-    for (int k = 0; k < t.n_dequant; ++k) t.d_block0[k] = place(t.d[k], t.d[k].cps, dequant_step);
+    for (int k = 0; k < t.n_dequant; ++k) t.d_block0[k] = place(t.d[k], dequant_step);
     t.total_blocks = blocks;
     return covers;
 }
@@ -394,20 +434,22 @@ LargeGeom large_geometry(const QuantJob& a) {
 // 36.8 -> 35.9).  For the same reason nearest rounding of 16-bit types stays with one workgroup (8
 // groups of 49152, encode alone 10.1 -> 7.6, four calls 19.2 -> 18.0 to 21.7 with how fast the host
 // issues the fifth launch), and nearest grad_quant gains nothing (6.0 -> 6.5).
-bool split_pays(const QuantJob& a, int dtype, int rounding) {
-    const int64_t groups = a.gps * a.batch;
+bool split_pays(int64_t groups, bool has_buf, int dtype, int rounding) {
     return rounding == AQSGD_ROUND_STOCHASTIC ? groups <= 64
-                                              : dtype == AQSGD_F32 && a.m_buf != nullptr && groups <= 32;
+                                              : dtype == AQSGD_F32 && has_buf && groups <= 32;
 }
 
-// Their spans are of nearly equal length, so that the last one, too, has codes enough for the
-// slots (groups of 32769 elements and more: never fewer than 1800 elements a span).
-LargeGeom split_geometry(const QuantJob& a) {
-    LargeGeom g;
-    const int spans = (a.group + kSplitSpanElements - 1) / kSplitSpanElements;
-    g.spans = spans < kSplitMaxSpans ? spans : kSplitMaxSpans;
-    g.span_pieces = (a.cpg + g.spans - 1) / g.spans;
-    return g;
+// The same for the wide groups of a shared launch (`groups` in all, activations among them: has_buf),
+// where the second launch is one for all messages and the dequantising jobs fill what the maxima leave
+// idle.  A time slot of one boundary, groups of 49152, one workgroup each -> spans, in us:
+//   stochastic   64 groups  float16 13.4 -> 13.5, float32 19.1;  96 groups 19.0 -> 16.1, 26.1 -> 24.2;
+//                128 groups 19.5 -> 18.9, 29.2 -> 29.9
+//   nearest      float32  48 groups 18.4 -> 15.1, 64 groups 19.9 -> 19.0, 96 groups 22.6 -> 24.2
+//                float16   8 groups 10.8 -> 9.2, 32 groups 11.9 -> 10.5, 64 groups 13.3 -> 13.1, 96 groups 14.8 -> 15.5
+//                bfloat16  8 groups 10.1 -> 9.4, 32 groups 11.1 -> 10.6, 64 groups 12.6 -> 12.9
+bool split_pays_shared(int64_t groups, bool has_buf, int dtype, int rounding) {
+    if (rounding == AQSGD_ROUND_STOCHASTIC) return groups <= 96;
+    return has_buf && groups <= (dtype == AQSGD_F32 ? 64 : 32);
 }
 
 // The rectangle of a message launched by itself: one workgroup for every sample and step if
@@ -441,7 +483,7 @@ hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_b
         return launch_quant_single(p.dtype, p.rounding, p.shape, covers, a, stream);
     }
     case Route::kWide:
-        if (split_pays(a, p.dtype, p.rounding)) {
+        if (split_pays(a.gps * a.batch, a.m_buf != nullptr, p.dtype, p.rounding)) {
             const LargeGeom sg = split_geometry(a);
             if (one_step_grid(a, a.gps * sg.spans, 1, max_blocks))
                 return launch_quant_split(p.dtype, p.rounding, a, sg, stream);
@@ -464,9 +506,7 @@ hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_b
 hipError_t launch_dequant_alone(DequantPlan& p, int64_t max_blocks, hipStream_t stream) {
     DequantJob& a = p.job;
     if (p.route == Route::kOdd) {
-        const int64_t piece = p.dtype == AQSGD_F32 ? kUnit : kChunk;
-        const bool covers = one_step_grid(a, a.gps * ((a.group + piece - 1) / piece),
-                                          static_cast<int64_t>(kBlock) * kOddUnroll, max_blocks);
+        const bool covers = one_step_grid(a, odd_pieces(a, p.dtype), static_cast<int64_t>(kBlock) * kOddUnroll, max_blocks);
         return launch_dequant_odd(p.dtype, covers, a, stream);
     }
     const LaunchGeom g = geometry(a.gps, kBlock, a.batch, max_blocks);
@@ -505,18 +545,70 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
             }
         }
     }
-    auto add_dequant = [&](JobTable& t, int dtype) {
+    const auto whole = [](const auto& a) { return whole_units(a); };
+    auto add_dequant = [&](JobTable& t, int dtype, Route route) {
         for (size_t k = 0; k < ds.size() && t.n_dequant < kMaxDequantJobs; ++k) {
-            if (d_done[k] || ds[k].route != Route::kJob || ds[k].dtype != dtype) continue;
+            if (d_done[k] || ds[k].route != route || ds[k].dtype != dtype) continue;
             t.d[t.n_dequant++] = ds[k].job;
             d_done[k] = true;
         }
+    };
+    // Odd and wide groups: those of one kind (dtype, rounding mode; odd ones also team shape) and
+    // the dequantising jobs that are ready with them as one table, if that has more than one
+    // job and a workgroup for each of their steps.
+    auto launch_shared = [&](size_t i) {
+        const QuantPlan& lead = qs[i];
+        const bool odd = lead.route == Route::kOdd;
+        if ((!odd && lead.route != Route::kWide) || launch_blocks > 0) return false;
+        const std::vector<bool> q_before = q_done, d_before = d_done;
+        JobTable t;
+        t.n_quant = t.n_dequant = 0;
+        int64_t groups = 0;
+        bool has_buf = false;
+        for (size_t k = i; k < qs.size() && t.n_quant < kMaxQuantJobs; ++k) {
+            const QuantPlan& c = qs[k];
+            if (q_done[k] || c.route != lead.route || c.dtype != lead.dtype || c.rounding != lead.rounding ||
+                (odd && c.shape != lead.shape))
+                continue;
+            groups += c.job.gps * c.job.batch;
+            has_buf = has_buf || c.job.m_buf != nullptr;
+            t.q[t.n_quant++] = c.job;
+            q_done[k] = true;
+        }
+        add_dequant(t, lead.dtype, odd ? Route::kOdd : Route::kJob);
+        bool covers = t.n_quant + t.n_dequant > 1;
+        if (covers && odd) {
+            struct {
+                int dtype;
+                int64_t operator()(const QuantJob& a) const { return a.gps; }
+                int64_t operator()(const DequantJob& a) const { return odd_pieces(a, dtype); }
+            } units{lead.dtype};
+            covers = number_blocks(t, -1, groups_per_block_step(lead.shape),
+                                   static_cast<int64_t>(threads_of_shape(lead.shape)) * kOddUnroll, max_blocks, 0, units);
+            if (covers) err = launch_odd_jobs(lead.dtype, lead.rounding, lead.shape, t, stream);
+        } else if (covers && (split_pays(groups, has_buf, lead.dtype, lead.rounding))) {
+            struct {
+                int64_t operator()(const QuantJob& a) const { return a.gps * split_geometry(a).spans; }
+                int64_t operator()(const DequantJob& a) const { return a.cps; }
+            } units;
+            covers = number_blocks(t, -1, 1, static_cast<int64_t>(kBlock) * kHostedDequantUnroll, max_blocks, 0, units);
+            if (covers) err = launch_split_jobs(lead.dtype, lead.rounding, t, stream);
+        } else if (covers) {
+            covers = number_blocks(t, -1, 1, static_cast<int64_t>(kWideThreads) * kHostedDequantUnroll, max_blocks, 0, whole);
+            if (covers) err = launch_wide_jobs(lead.dtype, lead.rounding, t, stream);
+        }
+        if (!covers) {
+            q_done = q_before;
+            d_done = d_before;
+        }
+        return covers;
     };
 
     for (size_t i = 0; i < qs.size() && err == hipSuccess; ++i) {
         if (q_done[i]) continue;
         QuantPlan& lead = qs[i];
         if (lead.route != Route::kJob) {
+            if (launch_shared(i)) continue;
             err = launch_quant_alone(lead, max_blocks, launch_blocks, stream);
             q_done[i] = true;
             continue;
@@ -533,10 +625,10 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
             t.q[t.n_quant++] = c.job;
             q_done[k] = true;
         }
-        add_dequant(t, lead.dtype);
+        add_dequant(t, lead.dtype, Route::kJob);
         const bool covers = number_blocks(t, lead.shape, groups_per_block_step(lead.shape),
                                           static_cast<int64_t>(threads_of_shape(lead.shape)) * kHostedDequantUnroll,
-                                          max_blocks, launch_blocks);
+                                          max_blocks, launch_blocks, whole);
         const TableKind kind = covers ? (three ? kTableOneStepThree : kTableOneStep)
                                       : (three ? kTableLoopsThree : kTableLoops);
         err = launch_codec_jobs(lead.dtype, lead.rounding, lead.shape, kind, t, stream);
@@ -550,8 +642,8 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
         }
         JobTable t;
         t.n_quant = t.n_dequant = 0;
-        add_dequant(t, ds[i].dtype);
-        number_blocks(t, -1, 1, static_cast<int64_t>(kBlock) * unroll, max_blocks, launch_blocks);
+        add_dequant(t, ds[i].dtype, Route::kJob);
+        number_blocks(t, -1, 1, static_cast<int64_t>(kBlock) * unroll, max_blocks, launch_blocks, whole);
         err = launch_dequant_jobs(ds[i].dtype, unroll, t, stream);
     }
     return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;

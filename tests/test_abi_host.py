@@ -236,3 +236,17 @@ def test_header_is_plain_c_and_a_c_client_links(tmp_path):
     assert out[0] == str(4 * 1638400 * 4 // 8) and out[1] == str(4 * 1638400 // 1600)
     assert int(out[2]) == ctypes.sizeof(B.Job)           # the binding's mirror of aqsgd_job has the C size
     assert "group" in out[3]
+
+
+def test_no_kernel_asks_for_more_scratch_than_a_workgroup_can_be_given():
+    """A kernel that copies its job table (2000 bytes) to every lane's scratch memory asks for 140 KB a wave: a
+    workgroup of 1024 lanes is never given that and never starts.  What spills does (the kernels with loops for
+    1024-lane teams) stays below 600 bytes."""
+    lib = B.LIB_PATH.read_bytes()
+    key = b".private_segment_fixed_size"
+    sizes = []
+    for at in re.finditer(re.escape(key), lib):          # the kernels' metadata, msgpack: key, then an integer
+        v = lib[at.end():at.end() + 5]
+        sizes.append(v[0] if v[0] < 0x80 else int.from_bytes(v[1:3], "big") if v[0] == 0xCD
+                     else v[1] if v[0] == 0xCC else int.from_bytes(v[1:5], "big"))
+    assert len(sizes) > 500 and max(sizes) < 600, max(sizes)

@@ -245,6 +245,59 @@ def test_more_jobs_than_one_grid_holds_and_any_shape_jobs(H):
         b.verify(f"job set member {i}")
 
 
+ALONE = [
+    # dtype, fwd bits/group/rounding, bwd bits/group/rounding, boundaries, batch, groups per sample
+    ("f16", 8, 10, 0, 8, 10, 0, 3, 3, 701),              # odd groups: teams of 2 lanes ...
+    ("f32", 4, 12, 0, 8, 12, 0, 1, 3, 257),              # ... 2 and 8 lanes apart: float32 nearest with m keeps 8
+    ("bf16", 4, 62, 1, 8, 62, 0, 2, 2, 130),             # rounding modes apart
+    ("f16", 2, 124, 1, 4, 124, 1, 2, 2, 67),
+    ("f32", 8, 250, 1, 8, 250, 1, 3, 2, 33),
+    ("bf16", 4, 510, 0, 6, 500, 0, 5, 2, 9),             # ten quantising jobs: a second table
+    ("f16", 4, 1020, 0, 8, 1020, 0, 1, 4, 25),
+    ("f32", 4, 1530, 0, 8, 1530, 1, 2, 1, 5),
+    ("f16", 4, 2046, 1, 4, 2046, 1, 1, 2, 7),
+    ("bf16", 8, 4090, 0, 8, 4090, 0, 2, 2, 3),
+    ("f16", 4, 8190, 0, 8, 8190, 0, 2, 1, 3),
+    ("bf16", 4, 16382, 1, 8, 16382, 1, 2, 1, 2),
+    ("f32", 8, 32766, 1, 8, 32766, 1, 1, 2, 2),
+    ("f16", 4, 1020, 0, 8, 1024, 0, 2, 2, 256),          # odd forward, whole backward groups
+    ("bf16", 8, 32776, 0, 8, 32776, 0, 2, 2, 2),         # wide groups, 16: spans in two launches
+    ("f16", 4, 65536, 0, 6, 65536, 0, 3, 6, 1),          # 36: one workgroup each
+    ("f16", 2, 36864, 1, 4, 36864, 1, 2, 4, 3),          # stochastic, 48: spans
+    ("bf16", 3, 49152, 1, 8, 49152, 1, 3, 17, 1),        # 102: one workgroup each
+    ("f32", 4, 49152, 0, 8, 49152, 0, 1, 3, 2),          # float32 with m, 12: spans
+    ("f32", 3, 32776, 0, 8, 32776, 0, 3, 11, 1),         # 66: one workgroup each
+    ("f32", 8, 49152, 1, 8, 49152, 1, 3, 17, 1),
+    ("f16", 4, 32770, 1, 8, 32770, 1, 1, 2, 2),          # wide and odd
+    ("f16", 8, 65544, 0, 8, 32772, 0, 1, 1, 3),          # forward groups beyond a workgroup, wide and odd backward ones
+]
+
+
+@pytest.mark.parametrize("case", ALONE, ids=[f"{c[0]}-fw{c[1]}g{c[2]}r{c[3]}-bw{c[4]}g{c[5]}r{c[6]}x{c[7]}" for c in ALONE])
+def test_time_slots_of_odd_and_wide_groups(H, case):
+    """Whole time slots of several boundaries whose groups are no whole chunks, or larger than the job
+    kernels' shapes: their jobs share launches of their own."""
+    dtype, fb, fg, fr, bb, bg, br, boundaries, batch, gps = case
+    n_per = fg * gps
+    if n_per % bg:
+        n_per = fg * bg // np.gcd(fg, bg)
+    rng = np.random.default_rng(3000 + ALONE.index(case))
+    bs = [Boundary(H, rng, dtype, fb, fg, fr, bb, bg, br, batch, int(n_per), n_rows=2 * batch + 1, seed=500 + i)
+          for i in range(boundaries)]
+    for step in range(4):
+        print("odd and wide", case, "slot", step, flush=True)
+        jobs = []
+        for b in bs:
+            if step >= 2:
+                jobs.append(b.grad_dequant_job())
+            if step >= 1:
+                jobs += [b.decode_job(), b.grad_quant_job()]
+            jobs.append(b.encode_job(step))
+        B.run_jobs(jobs)
+        for i, b in enumerate(bs):
+            b.verify(f"{case} boundary {i} slot {step}")
+
+
 def test_a_bad_job_stops_the_whole_call_before_any_launch(H):
     rng = np.random.default_rng(7)
     b = Boundary(H, rng, "f16", 4, 256, 0, 8, 256, 0, 2, 256 * 5, n_rows=4, seed=1)

@@ -120,6 +120,18 @@ def test_first_visit_calls_as_jobs_of_a_stage_launch(H, dtype):
             as_jobs=True)
 
 
+@pytest.mark.parametrize("dtype,bits,group,gps,batch,rounding", [
+    ("f16", 4, 1020, 5, 4, 0),           # odd groups
+    ("f32", 8, 10, 70, 4, 1),
+    ("bf16", 4, 49152, 1, 4, 0),         # wide groups, one workgroup each
+    ("f32", 4, 49152, 1, 4, 0),          # ... as spans in two launches
+    ("f16", 2, 32776, 2, 4, 1),
+])
+def test_first_visit_jobs_of_odd_and_wide_groups(H, dtype, bits, group, gps, batch, rounding):
+    _replay(H, dtype, bits=bits, group=group, n_per=group * gps, n_rows=11, batch=batch, steps=5, rounding=rounding,
+            seed=group, as_jobs=True)
+
+
 def test_seen_jobs_reject_bad_arguments(H):
     import ctypes
     ok = B.make_desc(batch=2, n_per=1600, n_samples=4, bits=4, group=1600, dtype="f16")
