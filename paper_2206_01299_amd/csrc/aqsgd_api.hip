@@ -284,7 +284,7 @@ struct SeenArgs {
 // Pieces of 16 bytes (the dequantising side's unit for odd groups) of a sample.
 int64_t odd_pieces(const DequantJob& a, int dtype) {
     const int64_t piece = dtype == AQSGD_F32 ? kUnit : kChunk;
-    return a.gps * ((a.group + piece - 1) / piece);
+    return (a.n_per + piece - 1) / piece;
 }
 
 // Which kernels a message takes.  Groups of whole chunks that fit a workgroup's registers are
