@@ -53,9 +53,9 @@ __device__ __forceinline__ void store_piece(char* p, const float (&v)[N]) {
     if constexpr (DT == AQSGD_F32) {
 #pragma unroll
         for (int q = 0; q < N / 4; ++q)
-            store16_through(p + 16 * q, f32x4_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]});
+            store16(p + 16 * q, f32x4_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}, false);
     } else {
-        store16_through(p, pack_raw<DT>(v).v);
+        store16(p, pack_raw<DT>(v).v, false);
     }
 }
 
@@ -306,7 +306,7 @@ __device__ __forceinline__ void quant_wide_body(const QuantJob& a, uint32_t bx, 
                 if (k < rounds) {
                     const uint32_t at = place(k) * kEB;
 #pragma unroll
-                    for (int q = 0; q < N * kEB / 16; ++q) store16_through(m_g + at + 16 * q, ra[k].v[q]);
+                    for (int q = 0; q < N * kEB / 16; ++q) store16(m_g + at + 16 * q, ra[k].v[q], false);
                 }
         }
         return;

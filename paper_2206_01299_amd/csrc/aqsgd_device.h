@@ -72,23 +72,30 @@ __device__ __forceinline__ Raw<DT> load_raw_any(const char* p) {
     return r;
 }
 
-// A 16-byte streaming store that is also written through the L2 at system scope (nt with
-// sc0 sc1).  The launches here end with tens of MB of freshly written lines, and lines
-// that only stream (nt) still wait in the eight L2s for the write-back at the end of the
-// kernel; written through, they leave while the kernel is still reading.  Measured on the
-// GPT2 boundary: forward pair in the pipelined schedule 13.9-14.2 -> 13.3-13.4 us, DeBERTa
-// step 36.7 -> 35.6 us.  The compiler has no spelling for this combination on a 16-byte
-// store, so the instruction is written out; the data registers of a store of more than
-// eight bytes must not be overwritten in the next two cycles, which the compiler's hazard
-// pass cannot see through the asm statement, hence the s_nop.
+// A 16-byte streaming store (nt), or one that is also written through the L2 at system scope (nt
+// with sc0 sc1).
+//
+// The large shared launches end with tens of MB of freshly written lines, and lines that only
+// stream still wait in the eight L2s for the write-back at the end of the kernel; written
+// through, they leave while the kernel is still reading.  With two streams' launches side by side
+// that is what counts: forward pair of the GPT2 boundary in the pipelined schedule 957-959 GB/s
+// streaming, 975-982 through, DeBERTa step 36.0 and 35.4 us.
+// Everywhere else streaming alone is better.  A store that is written through is over only when
+// memory has it, which a small launch waits for at its end: float16 [4,32,1024], encode 3.21 us
+// through, 2.71 streaming, decode 3.14 and 2.71; and where rows or groups are no whole 128-byte
+// lines the two halves of a line go to memory one by one instead of meeting in the L2: bfloat16
+// [7,1001,2008] decode 20.9 and 18.2, rows of 2048 17.1 and 17.4.  (Ordinary stores are as good as
+// streaming ones in small launches and lose in all others: float32 [8,2048,4096], four calls 407 us
+// against 358.)  So the caller says which: `through` is a constant but in the shared launches.
+//
+// The compiler has no spelling for nt sc0 sc1 on a 16-byte store, so the instruction is written
+// out; the data registers of a store of more than eight bytes must not be overwritten in the next
+// two cycles, which the compiler's hazard pass cannot see through the asm statement, hence the s_nop.
 template <typename V>
-__device__ __forceinline__ void store16_through(void* p, const V& v) {
+__device__ __forceinline__ void store16(void* p, const V& v, bool through) {
     static_assert(sizeof(V) == 16, "one 16-byte piece");
-#if defined(AQSGD_PLAIN_STREAMING_STORES)
-    __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
-#else
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 2" : : "v"(p), "v"(v) : "memory");
-#endif
+    if (through) asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 2" : : "v"(p), "v"(v) : "memory");
+    else __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
 }
 
 // A float32 chunk is two 16-byte stores per lane, 32 bytes apart between lanes:
@@ -96,13 +103,13 @@ __device__ __forceinline__ void store16_through(void* p, const V& v) {
 // stores of that shape reach 2.4 TB/s, ordinary stores, which L2 merges, 6.6;
 // the contiguous 16-byte-per-lane stores of the 16-bit types stream at full rate.
 template <int DT>
-__device__ __forceinline__ void store_raw_at(char* p, const Raw<DT>& r) {
+__device__ __forceinline__ void store_raw_at(char* p, const Raw<DT>& r, bool through) {
     if constexpr (DT == AQSGD_F32) {
         f32x4_t* q = reinterpret_cast<f32x4_t*>(p);
         q[0] = r.lo;
         q[1] = r.hi;
     } else {
-        store16_through(p, r.v);
+        store16(p, r.v, through);
     }
 }
 
@@ -660,9 +667,9 @@ __device__ __forceinline__ Raw<AQSGD_F32> load_raw_units_any(const char* pa, con
     return r;
 }
 
-__device__ __forceinline__ void store_raw_units(char* pa, char* pb, const Raw<AQSGD_F32>& r) {
-    store16_through(pa, r.lo);
-    store16_through(pb, r.hi);
+__device__ __forceinline__ void store_raw_units(char* pa, char* pb, const Raw<AQSGD_F32>& r, bool through) {
+    store16(pa, r.lo, through);
+    store16(pb, r.hi, through);
 }
 
 // The two halves of pack_levels' word: levels 0..3 and 4..7, 4*BITS bits each.

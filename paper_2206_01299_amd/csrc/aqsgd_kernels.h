@@ -63,6 +63,7 @@ struct QuantJob {
     int32_t bits;
     uint32_t grid_x, grid_y;   // its workgroups: grid_x per sample row, grid_y rows
     float rcp_grid_x;          // 1 / grid_x, for the workgroup's position in that rectangle
+    uint32_t through;          // m is written through the L2 (see store16)
     uint64_t seed;
     uint32_t* seen;            // or nullptr: no first-visit handling
     int32_t* first;            // with seen: first[i] = 1 if sample i was new, else 0
@@ -85,6 +86,7 @@ struct DequantJob {
     int32_t bits;
     uint32_t grid_x, grid_y;
     float rcp_grid_x;
+    uint32_t through;          // m and out are written through the L2
     uint32_t* seen;            // or nullptr
     uint32_t stamp;
 };
@@ -292,7 +294,7 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
                 store_codes_of_unit<BITS, ODD>(group_codes + Unit::template code_byte<BITS>(ub[k]), high_unit_codes<BITS>(w));
                 if constexpr (HAS_BUF)
                     store_raw_units(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB,
-                                    updated_chunk<DT>(rm[u][k], dh));
+                                    updated_chunk<DT>(rm[u][k], dh), a.through != 0);
                 continue;
             }
             if (BITS == 3 && TEAM % 4 == 0 && a.cpg % 4 == 0) {
@@ -306,7 +308,7 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
                 store_codes_at<BITS>(group_codes + cc[k] * BITS, pack_levels<BITS>(q));
             }
             if constexpr (HAS_BUF)
-                store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, updated_chunk<DT>(rm[u][k], dh));
+                store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, updated_chunk<DT>(rm[u][k], dh), a.through != 0);
         }
         if (lane_in_team == 0) scales_s[g0 + u * gstride] = sc[u].s_tx;
     }
@@ -337,9 +339,9 @@ __device__ __forceinline__ void copy_team_group(const QuantJob& a, const char* s
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
         if constexpr (kUnits)
-            store_raw_units(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB, ra[k]);
+            store_raw_units(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB, ra[k], a.through != 0);
         else
-            store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, ra[k]);
+            store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, ra[k], a.through != 0);
     }
 }
 
@@ -456,8 +458,8 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
                     const char* full_s = static_cast<const char*>(a.full) + out0 * kEB;
                     for (uint32_t c = bx * THREADS + threadIdx.x; c < cps; c += a.grid_x * THREADS) {
                         const Raw<DT> v = load_raw_at<DT>(full_s + static_cast<uint64_t>(c) * kChunkBytes);
-                        store_raw_at<DT>(m_s + static_cast<uint64_t>(c) * kChunkBytes, v);
-                        store_raw_at<DT>(out_s + static_cast<uint64_t>(c) * kChunkBytes, v);
+                        store_raw_at<DT>(m_s + static_cast<uint64_t>(c) * kChunkBytes, v, a.through != 0);
+                        store_raw_at<DT>(out_s + static_cast<uint64_t>(c) * kChunkBytes, v, a.through != 0);
                     }
                     if constexpr (!LOOPS) return;
                     else continue;
@@ -507,11 +509,11 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
                     Raw<DT> packed;
                     if constexpr (HAS_BUF) {
                         packed = updated_chunk<DT>(rm[u], dh);
-                        store_raw_at<DT>(m_s + static_cast<uint64_t>(cs[u]) * kChunkBytes, packed);
+                        store_raw_at<DT>(m_s + static_cast<uint64_t>(cs[u]) * kChunkBytes, packed, a.through != 0);
                     } else {
                         packed = pack_raw<DT>(dh);
                     }
-                    store_raw_at<DT>(out_s + static_cast<uint64_t>(cs[u]) * kChunkBytes, packed);
+                    store_raw_at<DT>(out_s + static_cast<uint64_t>(cs[u]) * kChunkBytes, packed, a.through != 0);
                 }
             }
             if constexpr (!LOOPS) break;
@@ -549,8 +551,8 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
                     for (uint32_t u = bx * THREADS + threadIdx.x; u < ups; u += a.grid_x * THREADS) {
                         const f32x4_t v = __builtin_nontemporal_load(
                             reinterpret_cast<const f32x4_t*>(full_s + static_cast<uint64_t>(u) * kUnitBytes));
-                        store16_through(m_s + static_cast<uint64_t>(u) * kUnitBytes, v);
-                        store16_through(out_s + static_cast<uint64_t>(u) * kUnitBytes, v);
+                        store16(m_s + static_cast<uint64_t>(u) * kUnitBytes, v, a.through != 0);
+                        store16(out_s + static_cast<uint64_t>(u) * kUnitBytes, v, a.through != 0);
                     }
                     if constexpr (!LOOPS) return;
                     else continue;
@@ -600,8 +602,8 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
                     else v[e] = dh;
                 }
                 if (ok[u]) {
-                    if constexpr (HAS_BUF) store16_through(m_s + static_cast<uint64_t>(us[u]) * kUnitBytes, v);
-                    store16_through(out_s + static_cast<uint64_t>(us[u]) * kUnitBytes, v);
+                    if constexpr (HAS_BUF) store16(m_s + static_cast<uint64_t>(us[u]) * kUnitBytes, v, a.through != 0);
+                    store16(out_s + static_cast<uint64_t>(us[u]) * kUnitBytes, v, a.through != 0);
                 }
             }
             if constexpr (!LOOPS) break;

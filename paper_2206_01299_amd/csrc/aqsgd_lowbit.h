@@ -302,7 +302,7 @@ __device__ __forceinline__ void lowbit_team_group(const LowbitArgs& a, const cha
 #pragma unroll
         for (int e = 0; e < kChunk; ++e) q2[e] = level_of<MBITS, AQSGD_ROUND_NEAREST>(v[k][e], ssc, kNearestOffset32);
         store_codes_at<MBITS>(m_group + cc[k] * static_cast<uint32_t>(MBITS), pack_levels<MBITS>(q2));
-        if constexpr (!SENDER) store_raw_at<DT>(out_s + goff * kEB + cc[k] * kChunkBytes, pack_raw<DT>(v[k]));
+        if constexpr (!SENDER) store_raw_at<DT>(out_s + goff * kEB + cc[k] * kChunkBytes, pack_raw<DT>(v[k]), false);
     }
     if constexpr (TAIL) {
         const float q2 = level_of<MBITS, AQSGD_ROUND_NEAREST>(tail_v, ssc, kNearestOffset32);

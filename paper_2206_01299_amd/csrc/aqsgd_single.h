@@ -56,7 +56,7 @@ void quant_single_kernel(AQSGD_QUANT_ARGS) {
     a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
     a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
     a.cpg = static_cast<int32_t>((static_cast<uint32_t>(group) + kChunk - 1) / kChunk);
-    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f;
+    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f; a.through = 0;
     a.seed = seed; a.seen = seen; a.first = first; a.stamp = stamp;
     if constexpr (KIND == kSingleThree) {
         single_quant_bits<DT, 3, ROUND, TEAM, CPL, false, false>(a, wave_max);
@@ -77,7 +77,7 @@ void dequant_single_kernel(AQSGD_DEQUANT_ARGS) {
     a.codes = codes; a.scales = scales; a.ids = ids; a.m_buf = m_buf; a.out = out; a.full = full;
     a.n_per = n_per; a.gps = gps; a.cps = n_per >> 3; a.batch = batch; a.group = group;
     a.cpg = static_cast<int32_t>(static_cast<uint32_t>(group) / kChunk); a.bits = bits;
-    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f;
+    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f; a.through = 0;
     a.seen = seen; a.stamp = stamp;
     dequant_job<DT, UNROLL, kBlock, false>(a, blockIdx.x, blockIdx.y);
 }

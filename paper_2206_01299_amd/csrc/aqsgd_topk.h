@@ -700,7 +700,7 @@ __device__ __forceinline__ void topk_dequant_group(const TopkArgs& a, int64_t g,
             x[e] = on ? v : 0.0f;
             pos += on;
         }
-        if (valid[k]) store_raw_at<DT>(dst + cc[k] * kChunkBytes, pack_raw<DT>(x));
+        if (valid[k]) store_raw_at<DT>(dst + cc[k] * kChunkBytes, pack_raw<DT>(x), true);
         row_start += kept_total[k];
     }
     wave_lds_sync();

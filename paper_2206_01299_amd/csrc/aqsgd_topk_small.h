@@ -340,7 +340,7 @@ __device__ __forceinline__ void topk_small_dequant(const TopkArgs& a, int64_t g0
             pos += on;
         }
         if (valid[k] && stores)
-            store_raw_at<DT>(static_cast<char*>(a.out) + (e0 + cc[k] * kChunk) * kEB, pack_raw<DT>(x));
+            store_raw_at<DT>(static_cast<char*>(a.out) + (e0 + cc[k] * kChunk) * kEB, pack_raw<DT>(x), true);
     }
     wave_lds_sync();
 }
