@@ -645,12 +645,15 @@ __device__ __forceinline__ uint64_t load_bytes_any(const uint8_t* p) {
 // width apart, so that consecutive lanes access consecutive 16 bytes, as the
 // 16-bit types do (measured on the float32 stress shape with encode's traffic:
 // 6.3 instead of 5.2 TB/s).  Four b-bit codes are b/2 bytes, whole bytes for every
-// width but 3, which keeps the one-piece layout.
+// width but 3, where two neighbouring units share a byte: a reader takes the two bytes
+// around its 12 bits, the writers of eight units make three dwords (below).  (In one
+// piece, float32 [4,2048,1024] at 3 bits: encode 21.1 us, decode 24.2 and
+// grad_dequant 11.1; so 18.1, 18.9 and 7.0.)
 // ---------------------------------------------------------------------------
 constexpr int kUnit = 4;           // elements of a 16-byte float32 unit
 
-template <int DT, int BITS> struct UnitLayout {
-    static constexpr bool value = DT == AQSGD_F32 && BITS != 3;
+template <int DT> struct UnitLayout {
+    static constexpr bool value = DT == AQSGD_F32;
 };
 
 __device__ __forceinline__ Raw<AQSGD_F32> load_raw_units(const char* pa, const char* pb) {
@@ -682,8 +685,7 @@ __device__ __forceinline__ uint32_t high_unit_codes(uint64_t w) {
     return static_cast<uint32_t>(w >> (4 * BITS));
 }
 
-// Codes of one unit to / from the byte stream; unit u of the call starts at byte
-// u * BITS / 2.
+// Codes of one unit to / from the byte stream; unit u of the call starts at bit 4 BITS u.
 template <int BITS>
 __device__ __forceinline__ void store_unit_codes(uint8_t* p, uint32_t w) {
     static_assert(BITS == 2 || BITS == 4 || BITS == 6 || BITS == 8, "whole bytes per unit");
@@ -700,18 +702,44 @@ __device__ __forceinline__ void store_unit_codes(uint8_t* p, uint32_t w) {
     }
 }
 
+// `unit`: the unit's number in the stream that starts at p.  Three bits: a pair of units is three
+// bytes, and every sample's units are pairs, so the two bytes around 12 bits are the pair's own.
 template <int BITS>
-__device__ __forceinline__ uint32_t load_unit_codes(const uint8_t* p) {
-    static_assert(BITS == 2 || BITS == 4 || BITS == 6 || BITS == 8, "whole bytes per unit");
-    if constexpr (BITS == 8) {
-        return *reinterpret_cast<const uint32_t*>(p);
-    } else if constexpr (BITS == 4) {
-        return *reinterpret_cast<const uint16_t*>(p);
-    } else if constexpr (BITS == 2) {
-        return p[0];
+__device__ __forceinline__ uint32_t load_unit_codes(const uint8_t* p, uint32_t unit) {
+    if constexpr (BITS == 3) {
+        const uint32_t byte = unit + (unit >> 1);        // 12 bits a unit: a byte and a half
+        return (static_cast<uint32_t>(*reinterpret_cast<const u16_any_t*>(p + byte)) >> (4 * (unit & 1))) & 0xfffu;
     } else {
-        return static_cast<uint32_t>(p[0]) | (static_cast<uint32_t>(p[1]) << 8) |
-               (static_cast<uint32_t>(p[2]) << 16);
+        p += static_cast<uint64_t>(unit) * (BITS / 2);
+        if constexpr (BITS == 8) return *reinterpret_cast<const uint32_t*>(p);
+        else if constexpr (BITS == 4) return *reinterpret_cast<const uint16_t*>(p);
+        else if constexpr (BITS == 2) return p[0];
+        else return static_cast<uint32_t>(p[0]) | (static_cast<uint32_t>(p[1]) << 8) | (static_cast<uint32_t>(p[2]) << 16);
+    }
+}
+
+// Three-bit codes of consecutive units in consecutive lanes (`lane` 0 holds a unit whose number is a
+// multiple of eight; every lane calls it, `live`: its unit is one of the group's, which are pairs).
+// An even lane puts its 12 bits and the next lane's together; where the group's units are whole
+// octets (`octets`, uniform over the team), the four even lanes of an octet then make three
+// aligned dwords of their 24 bits as store_codes3_quad does, else each stores its three bytes.
+// group_codes: the group's first byte; unit: the lane's unit in the group.
+__device__ __forceinline__ void store_unit_codes3(uint8_t* group_codes, uint32_t unit, uint32_t w, int lane, bool live,
+                                                  bool octets) {
+    const uint32_t odd = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+        0, static_cast<int>(w), 0xF5 /* quad_perm [1,1,3,3] */, 0xf, 0xf, false));
+    const uint32_t pair = w | (odd << 12);
+    if (octets) {
+        const uint32_t next = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+            0, static_cast<int>(pair), 0x102 /* row_shl:2: from two lanes on */, 0xf, 0xf, true));
+        const int j = (lane & 7) >> 1;
+        const uint32_t word = (pair >> (8 * j)) | (next << (24 - 8 * j));        // j = 0, 1, 2
+        if (live && (lane & 1) == 0 && j < 3) reinterpret_cast<uint32_t*>(group_codes + (unit >> 3) * 12)[j] = word;
+    } else if (live && (lane & 1) == 0) {
+        uint8_t* p = group_codes + (unit >> 1) * 3;
+        p[0] = static_cast<uint8_t>(pair);
+        p[1] = static_cast<uint8_t>(pair >> 8);
+        p[2] = static_cast<uint8_t>(pair >> 16);
     }
 }
 

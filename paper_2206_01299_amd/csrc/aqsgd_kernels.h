@@ -171,7 +171,7 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
     constexpr bool kMultiWave = TEAM > kWave;
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
     constexpr int kEB = ElemBytes<DT>::value;
-    constexpr bool kUnits = UnitLayout<DT, BITS>::value;   // float32: a chunk is two separate 16-byte units
+    constexpr bool kUnits = UnitLayout<DT>::value;   // float32: a chunk is two separate 16-byte units
     using Chunk = Place<ODD, kChunk>;
     using Unit = Place<ODD, kUnit>;
     static_assert(NG == 1 || !kMultiWave, "several groups per step: teams inside a wavefront only");
@@ -290,8 +290,16 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
             char* m_g = HAS_BUF ? m_s + goff[u] * kEB : nullptr;
             if constexpr (kUnits) {
                 const uint64_t w = pack_levels<BITS>(q);
-                store_codes_of_unit<BITS, ODD>(group_codes + Unit::template code_byte<BITS>(ua[k]), low_unit_codes<BITS>(w));
-                store_codes_of_unit<BITS, ODD>(group_codes + Unit::template code_byte<BITS>(ub[k]), high_unit_codes<BITS>(w));
+                if constexpr (BITS == 3) {
+                    // lanes past the group's end hold its last unit once more and store nothing
+                    const int u0 = 2 * k * TEAM + lane_in_team, u1 = u0 + TEAM;
+                    const bool octets = a.cpg % 4 == 0;
+                    store_unit_codes3(group_codes, ua[k], low_unit_codes<BITS>(w), lane_in_team, u0 < 2 * a.cpg, octets);
+                    store_unit_codes3(group_codes, ub[k], high_unit_codes<BITS>(w), lane_in_team, u1 < 2 * a.cpg, octets);
+                } else {
+                    store_codes_of_unit<BITS, ODD>(group_codes + Unit::template code_byte<BITS>(ua[k]), low_unit_codes<BITS>(w));
+                    store_codes_of_unit<BITS, ODD>(group_codes + Unit::template code_byte<BITS>(ub[k]), high_unit_codes<BITS>(w));
+                }
                 if constexpr (HAS_BUF)
                     store_raw_units(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB,
                                     updated_chunk<DT>(rm[u][k], dh), a.through != 0);
@@ -317,12 +325,12 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
 // First visit of a sample on the sender: the team's chunks of the group go from act
 // to m unchanged (the activation itself is the message).  Same chunk ownership and
 // clamping as above, so the two paths write a row with the same access pattern.
-template <int DT, int BITS, int TEAM, int CPL, bool ODD>
+template <int DT, int TEAM, int CPL, bool ODD>
 __device__ __forceinline__ void copy_team_group(const QuantJob& a, const char* src_s, char* m_s, int64_t g,
                                                 const uint32_t (&cc)[CPL], const uint32_t (&ua)[CPL],
                                                 const uint32_t (&ub)[CPL]) {
     constexpr int kEB = ElemBytes<DT>::value;
-    constexpr bool kUnits = UnitLayout<DT, BITS>::value;
+    constexpr bool kUnits = UnitLayout<DT>::value;
     using Chunk = Place<ODD, kChunk>;
     using Unit = Place<ODD, kUnit>;
     const int64_t goff = g * a.group;
@@ -414,7 +422,7 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
                     if (g >= a.gps) continue;
                     if constexpr (HAS_BUF) {
                         if (fresh) {                     // uniform over the workgroup
-                            copy_team_group<DT, BITS, TEAM, CPL, ODD>(a, src_s, m_s, g, cc, ua, ub);
+                            copy_team_group<DT, TEAM, CPL, ODD>(a, src_s, m_s, g, cc, ua, ub);
                             continue;
                         }
                     }
@@ -524,7 +532,7 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
 
 // The same for float32 in 16-byte units (see UnitLayout): one unit of four elements
 // per lane and access, UNITS of them per step, so consecutive lanes touch
-// consecutive 16 bytes of m, out and, b/2 bytes each, of the codes.
+// consecutive 16 bytes of m, out and, half of a chunk's bytes each, of the codes.
 constexpr int64_t kMaxUnitChunks = int64_t{1} << 30;     // unit indices of a sample fit 32 bits
 
 template <int BITS, int UNITS, bool HAS_BUF, int THREADS, bool LOOPS>
@@ -582,7 +590,7 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
                     if (dg * upg > x) --dg;
                     else if ((dg + 1) * upg <= x) ++dg;
                 }
-                w[u] = load_unit_codes<BITS>(codes_s + static_cast<uint64_t>(us[u]) * (BITS / 2));
+                w[u] = load_unit_codes<BITS>(codes_s, us[u]);
                 scale[u] = scales_s[g0 + dg];
                 if constexpr (HAS_BUF)
                     rm[u] = __builtin_nontemporal_load(
@@ -616,7 +624,7 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
 // and for with / without previous messages.
 template <int DT, int BITS, int UNROLL, int THREADS, bool LOOPS>
 __device__ __forceinline__ void dequant_job_bits(const DequantJob& a, uint32_t bx, uint32_t by) {
-    if constexpr (UnitLayout<DT, BITS>::value) {
+    if constexpr (UnitLayout<DT>::value) {
         if (a.cps <= kMaxUnitChunks) {                   // else the unit index would pass 32 bits
             if (a.m_buf) dequant_units_body<BITS, 2 * UNROLL, true, THREADS, LOOPS>(a, bx, by);
             else dequant_units_body<BITS, 2 * UNROLL, false, THREADS, LOOPS>(a, bx, by);

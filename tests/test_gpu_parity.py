@@ -68,6 +68,14 @@ def test_sweep_group_sizes_stochastic(H, dtype, bits):
         _sweep(H, dtype, bits, group, W.STOCHASTIC, gps)
 
 
+@pytest.mark.parametrize("group", [16, 32, 40, 96, 248, 504, 512, 1016, 1544, 4104, 4128, 32736, 32760])
+def test_sweep_three_bits_in_float32_units(H, group):
+    """Two units share a byte: groups of whole octets of units and not, at the edges of the team shapes."""
+    for rounding in (W.NEAREST, W.STOCHASTIC):
+        print(f"sweep f32 b3 G{group} r{rounding}", flush=True)
+        _sweep(H, "f32", 3, group, rounding, 37 if group <= 2048 else 3)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 def test_sweep_any_shape_fallback(H, dtype):
     for bits, groups in ODD_GROUPS.items():
