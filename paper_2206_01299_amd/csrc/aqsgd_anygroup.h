@@ -222,15 +222,20 @@ void dequant_odd_kernel(AQSGD_DEQUANT_ARGS) {
 // group is read once, in one launch, where the large groups' way takes three launches and two
 // readings.  All loads of a workgroup are back before its first store (the maximum waits for
 // them), so a group's last piece may repeat elements of the one before it: same values, same
-// results, same place.  Few groups are bound by one compute unit's arithmetic (about 10 us for an
-// encode of 49152 elements, however few groups; those are split, see below), many by memory.  Measured as four calls on
-// groups of 49152, large groups' way -> this: bfloat16, 8 groups 29.4 -> 19.2 us, 256 groups
-// 74 -> 48.5, 1024 groups 237 -> 182; float32, 8 groups 27.6 -> 26.0, 256 groups 117 -> 80,
-// 1024 groups 431 -> 326.
+// results, same place.  Few groups are bound by one compute unit's arithmetic (7 to 10 us for a
+// nearest encode of 49152 elements, 12 to 15 with stochastic rounding; those are split where it pays,
+// see below), many by memory.  Measured as four calls on groups of 49152, large groups' way -> this:
+// bfloat16, 256 groups 74 -> 48.5 us, 1024 groups 237 -> 182; float32, 256 groups 117 -> 80, 1024
+// groups 431 -> 326.
 // ---------------------------------------------------------------------------
 constexpr int kWideThreads = 1024;
 template <int DT> struct WideRounds { static constexpr int value = DT == AQSGD_F32 ? 12 : 8; };
 // Largest group: pieces of 16 bytes, one per lane and round.
+// Rounds of a group: pieces of 16 bytes (32 of binary32 at 3 bits), one per lane and round.
+constexpr int wide_rounds(int dtype, int bits, int group) {
+    const int piece = dtype == AQSGD_F32 && bits != 3 ? 4 : 8;
+    return ((group + piece - 1) / piece + kWideThreads - 1) / kWideThreads;
+}
 constexpr int wide_most_elements(int dtype) {
     return dtype == AQSGD_F32 ? kWideThreads * 4 * WideRounds<AQSGD_F32>::value
                               : kWideThreads * 8 * WideRounds<AQSGD_F16>::value;
@@ -257,9 +262,34 @@ __device__ __forceinline__ void piece_values(const PieceRaw<DT, N>& r, float (&f
     }
 }
 
-// One group in a workgroup: bx is the group of the sample, by the sample.
+// The change of a piece, in binary32; without previous messages the values themselves.  float16
+// operands are widened by the subtraction (see delta_chunk): one encode of eight groups of 49152 8.4 us
+// with conversions of their own and 7.9 so.
+template <int DT, int N, bool HAS_BUF>
+__device__ __forceinline__ void piece_change(const PieceRaw<DT, N>& a, const PieceRaw<DT, N>& m, float (&d)[N]) {
+    if constexpr (HAS_BUF && DT == AQSGD_F16) {
+        delta_chunk<DT>(Raw<DT>{a.v[0]}, Raw<DT>{m.v[0]}, d);
+    } else {
+        piece_values<DT, N>(a, d);
+        if constexpr (HAS_BUF) {
+            float mv[N];
+            piece_values<DT, N>(m, mv);
+#pragma unroll
+            for (int e = 0; e < N; ++e) d[e] = d[e] - mv[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < N; ++e) d[e] = d[e] - 0.0f;
+        }
+    }
+}
+
+// One group in a workgroup: bx is the group of the sample, by the sample.  Without previous messages
+// nothing that a workgroup reads is written in the launch, so several can share a group: each takes
+// the maximum of all of it and quantises `share` rounds from share * part on (few groups leave most
+// compute units idle, and the levels are two thirds of the arithmetic; see wide_parts()).
 template <int DT, int BITS, int ROUND, bool HAS_BUF>
-__device__ __forceinline__ void quant_wide_body(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
+__device__ __forceinline__ void quant_wide_body(const QuantJob& a, uint32_t bx, uint32_t by, uint32_t part, int share,
+                                                float* wave_max) {
     using P = Piece<DT, BITS>;
     constexpr int N = P::elems;
     constexpr int kEB = ElemBytes<DT>::value;
@@ -315,11 +345,10 @@ __device__ __forceinline__ void quant_wide_body(const QuantJob& a, uint32_t bx, 
 #pragma unroll
     for (int k = 0; k < kRounds; ++k)
         if (k < rounds) {
-            float x[N], m[N];
-            piece_values<DT, N>(ra[k], x);
-            if constexpr (HAS_BUF) piece_values<DT, N>(rm[k], m);
+            float d[N];
+            piece_change<DT, N, HAS_BUF>(ra[k], rm[k], d);
 #pragma unroll
-            for (int e = 0; e < N; ++e) mx = __builtin_fmaxf(mx, __builtin_fabsf(HAS_BUF ? x[e] - m[e] : x[e] - 0.0f));
+            for (int e = 0; e < N; ++e) mx = __builtin_fmaxf(mx, __builtin_fabsf(d[e]));
 #pragma unroll
             for (int w = 0; w < N * kEB / 16; ++w) asm volatile("" : "+v"(ra[k].v[w]));  // the change is formed again, not kept
         }
@@ -329,10 +358,11 @@ __device__ __forceinline__ void quant_wide_body(const QuantJob& a, uint32_t bx, 
 #pragma unroll
     for (int w = 0; w < kWideThreads / kWave; ++w) mx = __builtin_fmaxf(mx, wave_max[w]);
     const GroupScale sc = make_scale<BITS>(mx);
+    const int first = HAS_BUF ? 0 : static_cast<int>(part) * share, end = HAS_BUF ? rounds : min(first + share, rounds);
 #pragma unroll
     for (int k = 0; k < kRounds; ++k)
-        if (k < rounds) {
-            float x[N], m[N], r[N], q[N], v[N];
+        if (k >= first && k < end) {                     // uniform over the workgroup
+            float d[N], r[N], q[N], v[N];
             const uint32_t at = place(k);
             if constexpr (ROUND == AQSGD_ROUND_STOCHASTIC) {
                 if (a.group % 4 != 0) {                  // uniform over the launch
@@ -345,35 +375,43 @@ __device__ __forceinline__ void quant_wide_body(const QuantJob& a, uint32_t bx, 
 #pragma unroll
                 for (int e = 0; e < N; ++e) r[e] = kNearestOffset32;
             }
-            piece_values<DT, N>(ra[k], x);
-            if constexpr (HAS_BUF) piece_values<DT, N>(rm[k], m);
+            piece_change<DT, N, HAS_BUF>(ra[k], rm[k], d);
 #pragma unroll
             for (int e = 0; e < N; ++e) {
-                q[e] = level_of<BITS, ROUND>(HAS_BUF ? x[e] - m[e] : x[e] - 0.0f, sc, r[e]);
+                q[e] = level_of<BITS, ROUND>(d[e], sc, r[e]);
                 v[e] = value_of(q[e], sc);
-                if constexpr (HAS_BUF) v[e] = m[e] + v[e];
             }
             store_bytes_any<P::code_bytes>(codes_g + at * BITS / 8, pack_piece<BITS, N>(q));
-            if constexpr (HAS_BUF) store_piece<DT, N>(m_g + at * kEB, v);
+            if constexpr (HAS_BUF && DT == AQSGD_F16) {
+                store16(m_g + at * kEB, updated_chunk<DT>(Raw<DT>{rm[k].v[0]}, v).v, false);
+            } else if constexpr (HAS_BUF) {
+                float m[N];
+                piece_values<DT, N>(rm[k], m);
+#pragma unroll
+                for (int e = 0; e < N; ++e) v[e] = m[e] + v[e];
+                store_piece<DT, N>(m_g + at * kEB, v);
+            }
             __builtin_amdgcn_sched_barrier(0);           // one piece's temporaries at a time
         }
-    if (lane == 0) a.scales[static_cast<int64_t>(i) * a.gps + g] = sc.s_tx;
+    if (lane == 0 && (HAS_BUF || part == 0)) a.scales[static_cast<int64_t>(i) * a.gps + g] = sc.s_tx;
 }
 
 template <int DT, int BITS, int ROUND>
-__device__ __forceinline__ void quant_wide_bits(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
-    if (a.m_buf) quant_wide_body<DT, BITS, ROUND, true>(a, bx, by, wave_max);
-    else quant_wide_body<DT, BITS, ROUND, false>(a, bx, by, wave_max);
+__device__ __forceinline__ void quant_wide_bits(const QuantJob& a, uint32_t bx, uint32_t by, uint32_t part, int share,
+                                                float* wave_max) {
+    if (a.m_buf) quant_wide_body<DT, BITS, ROUND, true>(a, bx, by, part, share, wave_max);
+    else quant_wide_body<DT, BITS, ROUND, false>(a, bx, by, part, share, wave_max);
 }
 
 template <int DT, int ROUND>
-__device__ __forceinline__ void quant_wide_job(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
+__device__ __forceinline__ void quant_wide_job(const QuantJob& a, uint32_t bx, uint32_t by, uint32_t part, int share,
+                                               float* wave_max) {
     switch (a.bits) {                                    // uniform over the workgroup
-    case 2: quant_wide_bits<DT, 2, ROUND>(a, bx, by, wave_max); break;
-    case 3: quant_wide_bits<DT, 3, ROUND>(a, bx, by, wave_max); break;
-    case 4: quant_wide_bits<DT, 4, ROUND>(a, bx, by, wave_max); break;
-    case 6: quant_wide_bits<DT, 6, ROUND>(a, bx, by, wave_max); break;
-    default: quant_wide_bits<DT, 8, ROUND>(a, bx, by, wave_max); break;
+    case 2: quant_wide_bits<DT, 2, ROUND>(a, bx, by, part, share, wave_max); break;
+    case 3: quant_wide_bits<DT, 3, ROUND>(a, bx, by, part, share, wave_max); break;
+    case 4: quant_wide_bits<DT, 4, ROUND>(a, bx, by, part, share, wave_max); break;
+    case 6: quant_wide_bits<DT, 6, ROUND>(a, bx, by, part, share, wave_max); break;
+    default: quant_wide_bits<DT, 8, ROUND>(a, bx, by, part, share, wave_max); break;
     }
 }
 
@@ -385,9 +423,9 @@ void quant_wide_kernel(AQSGD_QUANT_ARGS) {
     a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
     a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group;
     a.grid_x = grid_x; a.grid_y = grid_y;
-    a.bits = bits;
+    a.bits = bits & 255;
     a.seed = seed; a.seen = seen; a.first = first; a.stamp = stamp;
-    quant_wide_job<DT, ROUND>(a, blockIdx.x, blockIdx.y, wave_max);
+    quant_wide_job<DT, ROUND>(a, blockIdx.x, blockIdx.y, blockIdx.z, bits >> 8, wave_max);
 }
 
 // ---------------------------------------------------------------------------
@@ -706,7 +744,8 @@ void split_quant_kernel(AQSGD_QUANT_ARGS, int32_t spans, int32_t span_pieces) {
 
 // Per-dtype pieces (defined by AQSGD_INSTANTIATE_ANYGROUP_DTYPE in the dtype's .hip file).
 template <int DT> hipError_t launch_dequant_odd_dt(bool covers, const DequantJob& a, hipStream_t stream);
-template <int DT> hipError_t launch_quant_wide_dt(int rounding, const QuantJob& a, hipStream_t stream);
+// `parts` workgroups a group, `share` rounds each (1 and all rounds with previous messages).
+template <int DT> hipError_t launch_quant_wide_dt(int rounding, int parts, int share, const QuantJob& a, hipStream_t stream);
 template <int DT> hipError_t launch_quant_large_dt(int rounding, const QuantJob& a, const LargeGeom& geom,
                                                    hipStream_t stream);
 template <int DT> hipError_t launch_quant_split_dt(int rounding, const QuantJob& a, const LargeGeom& geom,
@@ -720,10 +759,14 @@ hipError_t launch_dequant_odd_dt(bool covers, const DequantJob& a, hipStream_t s
 }
 
 template <int DT>
-hipError_t launch_quant_wide_dt(int rounding, const QuantJob& a, hipStream_t s) {
-    return rounding == AQSGD_ROUND_STOCHASTIC
-               ? launch_quant_with(quant_wide_kernel<DT, AQSGD_ROUND_STOCHASTIC>, dim3(kWideThreads), a, s)
-               : launch_quant_with(quant_wide_kernel<DT, AQSGD_ROUND_NEAREST>, dim3(kWideThreads), a, s);
+hipError_t launch_quant_wide_dt(int rounding, int parts, int share, const QuantJob& a, hipStream_t s) {
+    auto go = [&](auto kernel) {
+        return launch_kernel(kernel, dim3(a.grid_x, a.grid_y, parts), dim3(kWideThreads), s, a.src, a.ids, a.m_buf, a.codes,
+                             a.scales, a.group, a.bits | (share << 8), a.n_per, a.gps, a.batch, a.grid_x, a.grid_y,
+                             a.stamp, a.seed, a.seen, a.first);
+    };
+    return rounding == AQSGD_ROUND_STOCHASTIC ? go(quant_wide_kernel<DT, AQSGD_ROUND_STOCHASTIC>)
+                                              : go(quant_wide_kernel<DT, AQSGD_ROUND_NEAREST>);
 }
 
 template <int DT>
@@ -758,7 +801,7 @@ hipError_t launch_quant_split_dt(int rounding, const QuantJob& a, const LargeGeo
 
 #define AQSGD_INSTANTIATE_ANYGROUP_DTYPE(DT)                                                          \
     template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);                   \
-    template hipError_t launch_quant_wide_dt<DT>(int, const QuantJob&, hipStream_t);                       \
+    template hipError_t launch_quant_wide_dt<DT>(int, int, int, const QuantJob&, hipStream_t);             \
     template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t);   \
     template hipError_t launch_quant_split_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t);
 

@@ -20,7 +20,7 @@ namespace aqsgd {
     extern template hipError_t launch_quant_single_dt<DT>(int, int, bool, const QuantJob&, hipStream_t); \
     extern template hipError_t launch_dequant_single_dt<DT>(int, const DequantJob&, hipStream_t);     \
     extern template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);       \
-    extern template hipError_t launch_quant_wide_dt<DT>(int, const QuantJob&, hipStream_t);           \
+    extern template hipError_t launch_quant_wide_dt<DT>(int, int, int, const QuantJob&, hipStream_t); \
     extern template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
     extern template hipError_t launch_quant_split_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
     extern template hipError_t launch_odd_jobs_dt<DT>(int, int, const JobTable&, hipStream_t);        \
@@ -91,11 +91,11 @@ hipError_t launch_dequant_odd(int dtype, bool covers, const DequantJob& a, hipSt
     default:         return hipErrorInvalidValue;
     }
 }
-hipError_t launch_quant_wide(int dtype, int rounding, const QuantJob& a, hipStream_t s) {
+hipError_t launch_quant_wide(int dtype, int rounding, int parts, int share, const QuantJob& a, hipStream_t s) {
     switch (dtype) {
-    case AQSGD_F32:  return launch_quant_wide_dt<AQSGD_F32>(rounding, a, s);
-    case AQSGD_F16:  return launch_quant_wide_dt<AQSGD_F16>(rounding, a, s);
-    case AQSGD_BF16: return launch_quant_wide_dt<AQSGD_BF16>(rounding, a, s);
+    case AQSGD_F32:  return launch_quant_wide_dt<AQSGD_F32>(rounding, parts, share, a, s);
+    case AQSGD_F16:  return launch_quant_wide_dt<AQSGD_F16>(rounding, parts, share, a, s);
+    case AQSGD_BF16: return launch_quant_wide_dt<AQSGD_BF16>(rounding, parts, share, a, s);
     default:         return hipErrorInvalidValue;
     }
 }
@@ -414,29 +414,27 @@ LargeGeom large_geometry(const QuantJob& a) {
     return g;
 }
 
-// Few wide groups go out as spans (see split_max_kernel) where one compute unit's arithmetic on a
-// group lasts longer than a second launch: with stochastic rounding, and in float32 with previous
-// messages, up to the number of groups from which one workgroup each is as fast.  One call on the
-// device, 8-bit, one workgroup each -> spans, in us:
-//   stochastic           8 groups                64 groups               96 groups
-//     encode     f32     32776  16.1 ->  9.6     17.4 -> 13.4            18.7 -> 17.8
-//                        49152  19.1 ->  8.8     20.1 -> 13.1            20.6 -> 20.1
-//                bf16    32776  12.7 ->  9.0     13.3 -> 12.0            13.6 -> 13.8
-//                        65536  18.1 ->  8.5     18.8 -> 13.0            19.7 -> 16.9
-//     grad_quant f32     32776   8.8 ->  7.3      9.7 ->  9.2             9.2 -> 11.2
-//                        49152  10.7 ->  7.2     11.1 ->  9.3            12.8 -> 12.4
-//                bf16    32776   8.8 ->  6.8      9.0 ->  8.9             9.3 -> 10.2
-//                        65536  12.3 ->  6.8     12.8 -> 10.2            13.2 -> 13.0
-// so 64 is the last size at which every one gains.  Nearest encode in float32, which has less
-// arithmetic to spread: 8 groups of 32776 14.1 -> 9.1, of 49152 15.2 -> 8.2; 32 groups 14.8 -> 10.3
-// and 15.5 -> 9.7; 96 groups 16.5 -> 17.4 and 17.0 -> 19.0.  It stops at 32: in a row of single calls
-// the second launch is host time too (four calls, 32 groups of 49152 31.1 -> 27.3 us, 64 groups
-// 36.8 -> 35.9).  For the same reason nearest rounding of 16-bit types stays with one workgroup (8
-// groups of 49152, encode alone 10.1 -> 7.6, four calls 19.2 -> 18.0 to 21.7 with how fast the host
-// issues the fifth launch), and nearest grad_quant gains nothing (6.0 -> 6.5).
-bool split_pays(int64_t groups, bool has_buf, int dtype, int rounding) {
-    return rounding == AQSGD_ROUND_STOCHASTIC ? groups <= 64
-                                              : dtype == AQSGD_F32 && has_buf && groups <= 32;
+// Few wide groups with previous messages go out as spans (see split_max_kernel) where one compute
+// unit's arithmetic on a group lasts longer than a second launch, up to the number of groups from
+// which one workgroup each is as fast.  (Without previous messages the workgroups of one launch
+// share a group: wide_share().)  One encode on the device, 8-bit, one workgroup each -> spans, in us:
+//                        8 groups          32 groups         64 groups         96 groups
+//   stochastic  float32   33024  12.7 ->  7.7  13.6 -> 10.2  14.5 -> 14.2  15.8 -> 17.8
+//                         49152  15.2 ->  6.9  17.5 -> 10.7  19.1 -> 15.6  20.1 -> 21.9
+//               bfloat16  33024  11.0 ->  7.3  11.8 ->  8.9  12.5 -> 10.6  13.1 -> 13.4
+//                         65536  14.9 ->  6.7  17.8 ->  9.5  19.0 -> 13.5  21.2 -> 17.7
+//   nearest     float32   33024   8.2 ->  7.2   9.9 ->  9.8  10.5 -> 13.6
+//                         49152  10.5 ->  6.6  12.4 -> 10.2  14.1 -> 14.9
+//               bfloat16  49152   7.4 ->  6.1   9.7 ->  8.4  10.6 -> 10.6
+//                         65536   8.8 ->  6.3  11.8 ->  8.8  13.0 -> 12.4
+// so 64 is the last size at which every stochastic one gains.  Nearest rounding has less to spread,
+// and in a row of single calls the second launch is host time too (2.3 us): float32 stops at 32, and
+// 16-bit types gain enough only in groups larger than 49152.
+bool split_pays(const QuantJob& a, int dtype, int rounding) {
+    const int64_t groups = a.gps * a.batch;
+    if (a.m_buf == nullptr) return false;
+    if (rounding == AQSGD_ROUND_STOCHASTIC) return groups <= 64;
+    return groups <= 32 && (dtype == AQSGD_F32 || a.group > 49152);
 }
 
 // The same for the wide groups of a shared launch (`groups` in all, activations among them: has_buf),
@@ -472,6 +470,21 @@ bool one_step_grid(Job& a, int64_t units, int64_t units_per_block, int64_t cap) 
 // samples 26.6 -> 28.9).
 bool many_short_samples(const DequantJob& a) { return a.cps <= kBlock && a.batch >= 1024; }
 
+// Rounds of a wide group that a workgroup quantises: all of them with previous messages, which it
+// updates in place; without, as few as keep the launch at one workgroup for each of the 256 compute
+// units, as long as every workgroup reading a whole group costs less than the levels it saves.  One
+// grad_quant, all rounds -> shared, in us: bfloat16 8 groups of 49152 4.99 -> 4.03, stochastic 6.21
+// -> 4.70 (as spans in two launches 5.62), 64 groups of 40960 6.0 -> 5.3 and 9.1 -> 6.7; float16 100 groups
+// of 65536 8.2 -> 8.4; float32 16 groups of 33024 5.64 -> 5.42, 70 groups of 49152 8.3 -> 9.8.
+int wide_share(const QuantJob& a, int dtype, int rounding, int64_t max_blocks) {
+    const int rounds = wide_rounds(dtype, a.bits, a.group);
+    const int64_t groups = a.gps * a.batch, room = max_blocks < 256 ? max_blocks : 256;
+    const bool pays = groups <= (dtype == AQSGD_F32 && rounding == AQSGD_ROUND_NEAREST ? 32 : 64);
+    if (a.m_buf != nullptr || !pays || room < 2 * groups) return rounds;
+    const int64_t parts = room / groups;
+    return static_cast<int>((rounds + parts - 1) / parts);
+}
+
 // A quantising message outside the job kernels' range.
 hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_blocks, hipStream_t stream) {
     QuantJob& a = p.job;
@@ -483,12 +496,16 @@ hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_b
         return launch_quant_single(p.dtype, p.rounding, p.shape, covers, a, stream);
     }
     case Route::kWide:
-        if (split_pays(a.gps * a.batch, a.m_buf != nullptr, p.dtype, p.rounding)) {
+        if (split_pays(a, p.dtype, p.rounding)) {
             const LargeGeom sg = split_geometry(a);
             if (one_step_grid(a, a.gps * sg.spans, 1, max_blocks))
                 return launch_quant_split(p.dtype, p.rounding, a, sg, stream);
         }
-        if (one_step_grid(a, a.gps, 1, max_blocks)) return launch_quant_wide(p.dtype, p.rounding, a, stream);
+        if (one_step_grid(a, a.gps, 1, max_blocks)) {
+            const int rounds = wide_rounds(p.dtype, a.bits, a.group);
+            const int share = wide_share(a, p.dtype, p.rounding, max_blocks);
+            return launch_quant_wide(p.dtype, p.rounding, (rounds + share - 1) / share, share, a, stream);
+        }
         [[fallthrough]];                                 // too many for a grid: the kernels that loop
     case Route::kLarge: {
         const LargeGeom lg = large_geometry(a);
@@ -607,7 +624,7 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
             covers = number_blocks(t, -1, groups_per_block_step(lead.shape),
                                    static_cast<int64_t>(threads_of_shape(lead.shape)) * kOddUnroll, max_blocks, 0, units);
             if (covers) err = launch_odd_jobs(lead.dtype, lead.rounding, lead.shape, t, stream);
-        } else if (covers && (split_pays(groups, has_buf, lead.dtype, lead.rounding))) {
+        } else if (covers && split_pays_shared(groups, has_buf, lead.dtype, lead.rounding)) {
             struct {
                 int64_t operator()(const QuantJob& a) const { return a.gps * split_geometry(a).spans; }
                 int64_t operator()(const DequantJob& a) const { return a.cps; }

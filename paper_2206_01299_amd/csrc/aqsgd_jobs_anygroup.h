@@ -72,7 +72,7 @@ __global__ __launch_bounds__(kWideThreads)
 void wide_jobs_kernel(const JobTable t) {
     __shared__ float wave_max[kWideThreads / kWave];
     run_table_job(t,
-        [&](const QuantJob& a, uint32_t bx, uint32_t by) AQSGD_INLINE { quant_wide_job<DT, ROUND>(a, bx, by, wave_max); },
+        [&](const QuantJob& a, uint32_t bx, uint32_t by) AQSGD_INLINE { quant_wide_job<DT, ROUND>(a, bx, by, 0, 1 << 20, wave_max); },
         [&](const DequantJob& a, uint32_t bx, uint32_t by) AQSGD_INLINE {
             dequant_job<DT, kHostedDequantUnroll, kWideThreads, false>(a, bx, by);
         });

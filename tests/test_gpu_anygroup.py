@@ -81,6 +81,17 @@ def test_wide_groups_few_and_many(H, dtype, bits, group, gps):
         _sweep(H, dtype, bits, group, rounding, n, batch=2)
 
 
+@pytest.mark.parametrize("dtype,bits,group", [("bf16", 8, 49152), ("f16", 4, 32776), ("f16", 6, 65536), ("f32", 3, 49152),
+                                              ("f32", 8, 36868), ("bf16", 4, 57354)])
+def test_wide_groups_shared_by_workgroups(H, dtype, bits, group):
+    """grad_quant of few wide groups: as many workgroups a group as keep the launch at one a compute unit,
+    shares that are and are not whole divisors of the rounds, and counts around where sharing stops."""
+    for rounding in (W.NEAREST, W.STOCHASTIC):
+        for groups in (1, 2, 32, 33, 64, 65):
+            print(f"shared {dtype} b{bits} G{group} r{rounding} x{groups}", flush=True)
+            _sweep(H, dtype, bits, group, rounding, groups, batch=1)
+
+
 def test_large_groups_without_a_change_send_scale_zero(H):
     """Groups whose maximum is zero or below the 2^-120 floor next to one that is not."""
     import oracle
