@@ -159,8 +159,10 @@ int aqsgd_grad_dequant(const aqsgd_desc* desc, const uint8_t* codes, const float
  * How jobs share launches: quantising jobs (ENCODE, GRAD_QUANT) with the same dtype,
  * rounding and group-size class share one grid whatever their bit widths, and the
  * dequantising jobs of that dtype join it; dequantising jobs without such a host share a grid of their own; up to
- * 8 + 8 jobs per grid, more are split; jobs whose group is not a multiple of 8 or larger
- * than 32768 run on their own.  The typical stage-side call (one ENCODE and one
+ * 8 + 8 jobs per grid, more are split.  Jobs whose group is not a multiple of 8, or larger than
+ * 32768, share grids of their own kind in the same way (few groups of more than 32768 elements as
+ * two launches for all of them); groups of 1 to 7 elements, and those beyond a workgroup (65536, in
+ * float32 49152), run on their own.  The typical stage-side call (one ENCODE and one
  * GRAD_DEQUANT, or one DECODE and one GRAD_QUANT) is one launch.
  * Every job is checked first; on an error (the first bad job's status, or
  * AQSGD_ERR_SHAPE for an unknown kind or a negative count) nothing is enqueued.

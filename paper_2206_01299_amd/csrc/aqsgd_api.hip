@@ -3,6 +3,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <limits>
+#include <type_traits>
 #include <vector>
 
 #include "aqsgd_anygroup.h"
@@ -540,49 +541,82 @@ hipError_t launch_dequant_alone(DequantPlan& p, int64_t max_blocks, hipStream_t 
 // and more, equal within 2 % and better with another stream beside it.
 constexpr int64_t kThroughBytes = int64_t{24} << 20;
 
+int64_t bytes_written(const QuantJob& a, int64_t eb) {
+    return a.batch * a.n_per * (a.m_buf ? 8 * eb + a.bits : a.bits) / 8;
+}
+int64_t bytes_written(const DequantJob& a, int64_t eb) { return a.batch * a.n_per * eb * (a.m_buf ? 2 : 1); }
+constexpr int64_t kLineBytes = 128;
+uint32_t whole_lines(const QuantJob& a, int64_t eb) {
+    return a.n_per * eb % kLineBytes == 0 && a.group * eb % kLineBytes == 0;
+}
+uint32_t whole_lines(const DequantJob& a, int64_t eb) { return a.n_per * eb % kLineBytes == 0; }
+
+// A reconstruction alone (measured in a row of four calls, through -> streaming: float32 [8,2048,4096]
+// 362 -> 366 us, bfloat16 [32,256,1536] 46.3 -> 46.8, first visits of float16 [4,1024,1600], 26 MB written,
+// 17.4 -> 17.7).
+void choose_stores(DequantJob& a, int dtype) {
+    const int64_t eb = dtype == AQSGD_F32 ? 4 : 2;
+    if (bytes_written(a, eb) >= kThroughBytes) a.through = whole_lines(a, eb);
+}
+
 void choose_stores(JobTable& t, int dtype) {
-    const int64_t eb = dtype == AQSGD_F32 ? 4 : 2, line = 128;
+    const int64_t eb = dtype == AQSGD_F32 ? 4 : 2;
     int64_t bytes = 0;
-    for (int k = 0; k < t.n_quant; ++k)
-        bytes += t.q[k].batch * t.q[k].n_per * (t.q[k].m_buf ? 8 * eb + t.q[k].bits : t.q[k].bits) / 8;
-    for (int k = 0; k < t.n_dequant; ++k) bytes += t.d[k].batch * t.d[k].n_per * eb * (t.d[k].m_buf ? 2 : 1);
+    for (int k = 0; k < t.n_quant; ++k) bytes += bytes_written(t.q[k], eb);
+    for (int k = 0; k < t.n_dequant; ++k) bytes += bytes_written(t.d[k], eb);
     if (bytes < kThroughBytes) return;
-    for (int k = 0; k < t.n_quant; ++k)
-        t.q[k].through = t.q[k].n_per * eb % line == 0 && t.q[k].group * eb % line == 0;
-    for (int k = 0; k < t.n_dequant; ++k) t.d[k].through = t.d[k].n_per * eb % line == 0;
+    for (int k = 0; k < t.n_quant; ++k) t.q[k].through = whole_lines(t.q[k], eb);
+    for (int k = 0; k < t.n_dequant; ++k) t.d[k].through = whole_lines(t.d[k], eb);
+}
+
+// A message that comes alone.  Without lists: a small message's call is over on the device in 2 to 3 us,
+// and the host's share of a call is what a row of them waits for.  The single-message kernels open
+// sooner (see aqsgd_single.h); their workgroups do one step each, so a message that would pass the
+// caps on a grid, or one in a sweep of launch sizes, goes out as a table of one instead (`false`).
+bool launch_alone(QuantPlan& q, int64_t max_blocks, int64_t launch_blocks, hipStream_t stream, hipError_t& err) {
+    if (q.route != Route::kJob) {
+        err = launch_quant_alone(q, max_blocks, launch_blocks, stream);
+        return true;
+    }
+    if (launch_blocks != 0 || !one_step_grid(q.job, q.job.gps, groups_per_block_step(q.shape), max_blocks)) return false;
+    err = launch_quant_single(q.dtype, q.rounding, q.shape, true, q.job, stream);
+    return true;
+}
+
+bool launch_alone(DequantPlan& d, int64_t max_blocks, int64_t launch_blocks, hipStream_t stream, hipError_t& err) {
+    if (d.route != Route::kJob) {
+        err = launch_dequant_alone(d, max_blocks, stream);
+        return true;
+    }
+    const int chunks = many_short_samples(d.job) ? 1 : dequant_unroll_knob().load(std::memory_order_relaxed);
+    if (launch_blocks != 0 || !one_step_grid(d.job, d.job.cps, static_cast<int64_t>(kBlock) * chunks, max_blocks)) return false;
+    choose_stores(d.job, d.dtype);
+    err = launch_dequant_single(d.dtype, chunks, d.job, stream);
+    return true;
+}
+
+// A job's workgroup numbers must be exact in binary32 (place_in_job).
+int64_t blocks_cap() {
+    const int64_t knob = max_blocks_knob().load(std::memory_order_relaxed);
+    return knob < (int64_t{1} << 24) ? knob : (int64_t{1} << 24) - 1;
 }
 
 // The launches of a set of independent messages: quantising jobs that share dtype,
 // rounding mode and team shape go into one grid, together with the dequantising
-// jobs of that dtype that are still waiting; dequantising jobs without such a host get a
-// grid of their own; jobs outside the shared launches' range are launched one by one, and so
-// is a message that comes alone (its kernel opens sooner, see aqsgd_single.h).
+// jobs of that dtype that are still waiting; odd and wide groups likewise among themselves;
+// dequantising jobs without such a host get a grid of their own; what is left (groups of 1 to 7
+// elements, those beyond a workgroup, odd reconstructions without a host) is launched one by one.
 int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipStream_t stream) {
-    // a job's workgroup numbers must be exact in binary32 (place_in_job)
-    const int64_t knob = max_blocks_knob().load(std::memory_order_relaxed);
-    const int64_t max_blocks = knob < (int64_t{1} << 24) ? knob : (int64_t{1} << 24) - 1;
+    const int64_t max_blocks = blocks_cap();
     const int unroll = dequant_unroll_knob().load(std::memory_order_relaxed);
     std::vector<bool> q_done(qs.size(), false), d_done(ds.size(), false);
     hipError_t err = hipSuccess;
 
     const int64_t launch_blocks = launch_blocks_knob().load(std::memory_order_relaxed);
-    // A message that comes alone takes the single-message kernels, which open sooner (see
-    // aqsgd_single.h); their workgroups do one step each, so one that would pass the caps on a
-    // grid (or one asked for in a sweep) goes out as a table of one instead.
-    if (qs.size() + ds.size() == 1 && launch_blocks == 0) {
-        if (!qs.empty() && qs[0].route == Route::kJob &&
-            one_step_grid(qs[0].job, qs[0].job.gps, groups_per_block_step(qs[0].shape), max_blocks)) {
-            err = launch_quant_single(qs[0].dtype, qs[0].rounding, qs[0].shape, true, qs[0].job, stream);
-            return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
-        }
-        if (!ds.empty() && ds[0].route == Route::kJob) {
-            const int chunks = many_short_samples(ds[0].job) ? 1 : unroll;
-            if (one_step_grid(ds[0].job, ds[0].job.cps, static_cast<int64_t>(kBlock) * chunks, max_blocks)) {
-                err = launch_dequant_single(ds[0].dtype, chunks, ds[0].job, stream);
-                return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
-            }
-        }
-    }
+    if (qs.size() + ds.size() == 1 &&
+        (qs.empty() ? launch_alone(ds[0], max_blocks, launch_blocks, stream, err)
+                    : launch_alone(qs[0], max_blocks, launch_blocks, stream, err)))
+        return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
     const auto whole = [](const auto& a) { return whole_units(a); };
     auto add_dequant = [&](JobTable& t, int dtype, Route route) {
         for (size_t k = 0; k < ds.size() && t.n_dequant < kMaxDequantJobs; ++k) {
@@ -701,18 +735,16 @@ int without_exceptions(F&& f) {
     }
 }
 
-int launch_one(const QuantPlan& q, hipStream_t stream) {
-    return without_exceptions([&] {
-        std::vector<QuantPlan> qs(1, q);
-        std::vector<DequantPlan> ds;
-        return launch_plans(qs, ds, stream);
-    });
-}
-
-int launch_one(const DequantPlan& d, hipStream_t stream) {
+template <typename Plan>
+int launch_one(Plan p, hipStream_t stream) {
+    hipError_t err = hipSuccess;
+    if (launch_alone(p, blocks_cap(), launch_blocks_knob().load(std::memory_order_relaxed), stream, err))
+        return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
     return without_exceptions([&] {
         std::vector<QuantPlan> qs;
-        std::vector<DequantPlan> ds(1, d);
+        std::vector<DequantPlan> ds;
+        if constexpr (std::is_same_v<Plan, QuantPlan>) qs.push_back(p);
+        else ds.push_back(p);
         return launch_plans(qs, ds, stream);
     });
 }

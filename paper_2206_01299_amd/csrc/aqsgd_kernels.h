@@ -464,10 +464,21 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
                 if (fresh && bx == 0 && threadIdx.x == 0) a.seen[row] = a.stamp;       // one writer per sample
                 if (fresh) {             // first visit: the uncompressed row is the message
                     const char* full_s = static_cast<const char*>(a.full) + out0 * kEB;
-                    for (uint32_t c = bx * THREADS + threadIdx.x; c < cps; c += a.grid_x * THREADS) {
-                        const Raw<DT> v = load_raw_at<DT>(full_s + static_cast<uint64_t>(c) * kChunkBytes);
-                        store_raw_at<DT>(m_s + static_cast<uint64_t>(c) * kChunkBytes, v, a.through != 0);
-                        store_raw_at<DT>(out_s + static_cast<uint64_t>(c) * kChunkBytes, v, a.through != 0);
+                    for (uint32_t cbase = bx * kStep; cbase < cps; cbase += a.grid_x * kStep) {
+                        Raw<DT> v[UNROLL];               // all loads first, as below
+#pragma unroll
+                        for (int u = 0; u < UNROLL; ++u) {
+                            const uint32_t c = min(cbase + u * THREADS + threadIdx.x, cps - 1);
+                            v[u] = load_raw_at<DT>(full_s + static_cast<uint64_t>(c) * kChunkBytes);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int u = 0; u < UNROLL; ++u) {
+                            const uint32_t c = cbase + u * THREADS + threadIdx.x;
+                            if (c >= cps) continue;
+                            store_raw_at<DT>(m_s + static_cast<uint64_t>(c) * kChunkBytes, v[u], a.through != 0);
+                            store_raw_at<DT>(out_s + static_cast<uint64_t>(c) * kChunkBytes, v[u], a.through != 0);
+                        }
                     }
                     if constexpr (!LOOPS) return;
                     else continue;
@@ -556,11 +567,22 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
                 if (fresh && bx == 0 && threadIdx.x == 0) a.seen[row] = a.stamp;       // one writer per sample
                 if (fresh) {             // first visit: the uncompressed row is the message
                     const char* full_s = static_cast<const char*>(a.full) + out0 * 4;
-                    for (uint32_t u = bx * THREADS + threadIdx.x; u < ups; u += a.grid_x * THREADS) {
-                        const f32x4_t v = __builtin_nontemporal_load(
-                            reinterpret_cast<const f32x4_t*>(full_s + static_cast<uint64_t>(u) * kUnitBytes));
-                        store16(m_s + static_cast<uint64_t>(u) * kUnitBytes, v, a.through != 0);
-                        store16(out_s + static_cast<uint64_t>(u) * kUnitBytes, v, a.through != 0);
+                    for (uint32_t ubase = bx * kStep; ubase < ups; ubase += a.grid_x * kStep) {
+                        f32x4_t v[UNITS];                // all loads first, as below
+#pragma unroll
+                        for (int u = 0; u < UNITS; ++u) {
+                            const uint32_t unit = min(ubase + u * THREADS + threadIdx.x, ups - 1);
+                            v[u] = __builtin_nontemporal_load(
+                                reinterpret_cast<const f32x4_t*>(full_s + static_cast<uint64_t>(unit) * kUnitBytes));
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int u = 0; u < UNITS; ++u) {
+                            const uint32_t unit = ubase + u * THREADS + threadIdx.x;
+                            if (unit >= ups) continue;
+                            store16(m_s + static_cast<uint64_t>(unit) * kUnitBytes, v[u], a.through != 0);
+                            store16(out_s + static_cast<uint64_t>(unit) * kUnitBytes, v[u], a.through != 0);
+                        }
                     }
                     if constexpr (!LOOPS) return;
                     else continue;

@@ -70,14 +70,18 @@ void quant_single_kernel(AQSGD_QUANT_ARGS) {
     }
 }
 
-template <int DT, int UNROLL>
+// THROUGH: how m and out are stored (see store16).  A constant in these kernels, not a field of the job as
+// in the shared launches: a branch at every store costs a message of this size 1 to 2 % (first visits
+// of float16 [4,1024,1600] 17.6 -> 18.0 us).  Large reconstructions write through, the quantising
+// side, which stores half as much, always streams.
+template <int DT, int UNROLL, bool THROUGH>
 __global__ __launch_bounds__(kBlock)
 void dequant_single_kernel(AQSGD_DEQUANT_ARGS) {
     DequantJob a;
     a.codes = codes; a.scales = scales; a.ids = ids; a.m_buf = m_buf; a.out = out; a.full = full;
     a.n_per = n_per; a.gps = gps; a.cps = n_per >> 3; a.batch = batch; a.group = group;
     a.cpg = static_cast<int32_t>(static_cast<uint32_t>(group) / kChunk); a.bits = bits;
-    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f; a.through = 0;
+    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f; a.through = THROUGH;
     a.seen = seen; a.stamp = stamp;
     dequant_job<DT, UNROLL, kBlock, false>(a, blockIdx.x, blockIdx.y);
 }
@@ -138,14 +142,20 @@ static hipError_t launch_dequant_with(Kernel kernel, const DequantJob& a, hipStr
                          a.group, a.bits, a.n_per, a.gps, a.batch, a.grid_x, a.grid_y, a.stamp, a.seen, a.full);
 }
 
-template <int DT>
-hipError_t launch_dequant_single_dt(int unroll, const DequantJob& a, hipStream_t s) {
+template <int DT, bool THROUGH>
+static hipError_t launch_dequant_single_unroll(int unroll, const DequantJob& a, hipStream_t s) {
     switch (unroll) {
-    case 1: return launch_dequant_with(dequant_single_kernel<DT, 1>, a, s);
-    case 2: return launch_dequant_with(dequant_single_kernel<DT, 2>, a, s);
-    case 4: return launch_dequant_with(dequant_single_kernel<DT, 4>, a, s);
+    case 1: return launch_dequant_with(dequant_single_kernel<DT, 1, THROUGH>, a, s);
+    case 2: return launch_dequant_with(dequant_single_kernel<DT, 2, THROUGH>, a, s);
+    case 4: return launch_dequant_with(dequant_single_kernel<DT, 4, THROUGH>, a, s);
     default: return hipErrorInvalidValue;
     }
+}
+
+template <int DT>
+hipError_t launch_dequant_single_dt(int unroll, const DequantJob& a, hipStream_t s) {
+    return a.through ? launch_dequant_single_unroll<DT, true>(unroll, a, s)
+                     : launch_dequant_single_unroll<DT, false>(unroll, a, s);
 }
 
 #define AQSGD_INSTANTIATE_SINGLE_DTYPE(DT)                                                        \
