@@ -36,12 +36,13 @@ static_assert(sizeof(JobTable) == 2000, "the size named above");
 
 // Which bodies a quantising kernel holds: as in the shared launches the 3-bit ones, which
 // need more registers, are apart; odd groups have bodies of their own, and two kernels, for
-// they have no table to go out with when a grid cannot hold one workgroup for every step.
-enum SingleKind { kSingleWhole = 0, kSingleThree, kSingleOdd, kSingleOddLoops };
+// they have no table to go out with when a grid cannot hold one workgroup for every step.  The
+// last kind is the first with m written through the L2 (see store16); it holds no bodies without m.
+enum SingleKind { kSingleWhole = 0, kSingleThree, kSingleOdd, kSingleOddLoops, kSingleThrough };
 
-template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool ODD, bool LOOPS>
+template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool ODD, bool LOOPS, bool HAS_BUF = false>
 __device__ __forceinline__ void single_quant_bits(const QuantJob& a, float* wave_max) {
-    if (a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, ODD, LOOPS>(a, blockIdx.x, blockIdx.y, wave_max);
+    if (HAS_BUF || a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, ODD, LOOPS>(a, blockIdx.x, blockIdx.y, wave_max);
     else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false, ODD, LOOPS>(a, blockIdx.x, blockIdx.y, wave_max);
 }
 
@@ -51,29 +52,30 @@ void quant_single_kernel(AQSGD_QUANT_ARGS) {
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
     constexpr bool LOOPS = KIND == kSingleOddLoops;
     constexpr bool ODD = KIND == kSingleOdd || LOOPS;
+    constexpr bool HAS_BUF = KIND == kSingleThrough;
     [[maybe_unused]] __shared__ float wave_max[kThreads / kWave];
     QuantJob a;
     a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
     a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
     a.cpg = static_cast<int32_t>((static_cast<uint32_t>(group) + kChunk - 1) / kChunk);
-    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f; a.through = 0;
+    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f; a.through = KIND == kSingleThrough;
     a.seed = seed; a.seen = seen; a.first = first; a.stamp = stamp;
     if constexpr (KIND == kSingleThree) {
         single_quant_bits<DT, 3, ROUND, TEAM, CPL, false, false>(a, wave_max);
     } else {
         switch (bits) {                                  // uniform over the launch
-        case 2: single_quant_bits<DT, 2, ROUND, TEAM, CPL, ODD, LOOPS>(a, wave_max); break;
-        case 4: single_quant_bits<DT, 4, ROUND, TEAM, CPL, ODD, LOOPS>(a, wave_max); break;
-        case 6: single_quant_bits<DT, 6, ROUND, TEAM, CPL, ODD, LOOPS>(a, wave_max); break;
-        default: single_quant_bits<DT, 8, ROUND, TEAM, CPL, ODD, LOOPS>(a, wave_max); break;
+        case 2: single_quant_bits<DT, 2, ROUND, TEAM, CPL, ODD, LOOPS, HAS_BUF>(a, wave_max); break;
+        case 4: single_quant_bits<DT, 4, ROUND, TEAM, CPL, ODD, LOOPS, HAS_BUF>(a, wave_max); break;
+        case 6: single_quant_bits<DT, 6, ROUND, TEAM, CPL, ODD, LOOPS, HAS_BUF>(a, wave_max); break;
+        default: single_quant_bits<DT, 8, ROUND, TEAM, CPL, ODD, LOOPS, HAS_BUF>(a, wave_max); break;
         }
     }
 }
 
 // THROUGH: how m and out are stored (see store16).  A constant in these kernels, not a field of the job as
 // in the shared launches: a branch at every store costs a message of this size 1 to 2 % (first visits
-// of float16 [4,1024,1600] 17.6 -> 18.0 us).  Large reconstructions write through, the quantising
-// side, which stores half as much, always streams.
+// of float16 [4,1024,1600] 17.6 -> 18.0 us).  Large reconstructions write through; the quantising
+// side has a kind of its own for it (kSingleThrough).
 template <int DT, int UNROLL, bool THROUGH>
 __global__ __launch_bounds__(kBlock)
 void dequant_single_kernel(AQSGD_DEQUANT_ARGS) {
@@ -125,6 +127,7 @@ static hipError_t launch_quant_single_kind(int shape, bool covers, const QuantJo
     if (!covers) return hipErrorInvalidValue;
     if (a.group % kChunk != 0) return launch_quant_single_shape<DT, ROUND, kSingleOdd>(shape, a, s);
     if (a.bits == 3) return launch_quant_single_shape<DT, ROUND, kSingleThree>(shape, a, s);
+    if (a.through && a.m_buf) return launch_quant_single_shape<DT, ROUND, kSingleThrough>(shape, a, s);
     return launch_quant_single_shape<DT, ROUND, kSingleWhole>(shape, a, s);
 }
 

@@ -96,6 +96,15 @@ def test_long_samples_cross_block_strides(H):
     H.replay_and_compare(cfg, calls_per_epoch=2, epochs=2, log=lambda *a, **k: None)
 
 
+@pytest.mark.parametrize("dtype,bits,group,rounding,gps", [
+    ("f32", 8, 4096, W.NEAREST, 2081), ("f32", 2, 64, W.STOCHASTIC, 131137), ("f16", 4, 128, W.STOCHASTIC, 131200),
+    ("bf16", 6, 1600, W.NEAREST, 10500), ("f32", 4, 4096, W.NEAREST, 1900)])
+def test_messages_at_the_size_where_encode_writes_through(H, dtype, bits, group, rounding, gps):
+    """Two samples a call; 64 MiB of previous messages and codes is the line, the last lies below it."""
+    cfg = _case_cfg(dtype, bits, group, rounding, gps, batch=2, n_samples=2)
+    H.replay_and_compare(cfg, calls_per_epoch=1, epochs=2, log=lambda *a, **k: None)
+
+
 def test_more_samples_in_a_call_than_grid_rows(H):
     """70001 samples in one call: the launch has at most 65535 rows of workgroups, so
     the kernels' loop over samples must come round a second time."""
