@@ -91,11 +91,19 @@ __device__ __forceinline__ Raw<DT> load_raw_any(const char* p) {
 // The compiler has no spelling for nt sc0 sc1 on a 16-byte store, so the instruction is written
 // out; the data registers of a store of more than eight bytes must not be overwritten in the next
 // two cycles, which the compiler's hazard pass cannot see through the asm statement, hence the s_nop.
+// `p` is any element's address (odd and wide groups), so the streaming form goes through the
+// under-aligned types as the loads do: it is the same instruction, and nothing is promised of the address.
+__device__ __forceinline__ void stream16(void* p, const u32x4_t& v) {
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any_t*>(p));
+}
+__device__ __forceinline__ void stream16(void* p, const f32x4_t& v) {
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any_t*>(p));
+}
 template <typename V>
 __device__ __forceinline__ void store16(void* p, const V& v, bool through) {
     static_assert(sizeof(V) == 16, "one 16-byte piece");
     if (through) asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 2" : : "v"(p), "v"(v) : "memory");
-    else __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
+    else stream16(p, v);
 }
 
 // A float32 chunk is two 16-byte stores per lane, 32 bytes apart between lanes:
