@@ -630,9 +630,10 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
                     : launch_alone(qs[0], max_blocks, launch_blocks, stream, err)))
         return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
     const auto whole = [](const auto& a) { return whole_units(a); };
-    auto add_dequant = [&](JobTable& t, int dtype, Route route) {
+    auto add_dequant = [&](JobTable& t, int dtype, Route route, size_t* taken = nullptr) {
         for (size_t k = 0; k < ds.size() && t.n_dequant < kMaxDequantJobs; ++k) {
             if (d_done[k] || ds[k].route != route || ds[k].dtype != dtype) continue;
+            if (taken) taken[t.n_dequant] = k;
             t.d[t.n_dequant++] = ds[k].job;
             d_done[k] = true;
         }
@@ -644,9 +645,9 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
         const QuantPlan& lead = qs[i];
         const bool odd = lead.route == Route::kOdd;
         if ((!odd && lead.route != Route::kWide) || launch_blocks > 0) return false;
-        const std::vector<bool> q_before = q_done, d_before = d_done;
         JobTable t;
         t.n_quant = t.n_dequant = 0;
+        size_t taken_q[kMaxQuantJobs], taken_d[kMaxDequantJobs];     // no list: something may be enqueued by now
         int64_t groups = 0;
         bool has_buf = false;
         for (size_t k = i; k < qs.size() && t.n_quant < kMaxQuantJobs; ++k) {
@@ -656,10 +657,11 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
                 continue;
             groups += c.job.gps * c.job.batch;
             has_buf = has_buf || c.job.m_buf != nullptr;
+            taken_q[t.n_quant] = k;
             t.q[t.n_quant++] = c.job;
             q_done[k] = true;
         }
-        add_dequant(t, lead.dtype, odd ? Route::kOdd : Route::kJob);
+        add_dequant(t, lead.dtype, odd ? Route::kOdd : Route::kJob, taken_d);
         bool covers = t.n_quant + t.n_dequant > 1;
         if (covers && odd) {
             struct {
@@ -682,8 +684,8 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
             if (covers) err = launch_wide_jobs(lead.dtype, lead.rounding, t, stream);
         }
         if (!covers) {
-            q_done = q_before;
-            d_done = d_before;
+            for (int k = 0; k < t.n_quant; ++k) q_done[taken_q[k]] = false;
+            for (int k = 0; k < t.n_dequant; ++k) d_done[taken_d[k]] = false;
         }
         return covers;
     };

@@ -1,0 +1,53 @@
+"""The dispatch as a program sees it from the host: which launches a call makes, with the device runtime's
+launch call replaced in a client program (tests/dispatch_client.cpp).  No GPU, and no pointer is followed."""
+import shutil
+import subprocess
+from pathlib import Path
+
+import pytest
+
+ROOT = Path(__file__).resolve().parent.parent
+F32, F16, BF16 = 0, 1, 2
+ENCODE, DECODE, GRAD_QUANT, GRAD_DEQUANT = 0, 1, 2, 3
+
+
+@pytest.fixture(scope="module")
+def client(tmp_path_factory):
+    gxx = shutil.which("g++")
+    assert gxx, "g++ is part of the image"
+    exe = tmp_path_factory.mktemp("dispatch") / "client"
+    lib = ROOT / "paper_2206_01299_amd" / "libaqsgd.so"
+    subprocess.run([gxx, "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", f"-I{ROOT / 'include'}",
+                    str(ROOT / "tests" / "dispatch_client.cpp"), str(lib), f"-Wl,-rpath,{lib.parent}",
+                    "-Wl,-rpath,/opt/rocm/lib", "-ldl", "-o", str(exe)], check=True)
+
+    def run(*jobs, options=()):
+        """The launches, as (grid, workgroup size, kernel), and the call's status."""
+        words = [",".join(str(x) for x in j) for j in jobs]
+        out = subprocess.run([str(exe), *options, *words], check=True, capture_output=True, text=True).stdout.splitlines()
+        launches = []
+        for line in out[:-1]:
+            _, gx, gy, gz, _, block, kernel = line.split(maxsplit=6)
+            launches.append(((int(gx), int(gy), int(gz)), int(block), kernel))
+        return launches, int(out[-1].split()[1])
+
+    return run
+
+
+def test_nothing_is_allocated_once_something_is_enqueued(client):
+    """Want of host memory is reported before anything is enqueued, so a call that has made its first launch
+    allocates no more: job lists whose odd and wide groups go out one by one, in pairs, and with whole ones."""
+    lists = [
+        [(ENCODE, F16, 4, 0, 4, 1020, 1020), (ENCODE, F16, 8, 0, 4, 99990, 9)],               # two team shapes
+        [(ENCODE, F16, 4, 0, 4, 1020, 1020), (GRAD_QUANT, F16, 4, 0, 4, 1020, 1020),
+         (ENCODE, BF16, 4, 1, 4, 1020, 1020), (GRAD_DEQUANT, F16, 4, 0, 4, 1020, 1020)],
+        [(ENCODE, F16, 4, 0, 4, 49152, 49152), (ENCODE, F32, 4, 0, 4, 49152, 49152),
+         (DECODE, F32, 4, 0, 4, 49152, 49152)],
+        [(ENCODE, F16, 4, 0, 4, 1024, 1024), (ENCODE, F16, 4, 0, 4, 1020, 1020), (DECODE, F16, 4, 0, 4, 1020, 1020)],
+    ]
+    for jobs in lists:
+        plain, status = client(*jobs)
+        assert status == 0 and len(plain) >= 2
+        starved, status = client(*jobs, options=("starve",))
+        assert status == 0, f"{len(starved)} of {len(plain)} launches were made, then {status}"
+        assert starved == plain
