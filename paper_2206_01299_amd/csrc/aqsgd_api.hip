@@ -1,5 +1,6 @@
 // C ABI of the AQ-SGD boundary codec: argument checks and kernel dispatch.
 // See include/aqsgd.h for the contract of every entry point.
+#include <algorithm>
 #include <atomic>
 #include <cstdlib>
 #include <limits>
@@ -370,11 +371,14 @@ int64_t whole_units(const DequantJob& a) { return a.cps; }
 // Workgroup numbers of a table whose jobs are all in: every job gets the grid its size
 // asks for (at most max_blocks), shortened by the steps a workgroup takes (`shape`: team shape
 // of the quantising jobs, -1 for one step each).  quant_step / dequant_step: units one
-// workgroup step covers; units(job): those of a sample.  Tells whether there is a workgroup
-// for every step of every sample (else the kernel has to loop over what is left).
+// workgroup step covers; units(job): those of a sample.  `threads`: lanes of a workgroup; a
+// launch takes fewer than 2^32 of them along a dimension, and the jobs share one, so that
+// caps each job's part.  Tells whether there is a workgroup for every step of every sample
+// (else the kernel has to loop over what is left).
 template <typename Units>
-bool number_blocks(JobTable& t, int shape, int64_t quant_step, int64_t dequant_step, int64_t max_blocks,
+bool number_blocks(JobTable& t, int shape, int threads, int64_t quant_step, int64_t dequant_step, int64_t max_blocks,
                    int64_t launch_blocks, Units&& units) {
+    max_blocks = std::min(max_blocks, ((int64_t{1} << 32) - 1) / threads / (t.n_quant + t.n_dequant));
     int64_t total = 0;
     auto want = [&](const auto& a, int64_t step) {
         const LaunchGeom g = geometry(units(a), step, a.batch, max_blocks);
@@ -669,7 +673,7 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
                 int64_t operator()(const QuantJob& a) const { return a.gps; }
                 int64_t operator()(const DequantJob& a) const { return odd_pieces(a, dtype); }
             } units{lead.dtype};
-            covers = number_blocks(t, -1, groups_per_block_step(lead.shape),
+            covers = number_blocks(t, -1, threads_of_shape(lead.shape), groups_per_block_step(lead.shape),
                                    static_cast<int64_t>(threads_of_shape(lead.shape)) * kOddUnroll, max_blocks, 0, units);
             if (covers) err = launch_odd_jobs(lead.dtype, lead.rounding, lead.shape, t, stream);
         } else if (covers && split_pays_shared(groups, has_buf, lead.dtype, lead.rounding)) {
@@ -677,10 +681,11 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
                 int64_t operator()(const QuantJob& a) const { return a.gps * split_geometry(a).spans; }
                 int64_t operator()(const DequantJob& a) const { return a.cps; }
             } units;
-            covers = number_blocks(t, -1, 1, static_cast<int64_t>(kBlock) * kHostedDequantUnroll, max_blocks, 0, units);
+            covers = number_blocks(t, -1, kBlock, 1, static_cast<int64_t>(kBlock) * kHostedDequantUnroll, max_blocks, 0, units);
             if (covers) err = launch_split_jobs(lead.dtype, lead.rounding, t, stream);
         } else if (covers) {
-            covers = number_blocks(t, -1, 1, static_cast<int64_t>(kWideThreads) * kHostedDequantUnroll, max_blocks, 0, whole);
+            covers = number_blocks(t, -1, kWideThreads, 1, static_cast<int64_t>(kWideThreads) * kHostedDequantUnroll, max_blocks, 0,
+                                   whole);
             if (covers) err = launch_wide_jobs(lead.dtype, lead.rounding, t, stream);
         }
         if (!covers) {
@@ -713,7 +718,7 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
         }
         add_dequant(t, lead.dtype, Route::kJob);
         choose_stores(t, lead.dtype);
-        const bool covers = number_blocks(t, lead.shape, groups_per_block_step(lead.shape),
+        const bool covers = number_blocks(t, lead.shape, threads_of_shape(lead.shape), groups_per_block_step(lead.shape),
                                           static_cast<int64_t>(threads_of_shape(lead.shape)) * kHostedDequantUnroll,
                                           max_blocks, launch_blocks, whole);
         const TableKind kind = covers ? (three ? kTableOneStepThree : kTableOneStep)
@@ -731,7 +736,7 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
         t.n_quant = t.n_dequant = 0;
         add_dequant(t, ds[i].dtype, Route::kJob);
         choose_stores(t, ds[i].dtype);
-        number_blocks(t, -1, 1, static_cast<int64_t>(kBlock) * unroll, max_blocks, launch_blocks, whole);
+        number_blocks(t, -1, kBlock, 1, static_cast<int64_t>(kBlock) * unroll, max_blocks, launch_blocks, whole);
         err = launch_dequant_jobs(ds[i].dtype, unroll, t, stream);
     }
     return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;

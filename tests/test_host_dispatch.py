@@ -51,3 +51,19 @@ def test_nothing_is_allocated_once_something_is_enqueued(client):
         starved, status = client(*jobs, options=("starve",))
         assert status == 0, f"{len(starved)} of {len(plain)} launches were made, then {status}"
         assert starved == plain
+
+
+@pytest.mark.parametrize("lead", [(GRAD_QUANT, F16, 8, 1, 200, 49152, 49152), (GRAD_QUANT, F16, 8, 0, 4, 16384, 16384),
+                                  (ENCODE, F16, 8, 0, 4, 16380, 16380)], ids=["wide", "whole", "odd"])
+def test_shared_launches_stay_below_the_lanes_of_a_grid(client, lead):
+    """A launch takes fewer than 2^32 lanes along a dimension.  Reconstructions of 34 GB each that ride along
+    with workgroups of 1024 lanes pass that together (five of them fit the card); every unit of work still
+    has a workgroup, or a kernel that loops."""
+    n_per = 262144 if lead[6] % 8 == 0 else 261900
+    ride = (GRAD_DEQUANT, F16, 2, 0, 65535, n_per, 64 if lead[6] % 8 == 0 else 4 * 291)
+    launches, status = client(lead, *[ride] * 5)
+    assert status == 0
+    for grid, block, kernel in launches:
+        assert grid[0] * block < 1 << 32, (grid, block, kernel)
+    one, status = client(lead, ride)                     # as before where it fits
+    assert status == 0 and len(one) == 1 and "jobs_kernel" in one[0][2]
