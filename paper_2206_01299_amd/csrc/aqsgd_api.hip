@@ -19,8 +19,8 @@ namespace aqsgd {
 
 // Instantiated in the dtypes' own translation units.
 #define AQSGD_EXTERN_DTYPE(DT)                                                                        \
-    extern template hipError_t launch_quant_single_dt<DT>(int, int, bool, const QuantJob&, hipStream_t); \
-    extern template hipError_t launch_dequant_single_dt<DT>(int, const DequantJob&, hipStream_t);     \
+    extern template hipError_t launch_quant_single_dt<DT>(int, int, bool, bool, const QuantJob&, hipStream_t); \
+    extern template hipError_t launch_dequant_single_dt<DT>(int, bool, const DequantJob&, hipStream_t); \
     extern template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);       \
     extern template hipError_t launch_quant_wide_dt<DT>(int, int, int, const QuantJob&, hipStream_t); \
     extern template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t); \
@@ -36,21 +36,31 @@ AQSGD_EXTERN_DTYPE(AQSGD_BF16)
 thread_local ProfileRequest g_profile_request = {nullptr, nullptr};
 
 // -- dtype fan-out (each dtype's kernels live in their own translation unit) ----
-hipError_t launch_codec_jobs(int dtype, int rounding, int shape, TableKind kind, const JobTable& t, hipStream_t s) {
+template <bool THROUGH>
+hipError_t launch_codec_jobs_as(int dtype, int rounding, int shape, TableKind kind, const JobTable& t, hipStream_t s) {
     switch (dtype) {
-    case AQSGD_F32:  return launch_codec_jobs_dt<AQSGD_F32>(rounding, shape, kind, t, s);
-    case AQSGD_F16:  return launch_codec_jobs_dt<AQSGD_F16>(rounding, shape, kind, t, s);
-    case AQSGD_BF16: return launch_codec_jobs_dt<AQSGD_BF16>(rounding, shape, kind, t, s);
+    case AQSGD_F32:  return launch_codec_jobs_dt<AQSGD_F32, THROUGH>(rounding, shape, kind, t, s);
+    case AQSGD_F16:  return launch_codec_jobs_dt<AQSGD_F16, THROUGH>(rounding, shape, kind, t, s);
+    case AQSGD_BF16: return launch_codec_jobs_dt<AQSGD_BF16, THROUGH>(rounding, shape, kind, t, s);
     default:         return hipErrorInvalidValue;
     }
 }
-hipError_t launch_dequant_jobs(int dtype, int unroll, const JobTable& t, hipStream_t s) {
+hipError_t launch_codec_jobs(int dtype, int rounding, int shape, TableKind kind, bool through, const JobTable& t,
+                             hipStream_t s) {
+    return through ? launch_codec_jobs_as<true>(dtype, rounding, shape, kind, t, s)
+                   : launch_codec_jobs_as<false>(dtype, rounding, shape, kind, t, s);
+}
+template <bool THROUGH>
+hipError_t launch_dequant_jobs_as(int dtype, int unroll, const JobTable& t, hipStream_t s) {
     switch (dtype) {
-    case AQSGD_F32:  return launch_dequant_jobs_dt<AQSGD_F32>(unroll, t, s);
-    case AQSGD_F16:  return launch_dequant_jobs_dt<AQSGD_F16>(unroll, t, s);
-    case AQSGD_BF16: return launch_dequant_jobs_dt<AQSGD_BF16>(unroll, t, s);
+    case AQSGD_F32:  return launch_dequant_jobs_dt<AQSGD_F32, THROUGH>(unroll, t, s);
+    case AQSGD_F16:  return launch_dequant_jobs_dt<AQSGD_F16, THROUGH>(unroll, t, s);
+    case AQSGD_BF16: return launch_dequant_jobs_dt<AQSGD_BF16, THROUGH>(unroll, t, s);
     default:         return hipErrorInvalidValue;
     }
+}
+hipError_t launch_dequant_jobs(int dtype, int unroll, bool through, const JobTable& t, hipStream_t s) {
+    return through ? launch_dequant_jobs_as<true>(dtype, unroll, t, s) : launch_dequant_jobs_as<false>(dtype, unroll, t, s);
 }
 hipError_t launch_quant_anyshape(int dtype, int bits, int rounding, const QuantJob& a, hipStream_t s) {
     switch (dtype) {
@@ -69,19 +79,20 @@ hipError_t launch_dequant_anyshape(int dtype, const DequantJob& a, hipStream_t s
     }
 }
 
-hipError_t launch_quant_single(int dtype, int rounding, int shape, bool covers, const QuantJob& a, hipStream_t s) {
+hipError_t launch_quant_single(int dtype, int rounding, int shape, bool covers, bool through, const QuantJob& a,
+                               hipStream_t s) {
     switch (dtype) {
-    case AQSGD_F32:  return launch_quant_single_dt<AQSGD_F32>(rounding, shape, covers, a, s);
-    case AQSGD_F16:  return launch_quant_single_dt<AQSGD_F16>(rounding, shape, covers, a, s);
-    case AQSGD_BF16: return launch_quant_single_dt<AQSGD_BF16>(rounding, shape, covers, a, s);
+    case AQSGD_F32:  return launch_quant_single_dt<AQSGD_F32>(rounding, shape, covers, through, a, s);
+    case AQSGD_F16:  return launch_quant_single_dt<AQSGD_F16>(rounding, shape, covers, through, a, s);
+    case AQSGD_BF16: return launch_quant_single_dt<AQSGD_BF16>(rounding, shape, covers, through, a, s);
     default:         return hipErrorInvalidValue;
     }
 }
-hipError_t launch_dequant_single(int dtype, int unroll, const DequantJob& a, hipStream_t s) {
+hipError_t launch_dequant_single(int dtype, int unroll, bool through, const DequantJob& a, hipStream_t s) {
     switch (dtype) {
-    case AQSGD_F32:  return launch_dequant_single_dt<AQSGD_F32>(unroll, a, s);
-    case AQSGD_F16:  return launch_dequant_single_dt<AQSGD_F16>(unroll, a, s);
-    case AQSGD_BF16: return launch_dequant_single_dt<AQSGD_BF16>(unroll, a, s);
+    case AQSGD_F32:  return launch_dequant_single_dt<AQSGD_F32>(unroll, through, a, s);
+    case AQSGD_F16:  return launch_dequant_single_dt<AQSGD_F16>(unroll, through, a, s);
+    case AQSGD_BF16: return launch_dequant_single_dt<AQSGD_BF16>(unroll, through, a, s);
     default:         return hipErrorInvalidValue;
     }
 }
@@ -311,7 +322,7 @@ QuantPlan plan_quant(const aqsgd_desc* d, int64_t batch, int64_t n_per, const vo
     a.n_per = n_per; a.gps = n_per / d->group;
     a.batch = static_cast<int32_t>(batch); a.group = d->group; a.bits = d->bits;
     a.cpg = static_cast<int32_t>((static_cast<int64_t>(d->group) + kChunk - 1) / kChunk);
-    a.grid_x = a.grid_y = 1; a.rcp_grid_x = 1.0f; a.through = 0;
+    a.grid_x = a.grid_y = 1; a.rcp_grid_x = 1.0f;
     a.seed = d->rng_seed; a.seen = sa.seen; a.first = sa.first; a.stamp = sa.stamp;
     p.dtype = d->dtype; p.bits = d->bits; p.rounding = d->rounding;
     p.route = a.group < kChunk ? Route::kAnyShape
@@ -338,13 +349,15 @@ DequantPlan plan_dequant(const aqsgd_desc* d, int64_t batch, int64_t n_per, cons
     a.codes = codes; a.scales = scales; a.ids = ids; a.m_buf = m_buf; a.out = out; a.full = sa.full;
     a.n_per = n_per; a.gps = n_per / d->group; a.cps = n_per / kChunk;
     a.batch = static_cast<int32_t>(batch); a.group = d->group; a.cpg = d->group / kChunk; a.bits = d->bits;
-    a.grid_x = a.grid_y = 1; a.rcp_grid_x = 1.0f; a.through = 0;
+    a.grid_x = a.grid_y = 1; a.rcp_grid_x = 1.0f;
     a.seen = sa.seen; a.stamp = sa.stamp;
     p.dtype = d->dtype;
     const bool odd_fits = a.group >= kChunk && odd_pieces(a, d->dtype) < kMaxOddPieces;
     p.route = a.group % kChunk == 0 ? Route::kJob : odd_fits ? Route::kOdd : Route::kAnyShape;
     return p;
 }
+
+bool smaller_than_a_wave(int shape) { return shape == kTeam8x1 || shape == kTeam16x1 || shape == kTeam32x1; }
 
 // Steps a workgroup of a shared launch takes (`total`: steps of all its jobs; `shape`: team
 // shape of the quantising ones, -1 without).  One, but for small teams (one chunk per lane) in
@@ -359,7 +372,7 @@ DequantPlan plan_dequant(const aqsgd_desc* d, int64_t batch, int64_t n_per, cons
 // streams 13.3 -> 13.5; so the loops start at 4096.  The wider shapes (a step is four chunks per
 // lane or a workgroup's row) lose from loops throughout.
 int64_t steps_per_workgroup(int shape, int64_t total, int64_t launch_blocks) {
-    const bool small = shape == kTeam8x1 || shape == kTeam16x1 || shape == kTeam32x1;
+    const bool small = smaller_than_a_wave(shape);
     if (launch_blocks == 0 && small && total >= 4096) launch_blocks = 2048;
     return launch_blocks > 0 ? (total + launch_blocks - 1) / launch_blocks : 1;
 }
@@ -498,7 +511,7 @@ hipError_t launch_quant_alone(QuantPlan& p, int64_t max_blocks, int64_t launch_b
     case Route::kOdd: {
         const int64_t cap = launch_blocks > 0 && launch_blocks < max_blocks ? launch_blocks : max_blocks;
         const bool covers = one_step_grid(a, a.gps, groups_per_block_step(p.shape), cap);
-        return launch_quant_single(p.dtype, p.rounding, p.shape, covers, a, stream);
+        return launch_quant_single(p.dtype, p.rounding, p.shape, covers, false, a, stream);
     }
     case Route::kWide:
         if (split_pays(a, p.dtype, p.rounding)) {
@@ -536,13 +549,16 @@ hipError_t launch_dequant_alone(DequantPlan& p, int64_t max_blocks, hipStream_t 
     return launch_dequant_anyshape(p.dtype, a, stream);
 }
 
-// Which jobs of a shared launch write previous messages and reconstructions through the L2 (see
-// store16): those whose rows (and groups, on the quantising side, where a team of lanes stores its
-// own) are whole 128-byte lines, in launches that write more than about the eight L2s hold in lines
-// that have not left yet.  Measured, one stream, through -> streaming: bfloat16 [18,175,128], four
-// boundaries, 15 MB written 10.3 -> 9.1 us; [1,1537,384], two boundaries, 11 MB 7.2 -> 6.5; float32
-// [1,2048,2704] G = 2704 (groups of 84 and a half lines) four boundaries 140 -> 126; of whole lines, 60 MB
-// and more, equal within 2 % and better with another stream beside it.
+// Which launches write previous messages and reconstructions through the L2 (see store16): those whose
+// rows (and groups, on the quantising side, where a team of lanes stores its own) are whole 128-byte
+// lines and that write more than about the eight L2s hold in lines that have not left yet.
+//
+// Shared launches, a time slot on one stream, through -> streaming: bfloat16 [18,175,128], four boundaries,
+// 15 MB written 10.3 -> 9.1 us; [1,1537,384], two boundaries, 11 MB 7.2 -> 6.5; of whole lines, 60 MB and more,
+// equal within 2 % and better through with another stream beside it.  One job that is not of whole lines
+// makes the table stream: float32 [1,2048,2704] G = 2704 (groups of 84 and a half lines, whole
+// rows), four boundaries, 142 -> 125 (only its encode streaming 125); [8,512,2048] G = 16 79 -> 66 (75); float16
+// [8,512,2048] G = 32 31.8 -> 30.8 (31.3).
 constexpr int64_t kThroughBytes = int64_t{24} << 20;
 
 int64_t bytes_written(const QuantJob& a, int64_t eb) {
@@ -550,17 +566,17 @@ int64_t bytes_written(const QuantJob& a, int64_t eb) {
 }
 int64_t bytes_written(const DequantJob& a, int64_t eb) { return a.batch * a.n_per * eb * (a.m_buf ? 2 : 1); }
 constexpr int64_t kLineBytes = 128;
-uint32_t whole_lines(const QuantJob& a, int64_t eb) {
+bool whole_lines(const QuantJob& a, int64_t eb) {
     return a.n_per * eb % kLineBytes == 0 && a.group * eb % kLineBytes == 0;
 }
-uint32_t whole_lines(const DequantJob& a, int64_t eb) { return a.n_per * eb % kLineBytes == 0; }
+bool whole_lines(const DequantJob& a, int64_t eb) { return a.n_per * eb % kLineBytes == 0; }
 
 // A reconstruction alone (measured in a row of four calls, through -> streaming: float32 [8,2048,4096]
 // 362 -> 366 us, bfloat16 [32,256,1536] 46.3 -> 46.8, first visits of float16 [4,1024,1600], 26 MB written,
 // 17.4 -> 17.7).
-void choose_stores(DequantJob& a, int dtype) {
+bool writes_through(const DequantJob& a, int dtype) {
     const int64_t eb = dtype == AQSGD_F32 ? 4 : 2;
-    if (bytes_written(a, eb) >= kThroughBytes) a.through = whole_lines(a, eb);
+    return bytes_written(a, eb) >= kThroughBytes && whole_lines(a, eb);
 }
 
 // An encode alone stores half as much for what it reads, and its line lies higher (a row of four calls,
@@ -569,19 +585,25 @@ void choose_stores(DequantJob& a, int dtype) {
 // [15,2048,640] at 8 bits 69.8 -> 69.5).  Groups that are no octets and 3 bits always stream.
 constexpr int64_t kThroughEncodeBytes = int64_t{64} << 20;
 
-void choose_stores(QuantJob& a, int dtype) {
+bool writes_through(const QuantJob& a, int dtype) {
     const int64_t eb = dtype == AQSGD_F32 ? 4 : 2;
-    if (a.m_buf && bytes_written(a, eb) >= kThroughEncodeBytes) a.through = whole_lines(a, eb);
+    return a.m_buf && bytes_written(a, eb) >= kThroughEncodeBytes && whole_lines(a, eb);
 }
 
-void choose_stores(JobTable& t, int dtype) {
+// A table's jobs are stored alike: through if all that hold such stores are of whole lines.
+bool writes_through(const JobTable& t, int dtype) {
     const int64_t eb = dtype == AQSGD_F32 ? 4 : 2;
     int64_t bytes = 0;
-    for (int k = 0; k < t.n_quant; ++k) bytes += bytes_written(t.q[k], eb);
-    for (int k = 0; k < t.n_dequant; ++k) bytes += bytes_written(t.d[k], eb);
-    if (bytes < kThroughBytes) return;
-    for (int k = 0; k < t.n_quant; ++k) t.q[k].through = whole_lines(t.q[k], eb);
-    for (int k = 0; k < t.n_dequant; ++k) t.d[k].through = whole_lines(t.d[k], eb);
+    bool lines = true;
+    for (int k = 0; k < t.n_quant; ++k) {
+        bytes += bytes_written(t.q[k], eb);
+        lines = lines && (t.q[k].m_buf == nullptr || whole_lines(t.q[k], eb));
+    }
+    for (int k = 0; k < t.n_dequant; ++k) {
+        bytes += bytes_written(t.d[k], eb);
+        lines = lines && whole_lines(t.d[k], eb);
+    }
+    return lines && bytes >= kThroughBytes;
 }
 
 // A message that comes alone.  Without lists: a small message's call is over on the device in 2 to 3 us,
@@ -594,8 +616,7 @@ bool launch_alone(QuantPlan& q, int64_t max_blocks, int64_t launch_blocks, hipSt
         return true;
     }
     if (launch_blocks != 0 || !one_step_grid(q.job, q.job.gps, groups_per_block_step(q.shape), max_blocks)) return false;
-    choose_stores(q.job, q.dtype);
-    err = launch_quant_single(q.dtype, q.rounding, q.shape, true, q.job, stream);
+    err = launch_quant_single(q.dtype, q.rounding, q.shape, true, writes_through(q.job, q.dtype), q.job, stream);
     return true;
 }
 
@@ -606,8 +627,7 @@ bool launch_alone(DequantPlan& d, int64_t max_blocks, int64_t launch_blocks, hip
     }
     const int chunks = many_short_samples(d.job) ? 1 : dequant_unroll_knob().load(std::memory_order_relaxed);
     if (launch_blocks != 0 || !one_step_grid(d.job, d.job.cps, static_cast<int64_t>(kBlock) * chunks, max_blocks)) return false;
-    choose_stores(d.job, d.dtype);
-    err = launch_dequant_single(d.dtype, chunks, d.job, stream);
+    err = launch_dequant_single(d.dtype, chunks, writes_through(d.job, d.dtype), d.job, stream);
     return true;
 }
 
@@ -717,13 +737,13 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
             q_done[k] = true;
         }
         add_dequant(t, lead.dtype, Route::kJob);
-        choose_stores(t, lead.dtype);
         const bool covers = number_blocks(t, lead.shape, threads_of_shape(lead.shape), groups_per_block_step(lead.shape),
                                           static_cast<int64_t>(threads_of_shape(lead.shape)) * kHostedDequantUnroll,
                                           max_blocks, launch_blocks, whole);
         const TableKind kind = covers ? (three ? kTableOneStepThree : kTableOneStep)
                                       : (three ? kTableLoopsThree : kTableLoops);
-        err = launch_codec_jobs(lead.dtype, lead.rounding, lead.shape, kind, t, stream);
+        const bool through = (covers || smaller_than_a_wave(lead.shape)) && writes_through(t, lead.dtype);
+        err = launch_codec_jobs(lead.dtype, lead.rounding, lead.shape, kind, through, t, stream);
     }
     for (size_t i = 0; i < ds.size() && err == hipSuccess; ++i) {
         if (d_done[i]) continue;
@@ -735,9 +755,8 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
         JobTable t;
         t.n_quant = t.n_dequant = 0;
         add_dequant(t, ds[i].dtype, Route::kJob);
-        choose_stores(t, ds[i].dtype);
         number_blocks(t, -1, kBlock, 1, static_cast<int64_t>(kBlock) * unroll, max_blocks, launch_blocks, whole);
-        err = launch_dequant_jobs(ds[i].dtype, unroll, t, stream);
+        err = launch_dequant_jobs(ds[i].dtype, unroll, writes_through(t, ds[i].dtype), t, stream);
     }
     return err == hipSuccess ? AQSGD_OK : AQSGD_ERR_LAUNCH;
 }

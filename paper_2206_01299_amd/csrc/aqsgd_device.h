@@ -86,7 +86,7 @@ __device__ __forceinline__ Raw<DT> load_raw_any(const char* p) {
 // lines the two halves of a line go to memory one by one instead of meeting in the L2: bfloat16
 // [7,1001,2008] decode 20.9 and 18.2, rows of 2048 17.1 and 17.4.  (Ordinary stores are as good as
 // streaming ones in small launches and lose in all others: float32 [8,2048,4096], four calls 407 us
-// against 358.)  So the caller says which: `through` is a constant but in the shared launches.
+// against 358.)  So the caller says which: `through` is a constant of every kernel.
 //
 // The compiler has no spelling for nt sc0 sc1 on a 16-byte store, so the instruction is written
 // out; the data registers of a store of more than eight bytes must not be overwritten in the next

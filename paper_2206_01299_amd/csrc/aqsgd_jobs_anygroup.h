@@ -53,8 +53,8 @@ void odd_jobs_kernel(const JobTable t) {
         [&](const QuantJob& a, uint32_t bx, uint32_t by) AQSGD_INLINE {
             auto body = [&](auto bits) AQSGD_INLINE {
                 constexpr int BITS = decltype(bits)::value;
-                if (a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, true, false>(a, bx, by, wave_max);
-                else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false, true, false>(a, bx, by, wave_max);
+                if (a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, true, false, false>(a, bx, by, wave_max);
+                else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false, true, false, false>(a, bx, by, wave_max);
             };
             switch (a.bits) {                            // uniform over the workgroup
             case 2: body(std::integral_constant<int, 2>()); break;
@@ -74,7 +74,7 @@ void wide_jobs_kernel(const JobTable t) {
     run_table_job(t,
         [&](const QuantJob& a, uint32_t bx, uint32_t by) AQSGD_INLINE { quant_wide_job<DT, ROUND>(a, bx, by, 0, 1 << 20, wave_max); },
         [&](const DequantJob& a, uint32_t bx, uint32_t by) AQSGD_INLINE {
-            dequant_job<DT, kHostedDequantUnroll, kWideThreads, false>(a, bx, by);
+            dequant_job<DT, kHostedDequantUnroll, kWideThreads, false, false>(a, bx, by);
         });
 }
 
@@ -97,7 +97,7 @@ void split_jobs_kernel(const JobTable t) {
             split_quant_job<DT, ROUND>(a, split_geometry(a), Rect{bx, by, a.grid_x, a.grid_y});
         },
         [&](const DequantJob& a, uint32_t bx, uint32_t by) AQSGD_INLINE {
-            dequant_job<DT, kHostedDequantUnroll, kBlock, false>(a, bx, by);
+            dequant_job<DT, kHostedDequantUnroll, kBlock, false, false>(a, bx, by);
         });
 }
 

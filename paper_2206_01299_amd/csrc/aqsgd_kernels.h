@@ -63,7 +63,6 @@ struct QuantJob {
     int32_t bits;
     uint32_t grid_x, grid_y;   // its workgroups: grid_x per sample row, grid_y rows
     float rcp_grid_x;          // 1 / grid_x, for the workgroup's position in that rectangle
-    uint32_t through;          // m is written through the L2 (see store16)
     uint64_t seed;
     uint32_t* seen;            // or nullptr: no first-visit handling
     int32_t* first;            // with seen: first[i] = 1 if sample i was new, else 0
@@ -86,7 +85,6 @@ struct DequantJob {
     int32_t bits;
     uint32_t grid_x, grid_y;
     float rcp_grid_x;
-    uint32_t through;          // m and out are written through the L2
     uint32_t* seen;            // or nullptr
     uint32_t stamp;
 };
@@ -162,7 +160,7 @@ __device__ __forceinline__ int64_t code_offset(int64_t off) {
     return ODD ? off * BITS / 8 : off / kChunk * BITS;
 }
 
-template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF, int NG, bool ODD>
+template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF, int NG, bool ODD, bool THROUGH>
 __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* src_s, char* m_s,
                                                  uint8_t* codes_s, float* scales_s, int64_t src0,
                                                  int64_t g0, int64_t gstride, const uint32_t (&cc)[CPL],
@@ -302,7 +300,7 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
                 }
                 if constexpr (HAS_BUF)
                     store_raw_units(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB,
-                                    updated_chunk<DT>(rm[u][k], dh), a.through != 0);
+                                    updated_chunk<DT>(rm[u][k], dh), THROUGH);
                 continue;
             }
             if (BITS == 3 && TEAM % 4 == 0 && a.cpg % 4 == 0) {
@@ -316,7 +314,7 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
                 store_codes_at<BITS>(group_codes + cc[k] * BITS, pack_levels<BITS>(q));
             }
             if constexpr (HAS_BUF)
-                store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, updated_chunk<DT>(rm[u][k], dh), a.through != 0);
+                store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, updated_chunk<DT>(rm[u][k], dh), THROUGH);
         }
         if (lane_in_team == 0) scales_s[g0 + u * gstride] = sc[u].s_tx;
     }
@@ -325,7 +323,7 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
 // First visit of a sample on the sender: the team's chunks of the group go from act
 // to m unchanged (the activation itself is the message).  Same chunk ownership and
 // clamping as above, so the two paths write a row with the same access pattern.
-template <int DT, int TEAM, int CPL, bool ODD>
+template <int DT, int TEAM, int CPL, bool ODD, bool THROUGH>
 __device__ __forceinline__ void copy_team_group(const QuantJob& a, const char* src_s, char* m_s, int64_t g,
                                                 const uint32_t (&cc)[CPL], const uint32_t (&ua)[CPL],
                                                 const uint32_t (&ub)[CPL]) {
@@ -347,16 +345,16 @@ __device__ __forceinline__ void copy_team_group(const QuantJob& a, const char* s
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
         if constexpr (kUnits)
-            store_raw_units(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB, ra[k], a.through != 0);
+            store_raw_units(m_g + Unit::elem(ua[k]) * kEB, m_g + Unit::elem(ub[k]) * kEB, ra[k], THROUGH);
         else
-            store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, ra[k], a.through != 0);
+            store_raw_at<DT>(m_g + Chunk::elem(cc[k]) * kEB, ra[k], THROUGH);
     }
 }
 
 // Workgroup (bx, by) of a quantising job's grid_x x grid_y rectangle.  LOOPS: the rectangle may
 // be smaller than the message; without, every workgroup has exactly one sample and one step,
-// and nothing is kept for a next one.
-template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF, bool ODD = false, bool LOOPS = true>
+// and nothing is kept for a next one.  THROUGH: how m is stored (see store16).
+template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool HAS_BUF, bool ODD, bool LOOPS, bool THROUGH>
 __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
     constexpr bool kMultiWave = TEAM > kWave;
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
@@ -411,7 +409,7 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
         for (int64_t gbase = static_cast<int64_t>(bx) * kGroupsPerStep; !LOOPS || gbase < a.gps;
              gbase += static_cast<int64_t>(a.grid_x) * kGroupsPerStep) {
             if (kGroupsPerTeam > 1 && !fresh && gbase + kGroupsPerStep <= a.gps) {   // uniform over the workgroup
-                quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, kGroupsPerTeam, ODD>(
+                quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, kGroupsPerTeam, ODD, THROUGH>(
                     a, src_s, m_s, codes_s, scales_s, src0, gbase + team, kTeamsPerBlock, cc, ua, ub,
                     lane_in_team, wave_max);
             } else {
@@ -422,11 +420,11 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
                     if (g >= a.gps) continue;
                     if constexpr (HAS_BUF) {
                         if (fresh) {                     // uniform over the workgroup
-                            copy_team_group<DT, TEAM, CPL, ODD>(a, src_s, m_s, g, cc, ua, ub);
+                            copy_team_group<DT, TEAM, CPL, ODD, THROUGH>(a, src_s, m_s, g, cc, ua, ub);
                             continue;
                         }
                     }
-                    quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, 1, ODD>(
+                    quant_team_group<DT, BITS, ROUND, TEAM, CPL, HAS_BUF, 1, ODD, THROUGH>(
                         a, src_s, m_s, codes_s, scales_s, src0, g, 0, cc, ua, ub, lane_in_team, wave_max);
                 }
             }
@@ -440,9 +438,9 @@ __device__ __forceinline__ void quant_team_body(const QuantJob& a, uint32_t bx, 
 // decode / grad_dequant, flat chunk body: UNROLL chunks per lane and step, all
 // loads first.  The group of a chunk comes from one exact division per
 // workgroup step plus a small per-lane correction.  THREADS is the size of the
-// workgroup the body runs in (the hosting kernel's).
+// workgroup the body runs in (the hosting kernel's); THROUGH: how m and out are stored.
 // ---------------------------------------------------------------------------
-template <int DT, int BITS, int UNROLL, bool HAS_BUF, int THREADS, bool LOOPS>
+template <int DT, int BITS, int UNROLL, bool HAS_BUF, int THREADS, bool LOOPS, bool THROUGH>
 __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t bx, uint32_t by) {
     constexpr int kEB = ElemBytes<DT>::value;
     constexpr int kChunkBytes = kChunk * kEB;
@@ -476,8 +474,8 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
                         for (int u = 0; u < UNROLL; ++u) {
                             const uint32_t c = cbase + u * THREADS + threadIdx.x;
                             if (c >= cps) continue;
-                            store_raw_at<DT>(m_s + static_cast<uint64_t>(c) * kChunkBytes, v[u], a.through != 0);
-                            store_raw_at<DT>(out_s + static_cast<uint64_t>(c) * kChunkBytes, v[u], a.through != 0);
+                            store_raw_at<DT>(m_s + static_cast<uint64_t>(c) * kChunkBytes, v[u], THROUGH);
+                            store_raw_at<DT>(out_s + static_cast<uint64_t>(c) * kChunkBytes, v[u], THROUGH);
                         }
                     }
                     if constexpr (!LOOPS) return;
@@ -528,11 +526,11 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
                     Raw<DT> packed;
                     if constexpr (HAS_BUF) {
                         packed = updated_chunk<DT>(rm[u], dh);
-                        store_raw_at<DT>(m_s + static_cast<uint64_t>(cs[u]) * kChunkBytes, packed, a.through != 0);
+                        store_raw_at<DT>(m_s + static_cast<uint64_t>(cs[u]) * kChunkBytes, packed, THROUGH);
                     } else {
                         packed = pack_raw<DT>(dh);
                     }
-                    store_raw_at<DT>(out_s + static_cast<uint64_t>(cs[u]) * kChunkBytes, packed, a.through != 0);
+                    store_raw_at<DT>(out_s + static_cast<uint64_t>(cs[u]) * kChunkBytes, packed, THROUGH);
                 }
             }
             if constexpr (!LOOPS) break;
@@ -546,7 +544,7 @@ __device__ __forceinline__ void dequant_flat_body(const DequantJob& a, uint32_t 
 // consecutive 16 bytes of m, out and, half of a chunk's bytes each, of the codes.
 constexpr int64_t kMaxUnitChunks = int64_t{1} << 30;     // unit indices of a sample fit 32 bits
 
-template <int BITS, int UNITS, bool HAS_BUF, int THREADS, bool LOOPS>
+template <int BITS, int UNITS, bool HAS_BUF, int THREADS, bool LOOPS, bool THROUGH>
 __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t bx, uint32_t by) {
     constexpr int kUnitBytes = kUnit * 4;
     constexpr uint32_t kStep = THREADS * UNITS;
@@ -580,8 +578,8 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
                         for (int u = 0; u < UNITS; ++u) {
                             const uint32_t unit = ubase + u * THREADS + threadIdx.x;
                             if (unit >= ups) continue;
-                            store16(m_s + static_cast<uint64_t>(unit) * kUnitBytes, v[u], a.through != 0);
-                            store16(out_s + static_cast<uint64_t>(unit) * kUnitBytes, v[u], a.through != 0);
+                            store16(m_s + static_cast<uint64_t>(unit) * kUnitBytes, v[u], THROUGH);
+                            store16(out_s + static_cast<uint64_t>(unit) * kUnitBytes, v[u], THROUGH);
                         }
                     }
                     if constexpr (!LOOPS) return;
@@ -632,8 +630,8 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
                     else v[e] = dh;
                 }
                 if (ok[u]) {
-                    if constexpr (HAS_BUF) store16(m_s + static_cast<uint64_t>(us[u]) * kUnitBytes, v, a.through != 0);
-                    store16(out_s + static_cast<uint64_t>(us[u]) * kUnitBytes, v, a.through != 0);
+                    if constexpr (HAS_BUF) store16(m_s + static_cast<uint64_t>(us[u]) * kUnitBytes, v, THROUGH);
+                    store16(out_s + static_cast<uint64_t>(us[u]) * kUnitBytes, v, THROUGH);
                 }
             }
             if constexpr (!LOOPS) break;
@@ -644,27 +642,27 @@ __device__ __forceinline__ void dequant_units_body(const DequantJob& a, uint32_t
 
 // One dequantising job in a workgroup of THREADS lanes: the body for its bit width
 // and for with / without previous messages.
-template <int DT, int BITS, int UNROLL, int THREADS, bool LOOPS>
+template <int DT, int BITS, int UNROLL, int THREADS, bool LOOPS, bool THROUGH>
 __device__ __forceinline__ void dequant_job_bits(const DequantJob& a, uint32_t bx, uint32_t by) {
     if constexpr (UnitLayout<DT>::value) {
         if (a.cps <= kMaxUnitChunks) {                   // else the unit index would pass 32 bits
-            if (a.m_buf) dequant_units_body<BITS, 2 * UNROLL, true, THREADS, LOOPS>(a, bx, by);
-            else dequant_units_body<BITS, 2 * UNROLL, false, THREADS, LOOPS>(a, bx, by);
+            if (a.m_buf) dequant_units_body<BITS, 2 * UNROLL, true, THREADS, LOOPS, THROUGH>(a, bx, by);
+            else dequant_units_body<BITS, 2 * UNROLL, false, THREADS, LOOPS, THROUGH>(a, bx, by);
             return;
         }
     }
-    if (a.m_buf) dequant_flat_body<DT, BITS, UNROLL, true, THREADS, LOOPS>(a, bx, by);
-    else dequant_flat_body<DT, BITS, UNROLL, false, THREADS, LOOPS>(a, bx, by);
+    if (a.m_buf) dequant_flat_body<DT, BITS, UNROLL, true, THREADS, LOOPS, THROUGH>(a, bx, by);
+    else dequant_flat_body<DT, BITS, UNROLL, false, THREADS, LOOPS, THROUGH>(a, bx, by);
 }
 
-template <int DT, int UNROLL, int THREADS, bool LOOPS = true>
+template <int DT, int UNROLL, int THREADS, bool LOOPS, bool THROUGH>
 __device__ __forceinline__ void dequant_job(const DequantJob& a, uint32_t bx, uint32_t by) {
     switch (a.bits) {                                    // uniform over the workgroup
-    case 2: dequant_job_bits<DT, 2, UNROLL, THREADS, LOOPS>(a, bx, by); break;
-    case 3: dequant_job_bits<DT, 3, UNROLL, THREADS, LOOPS>(a, bx, by); break;
-    case 4: dequant_job_bits<DT, 4, UNROLL, THREADS, LOOPS>(a, bx, by); break;
-    case 6: dequant_job_bits<DT, 6, UNROLL, THREADS, LOOPS>(a, bx, by); break;
-    default: dequant_job_bits<DT, 8, UNROLL, THREADS, LOOPS>(a, bx, by); break;
+    case 2: dequant_job_bits<DT, 2, UNROLL, THREADS, LOOPS, THROUGH>(a, bx, by); break;
+    case 3: dequant_job_bits<DT, 3, UNROLL, THREADS, LOOPS, THROUGH>(a, bx, by); break;
+    case 4: dequant_job_bits<DT, 4, UNROLL, THREADS, LOOPS, THROUGH>(a, bx, by); break;
+    case 6: dequant_job_bits<DT, 6, UNROLL, THREADS, LOOPS, THROUGH>(a, bx, by); break;
+    default: dequant_job_bits<DT, 8, UNROLL, THREADS, LOOPS, THROUGH>(a, bx, by); break;
     }
 }
 
@@ -745,31 +743,37 @@ enum TableKind {
 
 // One quantising job in a team kernel: the body for its bit width and for with /
 // without previous messages.
-template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool LOOPS>
+template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool LOOPS, bool THROUGH>
 __device__ __forceinline__ void quant_job_bits(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
-    if (a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, false, LOOPS>(a, bx, by, wave_max);
-    else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false, false, LOOPS>(a, bx, by, wave_max);
+    if (a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, false, LOOPS, THROUGH>(a, bx, by, wave_max);
+    else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false, false, LOOPS, false>(a, bx, by, wave_max);
 }
 
-template <int DT, int ROUND, int TEAM, int CPL, int KIND>
+template <int DT, int ROUND, int TEAM, int CPL, int KIND, bool THROUGH>
 __device__ __forceinline__ void quant_job(const QuantJob& a, uint32_t bx, uint32_t by, float* wave_max) {
     constexpr bool LOOPS = KIND == kTableLoops || KIND == kTableLoopsThree;
     if constexpr (KIND == kTableOneStepThree || KIND == kTableLoopsThree) {
         if (a.bits == 3) {                               // uniform over the workgroup
-            quant_job_bits<DT, 3, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max);
+            quant_job_bits<DT, 3, ROUND, TEAM, CPL, LOOPS, THROUGH>(a, bx, by, wave_max);
             return;
         }
     }
     switch (a.bits) {
-    case 2: quant_job_bits<DT, 2, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max); break;
-    case 4: quant_job_bits<DT, 4, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max); break;
-    case 6: quant_job_bits<DT, 6, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max); break;
-    default: quant_job_bits<DT, 8, ROUND, TEAM, CPL, LOOPS>(a, bx, by, wave_max); break;
+    case 2: quant_job_bits<DT, 2, ROUND, TEAM, CPL, LOOPS, THROUGH>(a, bx, by, wave_max); break;
+    case 4: quant_job_bits<DT, 4, ROUND, TEAM, CPL, LOOPS, THROUGH>(a, bx, by, wave_max); break;
+    case 6: quant_job_bits<DT, 6, ROUND, TEAM, CPL, LOOPS, THROUGH>(a, bx, by, wave_max); break;
+    default: quant_job_bits<DT, 8, ROUND, TEAM, CPL, LOOPS, THROUGH>(a, bx, by, wave_max); break;
     }
 }
 
-// The quantising jobs of one rounding mode and team shape plus any dequantising jobs.
-template <int DT, int ROUND, int TEAM, int CPL, int KIND>
+// The quantising jobs of one rounding mode and team shape plus any dequantising jobs.  THROUGH: how
+// their m and out are stored (see store16).  It is a constant of the kernel: as a field of the job, a
+// branch at every store keeps the compiler from interleaving the stores with the arithmetic.  Time
+// slots, field -> constant: float32 [16,512,2048] G = 128, stochastic, 107.0 -> 101.8 us, [8,250,1536]
+// G = 256 20.6 -> 20.2, [11,130,3392] G = 64 33.0 -> 32.4, float16 [8,512,2048] G = 64 28.9 -> 27.9.
+// (Two bodies in one kernel, picked by the field, are no way out: the compiler then copies the job
+// table to every lane's scratch memory.)
+template <int DT, int ROUND, int TEAM, int CPL, int KIND, bool THROUGH>
 __global__ __launch_bounds__((TEAM > kWave ? TEAM : kBlock))
 void codec_jobs_kernel(const JobTable t) {
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
@@ -786,19 +790,19 @@ void codec_jobs_kernel(const JobTable t) {
         const int j = job_of_block(qs, t.n_quant, b);
         const QuantJob& a = t.q[j];
         place_in_job(b - start_of_job(qs, j), a.grid_x, a.rcp_grid_x, bx, by);
-        quant_job<DT, ROUND, TEAM, CPL, KIND>(a, bx, by, wave_max);
+        quant_job<DT, ROUND, TEAM, CPL, KIND, THROUGH>(a, bx, by, wave_max);
     } else {
         const BlockStarts ds = block_starts(t.d_block0);
         const int j = job_of_block(ds, t.n_dequant, b);
         const DequantJob& d = t.d[j];
         place_in_job(b - start_of_job(ds, j), d.grid_x, d.rcp_grid_x, bx, by);
         constexpr bool LOOPS = KIND == kTableLoops || KIND == kTableLoopsThree;
-        dequant_job<DT, kHostedDequantUnroll, kThreads, LOOPS>(d, bx, by);
+        dequant_job<DT, kHostedDequantUnroll, kThreads, LOOPS, THROUGH>(d, bx, by);
     }
 }
 
 // Dequantising jobs alone.
-template <int DT, int UNROLL>
+template <int DT, int UNROLL, bool THROUGH>
 __global__ __launch_bounds__(kBlock)
 void dequant_jobs_kernel(const JobTable t) {
     const uint32_t b = blockIdx.x;
@@ -809,7 +813,7 @@ void dequant_jobs_kernel(const JobTable t) {
     const DequantJob& a = t.d[j];
     uint32_t bx, by;
     place_in_job(b - start_of_job(ds, j), a.grid_x, a.rcp_grid_x, bx, by);
-    dequant_job<DT, UNROLL, kBlock>(a, bx, by);
+    dequant_job<DT, UNROLL, kBlock, true, THROUGH>(a, bx, by);
 }
 
 // ---------------------------------------------------------------------------
@@ -998,16 +1002,17 @@ enum TeamShape {
 
 // A launch of codec_jobs_kernel (the table's quantising jobs all have this rounding
 // mode and team shape) or, with no quantising job, of dequant_jobs_kernel.
-hipError_t launch_codec_jobs(int dtype, int rounding, int shape, TableKind kind, const JobTable& t,
+// `through`: how m and out are stored (loops of teams of a wavefront and more: never).
+hipError_t launch_codec_jobs(int dtype, int rounding, int shape, TableKind kind, bool through, const JobTable& t,
                              hipStream_t stream);
-hipError_t launch_dequant_jobs(int dtype, int unroll, const JobTable& t, hipStream_t stream);
+hipError_t launch_dequant_jobs(int dtype, int unroll, bool through, const JobTable& t, hipStream_t stream);
 hipError_t launch_quant_anyshape(int dtype, int bits, int rounding, const QuantJob& a, hipStream_t stream);
 hipError_t launch_dequant_anyshape(int dtype, const DequantJob& a, hipStream_t stream);
 
 // Per-dtype pieces (defined by AQSGD_INSTANTIATE_DTYPE in the dtype's .hip file).
-template <int DT> hipError_t launch_codec_jobs_dt(int rounding, int shape, TableKind kind, const JobTable& t,
-                                                  hipStream_t stream);
-template <int DT> hipError_t launch_dequant_jobs_dt(int unroll, const JobTable& t, hipStream_t stream);
+template <int DT, bool THROUGH> hipError_t launch_codec_jobs_dt(int rounding, int shape, TableKind kind, const JobTable& t,
+                                                                hipStream_t stream);
+template <int DT, bool THROUGH> hipError_t launch_dequant_jobs_dt(int unroll, const JobTable& t, hipStream_t stream);
 template <int DT> hipError_t launch_quant_anyshape_dt(int bits, int rounding, const QuantJob& a,
                                                       hipStream_t stream);
 template <int DT> hipError_t launch_dequant_anyshape_dt(const DequantJob& a, hipStream_t stream);

@@ -40,10 +40,11 @@ static_assert(sizeof(JobTable) == 2000, "the size named above");
 // last kind is the first with m written through the L2 (see store16); it holds no bodies without m.
 enum SingleKind { kSingleWhole = 0, kSingleThree, kSingleOdd, kSingleOddLoops, kSingleThrough };
 
-template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool ODD, bool LOOPS, bool HAS_BUF = false>
+template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool ODD, bool LOOPS, bool THROUGH = false>
 __device__ __forceinline__ void single_quant_bits(const QuantJob& a, float* wave_max) {
-    if (HAS_BUF || a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, ODD, LOOPS>(a, blockIdx.x, blockIdx.y, wave_max);
-    else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false, ODD, LOOPS>(a, blockIdx.x, blockIdx.y, wave_max);
+    const uint32_t bx = blockIdx.x, by = blockIdx.y;
+    if (THROUGH || a.m_buf) quant_team_body<DT, BITS, ROUND, TEAM, CPL, true, ODD, LOOPS, THROUGH>(a, bx, by, wave_max);
+    else quant_team_body<DT, BITS, ROUND, TEAM, CPL, false, ODD, LOOPS, false>(a, bx, by, wave_max);
 }
 
 template <int DT, int ROUND, int TEAM, int CPL, int KIND>
@@ -52,30 +53,28 @@ void quant_single_kernel(AQSGD_QUANT_ARGS) {
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
     constexpr bool LOOPS = KIND == kSingleOddLoops;
     constexpr bool ODD = KIND == kSingleOdd || LOOPS;
-    constexpr bool HAS_BUF = KIND == kSingleThrough;
+    constexpr bool THROUGH = KIND == kSingleThrough;
     [[maybe_unused]] __shared__ float wave_max[kThreads / kWave];
     QuantJob a;
     a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
     a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
     a.cpg = static_cast<int32_t>((static_cast<uint32_t>(group) + kChunk - 1) / kChunk);
-    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f; a.through = KIND == kSingleThrough;
+    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f;
     a.seed = seed; a.seen = seen; a.first = first; a.stamp = stamp;
     if constexpr (KIND == kSingleThree) {
         single_quant_bits<DT, 3, ROUND, TEAM, CPL, false, false>(a, wave_max);
     } else {
         switch (bits) {                                  // uniform over the launch
-        case 2: single_quant_bits<DT, 2, ROUND, TEAM, CPL, ODD, LOOPS, HAS_BUF>(a, wave_max); break;
-        case 4: single_quant_bits<DT, 4, ROUND, TEAM, CPL, ODD, LOOPS, HAS_BUF>(a, wave_max); break;
-        case 6: single_quant_bits<DT, 6, ROUND, TEAM, CPL, ODD, LOOPS, HAS_BUF>(a, wave_max); break;
-        default: single_quant_bits<DT, 8, ROUND, TEAM, CPL, ODD, LOOPS, HAS_BUF>(a, wave_max); break;
+        case 2: single_quant_bits<DT, 2, ROUND, TEAM, CPL, ODD, LOOPS, THROUGH>(a, wave_max); break;
+        case 4: single_quant_bits<DT, 4, ROUND, TEAM, CPL, ODD, LOOPS, THROUGH>(a, wave_max); break;
+        case 6: single_quant_bits<DT, 6, ROUND, TEAM, CPL, ODD, LOOPS, THROUGH>(a, wave_max); break;
+        default: single_quant_bits<DT, 8, ROUND, TEAM, CPL, ODD, LOOPS, THROUGH>(a, wave_max); break;
         }
     }
 }
 
-// THROUGH: how m and out are stored (see store16).  A constant in these kernels, not a field of the job as
-// in the shared launches: a branch at every store costs a message of this size 1 to 2 % (first visits
-// of float16 [4,1024,1600] 17.6 -> 18.0 us).  Large reconstructions write through; the quantising
-// side has a kind of its own for it (kSingleThrough).
+// THROUGH: how m and out are stored (see store16), a constant as in the shared launches.  Large
+// reconstructions write through; the quantising side has a kind of its own for it (kSingleThrough).
 template <int DT, int UNROLL, bool THROUGH>
 __global__ __launch_bounds__(kBlock)
 void dequant_single_kernel(AQSGD_DEQUANT_ARGS) {
@@ -83,9 +82,9 @@ void dequant_single_kernel(AQSGD_DEQUANT_ARGS) {
     a.codes = codes; a.scales = scales; a.ids = ids; a.m_buf = m_buf; a.out = out; a.full = full;
     a.n_per = n_per; a.gps = gps; a.cps = n_per >> 3; a.batch = batch; a.group = group;
     a.cpg = static_cast<int32_t>(static_cast<uint32_t>(group) / kChunk); a.bits = bits;
-    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f; a.through = THROUGH;
+    a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f;
     a.seen = seen; a.stamp = stamp;
-    dequant_job<DT, UNROLL, kBlock, false>(a, blockIdx.x, blockIdx.y);
+    dequant_job<DT, UNROLL, kBlock, false, THROUGH>(a, blockIdx.x, blockIdx.y);
 }
 
 template <typename Kernel>
@@ -122,21 +121,21 @@ static hipError_t launch_quant_single_shape(int shape, const QuantJob& a, hipStr
 }
 
 template <int DT, int ROUND>
-static hipError_t launch_quant_single_kind(int shape, bool covers, const QuantJob& a, hipStream_t s) {
+static hipError_t launch_quant_single_kind(int shape, bool covers, bool through, const QuantJob& a, hipStream_t s) {
     if (!covers && a.group % kChunk != 0) return launch_quant_single_shape<DT, ROUND, kSingleOddLoops>(shape, a, s);
     if (!covers) return hipErrorInvalidValue;
     if (a.group % kChunk != 0) return launch_quant_single_shape<DT, ROUND, kSingleOdd>(shape, a, s);
     if (a.bits == 3) return launch_quant_single_shape<DT, ROUND, kSingleThree>(shape, a, s);
-    if (a.through && a.m_buf) return launch_quant_single_shape<DT, ROUND, kSingleThrough>(shape, a, s);
+    if (through && a.m_buf) return launch_quant_single_shape<DT, ROUND, kSingleThrough>(shape, a, s);
     return launch_quant_single_shape<DT, ROUND, kSingleWhole>(shape, a, s);
 }
 
-// `covers`: the job's rectangle has a workgroup for every sample and step.
+// `covers`: the job's rectangle has a workgroup for every sample and step; `through`: how m is stored.
 template <int DT>
-hipError_t launch_quant_single_dt(int rounding, int shape, bool covers, const QuantJob& a, hipStream_t s) {
+hipError_t launch_quant_single_dt(int rounding, int shape, bool covers, bool through, const QuantJob& a, hipStream_t s) {
     return rounding == AQSGD_ROUND_STOCHASTIC
-               ? launch_quant_single_kind<DT, AQSGD_ROUND_STOCHASTIC>(shape, covers, a, s)
-               : launch_quant_single_kind<DT, AQSGD_ROUND_NEAREST>(shape, covers, a, s);
+               ? launch_quant_single_kind<DT, AQSGD_ROUND_STOCHASTIC>(shape, covers, through, a, s)
+               : launch_quant_single_kind<DT, AQSGD_ROUND_NEAREST>(shape, covers, through, a, s);
 }
 
 template <typename Kernel>
@@ -156,13 +155,13 @@ static hipError_t launch_dequant_single_unroll(int unroll, const DequantJob& a, 
 }
 
 template <int DT>
-hipError_t launch_dequant_single_dt(int unroll, const DequantJob& a, hipStream_t s) {
-    return a.through ? launch_dequant_single_unroll<DT, true>(unroll, a, s)
-                     : launch_dequant_single_unroll<DT, false>(unroll, a, s);
+hipError_t launch_dequant_single_dt(int unroll, bool through, const DequantJob& a, hipStream_t s) {
+    return through ? launch_dequant_single_unroll<DT, true>(unroll, a, s)
+                   : launch_dequant_single_unroll<DT, false>(unroll, a, s);
 }
 
 #define AQSGD_INSTANTIATE_SINGLE_DTYPE(DT)                                                        \
-    template hipError_t launch_quant_single_dt<DT>(int, int, bool, const QuantJob&, hipStream_t); \
-    template hipError_t launch_dequant_single_dt<DT>(int, const DequantJob&, hipStream_t);
+    template hipError_t launch_quant_single_dt<DT>(int, int, bool, bool, const QuantJob&, hipStream_t); \
+    template hipError_t launch_dequant_single_dt<DT>(int, bool, const DequantJob&, hipStream_t);
 
 }  // namespace aqsgd

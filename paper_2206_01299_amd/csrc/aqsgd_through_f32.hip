@@ -1,0 +1,6 @@
+// Kernels of large shared launches, which write through the L2, instantiated for f32 activations, buffers and outputs.
+#include "aqsgd_instantiate.h"
+
+namespace aqsgd {
+AQSGD_INSTANTIATE_TABLES(AQSGD_F32, true)
+}

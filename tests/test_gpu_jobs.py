@@ -298,6 +298,34 @@ def test_time_slots_of_odd_and_wide_groups(H, case):
             b.verify(f"{case} boundary {i} slot {step}")
 
 
+@pytest.mark.parametrize("dtype,bits,group,rounding,batch,n_per,boundaries", [
+    ("f32", 4, 4096, 0, 3, 4096 * 60, 4),                # one step a workgroup
+    ("f16", 3, 1600, 1, 3, 1600 * 512, 2),
+    ("bf16", 2, 64, 1, 3, 64 * 16400, 2),                # teams below a wavefront: one step, ...
+    ("f32", 3, 128, 0, 4, 128 * 8200, 2),
+    ("f32", 4, 128, 1, 8, 128 * 8200, 1),                # ... and loops
+    ("f16", 6, 32, 0, 3, 64 * 16400, 2),                 # groups of half a line: streaming
+], ids=str)
+def test_time_slots_that_write_more_than_24_mib(H, dtype, bits, group, rounding, batch, n_per, boundaries):
+    """Shared launches from the size at which those of whole 128-byte lines write through the L2."""
+    eb = 4 if dtype == "f32" else 2
+    assert boundaries * batch * n_per * eb * 4 > 24 << 20
+    rng = np.random.default_rng(group)
+    bs = [Boundary(H, rng, dtype, bits, group, rounding, 8, group, rounding, batch, n_per, n_rows=batch + 1, seed=50 + i)
+          for i in range(boundaries)]
+    for step in range(3):
+        jobs = []
+        for b in bs:
+            if step >= 2:
+                jobs.append(b.grad_dequant_job())
+            if step >= 1:
+                jobs += [b.decode_job(), b.grad_quant_job()]
+            jobs.append(b.encode_job(step))
+        B.run_jobs(jobs)
+        for i, b in enumerate(bs):
+            b.verify(f"{dtype} G{group} boundary {i} slot {step}")
+
+
 def test_a_bad_job_stops_the_whole_call_before_any_launch(H):
     rng = np.random.default_rng(7)
     b = Boundary(H, rng, "f16", 4, 256, 0, 8, 256, 0, 2, 256 * 5, n_rows=4, seed=1)

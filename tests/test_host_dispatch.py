@@ -67,3 +67,41 @@ def test_shared_launches_stay_below_the_lanes_of_a_grid(client, lead):
         assert grid[0] * block < 1 << 32, (grid, block, kernel)
     one, status = client(lead, ride)                     # as before where it fits
     assert status == 0 and len(one) == 1 and "jobs_kernel" in one[0][2]
+
+
+def _slot(dtype, batch, n_per, group, boundaries=1):
+    return [(kind, dtype, bits, 0, batch, n_per, group) for _ in range(boundaries)
+            for kind, bits in ((ENCODE, 4), (DECODE, 4), (GRAD_QUANT, 8), (GRAD_DEQUANT, 8))]
+
+
+@pytest.mark.parametrize("dtype,batch,n_per,group,boundaries,through", [
+    (F16, 4, 1024 * 1600, 1600, 1, True),        # 62 MB written, whole 128-byte lines
+    (F32, 8, 128 * 4096, 4096, 4, True),
+    (F32, 16, 512 * 2048, 128, 1, True),
+    (F32, 11, 130 * 3392, 64, 1, True),
+    (F16, 8, 512 * 2048, 64, 1, True),           # teams below a wavefront that loop
+    (F16, 4, 250 * 1024, 1024, 1, False),        # 10 MB
+    (BF16, 18, 175 * 128, 128, 4, False),
+    (F16, 8, 1001 * 1000, 1000, 1, False),       # rows of 2000 bytes
+    (F32, 4, 2048 * 2704, 2704, 4, False),
+    (F16, 8, 512 * 2048, 32, 1, False),          # groups of half a line
+])
+def test_large_shared_launches_of_whole_lines_write_through(client, dtype, batch, n_per, group, boundaries, through):
+    """The store policy is a constant of the kernel (its last template argument), chosen by what the launch writes."""
+    launches, status = client(*_slot(dtype, batch, n_per, group, boundaries))
+    assert status == 0 and all("codec_jobs_kernel<" in k for _, _, k in launches), launches
+    for _, _, kernel in launches:
+        assert kernel.split(">(")[0].endswith(", true" if through else ", false"), kernel
+    alone, status = client((DECODE, dtype, 4, 0, batch, n_per, group), (GRAD_DEQUANT, dtype, 8, 0, batch, n_per, group))
+    assert status == 0 and len(alone) == 1 and "dequant_jobs_kernel<" in alone[0][2]
+
+
+def test_launches_that_loop_have_a_kernel_for_every_store_policy(client):
+    """More samples than a grid has rows: kernels that loop, of teams below and above a wavefront."""
+    for group in (64, 128, 256, 512, 1024, 1536, 2048, 4096, 8192, 16384, 32768):
+        for dtype in (F32, F16, BF16):
+            for bits in (3, 4):
+                n_per = group * max(1, 4096 // group)
+                launches, status = client((ENCODE, dtype, bits, 0, 70001, n_per, group),
+                                          (DECODE, dtype, bits, 1, 70001, n_per, group))
+                assert status == 0 and len(launches) == 1, (group, dtype, launches, status)
