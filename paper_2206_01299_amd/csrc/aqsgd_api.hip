@@ -579,15 +579,22 @@ bool writes_through(const DequantJob& a, int dtype) {
     return bytes_written(a, eb) >= kThroughBytes && whole_lines(a, eb);
 }
 
-// An encode alone stores half as much for what it reads, and its line lies higher (a row of four calls,
-// through -> streaming: m of 67 MB, float32 [4,1024,4096] 95.6 -> 96.0 us; 268 MB, float32 [8,2048,4096]
-// 357.5 -> 358.9, float16 379.5 -> 380.4; but of 28 MB, bfloat16 [22,547,1152] 49.6 -> 48.7, and of 39 MB,
-// [15,2048,640] at 8 bits 69.8 -> 69.5).  Groups that are no octets and 3 bits always stream.
-constexpr int64_t kThroughEncodeBytes = int64_t{64} << 20;
+// An encode alone: time streaming over time through, by the MiB of m it writes (4 bits, G = 64 to 4096, both
+// roundings, geometric means over seven to twenty of them; the same rows every time, which the last-level
+// cache keeps, and others every time, which it does not):
+//                          2      8-10     12-14     16-18      22      28-40
+//   16 bits  same rows   0.89   0.92-0.94 0.95-0.97 1.02-1.03  1.05   1.03-1.04
+//            others      0.99   0.98-1.00   1.00    0.99-1.00  1.00     1.02
+//   float32  same rows   0.88   0.79-0.80 0.79-0.87 0.95-0.97  1.00     1.02
+//            others      0.97     1.00    0.99-1.00   0.99     0.99   1.00-1.01
+// and beyond, m of 67 MB and more, others 1.01 to 1.02 (one float32 [8,2048,4096] 125.9 us through, 127.7
+// streaming, float16 [16,2048,2048] 64.3 and 65.5).  The lines lie at 16 and 22 MiB of m.  3 bits the same:
+// bfloat16 [8,1024,2048] G = 256, 1.02 and 1.01, stochastic 1.07 and 1.02.  Groups that are no octets stream.
+constexpr int64_t through_encode_bytes(int dtype) { return int64_t{dtype == AQSGD_F32 ? 24 : 20} << 20; }
 
 bool writes_through(const QuantJob& a, int dtype) {
     const int64_t eb = dtype == AQSGD_F32 ? 4 : 2;
-    return a.m_buf && bytes_written(a, eb) >= kThroughEncodeBytes && whole_lines(a, eb);
+    return a.m_buf && bytes_written(a, eb) >= through_encode_bytes(dtype) && whole_lines(a, eb);
 }
 
 // A table's jobs are stored alike: through if all that hold such stores are of whole lines.

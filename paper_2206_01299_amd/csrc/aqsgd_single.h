@@ -37,8 +37,8 @@ static_assert(sizeof(JobTable) == 2000, "the size named above");
 // Which bodies a quantising kernel holds: as in the shared launches the 3-bit ones, which
 // need more registers, are apart; odd groups have bodies of their own, and two kernels, for
 // they have no table to go out with when a grid cannot hold one workgroup for every step.  The
-// last kind is the first with m written through the L2 (see store16); it holds no bodies without m.
-enum SingleKind { kSingleWhole = 0, kSingleThree, kSingleOdd, kSingleOddLoops, kSingleThrough };
+// last kinds are the first two with m written through the L2 (see store16); they hold no bodies without m.
+enum SingleKind { kSingleWhole = 0, kSingleThree, kSingleOdd, kSingleOddLoops, kSingleThrough, kSingleThreeThrough };
 
 template <int DT, int BITS, int ROUND, int TEAM, int CPL, bool ODD, bool LOOPS, bool THROUGH = false>
 __device__ __forceinline__ void single_quant_bits(const QuantJob& a, float* wave_max) {
@@ -53,7 +53,7 @@ void quant_single_kernel(AQSGD_QUANT_ARGS) {
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
     constexpr bool LOOPS = KIND == kSingleOddLoops;
     constexpr bool ODD = KIND == kSingleOdd || LOOPS;
-    constexpr bool THROUGH = KIND == kSingleThrough;
+    constexpr bool THROUGH = KIND == kSingleThrough || KIND == kSingleThreeThrough;
     [[maybe_unused]] __shared__ float wave_max[kThreads / kWave];
     QuantJob a;
     a.src = src; a.ids = ids; a.m_buf = m_buf; a.codes = codes; a.scales = scales;
@@ -61,8 +61,8 @@ void quant_single_kernel(AQSGD_QUANT_ARGS) {
     a.cpg = static_cast<int32_t>((static_cast<uint32_t>(group) + kChunk - 1) / kChunk);
     a.grid_x = grid_x; a.grid_y = grid_y; a.rcp_grid_x = 0.0f;
     a.seed = seed; a.seen = seen; a.first = first; a.stamp = stamp;
-    if constexpr (KIND == kSingleThree) {
-        single_quant_bits<DT, 3, ROUND, TEAM, CPL, false, false>(a, wave_max);
+    if constexpr (KIND == kSingleThree || KIND == kSingleThreeThrough) {
+        single_quant_bits<DT, 3, ROUND, TEAM, CPL, false, false, THROUGH>(a, wave_max);
     } else {
         switch (bits) {                                  // uniform over the launch
         case 2: single_quant_bits<DT, 2, ROUND, TEAM, CPL, ODD, LOOPS, THROUGH>(a, wave_max); break;
@@ -74,7 +74,7 @@ void quant_single_kernel(AQSGD_QUANT_ARGS) {
 }
 
 // THROUGH: how m and out are stored (see store16), a constant as in the shared launches.  Large
-// reconstructions write through; the quantising side has a kind of its own for it (kSingleThrough).
+// reconstructions write through; the quantising side has kinds of its own for it (SingleKind).
 template <int DT, int UNROLL, bool THROUGH>
 __global__ __launch_bounds__(kBlock)
 void dequant_single_kernel(AQSGD_DEQUANT_ARGS) {
@@ -125,8 +125,10 @@ static hipError_t launch_quant_single_kind(int shape, bool covers, bool through,
     if (!covers && a.group % kChunk != 0) return launch_quant_single_shape<DT, ROUND, kSingleOddLoops>(shape, a, s);
     if (!covers) return hipErrorInvalidValue;
     if (a.group % kChunk != 0) return launch_quant_single_shape<DT, ROUND, kSingleOdd>(shape, a, s);
+    if (through && a.m_buf)
+        return a.bits == 3 ? launch_quant_single_shape<DT, ROUND, kSingleThreeThrough>(shape, a, s)
+                           : launch_quant_single_shape<DT, ROUND, kSingleThrough>(shape, a, s);
     if (a.bits == 3) return launch_quant_single_shape<DT, ROUND, kSingleThree>(shape, a, s);
-    if (through && a.m_buf) return launch_quant_single_shape<DT, ROUND, kSingleThrough>(shape, a, s);
     return launch_quant_single_shape<DT, ROUND, kSingleWhole>(shape, a, s);
 }
 

@@ -96,11 +96,20 @@ def test_long_samples_cross_block_strides(H):
     H.replay_and_compare(cfg, calls_per_epoch=2, epochs=2, log=lambda *a, **k: None)
 
 
-@pytest.mark.parametrize("dtype,bits,group,rounding,gps", [
-    ("f32", 8, 4096, W.NEAREST, 2081), ("f32", 2, 64, W.STOCHASTIC, 131137), ("f16", 4, 128, W.STOCHASTIC, 131200),
-    ("bf16", 6, 1600, W.NEAREST, 10500), ("f32", 4, 4096, W.NEAREST, 1900)])
-def test_messages_at_the_size_where_encode_writes_through(H, dtype, bits, group, rounding, gps):
-    """Two samples a call; 64 MiB of previous messages and codes is the line, the last lies below it."""
+@pytest.mark.parametrize("dtype,bits,group,rounding,gps,through", [
+    ("f32", 8, 4096, W.NEAREST, 2081, True), ("f32", 2, 64, W.STOCHASTIC, 131137, True),
+    ("f16", 4, 128, W.STOCHASTIC, 131200, True), ("bf16", 6, 1600, W.NEAREST, 10500, True),
+    # either side of the line: 24 MiB of previous messages and codes in float32, 20 MiB in the 16-bit types
+    ("f32", 4, 4096, W.NEAREST, 683, True), ("f32", 4, 4096, W.NEAREST, 682, False),
+    ("f32", 3, 256, W.STOCHASTIC, 11236, True), ("f32", 3, 256, W.STOCHASTIC, 11234, False),
+    ("bf16", 3, 64, W.STOCHASTIC, 68986, True), ("bf16", 3, 64, W.STOCHASTIC, 68984, False),
+    ("f16", 4, 1600, W.NEAREST, 2622, True), ("f16", 4, 1600, W.NEAREST, 2620, False),
+    ("bf16", 8, 4096, W.NEAREST, 854, True), ("bf16", 8, 4096, W.NEAREST, 853, False)])
+def test_messages_at_the_size_where_encode_writes_through(H, dtype, bits, group, rounding, gps, through):
+    """Two samples a call, rows and groups of whole 128-byte lines."""
+    eb, line = (4, 24 << 20) if dtype == "f32" else (2, 20 << 20)
+    assert gps * group * eb % 128 == 0 and group * eb % 128 == 0
+    assert (2 * gps * group * (8 * eb + bits) // 8 >= line) == through
     cfg = _case_cfg(dtype, bits, group, rounding, gps, batch=2, n_samples=2)
     H.replay_and_compare(cfg, calls_per_epoch=1, epochs=2, log=lambda *a, **k: None)
 

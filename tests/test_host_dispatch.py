@@ -105,3 +105,20 @@ def test_launches_that_loop_have_a_kernel_for_every_store_policy(client):
                 launches, status = client((ENCODE, dtype, bits, 0, 70001, n_per, group),
                                           (DECODE, dtype, bits, 1, 70001, n_per, group))
                 assert status == 0 and len(launches) == 1, (group, dtype, launches, status)
+
+
+@pytest.mark.parametrize("dtype,bits,group,rows,through", [
+    (F32, 4, 4096, 1366, True), (F32, 4, 4096, 1365, False),         # 24 MiB of m and codes
+    (F16, 4, 1600, 5243, True), (F16, 4, 1600, 5242, False),         # 20 MiB
+    (BF16, 3, 64, 137971, True), (BF16, 3, 64, 137970, False),
+    (F16, 4, 1000, 20000, False), (F16, 4, 32, 600000, False),       # rows, groups that are no whole lines
+    (F16, 4, 1020, 20000, False),                                    # groups that are no octets
+])
+def test_large_encodes_alone_write_through(client, dtype, bits, group, rows, through):
+    kinds = {0: "streaming", 1: "3 bits, streaming", 2: "odd, streaming", 4: "through", 5: "3 bits, through"}
+    launches, status = client((ENCODE, dtype, bits, 0, 1, rows * group, group), options=("alone",))
+    assert status == 0 and len(launches) == 1
+    kernel = launches[0][2].split("quant_single_kernel<")[1].split(">(")[0]
+    assert kinds[int(kernel.split(",")[-1])].endswith("through" if through else "streaming"), kernel
+    grads, status = client((GRAD_QUANT, dtype, bits, 0, 1, rows * group, group), options=("alone",))
+    assert status == 0 and int(grads[0][2].split("quant_single_kernel<")[1].split(">(")[0].split(",")[-1]) in (0, 1, 2)
