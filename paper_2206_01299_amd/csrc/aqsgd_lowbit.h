@@ -31,6 +31,7 @@ struct LowbitArgs {
     int32_t group;
     int32_t cpg;
     int32_t stochastic;        // sender: rounding mode of the message
+    int32_t through;           // receiver of a 16-bit type: out is written through the L2
     uint64_t seed;
 };
 
@@ -129,7 +130,7 @@ __device__ __forceinline__ uint32_t load_tail_level(const uint8_t* base, int l) 
 // occupancy per SIMD and with it the chance to hold a whole launch on the chip at a time.
 // TAIL (one-wave teams, 16-bit activations, nearest rounding): the group is CPL whole rounds
 // and `tail_entries` more elements, one per lane (see above).
-template <int DT, int BITS, int MBITS, int ROUND, int TEAM, int CPL, bool SENDER, bool TAIL = false>
+template <int DT, int BITS, int MBITS, int ROUND, int TEAM, int CPL, bool SENDER, bool THROUGH, bool TAIL = false>
 __device__ __forceinline__ void lowbit_team_group(const LowbitArgs& a, const char* act_s, char* out_s,
                                                   uint8_t* mcodes_s, float* mscales_s, uint8_t* codes_s,
                                                   float* scales_s, int64_t src0, int64_t g,
@@ -302,7 +303,7 @@ __device__ __forceinline__ void lowbit_team_group(const LowbitArgs& a, const cha
 #pragma unroll
         for (int e = 0; e < kChunk; ++e) q2[e] = level_of<MBITS, AQSGD_ROUND_NEAREST>(v[k][e], ssc, kNearestOffset32);
         store_codes_at<MBITS>(m_group + cc[k] * static_cast<uint32_t>(MBITS), pack_levels<MBITS>(q2));
-        if constexpr (!SENDER) store_raw_at<DT>(out_s + goff * kEB + cc[k] * kChunkBytes, pack_raw<DT>(v[k]), false);
+        if constexpr (!SENDER) store_raw_at<DT>(out_s + goff * kEB + cc[k] * kChunkBytes, pack_raw<DT>(v[k]), THROUGH);
     }
     if constexpr (TAIL) {
         const float q2 = level_of<MBITS, AQSGD_ROUND_NEAREST>(tail_v, ssc, kNearestOffset32);
@@ -314,8 +315,9 @@ __device__ __forceinline__ void lowbit_team_group(const LowbitArgs& a, const cha
     if (lane_in_team == 0) mscales_s[g] = ssc.s_tx;
 }
 
-// MODE: which side and, for the sender, how the message is rounded.
-enum LowbitMode { kLbReceiver = 0, kLbSenderNearest = 1, kLbSenderStochastic = 2 };
+// MODE: which side and, for the sender, how the message is rounded; for the receiver, how its output
+// is stored (see store16; 16-bit types, those of binary32 are ordinary stores).
+enum LowbitMode { kLbReceiver = 0, kLbSenderNearest = 1, kLbSenderStochastic = 2, kLbReceiverThrough = 3 };
 
 // Four waves per SIMD hold a whole GPT2-sized launch (one wave per row) on the chip at
 // once; the hint makes the register allocator aim for that.
@@ -330,7 +332,8 @@ void lowbit_team_kernel(void* data, const int64_t* ids, uint8_t* m_codes, float*
     a.act = data; a.out = data; a.ids = ids; a.m_codes = m_codes; a.m_scales = m_scales; a.codes = codes;
     a.scales = scales; a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.cpg = cpg;
     a.stochastic = MODE == kLbSenderStochastic; a.seed = seed;
-    constexpr bool SENDER = MODE != kLbReceiver;
+    constexpr bool SENDER = MODE == kLbSenderNearest || MODE == kLbSenderStochastic;
+    constexpr bool THROUGH = MODE == kLbReceiverThrough;
     constexpr int ROUND = MODE == kLbSenderStochastic ? AQSGD_ROUND_STOCHASTIC : AQSGD_ROUND_NEAREST;
     constexpr bool kMultiWave = TEAM > kWave;
     constexpr int kThreads = TEAM > kWave ? TEAM : kBlock;
@@ -367,7 +370,7 @@ void lowbit_team_kernel(void* data, const int64_t* ids, uint8_t* m_codes, float*
                  gbase += static_cast<int64_t>(gridDim.x) * kTeamsPerBlock) {
                 const int64_t g = gbase + team;
                 if (g < a.gps)
-                    lowbit_team_group<DT, BITS, MBITS, ROUND, TEAM, kRounds, SENDER, true>(
+                    lowbit_team_group<DT, BITS, MBITS, ROUND, TEAM, kRounds, SENDER, THROUGH, true>(
                         a, act_s, out_s, mcodes_s, mscales_s, codes_s, scales_s, src0, g, rc, lane_in_team,
                         wave_max, kChunk * tail_chunks);
             }
@@ -377,7 +380,7 @@ void lowbit_team_kernel(void* data, const int64_t* ids, uint8_t* m_codes, float*
              gbase += static_cast<int64_t>(gridDim.x) * kTeamsPerBlock) {
             const int64_t g = gbase + team;
             if (g < a.gps)
-                lowbit_team_group<DT, BITS, MBITS, ROUND, TEAM, CPL, SENDER>(a, act_s, out_s, mcodes_s,
+                lowbit_team_group<DT, BITS, MBITS, ROUND, TEAM, CPL, SENDER, THROUGH>(a, act_s, out_s, mcodes_s,
                                                                              mscales_s, codes_s, scales_s, src0,
                                                                              g, cc, lane_in_team, wave_max);
         }
@@ -411,7 +414,7 @@ inline bool lowbit_tail_chunks(int cpg, int cpl) {
 // ---- launch table (instantiated per dtype in aqsgd_lowbit_<dtype>.hip) ----------------
 template <int DT, int BITS, int MBITS, int MODE, int TEAM, int CPL, bool TAILK = false>
 static hipError_t launch_lb(LaunchGeom g, const LowbitArgs& a, hipStream_t s) {
-    void* data = MODE == kLbReceiver ? a.out : const_cast<void*>(a.act);
+    void* data = MODE == kLbReceiver || MODE == kLbReceiverThrough ? a.out : const_cast<void*>(a.act);
     return launch_kernel(lowbit_team_kernel<DT, BITS, MBITS, TEAM, CPL, MODE, TAILK>, dim3(g.grid_x, g.grid_y),
                          dim3(TEAM > kWave ? TEAM : kBlock), s, data, a.ids, a.m_codes, a.m_scales, a.codes,
                          a.group, a.cpg, a.n_per, a.scales, a.gps, a.batch, a.seed);
@@ -449,6 +452,10 @@ static hipError_t launch_lb_mode(int mode, int shape, LaunchGeom g, const Lowbit
     case kLbReceiver:         return launch_lb_shape<DT, BITS, MBITS, kLbReceiver>(shape, g, a, s);
     case kLbSenderNearest:    return launch_lb_shape<DT, BITS, MBITS, kLbSenderNearest>(shape, g, a, s);
     case kLbSenderStochastic: return launch_lb_shape<DT, BITS, MBITS, kLbSenderStochastic>(shape, g, a, s);
+    case kLbReceiverThrough:
+        if constexpr (ElemBytes<DT>::value == 2)
+            return launch_lb_shape<DT, BITS, MBITS, kLbReceiverThrough>(shape, g, a, s);
+        [[fallthrough]];
     default:                  return hipErrorInvalidValue;
     }
 }
@@ -456,7 +463,7 @@ static hipError_t launch_lb_mode(int mode, int shape, LaunchGeom g, const Lowbit
 template <int DT, int BITS>
 static hipError_t launch_lb_mbits(int m_bits, int shape, bool sender, LaunchGeom g, const LowbitArgs& a,
                                   hipStream_t s) {
-    const int mode = !sender ? kLbReceiver : (a.stochastic ? kLbSenderStochastic : kLbSenderNearest);
+    const int mode = !sender ? (a.through ? kLbReceiverThrough : kLbReceiver) : (a.stochastic ? kLbSenderStochastic : kLbSenderNearest);
     if (m_bits == 8) return launch_lb_mode<DT, BITS, 8>(mode, shape, g, a, s);
     if (m_bits == 2) return launch_lb_mode<DT, BITS, 2>(mode, shape, g, a, s);
     return hipErrorInvalidValue;

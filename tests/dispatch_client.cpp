@@ -1,7 +1,7 @@
 // A client of the C ABI that stands in for the device runtime's launch call: job lists and single calls go
 // through the library's checks and its dispatch, and every launch is printed instead of made (the pointers
 // are never followed).  Job: kind,dtype,bits,rounding,batch,n_per,group.  Options: "alone" makes each job a
-// call of its own; "starve" lets every allocation fail once something has been launched.
+// call of its own, "lowbit" decodes with previous messages kept at 8 bits; "starve" lets every allocation fail once something has been launched.
 #include <dlfcn.h>
 #include <cxxabi.h>
 
@@ -37,10 +37,11 @@ extern "C" hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void
 }
 
 int main(int argc, char** argv) {
-    bool alone = false;
+    bool alone = false, lowbit = false;
     std::vector<aqsgd_job> jobs;
     for (int i = 1; i < argc; ++i) {
         if (!std::strcmp(argv[i], "alone")) { alone = true; continue; }
+        if (!std::strcmp(argv[i], "lowbit")) { lowbit = true; continue; }
         if (!std::strcmp(argv[i], "starve")) { g_starve = true; continue; }
         int kind, dtype, bits, rounding;
         long batch, n_per;
@@ -58,7 +59,13 @@ int main(int argc, char** argv) {
         jobs.push_back(j);
     }
     int status = 0;
-    if (alone) {
+    if (lowbit) {
+        for (aqsgd_job& j : jobs) {
+            status = aqsgd_decode_lowbit(&j.desc, 8, j.codes, j.scales, j.sample_ids, static_cast<uint8_t*>(j.m_buf), j.scales,
+                                         j.out, nullptr);
+            if (status) break;
+        }
+    } else if (alone) {
         for (aqsgd_job& j : jobs) {
             switch (j.kind) {
             case AQSGD_JOB_ENCODE: status = aqsgd_encode(&j.desc, j.src, j.sample_ids, j.m_buf, j.codes, j.scales, nullptr); break;

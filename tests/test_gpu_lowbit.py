@@ -107,6 +107,18 @@ def test_lowbit_sweep(H, dtype, m_bits):
             _replay(H, _cfg(dtype, bits, group, rounding, gps), m_bits, calls_per_epoch=2, epochs=2)
 
 
+@pytest.mark.parametrize("dtype,bits,m_bits,group,gps,through", [
+    ("f16", 4, 8, 256, 4096, True), ("f16", 4, 8, 256, 4095, False),
+    ("bf16", 3, 2, 1024, 1024, True), ("bf16", 3, 2, 1024, 1023, False),
+    ("bf16", 2, 8, 1600, 656, True),                     # the last round as single elements per lane
+    ("f16", 8, 2, 16384, 64, True), ("bf16", 4, 8, 64, 16384, True),
+    ("f16", 4, 8, 2008, 601, False)])                    # rows that are no whole lines
+def test_lowbit_receivers_around_the_size_that_writes_through(H, dtype, bits, m_bits, group, gps, through):
+    """Two samples a call; 4 MiB of reconstructions in rows and groups of whole 128-byte lines is the line."""
+    assert (2 * gps * group * 2 >= 4 << 20 and group * 2 % 128 == 0) == through
+    _replay(H, _cfg(dtype, bits, group, W.NEAREST, gps, batch=2, n_samples=2), m_bits, calls_per_epoch=1, epochs=2)
+
+
 @pytest.mark.parametrize("dtype,scale", [("f16", 3e-7), ("f16", 2e-5), ("bf16", 1e-37), ("f32", 1e-36)])
 @pytest.mark.parametrize("m_bits", [2, 8])
 def test_lowbit_subnormal_activations(H, dtype, scale, m_bits):

@@ -122,3 +122,18 @@ def test_large_encodes_alone_write_through(client, dtype, bits, group, rows, thr
     assert kinds[int(kernel.split(",")[-1])].endswith("through" if through else "streaming"), kernel
     grads, status = client((GRAD_QUANT, dtype, bits, 0, 1, rows * group, group), options=("alone",))
     assert status == 0 and int(grads[0][2].split("quant_single_kernel<")[1].split(">(")[0].split(",")[-1]) in (0, 1, 2)
+
+
+@pytest.mark.parametrize("dtype,bits,group,rows,through", [
+    (F16, 4, 256, 8192, True), (F16, 4, 256, 8191, False),           # 4 MiB written
+    (BF16, 3, 1024, 2048, True), (BF16, 3, 1024, 2047, False),
+    (BF16, 2, 1600, 1600, True),                                     # one element a lane in the last round
+    (F16, 8, 16384, 512, True), (BF16, 4, 64, 524288, True),
+    (BF16, 4, 2008, 7007, False), (F16, 4, 32, 600000, False),       # rows, groups that are no whole lines
+    (F32, 4, 1024, 8192, False),                                     # ordinary stores
+])
+def test_low_precision_receivers_of_whole_lines_write_through(client, dtype, bits, group, rows, through):
+    launches, status = client((DECODE, dtype, bits, 0, 1, rows * group, group), options=("lowbit",))
+    assert status == 0 and len(launches) == 1
+    mode = launches[0][2].split("lowbit_team_kernel<")[1].split(">(")[0].split(",")[5]
+    assert int(mode) == (3 if through else 0), launches
