@@ -49,13 +49,13 @@ __device__ __forceinline__ void load_piece(const char* p, float (&v)[N]) {
     }
 }
 template <int DT, int N>
-__device__ __forceinline__ void store_piece(char* p, const float (&v)[N]) {
+__device__ __forceinline__ void store_piece(char* p, const float (&v)[N], bool through = false) {
     if constexpr (DT == AQSGD_F32) {
 #pragma unroll
         for (int q = 0; q < N / 4; ++q)
-            store16(p + 16 * q, f32x4_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}, false);
+            store16(p + 16 * q, f32x4_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}, through);
     } else {
-        store16(p, pack_raw<DT>(v).v, false);
+        store16(p, pack_raw<DT>(v).v, through);
     }
 }
 
@@ -84,18 +84,24 @@ __device__ __forceinline__ void unpack_piece(uint64_t w, float (&q)[N]) {
 // previous messages are updated in place: decode of float16 [2,2048,942] 9.1 us that way and 6.5
 // this, [16,400,102] 5.2 and 3.9, grad_dequant of [4,250,1020] 3.6 and 3.2.  Only a sample that is
 // no whole number of pieces ends in such a piece here.
+//
+// SEAMS: a piece may hold two groups.  float32 groups of whole pieces have none, and a body that looks
+// for them costs a grad_dequant a tenth: [8,500,1020] pieces that start with every group 4.29 us, with
+// seams 4.86, without 4.05; [8,1000,1020] 6.46, 7.28, 6.30.
 // ---------------------------------------------------------------------------
 constexpr int kOddUnroll = 2;
 constexpr int64_t kMaxOddPieces = int64_t{1} << 31;      // pieces of a sample: 32-bit indices with room for a step
 
-template <int DT, int BITS, bool HAS_BUF, int THREADS, bool LOOPS>
+template <int DT, int BITS, bool HAS_BUF, bool SEAMS, int THREADS, bool LOOPS, bool THROUGH = false>
 __device__ __forceinline__ void dequant_odd_body(const DequantJob& a, uint32_t bx, uint32_t by) {
     using P = Piece<DT, BITS>;
     constexpr int N = P::elems;
     constexpr int kEB = ElemBytes<DT>::value;
     constexpr uint32_t kStep = THREADS * kOddUnroll;
     const uint32_t group = static_cast<uint32_t>(a.group);
-    const double rcp_group = 1.0 / static_cast<double>(a.group);
+    // one Newton step brings the estimate of 1 / group well below the 2^-32 that a quotient needs
+    const double estimate = __builtin_amdgcn_rcp(static_cast<double>(a.group));
+    const double rcp_group = __builtin_fma(__builtin_fma(-static_cast<double>(a.group), estimate, 1.0), estimate, estimate);
     const float rcp_small = static_cast<float>(rcp_group);
     const uint32_t pps = static_cast<uint32_t>((a.n_per + N - 1) / N);   // pieces per sample: below 2^31, checked by the host
     const int rest = static_cast<int>(a.n_per % N);                      // elements of a last piece that is no whole one
@@ -140,7 +146,7 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a, uint32_t b
                     if (dg * group > x) --dg;
                     else if ((dg + 1) * group <= x) ++dg;
                 }
-                last[u] = rest != 0 && piece == pps - 1;         // ends with the sample, and with its group
+                last[u] = SEAMS && rest != 0 && piece == pps - 1;         // ends with the sample, and with its group
                 at[u] = last[u] ? a.n_per - N : static_cast<int64_t>(piece) * N;
                 left[u] = last[u] ? N : static_cast<int>(group - (x - dg * group));
                 if (fresh) {
@@ -150,7 +156,7 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a, uint32_t b
                 w[u] = load_bytes_any<P::code_bytes>(codes_s + static_cast<uint64_t>(at[u]) * BITS / 8);   // whole bytes
                 const float* s = scales_s + (g0 + dg);
                 scale[u] = s[0];
-                next_scale[u] = s[left[u] < N ? 1 : 0];
+                if constexpr (SEAMS) next_scale[u] = s[left[u] < N ? 1 : 0];
                 if constexpr (HAS_BUF) load_piece<DT, N>(m_s + at[u] * kEB, m[u]);
             }
             __builtin_amdgcn_sched_barrier(0);           // every load is out before the first use
@@ -162,14 +168,18 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a, uint32_t b
                     store_piece<DT, N>(out_s + at[u] * kEB, m[u]);
                     continue;
                 }
-                const GroupScale here = scale_from_wire<BITS>(scale[u]), next = scale_from_wire<BITS>(next_scale[u]);
+                const GroupScale here = scale_from_wire<BITS>(scale[u]);
+                [[maybe_unused]] GroupScale next;
+                if constexpr (SEAMS) next = scale_from_wire<BITS>(next_scale[u]);
                 float v[N];
                 unpack_piece<BITS, N>(w[u], v);
 #pragma unroll
                 for (int e = 0; e < N; ++e) {
-                    GroupScale sc;
-                    sc.offset = e < left[u] ? here.offset : next.offset;
-                    sc.step = e < left[u] ? here.step : next.step;
+                    GroupScale sc = here;
+                    if constexpr (SEAMS) {
+                        sc.offset = e < left[u] ? here.offset : next.offset;
+                        sc.step = e < left[u] ? here.step : next.step;
+                    }
                     v[e] = value_of(v[e], sc);
                     if constexpr (HAS_BUF) v[e] = m[u][e] + v[e];
                 }
@@ -178,7 +188,7 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a, uint32_t b
                     store_last_elems<DT, N>(out_s, at[u], v, rest);
                 } else {
                     if constexpr (HAS_BUF) store_piece<DT, N>(m_s + at[u] * kEB, v);
-                    store_piece<DT, N>(out_s + at[u] * kEB, v);
+                    store_piece<DT, N>(out_s + at[u] * kEB, v, THROUGH);
                 }
             }
             if constexpr (!LOOPS) break;
@@ -189,8 +199,15 @@ __device__ __forceinline__ void dequant_odd_body(const DequantJob& a, uint32_t b
 
 template <int DT, int BITS, int THREADS, bool LOOPS>
 __device__ __forceinline__ void dequant_odd_bits(const DequantJob& a, uint32_t bx, uint32_t by) {
-    if (a.m_buf) dequant_odd_body<DT, BITS, true, THREADS, LOOPS>(a, bx, by);
-    else dequant_odd_body<DT, BITS, false, THREADS, LOOPS>(a, bx, by);
+    if constexpr (Piece<DT, BITS>::elems < kChunk) {     // float32: groups of whole pieces, without seams
+        if (a.group % Piece<DT, BITS>::elems == 0) {     // uniform over the workgroup
+            if (a.m_buf) dequant_odd_body<DT, BITS, true, false, THREADS, LOOPS>(a, bx, by);
+            else dequant_odd_body<DT, BITS, false, false, THREADS, LOOPS>(a, bx, by);
+            return;
+        }
+    }
+    if (a.m_buf) dequant_odd_body<DT, BITS, true, true, THREADS, LOOPS>(a, bx, by);
+    else dequant_odd_body<DT, BITS, false, true, THREADS, LOOPS>(a, bx, by);
 }
 
 template <int DT, int THREADS, bool LOOPS>
@@ -203,7 +220,20 @@ __device__ __forceinline__ void dequant_odd_job(const DequantJob& a, uint32_t bx
     }
 }
 
-template <int DT, bool LOOPS>
+// Large float32 gradients of whole pieces, which are written through the L2 (see odd_writes_through()).
+template <int THREADS>
+__device__ __forceinline__ void dequant_odd_through(const DequantJob& a, uint32_t bx, uint32_t by) {
+    switch (a.bits) {                                    // uniform over the workgroup
+    case 2: dequant_odd_body<AQSGD_F32, 2, false, false, THREADS, false, true>(a, bx, by); break;
+    case 4: dequant_odd_body<AQSGD_F32, 4, false, false, THREADS, false, true>(a, bx, by); break;
+    case 6: dequant_odd_body<AQSGD_F32, 6, false, false, THREADS, false, true>(a, bx, by); break;
+    default: dequant_odd_body<AQSGD_F32, 8, false, false, THREADS, false, true>(a, bx, by); break;
+    }
+}
+
+enum OddKind { kOddOneStep = 0, kOddLoops, kOddThrough };
+
+template <int DT, int KIND>
 __global__ __launch_bounds__(kBlock)
 void dequant_odd_kernel(AQSGD_DEQUANT_ARGS) {
     DequantJob a;
@@ -211,7 +241,8 @@ void dequant_odd_kernel(AQSGD_DEQUANT_ARGS) {
     a.n_per = n_per; a.gps = gps; a.batch = batch; a.group = group; a.bits = bits;
     a.grid_x = grid_x; a.grid_y = grid_y;
     a.seen = seen; a.stamp = stamp;
-    dequant_odd_job<DT, kBlock, LOOPS>(a, blockIdx.x, blockIdx.y);
+    if constexpr (KIND == kOddThrough) dequant_odd_through<kBlock>(a, blockIdx.x, blockIdx.y);
+    else dequant_odd_job<DT, kBlock, KIND == kOddLoops>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -743,7 +774,8 @@ void split_quant_kernel(AQSGD_QUANT_ARGS, int32_t spans, int32_t span_pieces) {
 }
 
 // Per-dtype pieces (defined by AQSGD_INSTANTIATE_ANYGROUP_DTYPE in the dtype's .hip file).
-template <int DT> hipError_t launch_dequant_odd_dt(bool covers, const DequantJob& a, hipStream_t stream);
+// `through`: float32 without previous messages, groups of whole 16-byte pieces, one step for every workgroup.
+template <int DT> hipError_t launch_dequant_odd_dt(bool covers, bool through, const DequantJob& a, hipStream_t stream);
 // `parts` workgroups a group, `share` rounds each (1 and all rounds with previous messages).
 template <int DT> hipError_t launch_quant_wide_dt(int rounding, int parts, int share, const QuantJob& a, hipStream_t stream);
 template <int DT> hipError_t launch_quant_large_dt(int rounding, const QuantJob& a, const LargeGeom& geom,
@@ -753,9 +785,12 @@ template <int DT> hipError_t launch_quant_split_dt(int rounding, const QuantJob&
 
 // ---- launch tables (instantiated per dtype in aqsgd_anygroup_<dtype>.hip) --------------
 template <int DT>
-hipError_t launch_dequant_odd_dt(bool covers, const DequantJob& a, hipStream_t s) {
-    return covers ? launch_dequant_with(dequant_odd_kernel<DT, false>, a, s)
-                  : launch_dequant_with(dequant_odd_kernel<DT, true>, a, s);
+hipError_t launch_dequant_odd_dt(bool covers, bool through, const DequantJob& a, hipStream_t s) {
+    if constexpr (DT == AQSGD_F32) {
+        if (through) return covers ? launch_dequant_with(dequant_odd_kernel<DT, kOddThrough>, a, s) : hipErrorInvalidValue;
+    }
+    return covers ? launch_dequant_with(dequant_odd_kernel<DT, kOddOneStep>, a, s)
+                  : launch_dequant_with(dequant_odd_kernel<DT, kOddLoops>, a, s);
 }
 
 template <int DT>
@@ -800,7 +835,7 @@ hipError_t launch_quant_split_dt(int rounding, const QuantJob& a, const LargeGeo
 }
 
 #define AQSGD_INSTANTIATE_ANYGROUP_DTYPE(DT)                                                          \
-    template hipError_t launch_dequant_odd_dt<DT>(bool, const DequantJob&, hipStream_t);                   \
+    template hipError_t launch_dequant_odd_dt<DT>(bool, bool, const DequantJob&, hipStream_t);             \
     template hipError_t launch_quant_wide_dt<DT>(int, int, int, const QuantJob&, hipStream_t);             \
     template hipError_t launch_quant_large_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t);   \
     template hipError_t launch_quant_split_dt<DT>(int, const QuantJob&, const LargeGeom&, hipStream_t);

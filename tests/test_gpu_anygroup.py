@@ -57,6 +57,14 @@ def test_odd_groups_of_two_chunks(H, dtype, bits, group):
             _sweep(H, dtype, bits, group, rounding, gps)
 
 
+@pytest.mark.parametrize("bits,group,gps", [(8, 1020, 6169), (8, 1020, 6168), (2, 12, 524288), (6, 252, 24967), (4, 1022, 6157)])
+def test_large_odd_groups_of_float32(H, bits, group, gps):
+    """Gradients of 48 MiB and more in whole 16-byte pieces are written through the L2; one case lies below, and
+    the last has pieces that hold two groups."""
+    assert (2 * gps * group * 4 >= 48 << 20) == (gps != 6168)
+    _sweep(H, "f32", bits, group, W.NEAREST, gps, batch=2)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("bits,group", [(4, 32776), (3, 32776), (8, 32769), (2, 32772), (6, 40004), (8, 65537),
                                         (4, 262144), (3, 262152), (8, 300001),

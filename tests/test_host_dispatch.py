@@ -137,3 +137,17 @@ def test_low_precision_receivers_of_whole_lines_write_through(client, dtype, bit
     assert status == 0 and len(launches) == 1
     mode = launches[0][2].split("lowbit_team_kernel<")[1].split(">(")[0].split(",")[5]
     assert int(mode) == (3 if through else 0), launches
+
+
+@pytest.mark.parametrize("kind,dtype,bits,group,rows,through", [
+    (GRAD_DEQUANT, F32, 8, 1020, 12337, True), (GRAD_DEQUANT, F32, 8, 1020, 12336, False),       # 48 MiB
+    (GRAD_DEQUANT, F32, 2, 12, 2000000, True),
+    (GRAD_DEQUANT, F32, 4, 1022, 20000, False),          # pieces that hold two groups
+    (GRAD_DEQUANT, F16, 4, 1020, 40000, False),
+    (DECODE, F32, 4, 1020, 20000, False),                # previous messages
+])
+def test_large_odd_float32_gradients_write_through(client, kind, dtype, bits, group, rows, through):
+    launches, status = client((kind, dtype, bits, 0, 1, rows * group, group), options=("alone",))
+    assert status == 0 and len(launches) == 1
+    odd_kind = launches[0][2].split("dequant_odd_kernel<")[1].split(">(")[0].split(",")[-1]
+    assert int(odd_kind) == (2 if through else 0), launches
