@@ -468,6 +468,21 @@ bool split_pays_shared(int64_t groups, bool has_buf, int dtype, int rounding) {
     return has_buf && groups <= (dtype == AQSGD_F32 ? 64 : 32);
 }
 
+// Which table takes the dequantising jobs of whole groups if wide groups and a table of whole ones are to go
+// out (wide forward groups, a scale for every row backward): that of the wide groups while they leave
+// compute units idle, else the other.  Few wide groups that go out as spans leave little idle, too, but for
+// nearest rounding of 16-bit types, whose spans are short.  A time slot of one boundary, groups of
+// 49152 forward and 768 backward, with the wide ones -> with the others, in us:
+//                                  32 groups      64 groups      128 groups     160 groups     256 groups
+//   nearest     float16 15.3 -> 17.4  20.0 -> 20.4   26.4 -> 28.5   31.6 -> 31.3   48.6 -> 43.2
+//               float32 19.4 -> 18.9  31.6 -> 29.6   43.5 -> 44.4   53.7 -> 50.7   80.3 -> 74.6
+//   stochastic  bfloat16 16.0 -> 15.8  23.4 -> 20.6   30.2 -> 33.4   36.5 -> 37.2   56.8 -> 50.7
+//               float32 19.6 -> 19.4  31.4 -> 29.7   44.3 -> 47.1   54.9 -> 54.3   83.0 -> 78.5
+bool wide_groups_host(int64_t groups, int dtype, int rounding) {
+    const bool spans = groups <= 64 && (dtype == AQSGD_F32 || rounding == AQSGD_ROUND_STOCHASTIC);
+    return groups <= 144 && !spans;
+}
+
 // The rectangle of a message launched by itself: one workgroup for every sample and step if
 // that stays below `cap` and the grid's second dimension, which is what this tells.
 template <typename Job>
@@ -701,7 +716,11 @@ int launch_plans(std::vector<QuantPlan>& qs, std::vector<DequantPlan>& ds, hipSt
             t.q[t.n_quant++] = c.job;
             q_done[k] = true;
         }
-        add_dequant(t, lead.dtype, odd ? Route::kOdd : Route::kJob, taken_d);
+        bool waiting = false;                            // a table of whole groups is still to come
+        for (size_t k = i; k < qs.size(); ++k)
+            waiting = waiting || (!q_done[k] && qs[k].route == Route::kJob && qs[k].dtype == lead.dtype);
+        if (odd || !waiting || wide_groups_host(groups, lead.dtype, lead.rounding))
+            add_dequant(t, lead.dtype, odd ? Route::kOdd : Route::kJob, taken_d);
         bool covers = t.n_quant + t.n_dequant > 1;
         if (covers && odd) {
             struct {

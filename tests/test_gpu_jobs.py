@@ -298,6 +298,28 @@ def test_time_slots_of_odd_and_wide_groups(H, case):
             b.verify(f"{case} boundary {i} slot {step}")
 
 
+@pytest.mark.parametrize("dtype,bits,rounding,batch,gps,boundaries", [
+    ("f16", 4, 0, 2, 3, 1), ("bf16", 8, 1, 16, 4, 1), ("bf16", 3, 1, 13, 5, 1),      # 6, 64 and 65 wide groups
+    ("f32", 4, 0, 8, 2, 2), ("f32", 8, 0, 9, 4, 2),                                  # 32 and 72
+    ("f16", 2, 0, 24, 3, 2), ("f16", 4, 0, 29, 5, 1)])                               # 144 and 145
+def test_time_slots_of_wide_groups_forward_and_rows_backward(H, dtype, bits, rounding, batch, gps, boundaries):
+    """One scale per 49152 elements forward, one per row of 768 backward: with few and with many wide groups the
+    decodes and grad_dequants ride with the rows, in between with the wide groups."""
+    rng = np.random.default_rng(batch * gps)
+    bs = [Boundary(H, rng, dtype, bits, 49152, rounding, 8, 768, rounding, batch, 49152 * gps, n_rows=batch + 1, seed=70 + i)
+          for i in range(boundaries)]
+    for step in range(3):
+        jobs = []
+        for b in bs:
+            late = [b.grad_dequant_job()] if step >= 2 else []
+            mid = [b.decode_job(), b.grad_quant_job()] if step >= 1 else []
+            jobs += [b.encode_job(step)] + mid + late
+        print("wide and rows", dtype, batch * gps * boundaries, "groups, slot", step, flush=True)
+        B.run_jobs(jobs)
+        for i, b in enumerate(bs):
+            b.verify(f"{dtype} boundary {i} slot {step}")
+
+
 @pytest.mark.parametrize("dtype,bits,group,rounding,batch,n_per,boundaries", [
     ("f32", 4, 4096, 0, 3, 4096 * 60, 4),                # one step a workgroup
     ("f16", 3, 1600, 1, 3, 1600 * 512, 2),

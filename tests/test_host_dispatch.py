@@ -151,3 +151,24 @@ def test_large_odd_float32_gradients_write_through(client, kind, dtype, bits, gr
     assert status == 0 and len(launches) == 1
     odd_kind = launches[0][2].split("dequant_odd_kernel<")[1].split(">(")[0].split(",")[-1]
     assert int(odd_kind) == (2 if through else 0), launches
+
+
+@pytest.mark.parametrize("dtype,rounding,groups,with_wide", [
+    (F16, 0, 8, True), (BF16, 0, 64, True), (F16, 1, 8, False), (BF16, 1, 64, False), (F16, 1, 65, True),
+    (F32, 0, 32, False), (F32, 1, 64, False), (F32, 0, 65, True),
+    (F16, 0, 144, True), (F16, 0, 145, False), (BF16, 1, 512, False), (F32, 0, 144, True), (F32, 0, 145, False)])
+def test_reconstructions_ride_with_wide_groups_while_those_leave_the_chip_idle(client, dtype, rounding, groups, with_wide):
+    """Wide forward groups, a scale for every row backward: the table that takes the decode and the grad_dequant."""
+    n_per = 49152
+    fwd, bwd = (dtype, 4, rounding, groups, n_per, n_per), (dtype, 8, rounding, groups, n_per, 768)
+    launches, status = client((ENCODE, *fwd), (DECODE, *fwd), (GRAD_QUANT, *bwd), (GRAD_DEQUANT, *bwd))
+    assert status == 0
+    alone, status = client((GRAD_QUANT, *bwd), (ENCODE, *fwd))
+    assert status == 0
+    name = lambda kernels: {k.split("<")[0].split()[-1]: g[0] for g, _, k in kernels}
+    got, bare = name(launches), name(alone)
+    rows = next(k for k in got if k.endswith("codec_jobs_kernel"))
+    assert (got[rows] == bare[rows]) == with_wide, (launches, alone)
+    # without a table of whole groups to come they always ride along
+    stage, status = client((ENCODE, *fwd), (GRAD_DEQUANT, *bwd))
+    assert status == 0 and all("jobs_kernel" in k for _, _, k in stage), stage
