@@ -132,6 +132,26 @@ def test_first_visit_jobs_of_odd_and_wide_groups(H, dtype, bits, group, gps, bat
             seed=group, as_jobs=True)
 
 
+@pytest.mark.parametrize("dtype,bits,group,gps,batch,rounding", [
+    ("f32", 4, 4096, 400, 5, 0), ("f32", 3, 128, 9000, 6, 1), ("bf16", 3, 1024, 1600, 8, 0), ("f16", 8, 64, 26000, 8, 1)])
+def test_first_visits_of_messages_that_are_written_through(H, dtype, bits, group, gps, batch, rounding):
+    """Single calls of whole 128-byte lines above the sizes (24 MiB; 20 of m and codes in 16-bit types) from which
+    rows, copied and updated, are written through the L2: one call all new, then new and known samples mixed."""
+    eb = 4 if dtype == "f32" else 2
+    assert group * eb % 128 == 0 and batch * group * gps * eb >= 24 << 20
+    _replay(H, dtype, bits=bits, group=group, n_per=group * gps, n_rows=2 * batch, batch=batch, steps=3, rounding=rounding,
+            seed=group)
+
+
+@pytest.mark.parametrize("dtype,bits,group,gps,batch,rounding", [
+    ("f32", 4, 1024, 1100, 6, 0), ("f32", 8, 64, 20000, 6, 1), ("f16", 4, 1600, 1024, 8, 1), ("bf16", 3, 256, 7000, 8, 0)])
+def test_first_visit_jobs_in_launches_that_are_written_through(H, dtype, bits, group, gps, batch, rounding):
+    eb = 4 if dtype == "f32" else 2
+    assert group * eb % 128 == 0 and batch * group * gps * eb >= 24 << 20
+    _replay(H, dtype, bits=bits, group=group, n_per=group * gps, n_rows=2 * batch, batch=batch, steps=3, rounding=rounding,
+            seed=group, as_jobs=True)
+
+
 def test_seen_jobs_reject_bad_arguments(H):
     import ctypes
     ok = B.make_desc(batch=2, n_per=1600, n_samples=4, bits=4, group=1600, dtype="f16")
