@@ -595,12 +595,24 @@ bool whole_lines(const QuantJob& a, int64_t eb) {
 }
 bool whole_lines(const DequantJob& a, int64_t eb) { return a.n_per * eb % kLineBytes == 0; }
 
-// A reconstruction alone (measured in a row of four calls, through -> streaming: float32 [8,2048,4096]
-// 362 -> 366 us, bfloat16 [32,256,1536] 46.3 -> 46.8, first visits of float16 [4,1024,1600], 26 MB written,
-// 17.4 -> 17.7).
+// A reconstruction alone.  Large ones (measured in a row of four calls, through -> streaming: float32
+// [8,2048,4096] 362 -> 366 us, bfloat16 [32,256,1536] 46.3 -> 46.8, first visits of float16 [4,1024,1600], 26 MB
+// written, 17.4 -> 17.7), and gradients of the sizes of which much streams out of the L2s before the launch
+// ends when the output is the same buffer every time.  Time of a grad_dequant streaming over time through, by the MiB
+// written (G = 64 to 4096, geometric means over four and, of 16 bits, eight):
+//                               8     10     12     14     16     18     20     22
+//   16 bits  same output      0.95   0.94   1.05   1.06   1.01   0.97   0.97   0.94
+//            others           0.94   0.93   0.95   0.96   0.97   0.97   0.98   0.98
+//   float32  same output      0.95   0.94   1.15   1.10   1.11   1.05   1.00   1.00
+//            others           0.95   0.95   0.95   0.96   0.96   0.98   0.98   1.00
+// A decode, which writes m and out, has no such sizes (0.97 to 1.02 from 12 MiB written on).
+constexpr int64_t kThroughGradBytes = int64_t{11} << 20;
+constexpr int64_t stream_grad_bytes(int dtype) { return int64_t{dtype == AQSGD_F32 ? 19 : 17} << 20; }
+
 bool writes_through(const DequantJob& a, int dtype) {
-    const int64_t eb = dtype == AQSGD_F32 ? 4 : 2;
-    return bytes_written(a, eb) >= kThroughBytes && whole_lines(a, eb);
+    const int64_t eb = dtype == AQSGD_F32 ? 4 : 2, bytes = bytes_written(a, eb);
+    const bool grad = a.m_buf == nullptr && bytes >= kThroughGradBytes && bytes < stream_grad_bytes(dtype);
+    return (bytes >= kThroughBytes || grad) && whole_lines(a, eb);
 }
 
 // An encode alone: time streaming over time through, by the MiB of m it writes (4 bits, G = 64 to 4096, both

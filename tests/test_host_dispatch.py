@@ -172,3 +172,20 @@ def test_reconstructions_ride_with_wide_groups_while_those_leave_the_chip_idle(c
     # without a table of whole groups to come they always ride along
     stage, status = client((ENCODE, *fwd), (GRAD_DEQUANT, *bwd))
     assert status == 0 and all("jobs_kernel" in k for _, _, k in stage), stage
+
+
+@pytest.mark.parametrize("dtype,elements,through", [
+    (F32, 11 << 18, True), (F32, (11 << 18) - 32, False), (F32, (19 << 18) - 32, True), (F32, 19 << 18, False),
+    (F16, 11 << 19, True), (F16, (11 << 19) - 64, False), (BF16, (17 << 19) - 64, True), (BF16, 17 << 19, False),
+    (F32, 24 << 18, True), (F32, (24 << 18) - 32, False), (F16, 24 << 19, True), (BF16, (24 << 19) - 64, False),
+    (F16, (12 << 19) + 32, False),                       # not of whole lines
+])
+def test_gradients_alone_write_through_at_the_sizes_that_gain(client, dtype, elements, through):
+    """From 11 MiB to 17 (float32: 19), and from 24 MiB on."""
+    launches, status = client((GRAD_DEQUANT, dtype, 8, 0, 1, elements, 32), options=("alone",))
+    assert status == 0 and len(launches) == 1
+    assert launches[0][2].split("dequant_single_kernel<")[1].split(">(")[0].endswith("true" if through else "false"), launches
+    launches, status = client((DECODE, dtype, 8, 0, 1, elements, 32), options=("alone",))           # m and out
+    eb = 4 if dtype == F32 else 2
+    big = 2 * elements * eb >= 24 << 20 and elements * eb % 128 == 0
+    assert status == 0 and launches[0][2].split(">(")[0].endswith("true" if big else "false"), launches
