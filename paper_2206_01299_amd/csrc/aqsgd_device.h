@@ -80,7 +80,7 @@ __device__ __forceinline__ Raw<DT> load_raw_any(const char* p) {
 // through, they leave while the kernel is still reading.  With two streams' launches side by side
 // that is what counts: forward pair of the GPT2 boundary in the pipelined schedule 957-959 GB/s
 // streaming, 975-982 through, DeBERTa step 36.0 and 35.4 us.
-// Everywhere else streaming alone is better.  A store that is written through is over only when
+// In most other launches streaming alone is better.  A store that is written through is over only when
 // memory has it, which a small launch waits for at its end: float16 [4,32,1024], encode 3.21 us
 // through, 2.71 streaming, decode 3.14 and 2.71; and where rows or groups are no whole 128-byte
 // lines the two halves of a line go to memory one by one instead of meeting in the L2: bfloat16
@@ -726,25 +726,29 @@ __device__ __forceinline__ uint32_t load_unit_codes(const uint8_t* p, uint32_t u
     }
 }
 
-// Three-bit codes of consecutive units in consecutive lanes (`lane` 0 holds a unit whose number is a
-// multiple of eight; every lane calls it, `live`: its unit is one of the group's, which are pairs).
-// An even lane puts its 12 bits and the next lane's together; where the group's units are whole
-// octets (`octets`, uniform over the team), the four even lanes of an octet then make three
-// aligned dwords of their 24 bits as store_codes3_quad does, else each stores its three bytes.
-// group_codes: the group's first byte; unit: the lane's unit in the group.
-__device__ __forceinline__ void store_unit_codes3(uint8_t* group_codes, uint32_t unit, uint32_t w, int lane, bool live,
-                                                  bool octets) {
-    const uint32_t odd = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
-        0, static_cast<int>(w), 0xF5 /* quad_perm [1,1,3,3] */, 0xf, 0xf, false));
-    const uint32_t pair = w | (odd << 12);
+// Three-bit codes of a lane's two units, `unit` and `unit + apart`, the low and the high twelve bits of w (the
+// lanes of a team hold consecutive ones, lane 0 a multiple of eight; every lane calls it; the group's units,
+// `units` of them, are pairs).  Two lanes exchange their words, and the even one goes on with the pair of
+// the first units, the odd one with the pair of the second.  Where the group's units are whole octets
+// (`octets`, uniform over the team), three of the four lanes that hold an octet's pairs then make
+// three aligned dwords of their 24 bits as store_codes3_quad does, else each stores its three bytes.
+// (The two units one after the other, even lanes only, are twice the instructions: [4,41,1600], an encode
+// beside a grad_dequant 4.35 us and 4.12 so, alone 3.54 and 3.44; the one-piece layout, slower beyond 4 MB, 3.64, 3.25.)  group_codes: the group's first byte.
+__device__ __forceinline__ void store_unit_codes3(uint8_t* group_codes, uint32_t unit, uint32_t apart, uint32_t units,
+                                                  uint32_t w, int lane, bool octets) {
+    const uint32_t other = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+        0, static_cast<int>(w), 0xB1 /* quad_perm [1,0,3,2] */, 0xf, 0xf, false));
+    const bool odd = (lane & 1) != 0;
+    const uint32_t pair = odd ? (other >> 12) | (w & 0xfff000u) : (w & 0xfffu) | ((other & 0xfffu) << 12);
+    const uint32_t first = odd ? unit + apart - 1 : unit;
     if (octets) {
         const uint32_t next = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
             0, static_cast<int>(pair), 0x102 /* row_shl:2: from two lanes on */, 0xf, 0xf, true));
         const int j = (lane & 7) >> 1;
         const uint32_t word = (pair >> (8 * j)) | (next << (24 - 8 * j));        // j = 0, 1, 2
-        if (live && (lane & 1) == 0 && j < 3) reinterpret_cast<uint32_t*>(group_codes + (unit >> 3) * 12)[j] = word;
-    } else if (live && (lane & 1) == 0) {
-        uint8_t* p = group_codes + (unit >> 1) * 3;
+        if (first < units && j < 3) reinterpret_cast<uint32_t*>(group_codes + (first >> 3) * 12)[j] = word;
+    } else if (first < units) {
+        uint8_t* p = group_codes + (first >> 1) * 3;
         p[0] = static_cast<uint8_t>(pair);
         p[1] = static_cast<uint8_t>(pair >> 8);
         p[2] = static_cast<uint8_t>(pair >> 16);

@@ -290,10 +290,8 @@ __device__ __forceinline__ void quant_team_group(const QuantJob& a, const char* 
                 const uint64_t w = pack_levels<BITS>(q);
                 if constexpr (BITS == 3) {
                     // lanes past the group's end hold its last unit once more and store nothing
-                    const int u0 = 2 * k * TEAM + lane_in_team, u1 = u0 + TEAM;
-                    const bool octets = a.cpg % 4 == 0;
-                    store_unit_codes3(group_codes, ua[k], low_unit_codes<BITS>(w), lane_in_team, u0 < 2 * a.cpg, octets);
-                    store_unit_codes3(group_codes, ub[k], high_unit_codes<BITS>(w), lane_in_team, u1 < 2 * a.cpg, octets);
+                    store_unit_codes3(group_codes, 2 * k * TEAM + lane_in_team, TEAM, 2 * a.cpg, static_cast<uint32_t>(w),
+                                      lane_in_team, a.cpg % 4 == 0);
                 } else {
                     store_codes_of_unit<BITS, ODD>(group_codes + Unit::template code_byte<BITS>(ua[k]), low_unit_codes<BITS>(w));
                     store_codes_of_unit<BITS, ODD>(group_codes + Unit::template code_byte<BITS>(ub[k]), high_unit_codes<BITS>(w));
