@@ -1,9 +1,10 @@
-// Kernels for groups outside the job kernels' range (one message per launch):
+// Kernels for groups outside the job kernels' range, a message a launch, and the bodies that the shared
+// launches of such messages are made of (aqsgd_jobs_anygroup.h):
 //
 //   odd groups    8 elements or more but no whole number of chunks: a flat dequantising
 //                 body whose pieces may hold the end of one group and the start of the
-//                 next (the quantising side is the team bodies with ODD offsets, launched
-//                 from aqsgd_single.h)
+//                 next (the quantising side is the team bodies with ODD offsets; alone
+//                 they are launched from aqsgd_single.h)
 //   wide groups   more elements than the job kernels' shapes take (over 32768) that one
 //                 workgroup still holds in registers as stored: one pass
 //   large groups  more than that: the maximum is taken by many workgroups into the
@@ -261,12 +262,12 @@ void dequant_odd_kernel(AQSGD_DEQUANT_ARGS) {
 // ---------------------------------------------------------------------------
 constexpr int kWideThreads = 1024;
 template <int DT> struct WideRounds { static constexpr int value = DT == AQSGD_F32 ? 12 : 8; };
-// Largest group: pieces of 16 bytes, one per lane and round.
 // Rounds of a group: pieces of 16 bytes (32 of binary32 at 3 bits), one per lane and round.
 constexpr int wide_rounds(int dtype, int bits, int group) {
     const int piece = dtype == AQSGD_F32 && bits != 3 ? 4 : 8;
     return ((group + piece - 1) / piece + kWideThreads - 1) / kWideThreads;
 }
+// Elements of the largest group: pieces of 16 bytes, one per lane and round.
 constexpr int wide_most_elements(int dtype) {
     return dtype == AQSGD_F32 ? kWideThreads * 4 * WideRounds<AQSGD_F32>::value
                               : kWideThreads * 8 * WideRounds<AQSGD_F16>::value;
@@ -317,7 +318,7 @@ __device__ __forceinline__ void piece_change(const PieceRaw<DT, N>& a, const Pie
 // One group in a workgroup: bx is the group of the sample, by the sample.  Without previous messages
 // nothing that a workgroup reads is written in the launch, so several can share a group: each takes
 // the maximum of all of it and quantises `share` rounds from share * part on (few groups leave most
-// compute units idle, and the levels are two thirds of the arithmetic; see wide_parts()).
+// compute units idle, and the levels are two thirds of the arithmetic; see wide_share() in the dispatch).
 template <int DT, int BITS, int ROUND, bool HAS_BUF>
 __device__ __forceinline__ void quant_wide_body(const QuantJob& a, uint32_t bx, uint32_t by, uint32_t part, int share,
                                                 float* wave_max) {

@@ -301,9 +301,10 @@ int64_t odd_pieces(const DequantJob& a, int dtype) {
 }
 
 // Which kernels a message takes.  Groups of whole chunks that fit a workgroup's registers are
-// jobs of the shared launches; the rest are launched on their own: odd groups (8 elements or
-// more, not whole chunks), groups beyond the job kernels' team shapes and those beyond any
-// workgroup (quantising side only: reconstruction needs no maximum), and the scalar kernels for groups of 1 to 7 elements, which have no 16-byte piece.
+// jobs of the shared launches; odd groups (8 elements or more, not whole chunks) and groups beyond the
+// job kernels' team shapes share launches of their own.  Launched one by one: groups beyond any
+// workgroup (quantising side only: reconstruction needs no maximum), and those of 1 to 7 elements, which
+// have no 16-byte piece and take the scalar kernels.
 enum class Route { kJob, kOdd, kWide, kLarge, kAnyShape };
 
 // One message as the kernels see it.  Quantising side: aqsgd_encode, aqsgd_grad_quant.
@@ -458,8 +459,8 @@ bool split_pays(const QuantJob& a, int dtype, int rounding) {
 // The same for the wide groups of a shared launch (`groups` in all, activations among them: has_buf),
 // where the second launch is one for all messages and the dequantising jobs fill what the maxima leave
 // idle.  A time slot of one boundary, groups of 49152, one workgroup each -> spans, in us:
-//   stochastic   64 groups  float16 13.4 -> 13.5, float32 19.1;  96 groups 19.0 -> 16.1, 26.1 -> 24.2;
-//                128 groups 19.5 -> 18.9, 29.2 -> 29.9
+//   stochastic   float16  32 groups 15.2 -> 9.4, 64 groups 17.3 -> 13.1, 96 groups 18.9 -> 16.4, 128 groups 19.5 -> 18.9
+//                float32  32 groups 20.3 -> 11.7, 64 groups 22.5 -> 19.2, 96 groups 25.6 -> 24.8, 128 groups 29.2 -> 29.9
 //   nearest      float32  48 groups 18.4 -> 15.1, 64 groups 19.9 -> 19.0, 96 groups 22.6 -> 24.2
 //                float16   8 groups 10.8 -> 9.2, 32 groups 11.9 -> 10.5, 64 groups 13.3 -> 13.1, 96 groups 14.8 -> 15.5
 //                bfloat16  8 groups 10.1 -> 9.4, 32 groups 11.1 -> 10.6, 64 groups 12.6 -> 12.9
@@ -848,6 +849,8 @@ void seed_rows_kernel(const V* act, const int64_t* ids, V* m_buf, int64_t units_
              c += static_cast<int64_t>(gridDim.x) * kBlock) {
             if constexpr (sizeof(V) == 16) {
                 const V v = __builtin_nontemporal_load(src + c);
+                // written through at every size: streaming, in us, float16 [4,32768] 2.07 -> 2.18, [4,1638400] 3.45 -> 3.82,
+                // bfloat16 [32,393216] 5.4 -> 8.9 (the same rows every time; others 10.15 -> 10.09), float32 [8,8388608] 81.6 -> 80.3
                 store16(dst + c, v, true);
             } else {
                 dst[c] = src[c];

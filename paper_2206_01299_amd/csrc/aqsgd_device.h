@@ -86,7 +86,11 @@ __device__ __forceinline__ Raw<DT> load_raw_any(const char* p) {
 // lines the two halves of a line go to memory one by one instead of meeting in the L2: bfloat16
 // [7,1001,2008] decode 20.9 and 18.2, rows of 2048 17.1 and 17.4.  (Ordinary stores are as good as
 // streaming ones in small launches and lose in all others: float32 [8,2048,4096], four calls 407 us
-// against 358.)  So the caller says which: `through` is a constant of every kernel.
+// against 358.)  So the caller says which: `through` is a constant of every kernel.  The sizes from which
+// launches write through stand at writes_through(), odd_writes_through() and lowbit_writes_through() in the
+// dispatch; aqsgd_seed and the receivers of the sparsified message always do (figures at their stores);
+// the tables of odd and wide groups never do (reconstructions through, time slots in us: float16 [8,64,768],
+// one scale a sample, 7.3 -> 7.8, [512,64,768] 88.5 -> 90.0, float32 four boundaries of [32,64,768] 41.8 -> 41.4).
 //
 // The compiler has no spelling for nt sc0 sc1 on a 16-byte store, so the instruction is written
 // out; the data registers of a store of more than eight bytes must not be overwritten in the next

@@ -212,7 +212,7 @@ __device__ __forceinline__ void lanes_before(const uint32_t (&cnt)[CPL], int lan
 // A string of nb bytes between LDS (16-byte aligned) and any
 // address: four bytes a lane, or one where that is a single round.
 __device__ __forceinline__ void string_out(uint8_t* dst, const uint8_t* lds, int nb, int lane) {
-    if (nb <= kWave) {                                   // uniform over the launch
+    if (nb <= kWave) {                                   // uniform over the wave
         if (lane < nb) dst[lane] = lds[lane];
         return;
     }
@@ -700,6 +700,8 @@ __device__ __forceinline__ void topk_dequant_group(const TopkArgs& a, int64_t g,
             x[e] = on ? v : 0.0f;
             pos += on;
         }
+        // written through at every size: streaming, in us, float16 [4,1024,1600] 4.81 -> 5.52 (the same output every
+        // time; others 4.81 -> 5.00), bfloat16 [4,64,1024] 2.31 -> 2.36, [16,2048,1024] 15.1 -> 15.0
         if (valid[k]) store_raw_at<DT>(dst + cc[k] * kChunkBytes, pack_raw<DT>(x), true);
         row_start += kept_total[k];
     }

@@ -339,6 +339,8 @@ __device__ __forceinline__ void topk_small_dequant(const TopkArgs& a, int64_t g0
             x[e] = on ? v : 0.0f;
             pos += on;
         }
+        // written through at every size: streaming, in us, float16 512 groups of 64 2.07 -> 2.17, bfloat16 131072
+        // groups of 64 6.28 -> 6.50, float16 262144 of 128 14.9 -> 15.4
         if (valid[k] && stores)
             store_raw_at<DT>(static_cast<char*>(a.out) + (e0 + cc[k] * kChunk) * kEB, pack_raw<DT>(x), true);
     }

@@ -18,7 +18,9 @@ static hipError_t launch_small_team(TopkSmallShape shape, unsigned blocks, const
     case 8 * 8 + 2:  return launch_small_as<DT, MODE, 8, 2>(blocks, a, s);
     case 16 * 8 + 1: return launch_small_as<DT, MODE, 16, 1>(blocks, a, s);
     case 16 * 8 + 2: return launch_small_as<DT, MODE, 16, 2>(blocks, a, s);
-    case 16 * 8 + 4: return launch_small_as<DT, MODE, 16, 4>(blocks, a, s);
+    case 16 * 8 + 4:                                     // float32 senders and 16-bit receivers (topk_small_shape)
+        if constexpr ((MODE != 0) == (DT == AQSGD_F32)) return launch_small_as<DT, MODE, 16, 4>(blocks, a, s);
+        [[fallthrough]];
     default: return hipErrorInvalidValue;
     }
 }

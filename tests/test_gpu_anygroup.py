@@ -79,11 +79,13 @@ def test_groups_beyond_a_workgroup(H, dtype, bits, group):
 
 @pytest.mark.parametrize("dtype,bits,group,gps", [("bf16", 8, 32776, 16), ("bf16", 8, 32776, 17), ("f32", 3, 49152, 16),
                                                   ("f32", 3, 49152, 17), ("f32", 8, 32769, 16), ("f32", 8, 32769, 17),
-                                                  ("f16", 8, 32769, 16), ("f16", 8, 32769, 17)])
+                                                  ("f16", 8, 32769, 16), ("f16", 8, 32769, 17),
+                                                  ("bf16", 8, 49152, 16), ("bf16", 8, 49153, 16), ("bf16", 8, 49153, 17),
+                                                  ("f16", 4, 65536, 16), ("f16", 4, 65536, 17)])
 def test_wide_groups_few_and_many(H, dtype, bits, group, gps):
-    """The number of groups up to which a call goes out as spans, and one pair more: 64 with
-    stochastic rounding in every type, 32 with nearest rounding in float32 with previous messages
-    (the backward message, which has none, and 16-bit types never split there).  Two samples a call."""
+    """The number of groups up to which an encode goes out as spans, and one pair more: 64 with
+    stochastic rounding in every type; with nearest rounding 32, in float32 and in 16-bit groups of more
+    than 49152 elements (the backward message, which has no previous messages, never).  Two samples a call."""
     for rounding, n in ((W.NEAREST, gps), (W.STOCHASTIC, 2 * gps)):
         print(f"wide {dtype} b{bits} G{group} x {n} r{rounding}", flush=True)
         _sweep(H, dtype, bits, group, rounding, n, batch=2)

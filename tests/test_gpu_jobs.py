@@ -123,7 +123,7 @@ PAIRS = [
     ("f16", 2, 128, 1, 4, 128, 1, 2, 128 * 301),         # stochastic, half-wave teams
     ("bf16", 3, 64, 0, 6, 64, 0, 5, 64 * 517),           # 3- and 6-bit pieces, 8-lane teams
     ("f32", 4, 4096, 0, 8, 4096, 0, 2, 4096 * 9),        # float32 in 16-byte units, whole-workgroup teams
-    ("f32", 3, 64, 1, 2, 256, 0, 3, 256 * 33),           # float32 one-piece layout (3 bits)
+    ("f32", 3, 64, 1, 2, 256, 0, 3, 256 * 33),           # float32 at 3 bits: two units share a byte
     ("f16", 8, 16384, 0, 4, 32768, 1, 2, 32768 * 3),     # 1024-lane teams host the dequantising job
     ("bf16", 6, 512, 1, 3, 2048, 0, 2, 2048 * 11),
 ]
@@ -168,7 +168,7 @@ THREE_MIXES = [
     # dtype, group, rounding, forward bits of the boundaries, backward bits, batch, groups per sample
     ("bf16", 64, 0, (3, 4, 3), 6, 5, 517),               # the DeBERTa boundary's widths, 8-lane teams
     ("f16", 1600, 0, (3, 8), 2, 2, 37),                  # one-wave teams of four chunks per lane
-    ("f32", 512, 1, (2, 3), 4, 2, 19),                   # float32: unit layout and one-piece layout side by side
+    ("f32", 512, 1, (2, 3), 4, 2, 19),                   # float32: units of whole bytes and of a byte and a half side by side
     ("f16", 4096, 1, (6, 3), 8, 2, 5),                   # whole-workgroup teams
 ]
 
